@@ -209,6 +209,7 @@ static tsq_status ensure_prepared() {
     std::call_once(g_prepare_once, [] {
         g_prepare_rc = prepare_kernels();
         if (g_prepare_rc == 0) g_prepare_rc = prepare_fused_kernels();
+        if (g_prepare_rc == 0) g_prepare_rc = prepare_direct_kernels();
     });
     return hip_rc(g_prepare_rc);
 }
@@ -253,12 +254,28 @@ static bool is_capturing(hipStream_t s) {
     return st != hipStreamCaptureStatusNone;
 }
 
-static int launch_fused_ordered(const Params &p, const Geometry &g, uint32_t grid, const void *d_in, void *d_blob,
+// grid: computing workgroups of the persistent kernel; 0: one workgroup per token
+static int launch_single_pass(const Params &p, const Geometry &g, uint32_t grid, const void *d_in, void *d_blob, void *d_ws,
+                              void *stream) {
+    return grid ? launch_fused(p, g, grid, d_in, d_blob, d_ws, stream) : launch_direct(p, g, d_in, d_blob, d_ws, stream);
+}
+// Which of the two a plan's calls take.  A function of the shape alone: a workspace serves every plan of its shape,
+// and the persistent kernel must find no prefix words in it that another call left out.
+// One workgroup per token is the faster form while the whole call fits the device about once (24 waves on each of
+// 256 compute units): 2048 x 4096 f16 13.7 us against 17.7, 2048 x 5120 14.5 / 18.1, 1237 x 8192 14.2 / 15.1, but
+// 4096 x 4096 24.9 / 23.9 and 3000 x 5120 25.0 / 21.4.  Rows of one wave gain at any number of tokens, since the
+// persistent kernel's scanner, which would have one wave there, is what bounds it: 8192 x 768 27.1 / 43.7 us,
+// 65536 x 768 209 / 275, 65536 x 2048 246 / 278.
+static bool use_direct(const tsq_plan *plan) {
+    return plan->g.waves == 1 || (uint64_t)plan->p.tokens * plan->g.waves <= 6144u;
+}
+
+static int launch_ordered(const Params &p, const Geometry &g, uint32_t grid, const void *d_in, void *d_blob,
                                 void *d_ws, void *stream) {
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     int dev = -1;
     if (is_capturing(s) || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kStaticMaxDevicesForOrder)
-        return launch_fused(p, g, grid, d_in, d_blob, d_ws, stream);
+        return launch_single_pass(p, g, grid, d_in, d_blob, d_ws, stream);
     std::lock_guard<std::mutex> lock(g_order_mutex);
     FusedOrder &o = g_order[dev];
     if (o.any && o.last_stream != s && !is_capturing(o.last_stream)) {
@@ -271,7 +288,7 @@ static int launch_fused_ordered(const Params &p, const Geometry &g, uint32_t gri
             (void)hipGetLastError();
         }
     }
-    const int rc = launch_fused(p, g, grid, d_in, d_blob, d_ws, stream);
+    const int rc = launch_single_pass(p, g, grid, d_in, d_blob, d_ws, stream);
     if (rc == 0) { o.last_stream = s; o.any = true; }
     return rc;
 }
@@ -285,6 +302,7 @@ static tsq_status compress_call(const tsq_plan *plan, const void *d_in, uint32_t
     Params p = plan->p;
     p.rows_per_tensor = rows_per_tensor;
     if (plan->pipeline == TSQ_PIPE_FUSED && !force_staged) {
+        if (use_direct(plan)) return hip_rc(launch_ordered(p, plan->g, 0, d_in, d_blob, d_ws, stream));
         uint32_t grid = 0;
         st = fused_grid(plan, &grid);
         // TSQ_PIPE_AUTO: a device that cannot tell how many workgroups it holds, or holds fewer than the
@@ -293,7 +311,7 @@ static tsq_status compress_call(const tsq_plan *plan, const void *d_in, uint32_t
         if (!fits && plan->cfg.pipeline != TSQ_PIPE_AUTO) return st != TSQ_OK ? st : TSQ_ERR_UNSUPPORTED;
         if (fits) {
             p.fused_classes = grid < kTicketClasses ? grid : kTicketClasses;
-            return hip_rc(launch_fused_ordered(p, plan->g, grid, d_in, d_blob, d_ws, stream));
+            return hip_rc(launch_ordered(p, plan->g, grid, d_in, d_blob, d_ws, stream));
         }
     }
     int e = launch_row_stats(p, plan->g, d_in, d_blob, d_ws, stream);
@@ -372,10 +390,14 @@ tsq_status tsq_compress_timed(const tsq_plan *plan, const void *d_in, void *d_bl
     (void)hipEventRecord(ev[0], s);
     if (plan->pipeline == TSQ_PIPE_FUSED) {
         uint32_t grid = 0;
-        st = fused_grid(plan, &grid);
         Params p = plan->p;
-        p.fused_classes = grid < kTicketClasses ? grid : kTicketClasses;
-        if (st == TSQ_OK && grid >= 1) rc = launch_fused(p, plan->g, grid, d_in, d_blob, d_ws, stream); else rc = 1;
+        if (use_direct(plan)) {
+            rc = launch_direct(p, plan->g, d_in, d_blob, d_ws, stream);
+        } else {
+            st = fused_grid(plan, &grid);
+            p.fused_classes = grid < kTicketClasses ? grid : kTicketClasses;
+            if (st == TSQ_OK && grid >= 1) rc = launch_fused(p, plan->g, grid, d_in, d_blob, d_ws, stream); else rc = 1;
+        }
         (void)hipEventRecord(ev[1], s);
         n = 1;
     } else {

@@ -689,8 +689,7 @@ __device__ __forceinline__ Choice search_width(const Params &p, const Mags<DT> &
 }
 
 // The 128-byte header at the start of the blob (written by one thread).
-__device__ __forceinline__ void write_header(const Params &p, uint8_t *blob, uint64_t nnz, uint64_t payload_bytes,
-                                             uint32_t status) {
+__device__ __forceinline__ BlobHeader header_of(const Params &p, uint64_t nnz, uint64_t payload_bytes, uint32_t status) {
     BlobHeader h;
     h.magic = kMagic; h.version = kVersion; h.dtype = p.dtype; h.tokens = p.tokens; h.hidden = p.hidden;
     h.tau_bits = __float_as_uint(p.tau); h.bit_mask = p.bit_mask; h.budget_bits = __float_as_uint(p.budget);
@@ -701,7 +700,22 @@ __device__ __forceinline__ void write_header(const Params &p, uint8_t *blob, uin
     h.off_row_ptr = p.off_row_ptr; h.off_payload = p.off_payload; h.off_out_col = p.off_out_col;
     h.off_out_val = p.off_out_val; h.payload_capacity = p.payload_capacity;
     h.outlier_capacity = p.outlier_capacity;
-    *reinterpret_cast<BlobHeader *>(blob) = h;
+    return h;
+}
+__device__ __forceinline__ void write_header(const Params &p, uint8_t *blob, uint64_t nnz, uint64_t payload_bytes,
+                                             uint32_t status) {
+    *reinterpret_cast<BlobHeader *>(blob) = header_of(p, nnz, payload_bytes, status);
+}
+// all of it but the status word
+__device__ __forceinline__ void write_header_but_status(const Params &p, uint8_t *blob, uint64_t nnz, uint64_t payload_bytes) {
+    const BlobHeader h = header_of(p, nnz, payload_bytes, 0u);
+    BlobHeader *dst = reinterpret_cast<BlobHeader *>(blob);
+    dst->magic = h.magic; dst->version = h.version; dst->dtype = h.dtype; dst->tokens = h.tokens; dst->hidden = h.hidden;
+    dst->tau_bits = h.tau_bits; dst->bit_mask = h.bit_mask; dst->budget_bits = h.budget_bits; dst->mode = h.mode;
+    dst->nnz = h.nnz; dst->payload_bytes = h.payload_bytes;
+    dst->off_bits = h.off_bits; dst->off_scale = h.off_scale; dst->off_pay_off = h.off_pay_off;
+    dst->off_row_ptr = h.off_row_ptr; dst->off_payload = h.off_payload; dst->off_out_col = h.off_out_col;
+    dst->off_out_val = h.off_out_val; dst->payload_capacity = h.payload_capacity; dst->outlier_capacity = h.outlier_capacity;
 }
 
 }  // namespace tsq

@@ -1,0 +1,295 @@
+// Single-pass compress for calls of few tokens (gfx950): one workgroup per token, dispatched in token order,
+// nothing handed out and nobody in between.
+//
+// With as many workgroups as tokens a call is one chain of latencies: row from HBM, threshold split, width
+// search, publication of the token's size, sizes of the tokens before it, stores.  The persistent kernel
+// (tsq_fused.hip) adds to that chain a ticket before the row, a scanner's round between a token's publication
+// and its prefix, and a count of finished waves that the scanner waits for before it closes the blob; those
+// are worth their time when a workgroup has many tokens, and are most of the call when it has one.
+//
+// Placement: the tokens are cut into blocks of kDirectBlock.  A workgroup adds up, for itself, the published
+// words of the tokens before it in its block (one or a few words per thread) and the prefix word of the
+// block's first token, which the last token of the block before has published.  Whoever waits, waits for
+// tokens of lower index only, and workgroups start in index order (on each die, in the order of those it
+// gets): the lowest unfinished token never waits for one that has not started, so every call ends,
+// whatever the number of workgroups that fit the device.  Every wait is bounded by p.spin_limit all the same.
+//
+// The last token's workgroup closes the blob: by the time it has its prefix every token is published, so
+// everybody has read the call's epoch and it can be moved on.  The header's status word is stored (device
+// scope) before anything else by that workgroup, and it reads the workspace's error word after that store has
+// been performed; a workgroup that fails raises the error word first and stores TSQ_ERR_INTERNAL into the status
+// word after that.  Whichever comes first, a failure ends up in the header.
+#include <hip/hip_runtime.h>
+
+#include "tsq_device.hpp"
+#include "tsq_internal.hpp"
+#include "tsq_pass.hpp"
+
+namespace tsq {
+
+constexpr uint32_t kStatusWord = 9;                      // BlobHeader::status, in 32-bit words
+static_assert(offsetof(BlobHeader, status) == 4 * kStatusWord, "status word of the header");
+constexpr uint32_t kStatusFormat = 5u, kStatusInternal = 6u, kStatusCapacity = 3u;
+
+__device__ __forceinline__ void store_status(uint8_t *blob, uint32_t status) {
+    word_store(reinterpret_cast<uint32_t *>(blob) + kStatusWord, status);
+}
+__device__ __forceinline__ void memory_operations_performed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Payload words of a token of width b (0 for the width 0 of a word that counts nothing).
+__device__ __forceinline__ uint32_t token_words(const Params &p, uint32_t b) { return (p.hidden * b + 31u) >> 5; }
+
+template <int B, int DT>
+__device__ __forceinline__ void pack_codes(const uint32_t (&m)[8], const Mags<DT> &mg, uint32_t (&o)[8]) {
+    uint32_t t[B];
+    pack_regs<B, DT>(m, mg, t);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) o[k] = k < B ? t[k] : 0u;
+}
+
+// LDS map (dynamic): row, later the codes: runs*16 dwords | ring: four reduce areas
+template <int DT, int NW, bool FULL>
+__global__ void __launch_bounds__(64 * NW, DT == kF16 && NW <= 4 ? 8 : 5)
+k_direct(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ blob, uint8_t *__restrict__ ws) {
+    extern __shared__ __align__(16) uint32_t lds[];
+    const uint32_t t = blockIdx.x, tid = threadIdx.x, lane = tid & 63u, wv = uniform(tid >> 6);
+    const uint32_t runs = FULL ? 64u * NW : p.runs, pieces = FULL ? 256u * NW : p.pieces;
+    const bool owns = FULL || tid < runs;
+    const uint32_t left = FULL ? 4u : (owns ? pieces - 4u * tid : 0u);    // 16-byte pieces of the lane's run inside the row
+    uint32_t *lrow = lds, *ring = lds + runs * 16u;
+    const bool last = t == p.tokens - 1u;
+
+    RowPart part;
+    fetch_row_part<FULL>(reinterpret_cast<const uint4 *>(row_address(p, in, t, FULL ? 2048u * NW : p.hidden)), pieces, part);
+
+    // error word, shape and epoch of the workspace, one per lane of one load
+    uint32_t *ctrl = reinterpret_cast<uint32_t *>(ws + p.ws_ctrl);
+    uint32_t *tickets = reinterpret_cast<uint32_t *>(ws + p.ws_tickets);
+    uint32_t *error_flag = ctrl + kCtlError;
+    const uint32_t *mine = lane == 0 ? error_flag : lane == 1 ? ctrl + kCtlTokens : lane == 2 ? ctrl + kCtlHidden : tickets + kCntTickets;
+    const uint32_t state = __hip_atomic_load(mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+
+    write_row_part_sw<FULL>(lrow, runs, part);
+    Mags<DT> mg;
+    uint32_t omask = 0, amax_bits = 0, turn = 0;
+    {
+        uint32_t w[16];
+        load_run_sw(lrow, owns ? tid : 0u, w);
+        split_regs<DT, true>(w, p.thr_pk, mg, omask, amax_bits);
+    }
+    if (!owns) { omask = 0; amax_bits = 0; }
+
+    // a workspace of another shape (or never reset), or one that an earlier call left in its failed state: nothing
+    // in it is touched, and the blob says so
+    const bool shape_ok = workspace_shape_ok(lane_value(state, 1), lane_value(state, 2), p.tokens, p.hidden);
+    if (!shape_ok || lane_value(state, 0)) {
+        if (last && tid == 0) write_header(p, blob, 0, 0, shape_ok ? kStatusInternal : kStatusFormat);
+        return;
+    }
+    const uint32_t epoch = (lane_value(state, 3) >> kTicketBits) % 3u, tag = epoch + 1u;
+    if (last && tid == 0) store_status(blob, 0u);
+
+    const uint32_t nl = (uint32_t)__builtin_popcount(omask);
+    const uint32_t upto = wave_incl_scan_u32(nl);                 // outliers of the wave's lanes up to this one
+    const RowStats st = reduce_row_stats_counted<NW>(amax_bits, lane_value(upto, 63), ring, turn);
+    uint32_t m[8];
+    const Choice c = search_width<DT, NW>(p, mg, st.amax, owns, ring, turn, m);
+
+    uint32_t *sizes = reinterpret_cast<uint32_t *>(ws + p.ws_sizes);
+    uint64_t *pre = reinterpret_cast<uint64_t *>(ws + p.ws_prefix);
+    if (tid == 0) {
+        word_store(sizes + t, (tag << 30) | (c.width << 26) | st.cnt);
+        blob[p.off_bits + t] = (uint8_t)c.width;
+        reinterpret_cast<float *>(blob + p.off_scale)[t] = c.scale;
+    }
+
+    // ---- codes of the lane's run at the chosen width
+    uint32_t codes[8];
+    switch (c.width) {
+        case 2: pack_codes<2, DT>(m, mg, codes); break;
+        case 3: pack_codes<3, DT>(m, mg, codes); break;
+        case 4: pack_codes<4, DT>(m, mg, codes); break;
+        case 5: pack_codes<5, DT>(m, mg, codes); break;
+        case 6: pack_codes<6, DT>(m, mg, codes); break;
+        case 7: pack_codes<7, DT>(m, mg, codes); break;
+        default: pack_codes<8, DT>(m, mg, codes); break;
+    }
+    uint32_t ew = 0, ec = 0, bad = 0, spins = 0;
+
+    // ---- what lies before the token: asked for now, looked at when the codes are packed
+    constexpr uint32_t kAhead = 4;
+    const uint32_t t0 = t & ~(kDirectBlock - 1u);
+    const uint32_t none = tag << 30;                              // a word that counts nothing
+    uint64_t base = (uint64_t)none << 32;
+    if (t0 && wv == 0) base = prefix_load(pre + t0 + opaque_zero());
+    uint32_t w[kAhead];
+#pragma unroll
+    for (uint32_t k = 0; k < kAhead; ++k) {
+        const uint32_t j = t0 + tid + 64u * NW * k;
+        w[k] = none;
+        if (j < t) w[k] = word_load(sizes + j);
+    }
+
+    for (uint32_t j0 = t0;;) {
+        for (;;) {
+            bool missing = false;
+#pragma unroll
+            for (uint32_t k = 0; k < kAhead; ++k) missing |= (w[k] >> 30) != tag;
+            if (__builtin_amdgcn_ballot_w64(missing) == 0) break;
+            if (!keep_waiting(spins, p.spin_limit, error_flag)) { bad = 1; break; }
+#pragma unroll
+            for (uint32_t k = 0; k < kAhead; ++k)
+                if ((w[k] >> 30) != tag) w[k] = word_load(sizes + j0 + tid + 64u * NW * k);
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < kAhead; ++k) {
+            ew += token_words(p, (w[k] >> 26) & 15u);
+            ec += w[k] & 0xFFFFu;
+        }
+        j0 += 64u * NW * kAhead;
+        if (bad || j0 >= t) break;
+#pragma unroll
+        for (uint32_t k = 0; k < kAhead; ++k) {
+            const uint32_t j = j0 + tid + 64u * NW * k;
+            w[k] = none;
+            if (j < t) w[k] = word_load(sizes + j);
+        }
+    }
+    if (wv == 0) {
+        while ((uint32_t)(base >> 62) != tag && !bad) {
+            if (!keep_waiting(spins, p.spin_limit, error_flag)) bad = 1;
+            else base = prefix_load(pre + t0 + opaque_zero());
+        }
+        if (lane == 0) {
+            ew += (uint32_t)(base >> 32) & 0x3FFFFFFFu;
+            ec += (uint32_t)base;
+        }
+    }
+    if (NW > 1) {
+        // (a reduce area holds two values per wave; the third travels in the next one)
+        uint32_t *also = ring + ((turn + 1u) & 3u) * 2 * kMaxWaves;
+        if (lane == 0) also[wv] = bad;
+        block_sum2_nw<NW>(ew, ec, ring + (turn & 3u) * 2 * kMaxWaves);
+        bad = 0;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) bad |= also[k];
+        bad = uniform(bad);
+    } else {
+        block_sum2_nw<NW>(ew, ec, ring);
+    }
+
+    const uint32_t words = token_words(p, c.width);
+    const uint32_t payload_words = (uint32_t)(p.payload_capacity >> 2), outlier_capacity = (uint32_t)p.outlier_capacity;
+    if ((uint64_t)ew + words > (uint64_t)payload_words) bad = 1;     // never leaves the section, whatever the tables said
+    if (bad) {
+        if (lane == 0) {
+            raise_error(error_flag);
+            store_status(blob, kStatusInternal);
+        }
+        return;
+    }
+    if (tid == 0) {
+        if (((t + 1u) & (kDirectBlock - 1u)) == 0) prefix_store(pre + t + 1u, prefix_word(tag, ew + words, ec + st.cnt));
+        reinterpret_cast<uint64_t *>(blob + p.off_pay_off)[t] = (uint64_t)ew << 2;
+        reinterpret_cast<uint64_t *>(blob + p.off_row_ptr)[t] = ec;
+    }
+
+    // ---- T_above of the lane's run, in column order
+    if (nl && (uint64_t)ec + st.cnt <= (uint64_t)outlier_capacity) {
+        uint32_t pos = ec + st.cnt_before + upto - nl;
+        uint16_t *col = reinterpret_cast<uint16_t *>(blob + p.off_out_col), *val = reinterpret_cast<uint16_t *>(blob + p.off_out_val);
+        for (uint32_t rest = omask; rest; rest &= rest - 1u) {
+            const uint32_t j = (uint32_t)__builtin_ctz(rest);
+            col[pos] = (uint16_t)(tid * kRun + j);
+            val[pos] = raw_element_sw(lrow, tid, j);
+            ++pos;
+        }
+    }
+    // ---- the codes into the wave's part of the row's place in LDS (the row has been used), and from there to their
+    //      place in the blob, 16 bytes per lane and step
+    if (owns) {
+        uint32_t *dst = lrow + wv * (64u * 16u) + lane * c.width;
+        const uint32_t nd = (FULL || left >= 4) ? c.width : ((left * c.width + 3u) >> 2);
+        switch (c.width) {
+            case 2: put_codes<2, FULL>(dst, codes, nd); break;
+            case 3: put_codes<3, FULL>(dst, codes, nd); break;
+            case 4: put_codes<4, FULL>(dst, codes, nd); break;
+            case 5: put_codes<5, FULL>(dst, codes, nd); break;
+            case 6: put_codes<6, FULL>(dst, codes, nd); break;
+            case 7: put_codes<7, FULL>(dst, codes, nd); break;
+            default: put_codes<8, FULL>(dst, codes, nd); break;
+        }
+    }
+    {
+        const uint32_t first = 64u * wv * c.width;                    // the wave's first word of the row
+        const uint32_t n = words > first ? (words - first < 64u * c.width ? words - first : 64u * c.width) : 0u;
+        const uint32_t *img = lrow + wv * (64u * 16u);
+        uint8_t *dst = blob + p.off_payload + 4ull * (ew + first);
+        const uint32_t quads = n >> 2, rest = n & 3u;
+        const __amdgpu_buffer_rsrc_t window = raw_window(dst, n << 2);
+#pragma unroll
+        for (uint32_t k = 0; k < 2; ++k) {
+            const uint32_t i = lane + 64u * k;
+            if (i < quads) store_quad_through(window, 16u * i, *reinterpret_cast<const u32x4 *>(img + 4u * i));
+        }
+        if (lane < rest) *reinterpret_cast<uint32_t *>(dst + 4u * (4u * quads + lane)) = img[4u * quads + lane];
+    }
+    if (!last || wv != 0) return;
+
+    // ---- the last token's first wave closes the blob
+    const uint32_t all_words = ew + words;
+    const uint64_t all_outliers = (uint64_t)ec + st.cnt;
+    word_store(tickets + lane * kTicketStride + kCntTickets, ((epoch + 1u) % 3u) << kTicketBits);   // everybody has this call's
+    if (lane == 0) {
+        memory_operations_performed();                               // the status word's zero among them
+        const bool failed = word_load(error_flag + opaque_zero()) != 0;
+        reinterpret_cast<uint64_t *>(blob + p.off_row_ptr)[p.tokens] = all_outliers;
+        reinterpret_cast<uint64_t *>(blob + p.off_pay_off)[p.tokens] = (uint64_t)all_words << 2;
+        write_header_but_status(p, blob, all_outliers, (uint64_t)all_words << 2);
+        if (failed || all_outliers > p.outlier_capacity) store_status(blob, failed ? kStatusInternal : kStatusCapacity);
+    }
+}
+
+// ---------------------------------------------------------------- launcher
+
+typedef void (*DirectKernel)(const Params, const uint16_t *, uint8_t *, uint8_t *);
+
+template <int DT, bool FULL>
+static DirectKernel direct_kernel_for(uint32_t nw) {
+    switch (nw) {
+        case 1: return k_direct<DT, 1, FULL>;
+        case 2: return k_direct<DT, 2, FULL>;
+        case 3: return k_direct<DT, 3, FULL>;
+        case 4: return k_direct<DT, 4, FULL>;
+        case 8: return k_direct<DT, 8, FULL>;
+        default: return k_direct<DT, 16, FULL>;
+    }
+}
+static DirectKernel direct_kernel(uint32_t dtype, uint32_t nw, bool full) {
+    if (dtype == (uint32_t)kF16) return full ? direct_kernel_for<kF16, true>(nw) : direct_kernel_for<kF16, false>(nw);
+    return full ? direct_kernel_for<kBF16, true>(nw) : direct_kernel_for<kBF16, false>(nw);
+}
+
+static uint32_t direct_lds_bytes(uint32_t runs) { return (runs * 16u + 4u * 2u * kMaxWaves) * 4u; }
+
+int prepare_direct_kernels() {
+    const int big = (int)direct_lds_bytes(kMaxHidden / kRun);
+    static const uint32_t sizes[] = {1, 2, 3, 4, 8, 16};
+    for (uint32_t dt = 0; dt < 2; ++dt)
+        for (uint32_t nw : sizes)
+            for (int full = 0; full < 2; ++full) {
+                const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(direct_kernel(dt, nw, full != 0)),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, big);
+                if (e != hipSuccess) return (int)e;
+            }
+    return 0;
+}
+
+int launch_direct(const Params &p, const Geometry &g, const void *d_in, void *d_blob, void *d_ws, void *stream) {
+    hipLaunchKernelGGL(direct_kernel(p.dtype, g.waves, p.hidden == 2048u * g.waves), dim3(p.tokens), dim3(64u * g.waves),
+                       direct_lds_bytes(p.runs), reinterpret_cast<hipStream_t>(stream), p, static_cast<const uint16_t *>(d_in),
+                       static_cast<uint8_t *>(d_blob), static_cast<uint8_t *>(d_ws));
+    return (int)hipGetLastError();
+}
+
+}  // namespace tsq

@@ -26,6 +26,8 @@ constexpr uint32_t kStashWave = 232;
 constexpr uint32_t kFusedGridCap = 4096;
 constexpr uint32_t kTicketClasses = 64, kTicketStride = 64;
 constexpr uint32_t kFusedScratchDw = 4 * 2 * kMaxWaves + 8;
+// one workgroup per token (tsq_direct.hip): tokens per block of the placement
+constexpr uint32_t kDirectBlock = 2048;
 // words of a workspace's control block
 constexpr uint32_t kCtlError = 1, kCtlTokens = 2, kCtlHidden = 3;
 
@@ -131,9 +133,11 @@ int launch_pack(const Params &p, const Geometry &g, const void *d_in, void *d_bl
                 void *stream);
 int launch_fused(const Params &p, const Geometry &g, uint32_t grid, const void *d_in, void *d_blob,
                  void *d_ws, void *stream);
+int launch_direct(const Params &p, const Geometry &g, const void *d_in, void *d_blob, void *d_ws, void *stream);
 uint32_t compress_waves(uint32_t runs);
 int fused_resident_workgroups(const Params &p, const Geometry &g, uint32_t *out);
 int prepare_fused_kernels();
+int prepare_direct_kernels();
 int launch_ws_reset(const Params &p, void *d_ws, void *stream);
 int launch_unpack(const Params &p, const Geometry &g, const void *d_blob, void *d_out, void *stream);
 int launch_code_hist(const Params &p, const Geometry &g, const void *d_blob, void *d_hist, void *stream);
