@@ -442,6 +442,21 @@ _PIPES = {"auto": TSQ_PIPE_AUTO, "staged": TSQ_PIPE_STAGED, "fused": TSQ_PIPE_FU
 _RULES = {"last_passing": TSQ_RETURN_LAST_PASSING, "as_printed": TSQ_RETURN_AS_PRINTED}
 
 
+_current_stream = None
+
+
+def _find_current_stream():
+    """-> function without arguments: the handle of torch's current stream on the current device.  The raw handle
+    takes 0.2 us to get; torch.cuda.current_stream() makes a Stream object first (2.9 us, two thirds of what
+    enqueueing a call takes altogether)."""
+    import torch
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is None or device is None:
+        return lambda: int(torch.cuda.current_stream().cuda_stream)
+    torch.cuda.init()
+    return lambda: raw(device())
+
+
 class Plan:
     """Owns one tsq_plan plus helpers that allocate torch buffers and pass their pointers."""
 
@@ -463,8 +478,10 @@ class Plan:
 
     @staticmethod
     def _stream() -> int:
-        import torch
-        return int(torch.cuda.current_stream().cuda_stream)
+        global _current_stream
+        if _current_stream is None:
+            _current_stream = _find_current_stream()
+        return _current_stream()
 
     def new_blob(self):
         import torch
