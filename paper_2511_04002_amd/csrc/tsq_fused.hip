@@ -16,8 +16,8 @@
 //
 // Per token a workgroup publishes one 32-bit word (tag, payload words, outliers) in a table.
 // The scanner reads the table in order, 512 or 1024 words per round, and for the leading run of
-// published tokens writes (tag, words before, outliers before) into a second table, and the
-// blob's pay_off / row_ptr entries on the way.  Nobody else adds anything up.  (One wave alone
+// published tokens writes (tag, words before, outliers before) into a second table, and (except for
+// rows of two waves) the blob's pay_off / row_ptr entries on the way.  Nobody else adds anything up.  (One wave alone
 // does not keep up with 200 tokens per microsecond: its rounds are chains of dependent steps.)
 //
 // A token is stored two iterations after it was computed: iteration i computes token i,
@@ -63,6 +63,14 @@ constexpr uint32_t kScanWavesMax = 4;   // waves of workgroup 0 that scan
 // (rows of 8192 elements and more: at most 160 tokens per us; the smaller window polls fewer lines that the
 // computing workgroups are writing to, which they notice)
 constexpr int scan_groups(int waves) { return waves >= 4 ? 8 : 16; }
+
+// Who writes the blob's pay_off and row_ptr entries of a token.  A round of the scanner ends when its stores have been
+// acknowledged (loads and stores share one counter on this chip, so the next round's loads are waited for together with
+// them), and a scanner of two waves, 512 tokens each, is what bounds rows of up to 4096 elements: with the two entries
+// left to the workgroup that stores the token, 65536 x 4096 f16 goes from 237 to 196 us (187 without any wait for a prefix),
+// 16384 x 4096 bf16 from 68 to 62.  Three waves: 80 x 1024 x 5120 f16 314 us with the scanner's contiguous stores, 329
+// without; four: 131072 x 8192 748 against 760.
+template <int R> constexpr bool kComputeWritesOffsets = R == 2;
 
 // The scanner: R waves of workgroup 0 (this one has index wv) work in rounds.  A round looks at
 // the next 64 * scan_groups(R) tokens from the frontier on, cut into groups of 64 that are dealt out to
@@ -170,8 +178,10 @@ __device__ void scan_tokens(const Params &p, uint8_t *blob, uint8_t *ws, uint32_
                 const uint32_t ec = bc + gb + (packed ? before[i] & 0x3FFFFFu : before[i]);
                 const uint32_t j = pos + 64u * k + lane;
                 prefix_store(pre + j, prefix_word(tag, ew, ec));
-                pay_off[j] = (uint64_t)ew << 2;
-                row_ptr[j] = ec;
+                if (!kComputeWritesOffsets<R>) {
+                    pay_off[j] = (uint64_t)ew << 2;
+                    row_ptr[j] = ec;
+                }
             }
         }
         bw += lane_value(upto2, 63);
@@ -380,6 +390,14 @@ __device__ __forceinline__ bool store_wave_part(const StoreTargets &o, const Pen
     return true;
 }
 
+// The blob's offsets of a token whose prefix is known, where the workgroup that stores the token writes them.
+template <int NW>
+__device__ __forceinline__ void write_offsets(uint64_t *pay_off, uint64_t *row_ptr, uint32_t token, const Prefix &x) {
+    if (!kComputeWritesOffsets<NW> || threadIdx.x != 0 || x.bad) return;
+    pay_off[token] = (uint64_t)x.ew << 2;
+    row_ptr[token] = x.ec;
+}
+
 // LDS map (dynamic): row: runs*16 | two payload images: runs*8 each | ring: 4 reduce areas |
 // ticket slots (8 dwords) | stashes: 2 x NW x kStashWave dwords
 constexpr uint32_t kLdsRing = 4 * 2 * kMaxWaves;
@@ -428,6 +446,8 @@ k_fused(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ b
 
     uint8_t *bits = blob + p.off_bits;
     float *scale = reinterpret_cast<float *>(blob + p.off_scale);
+    uint64_t *pay_off = reinterpret_cast<uint64_t *>(blob + p.off_pay_off);
+    uint64_t *row_ptr = reinterpret_cast<uint64_t *>(blob + p.off_row_ptr);
     uint16_t *out_col = reinterpret_cast<uint16_t *>(blob + p.off_out_col);
     uint16_t *out_val = reinterpret_cast<uint16_t *>(blob + p.off_out_val);
     const uint32_t hidden = FULL ? 2048u * NW : p.hidden;
@@ -552,6 +572,7 @@ k_fused(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ b
 
         // ---- store this wave's part of the token of two iterations ago: its image and stash are needed now
         if (have_old) {
+            write_offsets<NW>(pay_off, row_ptr, old.token, xo);
             if (xo.bad || !store_wave_part<DT, NW>(out, old, xo)) failed = 1;
             have_old = false;
         }
@@ -600,11 +621,13 @@ k_fused(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ b
     if (old_reread) reread_run(out, old.token, again);
     if (have_old) {
         const Prefix x = prefix_finish(p, pre, tag, old.token, last_old, error_flag);
+        write_offsets<NW>(pay_off, row_ptr, old.token, x);
         if (x.bad || !store_wave_part<DT, NW>(out, old, x, nullptr, old_reread ? &again : nullptr)) failed = 1;
     }
     if (have_young) {
         // the row of the workgroup's last token was not overwritten by a next one
         const Prefix x = prefix_finish(p, pre, tag, young.token, last_young, error_flag);
+        write_offsets<NW>(pay_off, row_ptr, young.token, x);
         if (x.bad || !store_wave_part<DT, NW>(out, young, x, lrow)) failed = 1;
     }
     // ---- this wave is done
