@@ -210,6 +210,7 @@ static tsq_status ensure_prepared() {
         g_prepare_rc = prepare_kernels();
         if (g_prepare_rc == 0) g_prepare_rc = prepare_fused_kernels();
         if (g_prepare_rc == 0) g_prepare_rc = prepare_direct_kernels();
+        if (g_prepare_rc == 0) g_prepare_rc = prepare_rans_kernels();
     });
     return hip_rc(g_prepare_rc);
 }

@@ -67,6 +67,7 @@ constexpr uint32_t kLenBlock = 256;     // tokens per partial sum of stream leng
 constexpr uint32_t kBlockStride = 64;   // 32-bit words from one partial sum to the next: the encoder's waves add to them, and
                                         // adds to one 128-byte line from all over the chip hold up the stores queued behind them
 constexpr uint32_t kMaxPoolGroups = 512;    // counting workgroups of 1024 threads: two fit a compute unit, 256 compute units: one round
+constexpr uint32_t kMaxDecodeGroups = 512;  // decoding workgroups of 1024 threads: the same
 constexpr uint32_t kPoolCopies = 16;    // sets of pooled counts: 16 times fewer atomic adds per address
 
 // Kernel argument block (passed by value).
@@ -138,6 +139,7 @@ uint32_t compress_waves(uint32_t runs);
 int fused_resident_workgroups(const Params &p, const Geometry &g, uint32_t *out);
 int prepare_fused_kernels();
 int prepare_direct_kernels();
+int prepare_rans_kernels();
 int launch_ws_reset(const Params &p, void *d_ws, void *stream);
 int launch_unpack(const Params &p, const Geometry &g, const void *d_blob, void *d_out, void *stream);
 int launch_code_hist(const Params &p, const Geometry &g, const void *d_blob, void *d_hist, void *stream);

@@ -17,9 +17,8 @@
 // (k_rans_encode) and adds its length to the stream bytes of its block of 256 tokens -> every token
 // finds its offset from the block sums before it and the lengths before it inside its block, and its
 // stream moves to its place (k_rans_gather).
-// Decode: one wave per token (k_rans_decode) rebuilds the packed payload; the words it reads
-// pass through registers (windows of 64 words), so a token needs 5 KB of LDS for its tables
-// and nothing else, and a compute unit holds its full 32 waves.
+// Decode: workgroups of sixteen waves, a token per wave at a time (k_rans_decode); a workgroup lays out in LDS,
+// for every width class among its tokens, what each of the 4096 slots decodes to, and its waves share that.
 #include <hip/hip_runtime.h>
 
 #include "tsq_device.hpp"
@@ -147,21 +146,6 @@ __device__ __forceinline__ void load_table(const uint16_t *table, uint2 *ftab) {
     for (int i = 0; i < 4; ++i) {
         const uint32_t fi = f[i] ? f[i] : 1u;
         ftab[4u * lane + i] = make_uint2(fi | (cum << 16), __float_as_uint(reciprocal_just_below(fi)));
-        cum += f[i];
-    }
-}
-
-// The decoder's form of the table: f | cum << 16 only (it never divides), 1 KB, so that a token's
-// tables take 5 KB of LDS and a compute unit holds 32 tokens at once.  Unknown codes keep f = 0.
-__device__ __forceinline__ void load_table_decode(const uint16_t *table, uint32_t *ftab) {
-    const uint32_t lane = threadIdx.x & 63u;
-    uint32_t f[4], s = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) { f[i] = table[4u * lane + i]; s += f[i]; }
-    uint32_t cum = wave_incl_scan_u32(s) - s;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        ftab[4u * lane + i] = f[i] | (cum << 16);
         cum += f[i];
     }
 }
@@ -375,113 +359,124 @@ k_rans_gather(const Params p, const EntropyLayout e, const uint8_t *__restrict__
 
 // ---------------------------------------------------------------- decode
 
-// Inclusive running maximum over the lanes of a wave, in lane order.
-__device__ __forceinline__ uint32_t wave_incl_scan_max(uint32_t v) {
-    uint32_t n;
-    n = dpp<kDppRowShr + 1>(v); v = n > v ? n : v;     // lanes without a source inside their row see 0
-    n = dpp<kDppRowShr + 2>(v); v = n > v ? n : v;
-    n = dpp<kDppRowShr + 4>(v); v = n > v ? n : v;
-    n = dpp<kDppRowShr + 8>(v); v = n > v ? n : v;
-    const uint32_t r0 = lane_value(v, 15), r1 = lane_value(v, 31), r2 = lane_value(v, 47);
-    const uint32_t row = (threadIdx.x & 63) >> 4;
-    uint32_t before = 0;
-    if (row > 0) before = r0;
-    if (row > 1) before = r1 > before ? r1 : before;
-    if (row > 2) before = r2 > before ? r2 : before;
-    return v > before ? v : before;
-}
+// What a slot decodes to, in one word: (f - 1) << 20 | (slot - cum) << 8 | code, so that a step of the decoder is one
+// look-up and x -> f (x >> 12) + slot - cum.  A class's 4096 words take 16 KB; a workgroup holds up to kDecTables
+// classes at once (more of them among its tokens, which is rare, are taken in a second go).
+//
+// What bounds it is instruction issue (and, at few tokens, the chain of a step: table, product, comparison, place, word).
+// A token per workgroup of one wave, with tables of its own in two steps (slot -> code -> f, cum) and the words of the
+// stream fetched out of other lanes' registers, took 25 vector and 3 LDS instructions per step and 600 per token
+// for the tables; this form 14 and 2 per step (21 with tables and ring).  8192 x 8192 bf16 48 -> 39 us, 32768 x 4096 f16
+// 116 -> 81, 131072 x 768 235 -> 163, 2000 x 16384 59 -> 45, 300 x 5120 21 -> 19.
+constexpr uint32_t kDecWaves = 16, kDecThreads = 64u * kDecWaves, kDecTables = 4, kDecTableWords = kProbScale;
+// A wave's words of the stream: a ring of two halves of 128 words, and the first 64 of them once more behind it, so
+// that the up to 64 words of a step always stand in a row.
+constexpr uint32_t kHalfWords = 128, kRingWords = 2 * kHalfWords + 64;
+constexpr uint32_t kDecLdsRings = kDecTables * kDecTableWords * 4u, kDecLdsBytes = kDecLdsRings + kDecWaves * kRingWords * 2u;
+// While tables are laid out the rings' place holds, per table, the list of the codes that occur (256 words) and
+// one bit per slot where a code's range starts (128 words).
+constexpr uint32_t kBuildWords = 256 + 128;
+static_assert(kDecTables * kBuildWords * 4u <= kDecWaves * kRingWords * 2u, "scratch of the table builders");
+static_assert(2u * kDecLdsBytes <= 160u * 1024u, "two workgroups per compute unit");
 
-// slot -> code for all 4096 slots: a code's index is written at the slot where its range starts,
-// and a running maximum carries it over the range (later codes start at later slots).
-__device__ __forceinline__ void build_slot_table(const uint32_t *ftab, uint32_t *sym32) {
+// Step 1, by one wave per table: lane l takes the codes 4l .. 4l+3.  The codes that occur are listed in the form
+// of a table word with cum in the place of slot - cum, and the slots where their ranges start are marked.
+__device__ __forceinline__ void list_codes(const uint16_t *freq, uint32_t *list, uint32_t *starts) {
     const uint32_t lane = threadIdx.x & 63u;
-    uint8_t *sym = reinterpret_cast<uint8_t *>(sym32);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) sym32[16u * lane + i] = 0;
-    __syncthreads();
+    uint32_t f[4], s = 0, n = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const uint32_t c = 4u * lane + i, fc = ftab[c];
-        if (fc & 0xFFFFu) sym[frequency_slot(fc >> 16)] = (uint8_t)c;   // masked: a damaged table stays inside the array
+        f[i] = freq[4u * lane + i];
+        s += f[i];
+        n += f[i] ? 1u : 0u;
     }
-    __syncthreads();
-    // lane l owns the slots 64l .. 64l+63
-    uint32_t w[16], mx = 0;
+    starts[lane] = 0;
+    starts[64u + lane] = 0;
+    uint32_t cum = wave_incl_scan_u32(s) - s, rank = wave_incl_scan_u32(n) - n;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        w[i] = sym32[16u * lane + i];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const uint32_t v = (w[i] >> (8 * k)) & 0xFFu;
-            mx = v > mx ? v : mx;
+    for (int i = 0; i < 4; ++i) {
+        if (f[i]) {
+            const uint32_t at = frequency_slot(cum);              // masked: a damaged table stays inside the array
+            list[rank] = ((f[i] - 1u) << 20) | (at << 8) | (4u * lane + i);
+            atomicOr(starts + (at >> 5), 1u << (at & 31u));
+            ++rank;
         }
+        cum += f[i];
     }
-    const uint32_t incl = wave_incl_scan_max(mx);
-    // the maximum over the lanes before this one: shift the inclusive result down by one lane
-    uint32_t run = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(((lane + 63u) & 63u) << 2), (int)incl);
-    if (lane == 0) run = 0;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        uint32_t o = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const uint32_t v = (w[i] >> (8 * k)) & 0xFFu;
-            run = v > run ? v : run;
-            o |= run << (8 * k);
-        }
-        sym32[16u * lane + i] = o;
+}
+// Step 2, by the waves of a table (this one is number `part` of `parts`), 64 slots at a time: the rank of a slot's
+// code is the number of ranges that start up to it.
+__device__ __forceinline__ void fill_table(const uint32_t *list, const uint32_t *starts, uint32_t *table, uint32_t part,
+                                           uint32_t parts) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t lo = starts[2u * lane], hi = starts[2u * lane + 1u];       // the marks of slots 64 lane .. 64 lane + 63
+    const uint32_t n = (uint32_t)__builtin_popcount(lo) + (uint32_t)__builtin_popcount(hi);
+    const uint32_t before = wave_incl_scan_u32(n) - n;
+    for (uint32_t i = part; i < kProbScale / 64u; i += parts) {
+        const uint32_t mlo = lane_value(lo, (int)i), mhi = lane_value(hi, (int)i);
+        const uint64_t above = (((uint64_t)mhi << 32) | mlo) >> 1;            // a lane counts the marks up to its own
+        uint32_t rank = lane_value(before, (int)i) + (mlo & 1u) + rank_in(above);
+        rank = rank ? rank - 1u : 0u;                                         // (0: only in a damaged table)
+        const uint32_t slot = 64u * i + lane, entry = list[rank & 255u];
+        table[slot] = (entry & 0xFFF000FFu) | (((slot - (entry >> 8)) & 0xFFFu) << 8);
     }
-    __syncthreads();
 }
 
-// The token's words as the decoder consumes them: windows of 64 words in registers (lane l of window k
-// holds word base + 64k + l).  A step reads at most 64 words from the first two windows, which share a
-// register (low / high half: one permute reads both); when the first is used up the windows move on by
-// one.  Behind them: two registers of two windows each (pair, next) and two of one window each (far),
-// which move on by two windows at every second move, when two new windows are asked for.  So a window is
-// not touched until two moves after it was asked for: by then it has arrived (a window is a cache line of
-// its own, fetched from memory for the first time), and no step waits for memory.
-// Past the end of the stream a window repeats the stream's last word: a stream that is not damaged is never
-// read there.
+typedef __attribute__((address_space(3))) uint8_t *LdsBytes;
+__device__ __forceinline__ uint32_t lds_address(const void *p) { return (uint32_t)(uintptr_t)(LdsBytes)p; }
+template <typename T> __device__ __forceinline__ T lds_at(uint32_t address) {
+    return *reinterpret_cast<const __attribute__((address_space(3))) T *>(address);
+}
+
+// The words of a token's stream on their way into the wave's ring, 128 (two per lane) at a time: two portions in
+// the ring, one in a register, which replaces the older of the two when that is used up, and the one behind it
+// is asked for.  Past the end of the stream a lane repeats the stream's last words: a stream that is not damaged is
+// never read there.
+typedef uint32_t __attribute__((may_alias)) TwoWords;       // (written two words at a time, read one at a time)
 struct Words {
-    const uint16_t *src;
-    uint32_t last, base;       // index of the last word; first word of the first window
-    uint32_t cur;              // the first two windows
-    uint32_t pair, next;       // windows 0, 1 and 2, 3 (odd = 0) or -1, 0 and 1, 2 (odd = 1)
-    uint32_t far0, far1;       // the two windows after those
-    uint32_t odd;              // one window of `pair` is used up
+    const uint32_t *src;
+    uint32_t last;             // index of the last pair of words
+    uint32_t ahead, portion;   // the portion in the register and its number
+    uint32_t ring;             // LDS address of the wave's ring
+    uint32_t at, end;          // ... of the next word, and of the end of the half it is in
 };
-__device__ __forceinline__ uint32_t word_at(const Words &q, uint32_t k) {
-    const uint32_t i = k + (threadIdx.x & 63u);
-    return (uint32_t)q.src[i < q.last ? i : q.last];
+__device__ __forceinline__ uint32_t pair_at(const Words &q, uint32_t portion) {
+    const uint32_t i = portion * (kHalfWords / 2u) + (threadIdx.x & 63u);
+    return q.src[i < q.last ? i : q.last];
 }
-// count words at src; `fallback` is readable memory for the case of no words at all
-__device__ __forceinline__ void words_open(Words &q, const uint16_t *src, uint32_t count, const uint16_t *fallback) {
-    q.src = count ? src : fallback; q.last = count ? count - 1u : 0u; q.base = 0; q.odd = 0;
-    q.pair = word_at(q, 0) | (word_at(q, 64) << 16); q.next = word_at(q, 128) | (word_at(q, 192) << 16);
-    q.far0 = word_at(q, 256); q.far1 = word_at(q, 320);
-    q.cur = q.pair;
+__device__ __forceinline__ void put_portion(const Words &q, uint32_t half, uint32_t v) {
+    const uint32_t lane = threadIdx.x & 63u;
+    __attribute__((address_space(3))) TwoWords *ring = reinterpret_cast<__attribute__((address_space(3))) TwoWords *>(q.ring);
+    ring[half * (kHalfWords / 2u) + lane] = v;
+    if (half == 0 && lane < 32u) ring[kHalfWords + lane] = v;
 }
-// the first window is used up
-__device__ __forceinline__ void words_move_on(Words &q) {
-    q.base += 64u;
-    if (q.odd) {                                              // (uniform)
-        q.pair = q.next;
-        q.next = q.far0 | (q.far1 << 16);
-        // (the loads stay behind the last use of the registers they fill: moved ahead of it, they would need
-        // other registers and copies, which would wait for them)
-        asm volatile("; the far windows have moved, their registers are asked for again" : "+v"(q.pair), "+v"(q.next) : : "memory");
-        q.far0 = word_at(q, q.base + 256u);
-        q.far1 = word_at(q, q.base + 320u);
+// count words at src; `fallback` is readable memory for the case of no words at all (both 4-byte aligned)
+__device__ __forceinline__ void words_open(Words &q, const uint32_t *src, uint32_t count, const uint32_t *fallback, uint32_t ring) {
+    q.src = count ? src : fallback; q.last = count ? (count - 1u) >> 1 : 0u; q.ring = ring;
+    const uint32_t a = pair_at(q, 0), b = pair_at(q, 1);
+    q.ahead = pair_at(q, 2);
+    q.portion = 2;
+    put_portion(q, 0, a);
+    put_portion(q, 1, b);
+    q.at = ring;
+    q.end = ring + 2u * kHalfWords;
+}
+// `n` (at most 64) more words have been read
+__device__ __forceinline__ void words_advance(Words &q, uint32_t n) {
+    q.at += 2u * n;
+    if (q.at >= q.end) {                                      // (uniform)
+        put_portion(q, q.portion & 1u, q.ahead);
+        ++q.portion;
+        if (q.end == q.ring + 4u * kHalfWords) { q.at -= 4u * kHalfWords; q.end -= 4u * kHalfWords; }
+        q.end += 2u * kHalfWords;
+        q.ahead = pair_at(q, q.portion);
     }
-    q.odd ^= 1u;
-    q.cur = q.odd ? (q.pair >> 16) | (q.next << 16) : q.pair;
 }
 
 // A SIMD holds the waves of eight tokens, each a chain of dependent steps, and its arbiter prefers the oldest
 // wave: left alone, the waves finish one after the other and the last ones run with the SIMD half idle.  A wave
 // therefore lowers its issue priority as it gets ahead (by quarters of its rounds), which keeps the eight in
-// step: the decoder of C4 takes 54 us instead of 60.  (The encoder, whose steps wait less, gains nothing from it.)
+// step.  (The encoder, whose steps wait less, gains nothing from it.)
 // `done` of `total` rounds are behind the wave (uniform).
 __device__ __forceinline__ void priority_by_progress(uint32_t done, uint32_t total) {
     switch ((4u * done) / total) {
@@ -492,92 +487,153 @@ __device__ __forceinline__ void priority_by_progress(uint32_t done, uint32_t tot
     }
 }
 
+// The code of a step behind the codes that word d already holds: the low `bits` bits of `entry` become the top ones.
+__device__ __forceinline__ uint32_t append_code(uint32_t entry, uint32_t d, int bits) {
+    return __builtin_amdgcn_alignbit(entry, d, bits);
+}
+
+// The 32 steps of one round (a lane's run number `run`).  WHOLE: every lane's run lies inside the row or wholly
+// beyond it (valid >= 32 or <= 0): no step needs a range check, the lanes beyond the row run idle with a limit that
+// keeps them from taking words.  table: LDS address of the class's table, a multiple of its size.
+// A step is bound by instruction issue, so what the compiler would make more of than there is to it is pinned down by
+// empty asm statements: the comparison with a register, the word read by every lane, x + off before the product.
 template <int B, bool WHOLE>
-__device__ __forceinline__ void decode_round(uint32_t *dst_row, uint32_t run, int valid, const uint32_t *ftab,
-                                             const uint8_t *sym, Words &q, uint32_t &pos, uint32_t &x) {
+__device__ __forceinline__ void decode_round(uint32_t *dst_row, uint32_t run, int valid, uint32_t table, Words &q, uint32_t &x) {
     uint32_t d[B];
 #pragma unroll
     for (int k = 0; k < B; ++k) d[k] = 0;
+    uint32_t limit = valid > 0 ? kRansLow : 0u, mask = 4u * (kDecTableWords - 1u), base = table;
+    asm("" : "+v"(limit), "+v"(mask), "+v"(base));
 #pragma unroll
     for (int j = 0; j < 32; ++j) {
-        const bool active = WHOLE || j < valid;
-        const uint32_t slot = frequency_slot(x);
-        const uint32_t s = sym[slot];
-        const uint32_t fc = ftab[s];
-        if (active) {
-            x = __umul24(fc & 0xFFFFu, x >> kProbBits) + slot - (fc >> 16);    // f <= 2^12, x >> 12 < 2^20
-            const int off = j * B, k = off >> 5, sh = off & 31;
-            d[k] |= s << sh;
-            if (sh + B > 32) d[k + 1 < B ? k + 1 : k] |= s >> (32 - sh);
-        }
-        const bool need = active && x < kRansLow;
+        const uint32_t entry = lds_at<uint32_t>(bitop3<kAndOr>(x << 2, mask, base));
+        const uint32_t xh = x >> kProbBits;
+        uint32_t y = xh + ((entry >> 8) & 0xFFFu);
+        asm("" : "+v"(y));
+        y = __umul24(entry >> 20, xh) + y;                                 // f <= 2^12, x >> 12 < 2^20
+        const uint32_t s = WHOLE || j < valid ? entry : entry & ~0xFFu;
+        const int off = j * B, k = off >> 5, room = 32 - (off & 31);
+        d[k] = append_code(s, d[k], room < B ? room : B);
+        if (room < B) d[k + 1 < B ? k + 1 : k] = (s >> room) << (32 - (B - room));
+        const bool need = y < limit && (WHOLE || j < valid);
         const uint64_t who = __builtin_amdgcn_ballot_w64(need);
-        if (who) {
-            const uint32_t at = pos - q.base + rank_in(who);   // < 128
-            const uint32_t both = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((at & 63u) << 2), (int)q.cur);
-            if (need) x = (x << 16) | ((both >> ((at & 64u) >> 2)) & 0xFFFFu);
-            pos += (uint32_t)__builtin_popcountll(who);
-            if (pos - q.base >= 64u) words_move_on(q);
-        }
+        // (every lane reads: the words of a step and the up to 64 behind them are in the ring)
+        uint32_t word = lds_at<uint16_t>((rank_in(who) << 1) + q.at);
+        asm("" : "+v"(word));
+        x = need ? (y << 16) | word : y;
+        words_advance(q, (uint32_t)__builtin_popcountll(who));
     }
-    const uint32_t nd = (WHOLE || valid >= 32) ? (uint32_t)B : (valid > 0 ? ((uint32_t)valid * B + 31u) >> 5 : 0u);
     if (WHOLE) {
-        store_run_words<B>(dst_row + run * B, d);
+        if (valid > 0) store_run_words<B>(dst_row + run * B, d);
     } else {
+        const uint32_t nd = valid >= 32 ? (uint32_t)B : (valid > 0 ? ((uint32_t)valid * B + 31u) >> 5 : 0u);
 #pragma unroll
         for (int k = 0; k < B; ++k)
             if ((uint32_t)k < nd) dst_row[run * B + k] = d[k];
     }
 }
 
-__global__ void __launch_bounds__(64, 8)    // 8 waves per SIMD: all 32 tokens of a compute unit's share run at once
-k_rans_decode(const Params p, const EntropyLayout e, const uint8_t *__restrict__ eblob, uint8_t *__restrict__ blob) {
-    __shared__ uint32_t ftab[256];
-    __shared__ uint32_t sym32[1024];                                   // slot -> code, one byte per slot
-    const uint32_t t = blockIdx.x, lane = threadIdx.x;
-    if (!blob_is_valid(p, blob) || !eblob_is_valid(p, e, eblob)) return;
-    const uint32_t width = blob[p.off_bits + t];
-    const uint64_t po = reinterpret_cast<const uint64_t *>(blob + p.off_pay_off)[t];
-    if (!token_in_range(p, width, po)) return;
+// What a wave knows of a token before it decodes it.
+struct CodedToken {
+    uint32_t width;
+    uint64_t po, a, b;         // payload offset; stream [a, b)
+};
+__device__ __forceinline__ void ask_for_token(const Params &p, const EntropyLayout &e, const uint8_t *blob, const uint8_t *eblob,
+                                              uint32_t t, CodedToken &k) {
     const uint64_t *off = reinterpret_cast<const uint64_t *>(eblob + e.off_stream_off);
-    const uint64_t a = off[t], b = off[t + 1];
+    k.width = blob[p.off_bits + t];
+    k.po = reinterpret_cast<const uint64_t *>(blob + p.off_pay_off)[t];
+    k.a = off[t];
+    k.b = off[t + 1];
+}
+
+// Workgroup g decodes the tokens per * g .. per * g + per - 1, a token per wave and turn.
+__global__ void __launch_bounds__(kDecThreads, 8)    // 8 waves per SIMD: two workgroups per compute unit
+k_rans_decode(const Params p, const EntropyLayout e, const uint8_t *__restrict__ eblob, uint8_t *__restrict__ blob, uint32_t per) {
+    extern __shared__ __align__(4 * kDecTableWords) uint32_t lds[];     // (tables, each at a multiple of its size; then the rings)
+    const uint32_t lane = threadIdx.x & 63u, wv = uniform(threadIdx.x >> 6);
+    const uint32_t t0 = blockIdx.x * per, t1 = p.tokens - t0 < per ? p.tokens : t0 + per;
     const uint32_t coders = p.runs < 64u ? p.runs : 64u;  // states in the stream; the other coders start (and stay) at 2^16
-    if (!stream_span_ok(a, b, e.stream_capacity, coders, e.slot_bytes)) return;
-    load_table_decode(reinterpret_cast<const uint16_t *>(eblob + e.off_tables) + (width - 2u) * 256u, ftab);
-    __syncthreads();
-    build_slot_table(ftab, sym32);
-    const uint8_t *sym = reinterpret_cast<const uint8_t *>(sym32);
-    const uint8_t *stream = eblob + e.off_streams + a;
-    Words q;
-    words_open(q, reinterpret_cast<const uint16_t *>(stream + 4u * coders), (uint32_t)(b - a - 4u * coders) >> 1,
-               reinterpret_cast<const uint16_t *>(stream));
-    uint32_t x = lane < coders ? reinterpret_cast<const uint32_t *>(stream)[lane] : kRansLow, pos = 0;
-    uint32_t *dst_row = reinterpret_cast<uint32_t *>(blob + p.off_payload + po);
     const uint32_t rounds = (p.runs + 63u) / 64u;
-    for (uint32_t r = 0; r < rounds; ++r) {
-        priority_by_progress(r, rounds);
-        const uint32_t run = lane + 64u * r;
-        const int valid = (int)p.hidden - (int)(run * kRun);
-        if (__builtin_amdgcn_ballot_w64(valid < 32) == 0) {
-            switch (width) {
-                case 2: decode_round<2, true>(dst_row, run, valid, ftab, sym, q, pos, x); break;
-                case 3: decode_round<3, true>(dst_row, run, valid, ftab, sym, q, pos, x); break;
-                case 4: decode_round<4, true>(dst_row, run, valid, ftab, sym, q, pos, x); break;
-                case 5: decode_round<5, true>(dst_row, run, valid, ftab, sym, q, pos, x); break;
-                case 6: decode_round<6, true>(dst_row, run, valid, ftab, sym, q, pos, x); break;
-                case 7: decode_round<7, true>(dst_row, run, valid, ftab, sym, q, pos, x); break;
-                default: decode_round<8, true>(dst_row, run, valid, ftab, sym, q, pos, x); break;
+    if (!blob_is_valid(p, blob) || !eblob_is_valid(p, e, eblob)) return;
+    uint32_t t = t0 + wv;
+    CodedToken next = {};
+    if (t < t1) ask_for_token(p, e, blob, eblob, t, next);
+    uint32_t classes = 0;                                 // bit b: a token of width b is among the workgroup's
+    for (uint32_t i = t0; i < t1; i += 64u) {
+        const uint32_t b = i + lane < t1 ? blob[p.off_bits + i + lane] : 0u;
+#pragma unroll
+        for (uint32_t k = 2; k <= 8; ++k)
+            if (__builtin_amdgcn_ballot_w64(b == k)) classes |= 1u << k;
+    }
+
+    const uint32_t ring = lds_address(lds) + kDecLdsRings + wv * kRingWords * 2u;
+    for (classes = uniform(classes); classes;) {
+        // ---- the tables of the next classes: each laid out by the waves k, k + n, ...
+        const uint32_t present = (uint32_t)__builtin_popcount(classes), n = present < kDecTables ? present : kDecTables;
+        uint32_t batch = 0, mine = 0;
+        const uint32_t k = wv % n, part = wv / n, parts = (kDecWaves - 1u - k) / n + 1u;
+        for (uint32_t i = 0; i < n; ++i) {
+            const uint32_t b = (uint32_t)__builtin_ctz(classes);
+            classes &= classes - 1u;
+            batch |= 1u << b;
+            if (i == k) mine = b;
+        }
+        uint32_t *list = lds + kDecLdsRings / 4u + k * kBuildWords, *starts = list + 256;
+        if (part == 0) list_codes(reinterpret_cast<const uint16_t *>(eblob + e.off_tables) + (mine - 2u) * 256u, list, starts);
+        __syncthreads();
+        fill_table(list, starts, lds + k * kDecTableWords, part, parts);
+        __syncthreads();
+
+        // ---- the tokens of these classes
+        for (; t < t1; t += kDecWaves) {
+            const CodedToken c = next;
+            if (t + kDecWaves < t1) ask_for_token(p, e, blob, eblob, t + kDecWaves, next);
+            const uint32_t width = uniform(c.width);
+            // a damaged token is skipped rather than read or written out of bounds
+            if (!((batch >> (width & 31u)) & 1u) || !token_in_range(p, width, c.po) ||
+                !stream_span_ok(c.a, c.b, e.stream_capacity, coders, e.slot_bytes))
+                continue;
+            const uint32_t table = lds_address(lds) + (uint32_t)__builtin_popcount(batch & ((1u << width) - 1u)) * (4u * kDecTableWords);
+            const uint32_t *stream = reinterpret_cast<const uint32_t *>(eblob + e.off_streams + c.a);
+            uint32_t x = kRansLow;
+            if (lane < coders) x = stream[lane];
+            Words q;
+            words_open(q, stream + coders, (uint32_t)(c.b - c.a - 4u * coders) >> 1, stream, ring);
+            uint32_t *dst_row = reinterpret_cast<uint32_t *>(blob + p.off_payload + c.po);
+            for (uint32_t r = 0; r < rounds; ++r) {
+                priority_by_progress(r, rounds);
+                const uint32_t run = lane + 64u * r;
+                const int valid = (int)p.hidden - (int)(run * kRun);
+                if (__builtin_amdgcn_ballot_w64(valid > 0 && valid < 32) == 0) {
+                    switch (width) {
+                    case 2: decode_round<2, true>(dst_row, run, valid, table, q, x); break;
+                    case 3: decode_round<3, true>(dst_row, run, valid, table, q, x); break;
+                    case 4: decode_round<4, true>(dst_row, run, valid, table, q, x); break;
+                    case 5: decode_round<5, true>(dst_row, run, valid, table, q, x); break;
+                    case 6: decode_round<6, true>(dst_row, run, valid, table, q, x); break;
+                    case 7: decode_round<7, true>(dst_row, run, valid, table, q, x); break;
+                    default: decode_round<8, true>(dst_row, run, valid, table, q, x); break;
+                    }
+                } else {
+                    switch (width) {
+                    case 2: decode_round<2, false>(dst_row, run, valid, table, q, x); break;
+                    case 3: decode_round<3, false>(dst_row, run, valid, table, q, x); break;
+                    case 4: decode_round<4, false>(dst_row, run, valid, table, q, x); break;
+                    case 5: decode_round<5, false>(dst_row, run, valid, table, q, x); break;
+                    case 6: decode_round<6, false>(dst_row, run, valid, table, q, x); break;
+                    case 7: decode_round<7, false>(dst_row, run, valid, table, q, x); break;
+                    default: decode_round<8, false>(dst_row, run, valid, table, q, x); break;
+                    }
+                }
             }
-        } else {
-            switch (width) {
-                case 2: decode_round<2, false>(dst_row, run, valid, ftab, sym, q, pos, x); break;
-                case 3: decode_round<3, false>(dst_row, run, valid, ftab, sym, q, pos, x); break;
-                case 4: decode_round<4, false>(dst_row, run, valid, ftab, sym, q, pos, x); break;
-                case 5: decode_round<5, false>(dst_row, run, valid, ftab, sym, q, pos, x); break;
-                case 6: decode_round<6, false>(dst_row, run, valid, ftab, sym, q, pos, x); break;
-                case 7: decode_round<7, false>(dst_row, run, valid, ftab, sym, q, pos, x); break;
-                default: decode_round<8, false>(dst_row, run, valid, ftab, sym, q, pos, x); break;
-            }
+        }
+        if (classes) {
+            // (more classes than tables: once more from the first token on)
+            __builtin_amdgcn_s_setprio(0);
+            __syncthreads();
+            t = t0 + wv;
+            if (t < t1) ask_for_token(p, e, blob, eblob, t, next);
         }
     }
 }
@@ -601,9 +657,17 @@ int launch_rans_encode(const Params &p, const Geometry &g, const EntropyLayout &
     return (int)hipGetLastError();
 }
 
+int prepare_rans_kernels() {
+    return (int)hipFuncSetAttribute(reinterpret_cast<const void *>(k_rans_decode), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)kDecLdsBytes);
+}
+
 int launch_rans_decode(const Params &p, const EntropyLayout &e, const void *d_eblob, void *d_blob, void *stream) {
-    hipLaunchKernelGGL(k_rans_decode, dim3(p.tokens), dim3(64), 0, as_stream(stream), p, e,
-                       static_cast<const uint8_t *>(d_eblob), static_cast<uint8_t *>(d_blob));
+    // one round of workgroups (two on each of 256 compute units), a token per wave if there are enough of them;
+    // fewer tokens are spread over as many workgroups as there are
+    const uint32_t per = (p.tokens + kMaxDecodeGroups - 1u) / kMaxDecodeGroups;
+    hipLaunchKernelGGL(k_rans_decode, dim3((p.tokens + per - 1u) / per), dim3(kDecThreads), kDecLdsBytes, as_stream(stream), p, e,
+                       static_cast<const uint8_t *>(d_eblob), static_cast<uint8_t *>(d_blob), per);
     return (int)hipGetLastError();
 }
 
