@@ -262,13 +262,13 @@ static int launch_single_pass(const Params &p, const Geometry &g, uint32_t grid,
 }
 // Which of the two a plan's calls take.  A function of the shape alone: a workspace serves every plan of its shape,
 // and the persistent kernel must find no prefix words in it that another call left out.
-// One workgroup per token is the faster form while the whole call fits the device about once (24 waves on each of
-// 256 compute units): 2048 x 4096 f16 13.7 us against 17.7, 2048 x 5120 14.5 / 18.1, 1237 x 8192 14.2 / 15.1, but
-// 4096 x 4096 24.9 / 23.9 and 3000 x 5120 25.0 / 21.4.  Rows of one wave gain at any number of tokens, since the
-// persistent kernel's scanner, which would have one wave there, is what bounds it: 8192 x 768 27.1 / 43.7 us,
-// 65536 x 768 209 / 275, 65536 x 2048 246 / 278.
+// One workgroup per token is the faster form while the call fits the device about once (32 waves on each of 256
+// compute units): 2048 x 4096 f16 12.6 us against 17.4, 4096 x 4096 21.8 / 22.8, 2048 x 8192 bf16 17.9 / 20.6, 700 x 12000
+// 14.3 / 19.8, but 2200 x 8192 f16 19.7 / 19.1 and 5000 x 4096 f16 26.0 / 25.2.  Rows of one wave gain at any number of
+// tokens, since the persistent kernel's scanner, which would have one wave there, is what bounds it: 8192 x 768 24 / 44
+// us, 65536 x 768 189 / 275.
 static bool use_direct(const tsq_plan *plan) {
-    return plan->g.waves == 1 || (uint64_t)plan->p.tokens * plan->g.waves <= 6144u;
+    return plan->g.waves == 1 || (uint64_t)plan->p.tokens * plan->g.waves <= 8192u;
 }
 
 static int launch_ordered(const Params &p, const Geometry &g, uint32_t grid, const void *d_in, void *d_blob,

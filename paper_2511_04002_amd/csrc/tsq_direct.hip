@@ -47,7 +47,8 @@ __device__ __forceinline__ void pack_codes(const uint32_t (&m)[8], const Mags<DT
     for (int k = 0; k < 8; ++k) o[k] = k < B ? t[k] : 0u;
 }
 
-// LDS map (dynamic): row, later the codes: runs*16 dwords | ring: four reduce areas
+// LDS map (dynamic): row: runs*16 dwords | codes: runs*8 | ring (rows of more than one wave): four reduce areas
+constexpr uint32_t kDirectRing = 4u * 2u * kMaxWaves;
 template <int DT, int NW, bool FULL>
 __global__ void __launch_bounds__(64 * NW, DT == kF16 && NW <= 4 ? 8 : 5)
 k_direct(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ blob, uint8_t *__restrict__ ws) {
@@ -56,7 +57,7 @@ k_direct(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ 
     const uint32_t runs = FULL ? 64u * NW : p.runs, pieces = FULL ? 256u * NW : p.pieces;
     const bool owns = FULL || tid < runs;
     const uint32_t left = FULL ? 4u : (owns ? pieces - 4u * tid : 0u);    // 16-byte pieces of the lane's run inside the row
-    uint32_t *lrow = lds, *ring = lds + runs * 16u;
+    uint32_t *lrow = lds, *image = lds + runs * 16u, *ring = lds + runs * 24u;
     const bool last = t == p.tokens - 1u;
 
     RowPart part;
@@ -97,6 +98,13 @@ k_direct(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ 
 
     uint32_t *sizes = reinterpret_cast<uint32_t *>(ws + p.ws_sizes);
     uint64_t *pre = reinterpret_cast<uint64_t *>(ws + p.ws_prefix);
+    // (the last token's workgroup looks for failures now, with the status word's zero long in place, and not when it
+    // closes the blob, where everybody would wait for the answer)
+    uint32_t raised = 0;
+    if (last && wv == 0) {
+        memory_operations_performed();
+        raised = word_load(error_flag + opaque_zero());
+    }
     if (tid == 0) {
         word_store(sizes + t, (tag << 30) | (c.width << 26) | st.cnt);
         blob[p.off_bits + t] = (uint8_t)c.width;
@@ -114,10 +122,28 @@ k_direct(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ 
         case 7: pack_codes<7, DT>(m, mg, codes); break;
         default: pack_codes<8, DT>(m, mg, codes); break;
     }
+    // ---- ... into the wave's part of their place in LDS.  Before anybody looks for the tokens before: a look that comes
+    //      too early costs a memory round trip (codes put there behind the wait, over the row: 512 x 5120 step 14.5 us
+    //      against 12.6, 128 x 768 f16 6.7 / 5.9, 65536 x 768 201 / 189)
+    if (owns) {
+        uint32_t *dst = image + wv * (64u * 8u) + lane * c.width;
+        const uint32_t nd = (FULL || left >= 4) ? c.width : ((left * c.width + 3u) >> 2);
+        switch (c.width) {
+            case 2: put_codes<2, FULL>(dst, codes, nd); break;
+            case 3: put_codes<3, FULL>(dst, codes, nd); break;
+            case 4: put_codes<4, FULL>(dst, codes, nd); break;
+            case 5: put_codes<5, FULL>(dst, codes, nd); break;
+            case 6: put_codes<6, FULL>(dst, codes, nd); break;
+            case 7: put_codes<7, FULL>(dst, codes, nd); break;
+            default: put_codes<8, FULL>(dst, codes, nd); break;
+        }
+    }
     uint32_t ew = 0, ec = 0, bad = 0, spins = 0;
 
-    // ---- what lies before the token: asked for now, looked at when the codes are packed
-    constexpr uint32_t kAhead = 4;
+    // ---- what lies before the token, 256 words at a time, the lowest first: by the time the next ones are asked for
+    //      they have been published, too.  (512 words at a time: 2048 x 4096 f16 13.3 us against 12.1, 700 x 8192 11.3 / 9.7;
+    //      128: 14.6 / 12.1; all 2048 at once 18.7)
+    constexpr uint32_t kReaders = NW < 4 ? NW : 4, kAhead = 4 / kReaders;
     const uint32_t t0 = t & ~(kDirectBlock - 1u);
     const uint32_t none = tag << 30;                              // a word that counts nothing
     uint64_t base = (uint64_t)none << 32;
@@ -125,9 +151,9 @@ k_direct(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ 
     uint32_t w[kAhead];
 #pragma unroll
     for (uint32_t k = 0; k < kAhead; ++k) {
-        const uint32_t j = t0 + tid + 64u * NW * k;
+        const uint32_t j = t0 + tid + 64u * kReaders * k;
         w[k] = none;
-        if (j < t) w[k] = word_load(sizes + j);
+        if (wv < kReaders && j < t) w[k] = word_load(sizes + j);
     }
 
     for (uint32_t j0 = t0;;) {
@@ -139,20 +165,20 @@ k_direct(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ 
             if (!keep_waiting(spins, p.spin_limit, error_flag)) { bad = 1; break; }
 #pragma unroll
             for (uint32_t k = 0; k < kAhead; ++k)
-                if ((w[k] >> 30) != tag) w[k] = word_load(sizes + j0 + tid + 64u * NW * k);
+                if ((w[k] >> 30) != tag) w[k] = word_load(sizes + j0 + tid + 64u * kReaders * k);
         }
 #pragma unroll
         for (uint32_t k = 0; k < kAhead; ++k) {
             ew += token_words(p, (w[k] >> 26) & 15u);
             ec += w[k] & 0xFFFFu;
         }
-        j0 += 64u * NW * kAhead;
+        j0 += 64u * kReaders * kAhead;
         if (bad || j0 >= t) break;
 #pragma unroll
         for (uint32_t k = 0; k < kAhead; ++k) {
-            const uint32_t j = j0 + tid + 64u * NW * k;
+            const uint32_t j = j0 + tid + 64u * kReaders * k;
             w[k] = none;
-            if (j < t) w[k] = word_load(sizes + j);
+            if (wv < kReaders && j < t) w[k] = word_load(sizes + j);
         }
     }
     if (wv == 0) {
@@ -205,25 +231,11 @@ k_direct(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ 
             ++pos;
         }
     }
-    // ---- the codes into the wave's part of the row's place in LDS (the row has been used), and from there to their
-    //      place in the blob, 16 bytes per lane and step
-    if (owns) {
-        uint32_t *dst = lrow + wv * (64u * 16u) + lane * c.width;
-        const uint32_t nd = (FULL || left >= 4) ? c.width : ((left * c.width + 3u) >> 2);
-        switch (c.width) {
-            case 2: put_codes<2, FULL>(dst, codes, nd); break;
-            case 3: put_codes<3, FULL>(dst, codes, nd); break;
-            case 4: put_codes<4, FULL>(dst, codes, nd); break;
-            case 5: put_codes<5, FULL>(dst, codes, nd); break;
-            case 6: put_codes<6, FULL>(dst, codes, nd); break;
-            case 7: put_codes<7, FULL>(dst, codes, nd); break;
-            default: put_codes<8, FULL>(dst, codes, nd); break;
-        }
-    }
+    // ---- the codes to their place in the blob, 16 bytes per lane and step
     {
         const uint32_t first = 64u * wv * c.width;                    // the wave's first word of the row
         const uint32_t n = words > first ? (words - first < 64u * c.width ? words - first : 64u * c.width) : 0u;
-        const uint32_t *img = lrow + wv * (64u * 16u);
+        const uint32_t *img = image + wv * (64u * 8u);
         uint8_t *dst = blob + p.off_payload + 4ull * (ew + first);
         const uint32_t quads = n >> 2, rest = n & 3u;
         const __amdgpu_buffer_rsrc_t window = raw_window(dst, n << 2);
@@ -241,12 +253,15 @@ k_direct(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ 
     const uint64_t all_outliers = (uint64_t)ec + st.cnt;
     word_store(tickets + lane * kTicketStride + kCntTickets, ((epoch + 1u) % 3u) << kTicketBits);   // everybody has this call's
     if (lane == 0) {
-        memory_operations_performed();                               // the status word's zero among them
-        const bool failed = word_load(error_flag + opaque_zero()) != 0;
+        const bool full = all_outliers > p.outlier_capacity;
+        if (full) {
+            memory_operations_performed();
+            raised = word_load(error_flag + opaque_zero());
+        }
         reinterpret_cast<uint64_t *>(blob + p.off_row_ptr)[p.tokens] = all_outliers;
         reinterpret_cast<uint64_t *>(blob + p.off_pay_off)[p.tokens] = (uint64_t)all_words << 2;
         write_header_but_status(p, blob, all_outliers, (uint64_t)all_words << 2);
-        if (failed || all_outliers > p.outlier_capacity) store_status(blob, failed ? kStatusInternal : kStatusCapacity);
+        if (raised || full) store_status(blob, raised ? kStatusInternal : kStatusCapacity);
     }
 }
 
@@ -270,7 +285,7 @@ static DirectKernel direct_kernel(uint32_t dtype, uint32_t nw, bool full) {
     return full ? direct_kernel_for<kBF16, true>(nw) : direct_kernel_for<kBF16, false>(nw);
 }
 
-static uint32_t direct_lds_bytes(uint32_t runs) { return (runs * 16u + 4u * 2u * kMaxWaves) * 4u; }
+static uint32_t direct_lds_bytes(uint32_t runs) { return (runs * 24u + (runs > 64u ? kDirectRing : 0u)) * 4u; }
 
 int prepare_direct_kernels() {
     const int big = (int)direct_lds_bytes(kMaxHidden / kRun);

@@ -20,11 +20,12 @@ def rows(T, H, dtype, heavy=0):
     return synth.to_f16_bits(v) if dtype == "f16" else synth.to_bf16_bits(v)
 
 
-# 24 waves on each of 256 compute units: tokens * waves <= 6144 (rows of one wave: always one workgroup per token)
+# tokens * waves <= 8192: one workgroup per token (rows of one wave: always)
 @pytest.mark.parametrize("T,H,dtype", [(2047, 72, "f16"), (2048, 72, "bf16"), (2049, 72, "f16"), (6145, 1000, "bf16"),
                                        (3072, 4096, "f16"), (3073, 4088, "bf16"), (2048, 5120, "bf16"), (2049, 6144, "f16"),
                                        (1536, 8192, "bf16"), (1537, 8192, "f16"), (385, 16384, "f16"), (769, 8200, "bf16"),
-                                       (100, 32768, "bf16")])
+                                       (100, 32768, "bf16"), (4096, 4096, "f16"), (4097, 2056, "bf16"), (2730, 5120, "f16"),
+                                       (2731, 6144, "bf16"), (512, 32768, "f16"), (513, 16400, "bf16")])
 def test_both_sides_of_the_line_and_block_edges(tsq, oracle, T, H, dtype):
     check_parity(tsq, oracle, rows(T, H, dtype), dtype, 6.0, (2, 3, 4, 6, 8), 0.1, "rel_rms", "fused", label="T=%d H=%d" % (T, H))
 
