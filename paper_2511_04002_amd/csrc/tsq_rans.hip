@@ -511,11 +511,11 @@ __device__ __forceinline__ void decode_round(uint32_t *dst_row, uint32_t run, in
         uint32_t y = xh + ((entry >> 8) & 0xFFFu);
         asm("" : "+v"(y));
         y = __umul24(entry >> 20, xh) + y;                                 // f <= 2^12, x >> 12 < 2^20
-        const uint32_t s = WHOLE || j < valid ? entry : entry & ~0xFFu;
         const int off = j * B, k = off >> 5, room = 32 - (off & 31);
-        d[k] = append_code(s, d[k], room < B ? room : B);
-        if (room < B) d[k + 1 < B ? k + 1 : k] = (s >> room) << (32 - (B - room));
-        const bool need = y < limit && (WHOLE || j < valid);
+        d[k] = append_code(entry, d[k], room < B ? room : B);
+        if (room < B) d[k + 1 < B ? k + 1 : k] = (entry >> room) << (32 - (B - room));
+        // (beyond the end of the row the limit is 0: arithmetic, since a mask per step would fill the scalar registers)
+        const bool need = y < (WHOLE ? limit : limit & (uint32_t)((j - valid) >> 31));
         const uint64_t who = __builtin_amdgcn_ballot_w64(need);
         // (every lane reads: the words of a step and the up to 64 behind them are in the ring)
         uint32_t word = lds_at<uint16_t>((rank_in(who) << 1) + q.at);
@@ -526,10 +526,11 @@ __device__ __forceinline__ void decode_round(uint32_t *dst_row, uint32_t run, in
     if (WHOLE) {
         if (valid > 0) store_run_words<B>(dst_row + run * B, d);
     } else {
-        const uint32_t nd = valid >= 32 ? (uint32_t)B : (valid > 0 ? ((uint32_t)valid * B + 31u) >> 5 : 0u);
+        // what the steps beyond the end of the row left in the last word goes
+        const int bits = (valid < 32 ? valid : 32) * B;
 #pragma unroll
         for (int k = 0; k < B; ++k)
-            if ((uint32_t)k < nd) dst_row[run * B + k] = d[k];
+            if (32 * k < bits) dst_row[run * B + k] = bits - 32 * k >= 32 ? d[k] : d[k] & ((1u << (bits - 32 * k)) - 1u);
     }
 }
 
