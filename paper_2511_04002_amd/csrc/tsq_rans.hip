@@ -360,23 +360,29 @@ k_rans_gather(const Params p, const EntropyLayout e, const uint8_t *__restrict__
 // ---------------------------------------------------------------- decode
 
 // What a slot decodes to, in one word: (f - 1) << 20 | (slot - cum) << 8 | code, so that a step of the decoder is one
-// look-up and x -> f (x >> 12) + slot - cum.  A class's 4096 words take 16 KB; a workgroup holds up to kDecTables
-// classes at once (more of them among its tokens, which is rare, are taken in a second go).
+// look-up and x -> f (x >> 12) + slot - cum.  A class's 4096 words take 16 KB; two workgroups' worth of LDS holds three
+// such tables each, for the classes that most of the workgroup's tokens have.  The other classes (four at most) get
+// 5 KB: the rank of a slot's code among the codes that occur, a byte per slot, and a list of those codes with cum in the
+// place of slot - cum.  (Four tables, and a second turn for the tokens of further classes: 8192 x 8192 bf16 with five
+// classes 57 us, this form 42, a token per workgroup 45.)
 //
 // What bounds it is instruction issue (and, at few tokens, the chain of a step: table, product, comparison, place, word).
 // A token per workgroup of one wave, with tables of its own in two steps (slot -> code -> f, cum) and the words of the
 // stream fetched out of other lanes' registers, took 25 vector and 3 LDS instructions per step and 600 per token
 // for the tables; this form 14 and 2 per step (21 with tables and ring).  8192 x 8192 bf16 48 -> 39 us, 32768 x 4096 f16
 // 116 -> 81, 131072 x 768 235 -> 163, 2000 x 16384 59 -> 45, 300 x 5120 21 -> 19.
-constexpr uint32_t kDecWaves = 16, kDecThreads = 64u * kDecWaves, kDecTables = 4, kDecTableWords = kProbScale;
+constexpr uint32_t kDecWaves = 16, kDecThreads = 64u * kDecWaves, kDecTables = 3, kDecTableWords = kProbScale;
+constexpr uint32_t kDecLists = 4, kDecListBytes = kProbScale + 256u * 4u;     // ranks, then the list
 // A wave's words of the stream: a ring of two halves of 128 words, and the first 64 of them once more behind it, so
 // that the up to 64 words of a step always stand in a row.
 constexpr uint32_t kHalfWords = 128, kRingWords = 2 * kHalfWords + 64;
-constexpr uint32_t kDecLdsRings = kDecTables * kDecTableWords * 4u, kDecLdsBytes = kDecLdsRings + kDecWaves * kRingWords * 2u;
-// While tables are laid out the rings' place holds, per table, the list of the codes that occur (256 words) and
-// one bit per slot where a code's range starts (128 words).
-constexpr uint32_t kBuildWords = 256 + 128;
-static_assert(kDecTables * kBuildWords * 4u <= kDecWaves * kRingWords * 2u, "scratch of the table builders");
+constexpr uint32_t kDecLdsLists = kDecTables * kDecTableWords * 4u, kDecLdsRings = kDecLdsLists + kDecLists * kDecListBytes;
+constexpr uint32_t kDecLdsBytes = kDecLdsRings + kDecWaves * kRingWords * 2u;
+// While tables are laid out the rings' place holds, per class, one bit per slot where a code's range starts (128
+// words), and behind those the lists of the classes with a table (256 words each).
+constexpr uint32_t kMarkWords = 128, kDecClasses = kDecTables + kDecLists;
+static_assert((kDecClasses * kMarkWords + kDecTables * 256u) * 4u <= kDecWaves * kRingWords * 2u, "scratch of the table builders");
+static_assert(kDecClasses == 7, "a place for every width");
 static_assert(2u * kDecLdsBytes <= 160u * 1024u, "two workgroups per compute unit");
 
 // Step 1, by one wave per table: lane l takes the codes 4l .. 4l+3.  The codes that occur are listed in the form
@@ -404,8 +410,9 @@ __device__ __forceinline__ void list_codes(const uint16_t *freq, uint32_t *list,
         cum += f[i];
     }
 }
-// Step 2, by the waves of a table (this one is number `part` of `parts`), 64 slots at a time: the rank of a slot's
-// code is the number of ranges that start up to it.
+// Step 2, by all waves (this one is number `part` of `parts`), 64 slots at a time: the rank of a slot's code is the
+// number of ranges that start up to it.  Fills the table, or (RANKS) the ranks.
+template <bool RANKS>
 __device__ __forceinline__ void fill_table(const uint32_t *list, const uint32_t *starts, uint32_t *table, uint32_t part,
                                            uint32_t parts) {
     const uint32_t lane = threadIdx.x & 63u;
@@ -417,8 +424,13 @@ __device__ __forceinline__ void fill_table(const uint32_t *list, const uint32_t 
         const uint64_t above = (((uint64_t)mhi << 32) | mlo) >> 1;            // a lane counts the marks up to its own
         uint32_t rank = lane_value(before, (int)i) + (mlo & 1u) + rank_in(above);
         rank = rank ? rank - 1u : 0u;                                         // (0: only in a damaged table)
-        const uint32_t slot = 64u * i + lane, entry = list[rank & 255u];
-        table[slot] = (entry & 0xFFF000FFu) | (((slot - (entry >> 8)) & 0xFFFu) << 8);
+        const uint32_t slot = 64u * i + lane;
+        if (RANKS) {
+            reinterpret_cast<uint8_t *>(table)[slot] = (uint8_t)rank;
+        } else {
+            const uint32_t entry = list[rank & 255u];
+            table[slot] = (entry & 0xFFF000FFu) | (((slot - (entry >> 8)) & 0xFFFu) << 8);
+        }
     }
 }
 
@@ -494,10 +506,11 @@ __device__ __forceinline__ uint32_t append_code(uint32_t entry, uint32_t d, int 
 
 // The 32 steps of one round (a lane's run number `run`).  WHOLE: every lane's run lies inside the row or wholly
 // beyond it (valid >= 32 or <= 0): no step needs a range check, the lanes beyond the row run idle with a limit that
-// keeps them from taking words.  table: LDS address of the class's table, a multiple of its size.
+// keeps them from taking words.  table: LDS address of the class's table, a multiple of its size, or (RANKS) of its
+// ranks and list.
 // A step is bound by instruction issue, so what the compiler would make more of than there is to it is pinned down by
 // empty asm statements: the comparison with a register, the word read by every lane, x + off before the product.
-template <int B, bool WHOLE>
+template <int B, bool WHOLE, bool RANKS>
 __device__ __forceinline__ void decode_round(uint32_t *dst_row, uint32_t run, int valid, uint32_t table, Words &q, uint32_t &x) {
     uint32_t d[B];
 #pragma unroll
@@ -506,9 +519,16 @@ __device__ __forceinline__ void decode_round(uint32_t *dst_row, uint32_t run, in
     asm("" : "+v"(limit), "+v"(mask), "+v"(base));
 #pragma unroll
     for (int j = 0; j < 32; ++j) {
-        const uint32_t entry = lds_at<uint32_t>(bitop3<kAndOr>(x << 2, mask, base));
+        uint32_t entry, y;
         const uint32_t xh = x >> kProbBits;
-        uint32_t y = xh + ((entry >> 8) & 0xFFFu);
+        if (RANKS) {
+            const uint32_t slot = frequency_slot(x);
+            entry = lds_at<uint32_t>(table + kProbScale + 4u * lds_at<uint8_t>(table + slot));
+            y = xh + slot - ((entry >> 8) & 0xFFFu);
+        } else {
+            entry = lds_at<uint32_t>(bitop3<kAndOr>(x << 2, mask, base));
+            y = xh + ((entry >> 8) & 0xFFFu);
+        }
         asm("" : "+v"(y));
         y = __umul24(entry >> 20, xh) + y;                                 // f <= 2^12, x >> 12 < 2^20
         const int off = j * B, k = off >> 5, room = 32 - (off & 31);
@@ -560,81 +580,88 @@ k_rans_decode(const Params p, const EntropyLayout e, const uint8_t *__restrict__
     uint32_t t = t0 + wv;
     CodedToken next = {};
     if (t < t1) ask_for_token(p, e, blob, eblob, t, next);
-    uint32_t classes = 0;                                 // bit b: a token of width b is among the workgroup's
+    // how many of the workgroup's tokens have width k + 2
+    uint32_t count[kDecClasses] = {};
     for (uint32_t i = t0; i < t1; i += 64u) {
         const uint32_t b = i + lane < t1 ? blob[p.off_bits + i + lane] : 0u;
 #pragma unroll
-        for (uint32_t k = 2; k <= 8; ++k)
-            if (__builtin_amdgcn_ballot_w64(b == k)) classes |= 1u << k;
+        for (uint32_t k = 0; k < kDecClasses; ++k) count[k] += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(b == k + 2u));
     }
+    // the places of the classes that occur, the most frequent first: places 0 .. kDecTables - 1 are tables.  Four bits
+    // per class: its place (place_of), and the class at a place (class_at)
+    uint32_t place_of = 0, class_at = 0, n = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kDecClasses; ++k) {
+        uint32_t place = 0;
+#pragma unroll
+        for (uint32_t o = 0; o < kDecClasses; ++o) place += count[o] > count[k] || (count[o] == count[k] && o < k) ? 1u : 0u;
+        place_of |= place << (4u * k);
+        class_at |= k << (4u * place);
+        n += count[k] ? 1u : 0u;
+    }
+    place_of = uniform(place_of);
+    class_at = uniform(class_at);
+    n = uniform(n);
+
+    // ---- the tables
+    uint32_t *scratch = lds + kDecLdsRings / 4u;
+    auto marks_at = [&](uint32_t place) { return scratch + place * kMarkWords; };
+    auto list_at = [&](uint32_t place) {
+        return place < kDecTables ? scratch + kDecClasses * kMarkWords + place * 256u
+                                  : lds + (kDecLdsLists + (place - kDecTables) * kDecListBytes + kProbScale) / 4u;
+    };
+    if (wv < n)
+        list_codes(reinterpret_cast<const uint16_t *>(eblob + e.off_tables) + ((class_at >> (4u * wv)) & 15u) * 256u, list_at(wv), marks_at(wv));
+    __syncthreads();
+    for (uint32_t place = 0; place < n; ++place) {
+        if (place < kDecTables) fill_table<false>(list_at(place), marks_at(place), lds + place * kDecTableWords, wv, kDecWaves);
+        else fill_table<true>(nullptr, marks_at(place), list_at(place) - kProbScale / 4u, wv, kDecWaves);
+    }
+    __syncthreads();
 
     const uint32_t ring = lds_address(lds) + kDecLdsRings + wv * kRingWords * 2u;
-    for (classes = uniform(classes); classes;) {
-        // ---- the tables of the next classes: each laid out by the waves k, k + n, ...
-        const uint32_t present = (uint32_t)__builtin_popcount(classes), n = present < kDecTables ? present : kDecTables;
-        uint32_t batch = 0, mine = 0;
-        const uint32_t k = wv % n, part = wv / n, parts = (kDecWaves - 1u - k) / n + 1u;
-        for (uint32_t i = 0; i < n; ++i) {
-            const uint32_t b = (uint32_t)__builtin_ctz(classes);
-            classes &= classes - 1u;
-            batch |= 1u << b;
-            if (i == k) mine = b;
-        }
-        uint32_t *list = lds + kDecLdsRings / 4u + k * kBuildWords, *starts = list + 256;
-        if (part == 0) list_codes(reinterpret_cast<const uint16_t *>(eblob + e.off_tables) + (mine - 2u) * 256u, list, starts);
-        __syncthreads();
-        fill_table(list, starts, lds + k * kDecTableWords, part, parts);
-        __syncthreads();
-
-        // ---- the tokens of these classes
-        for (; t < t1; t += kDecWaves) {
-            const CodedToken c = next;
-            if (t + kDecWaves < t1) ask_for_token(p, e, blob, eblob, t + kDecWaves, next);
-            const uint32_t width = uniform(c.width);
-            // a damaged token is skipped rather than read or written out of bounds
-            if (!((batch >> (width & 31u)) & 1u) || !token_in_range(p, width, c.po) ||
-                !stream_span_ok(c.a, c.b, e.stream_capacity, coders, e.slot_bytes))
-                continue;
-            const uint32_t table = lds_address(lds) + (uint32_t)__builtin_popcount(batch & ((1u << width) - 1u)) * (4u * kDecTableWords);
-            const uint32_t *stream = reinterpret_cast<const uint32_t *>(eblob + e.off_streams + c.a);
-            uint32_t x = kRansLow;
-            if (lane < coders) x = stream[lane];
-            Words q;
-            words_open(q, stream + coders, (uint32_t)(c.b - c.a - 4u * coders) >> 1, stream, ring);
-            uint32_t *dst_row = reinterpret_cast<uint32_t *>(blob + p.off_payload + c.po);
-            for (uint32_t r = 0; r < rounds; ++r) {
-                priority_by_progress(r, rounds);
-                const uint32_t run = lane + 64u * r;
-                const int valid = (int)p.hidden - (int)(run * kRun);
-                if (__builtin_amdgcn_ballot_w64(valid > 0 && valid < 32) == 0) {
-                    switch (width) {
-                    case 2: decode_round<2, true>(dst_row, run, valid, table, q, x); break;
-                    case 3: decode_round<3, true>(dst_row, run, valid, table, q, x); break;
-                    case 4: decode_round<4, true>(dst_row, run, valid, table, q, x); break;
-                    case 5: decode_round<5, true>(dst_row, run, valid, table, q, x); break;
-                    case 6: decode_round<6, true>(dst_row, run, valid, table, q, x); break;
-                    case 7: decode_round<7, true>(dst_row, run, valid, table, q, x); break;
-                    default: decode_round<8, true>(dst_row, run, valid, table, q, x); break;
-                    }
+    // ---- the tokens
+    for (; t < t1; t += kDecWaves) {
+        const CodedToken c = next;
+        if (t + kDecWaves < t1) ask_for_token(p, e, blob, eblob, t + kDecWaves, next);
+        const uint32_t width = uniform(c.width);
+        // a damaged token is skipped rather than read or written out of bounds
+        if (!token_in_range(p, width, c.po) || !stream_span_ok(c.a, c.b, e.stream_capacity, coders, e.slot_bytes)) continue;
+        const uint32_t place = (place_of >> (4u * (width - 2u))) & 15u;
+        const bool ranks = place >= kDecTables;
+        const uint32_t table = lds_address(lds) + (ranks ? kDecLdsLists + (place - kDecTables) * kDecListBytes : place * (4u * kDecTableWords));
+        const uint32_t *stream = reinterpret_cast<const uint32_t *>(eblob + e.off_streams + c.a);
+        uint32_t x = kRansLow;
+        if (lane < coders) x = stream[lane];
+        Words q;
+        words_open(q, stream + coders, (uint32_t)(c.b - c.a - 4u * coders) >> 1, stream, ring);
+        uint32_t *dst_row = reinterpret_cast<uint32_t *>(blob + p.off_payload + c.po);
+        for (uint32_t r = 0; r < rounds; ++r) {
+            priority_by_progress(r, rounds);
+            const uint32_t run = lane + 64u * r;
+            const int valid = (int)p.hidden - (int)(run * kRun);
+#define TSQ_DECODE_ROUND(WHOLE, RANKS) \
+    switch (width) {                   \
+        case 2: decode_round<2, WHOLE, RANKS>(dst_row, run, valid, table, q, x); break;  \
+        case 3: decode_round<3, WHOLE, RANKS>(dst_row, run, valid, table, q, x); break;  \
+        case 4: decode_round<4, WHOLE, RANKS>(dst_row, run, valid, table, q, x); break;  \
+        case 5: decode_round<5, WHOLE, RANKS>(dst_row, run, valid, table, q, x); break;  \
+        case 6: decode_round<6, WHOLE, RANKS>(dst_row, run, valid, table, q, x); break;  \
+        case 7: decode_round<7, WHOLE, RANKS>(dst_row, run, valid, table, q, x); break;  \
+        default: decode_round<8, WHOLE, RANKS>(dst_row, run, valid, table, q, x); break; \
+    }
+            if (__builtin_amdgcn_ballot_w64(valid > 0 && valid < 32) == 0) {
+                if (ranks) {
+                    TSQ_DECODE_ROUND(true, true)
                 } else {
-                    switch (width) {
-                    case 2: decode_round<2, false>(dst_row, run, valid, table, q, x); break;
-                    case 3: decode_round<3, false>(dst_row, run, valid, table, q, x); break;
-                    case 4: decode_round<4, false>(dst_row, run, valid, table, q, x); break;
-                    case 5: decode_round<5, false>(dst_row, run, valid, table, q, x); break;
-                    case 6: decode_round<6, false>(dst_row, run, valid, table, q, x); break;
-                    case 7: decode_round<7, false>(dst_row, run, valid, table, q, x); break;
-                    default: decode_round<8, false>(dst_row, run, valid, table, q, x); break;
-                    }
+                    TSQ_DECODE_ROUND(true, false)
                 }
+            } else if (ranks) {
+                TSQ_DECODE_ROUND(false, true)
+            } else {
+                TSQ_DECODE_ROUND(false, false)
             }
-        }
-        if (classes) {
-            // (more classes than tables: once more from the first token on)
-            __builtin_amdgcn_s_setprio(0);
-            __syncthreads();
-            t = t0 + wv;
-            if (t < t1) ask_for_token(p, e, blob, eblob, t, next);
+#undef TSQ_DECODE_ROUND
         }
     }
 }

@@ -1,6 +1,7 @@
-"""The decoder's workgroups (512 at most, sixteen tokens at a time, four tables at a time) at the token counts and row
+"""The decoder's workgroups (512 at most, sixteen tokens at a time, a table each for the three most frequent width
+classes, ranks and a list for the others) at the token counts and row
 lengths where they can go wrong: fewer tokens than workgroups, one more than they take in a turn, more width
-classes among a workgroup's tokens than it holds tables, lanes beyond the row, rows that end inside a run, streams that
+classes among a workgroup's tokens than it has tables for, lanes beyond the row, rows that end inside a run, streams that
 go round a wave's ring of words.  Tables, offsets, streams and the restored payload against the oracle, byte for byte."""
 import numpy as np
 import pytest
@@ -29,4 +30,4 @@ def test_workgroups_of_the_decoder(tsq, oracle, RE, T, H, dtype):
     if T > 8192:
         per = -(-T // 512)
         classes = [len(set(ref.bits[i:i + per].tolist())) for i in range(0, T, per)]
-        assert max(classes) > 4, "a workgroup with more classes than tables is among them"
+        assert max(classes) > 4, "workgroups with classes beyond the third are among them"
