@@ -1,6 +1,7 @@
 """The two forms of the single-pass compress (one workgroup per token; persistent workgroups) at the shapes where they
 can go wrong: both sides of the line between them, edges of the placement's blocks of 2048 tokens, the last run
-of a row cut short, tokens with more outliers than a wave keeps in LDS.  Whole blobs against the oracle."""
+of a row cut short, tokens with more outliers than a wave keeps in LDS, more tokens than one launch can have workgroups
+for.  Whole blobs against the oracle."""
 import numpy as np
 import pytest
 
@@ -35,3 +36,39 @@ def test_tokens_full_of_outliers(tsq, oracle, T, H, dtype):
     ref, _ = check_parity(tsq, oracle, rows(T, H, dtype, heavy=30), dtype, 6.0, (2, 4, 8), 0.05, "rel_rms", "fused",
                           label="heavy rows T=%d H=%d" % (T, H))
     assert np.diff(ref.row_ptr.astype(np.int64)).max() == H
+
+
+@pytest.mark.parametrize("T", [2 ** 26 - 4096, 2 ** 26])
+def test_as_many_tokens_as_a_launch_has_threads_for(tsq, oracle, T):
+    """A launch's threads are counted in 32 bits, which ends one workgroup per token of one wave at 2^26 - 1 tokens: the
+    last thousands below that, and the first count beyond it.  The tokens are copies of a block of 4096, so every section
+    is the block's over and over, the offsets moved on by the block's totals; compared on the card."""
+    import torch
+    H, B = 8, 4096
+    x = rows(B, H, "f16")
+    ref = oracle.compress(x, oracle.F16, 6.0, (2, 4, 8), 0.05, 1, nthreads=8)
+    assert ref.nnz > 0 and len(set(ref.bits.tolist())) > 1
+    copies = T // B
+    plan = tsq.Plan(T, H, "f16", 6.0, (2, 4, 8), 0.05, pipeline="fused", max_outliers=copies * ref.nnz)
+    xd = torch.from_numpy(x.view(np.int16)).cuda().repeat(copies, 1)
+    blob, ws = plan.new_blob(), plan.new_workspace()
+    torch.cuda.synchronize()
+    print("compress", T, "tokens", flush=True)
+    plan.compress(xd, blob, ws)
+    info = plan.info(blob)
+    assert info.status == 0 and info.nnz == copies * ref.nnz and info.payload_bytes == copies * ref.payload_bytes
+    L = plan.layout
+
+    def same(at, want, dtype):
+        w = torch.from_numpy(want.view(np.uint8).copy()).cuda().view(dtype)
+        got = blob[int(at):int(at) + copies * w.numel() * w.element_size()].view(dtype).view(copies, w.numel())
+        return bool((got == w).all())
+
+    assert same(L.off_bits, ref.bits, torch.uint8) and same(L.off_scale, ref.scale, torch.int32)
+    assert same(L.off_payload, ref.payload, torch.uint8)
+    assert same(L.off_out_col, ref.out_col, torch.int16) and same(L.off_out_val, ref.out_val, torch.int16)
+    for at, want, total in ((L.off_pay_off, ref.pay_off, ref.payload_bytes), (L.off_row_ptr, ref.row_ptr, ref.nnz)):
+        got = blob[int(at):int(at) + 8 * T].view(torch.int64).view(copies, B)
+        w = torch.from_numpy(want[:B].astype(np.int64)).cuda()
+        assert bool((got == w + total * torch.arange(copies, device="cuda").view(-1, 1)).all())
+        assert int(blob[int(at) + 8 * T:int(at) + 8 * (T + 1)].view(torch.int64)) == copies * total
