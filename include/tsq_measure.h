@@ -1,8 +1,9 @@
 /*
- * tsq_measure.h — measurement aids exported by the same library as tsq.h.  Nothing here is part of
- * the method: a benchmark uses these calls to time the kernels of one compress call one by one and
+ * tsq_measure.h — measurement and test aids exported by the same library as tsq.h.  Nothing here is
+ * part of the method: a benchmark uses these calls to time the kernels of one compress call one by one and
  * to find out what a kernel that only moves bytes reaches on the device at hand (the ceiling that
- * the achieved bandwidth of compress and restore is reported against, next to the published peak).
+ * the achieved bandwidth of compress and restore is reported against, next to the published peak);
+ * a test uses them to make a device-side wait expire.
  * Conventions as in tsq.h: d_* are device pointers, `stream` is a hipStream_t passed as void*,
  * errors are return codes.
  */
@@ -35,6 +36,13 @@ tsq_status tsq_measure_copy(void *d_dst, const void *d_src, size_t bytes, void *
  * always) nothing; d_sink points to 4 writable bytes.  Enqueues only.
  */
 tsq_status tsq_measure_read(const void *d_src, size_t bytes, void *d_sink, void *stream);
+
+/*
+ * Bounds every device-side wait of the plan's later single-pass calls to `rounds` looks (>= 1; a new
+ * plan has 2^20, about a second), so that a test can see what a call does whose waits expire.  Host
+ * only.  The one call that writes to a plan: not while another thread uses it.
+ */
+tsq_status tsq_plan_limit_waits(tsq_plan *plan, uint32_t rounds);
 
 #ifdef __cplusplus
 }

@@ -645,7 +645,12 @@ int tsq_check_workspace_shape(uint32_t ws_tokens, uint32_t ws_hidden, uint32_t t
     return workspace_shape_ok(ws_tokens, ws_hidden, tokens, hidden) ? 1 : 0;
 }
 
-// ---- copy ceilings (include/tsq_measure.h)
+// ---- include/tsq_measure.h
+tsq_status tsq_plan_limit_waits(tsq_plan *plan, uint32_t rounds) {
+    if (!plan || rounds == 0) return TSQ_ERR_INVALID_ARG;
+    plan->p.spin_limit = rounds;
+    return TSQ_OK;
+}
 tsq_status tsq_measure_copy(void *d_dst, const void *d_src, size_t bytes, void *stream) {
     if (!d_dst || !d_src || bytes == 0 || (bytes & 15u) || ((uintptr_t)d_dst & 15u) || ((uintptr_t)d_src & 15u))
         return TSQ_ERR_INVALID_ARG;

@@ -30,6 +30,11 @@ namespace tsq {
 constexpr uint32_t kStatusWord = 9;                      // BlobHeader::status, in 32-bit words
 static_assert(offsetof(BlobHeader, status) == 4 * kStatusWord, "status word of the header");
 constexpr uint32_t kStatusFormat = 5u, kStatusInternal = 6u, kStatusCapacity = 3u;
+// what a wave adds to its count of outliers when it has seen the workspace's error word, or another plan's shape: the
+// sums over a workgroup's waves leave the counts (at most kMaxHidden in all) and one another alone
+constexpr uint32_t kSawError = 1u << 20, kSawShape = 1u << 25;
+static_assert(kMaxHidden < kSawError && kMaxHidden + kMaxWaves * kSawError < kSawShape && kMaxWaves * kSawShape < (1u << 31),
+              "fields of the waves' sums");
 
 __device__ __forceinline__ void store_status(uint8_t *blob, uint32_t status) {
     word_store(reinterpret_cast<uint32_t *>(blob) + kStatusWord, status);
@@ -80,19 +85,21 @@ k_direct(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ 
     }
     if (!owns) { omask = 0; amax_bits = 0; }
 
-    // a workspace of another shape (or never reset), or one that an earlier call left in its failed state: nothing
-    // in it is touched, and the blob says so
+    // A workspace of another shape (or never reset), or one that a call left in its failed state: nothing in it is
+    // touched, and the blob says so.  Every wave has looked for itself, and another workgroup may raise the error word
+    // between two of the looks, so the waves decide together: what a wave saw travels above its count of outliers.
     const bool shape_ok = workspace_shape_ok(lane_value(state, 1), lane_value(state, 2), p.tokens, p.hidden);
-    if (!shape_ok || lane_value(state, 0)) {
-        if (last && tid == 0) write_header(p, blob, 0, 0, shape_ok ? kStatusInternal : kStatusFormat);
-        return;
-    }
+    const uint32_t refused = (lane_value(state, 0) ? kSawError : 0u) + (shape_ok ? 0u : kSawShape);
     const uint32_t epoch = (lane_value(state, 3) >> kTicketBits) % 3u, tag = epoch + 1u;
     if (last && tid == 0) store_status(blob, 0u);
 
     const uint32_t nl = (uint32_t)__builtin_popcount(omask);
     const uint32_t upto = wave_incl_scan_u32(nl);                 // outliers of the wave's lanes up to this one
-    const RowStats st = reduce_row_stats_counted<NW>(amax_bits, lane_value(upto, 63), ring, turn);
+    const RowStats st = reduce_row_stats_counted<NW>(amax_bits, lane_value(upto, 63) + refused, ring, turn);
+    if (st.cnt >= kSawError) {
+        if (last && tid == 0) write_header(p, blob, 0, 0, st.cnt >= kSawShape ? kStatusFormat : kStatusInternal);
+        return;
+    }
     uint32_t m[8];
     const Choice c = search_width<DT, NW>(p, mg, st.amax, owns, ring, turn, m);
 

@@ -113,6 +113,8 @@ def test_null_arguments(L):
         assert L.tsq_entropy_prefix_bytes(plan, 0x2000, 0x3000, None, c.tokens + 2, out, None) == tsq.TSQ_ERR_INVALID_ARG
         assert L.tsq_entropy_prefix_bytes(plan, 0x2000, 0x3000, ks, 2, out, None) == tsq.TSQ_ERR_INVALID_ARG
         assert L.tsq_compress_static(plan, None, 0x2000, None) == tsq.TSQ_ERR_INVALID_ARG
+        assert L.tsq_plan_limit_waits(None, 1) == tsq.TSQ_ERR_INVALID_ARG
+        assert L.tsq_plan_limit_waits(plan, 0) == tsq.TSQ_ERR_INVALID_ARG
     finally:
         tsq.tsq_plan_destroy(plan)
     # the measurement calls: sizes are multiples of 16 bytes, pointers 16-byte aligned

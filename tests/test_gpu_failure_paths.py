@@ -146,6 +146,60 @@ def test_a_workspace_in_an_arbitrary_state_is_reported_and_recovers(tsq, oracle)
     assert np.array_equal(plan.sections(blob)["payload"], ref.payload)
 
 
+def guarded(n):
+    """-> buffer of n bytes with a megabyte of a pattern on either side, and a check that both still hold it."""
+    import torch
+    g = 1 << 20
+    whole = torch.full((g + n + g,), 0x5C, dtype=torch.uint8, device="cuda")
+    return whole[g:g + n], lambda: bool((whole[:g] == 0x5C).all()) and bool((whole[g + n:] == 0x5C).all())
+
+
+def loud_rows(T, H, dtype):
+    """Rows of mixed loudness, some of them full of outliers."""
+    g = np.random.Generator(np.random.PCG64(T + H))
+    v = g.standard_normal((T, H)) * g.lognormal(0.0, 0.8, (T, 1))
+    v[g.random((T, H)) < 0.01] *= 30.0
+    v[::37] = 50.0
+    return synth.to_f16_bits(v) if dtype == "f16" else synth.to_bf16_bits(v)
+
+
+EXPIRING = [(9000, 768, "f16"), (2047, 2048, "bf16"), (4096, 4096, "f16"), (2730, 6144, "bf16"), (2048, 8192, "bf16"),
+            (1024, 16384, "f16"), (512, 32768, "bf16")]
+
+
+@pytest.mark.parametrize("T,H,dtype", EXPIRING)
+def test_a_call_whose_waits_expire_writes_nothing_outside_its_sections(tsq, oracle, T, H, dtype):
+    """Waits bounded to a single look: some workgroups give up while others are still on their way in, so that waves of
+    one workgroup can find the workspace's error word before and after it was raised.  Whatever they find, nothing
+    outside the blob and the workspace changes, the workspace stays failed, and after a reset, with the bound as it
+    was, the same buffers give the oracle's blob."""
+    import torch
+    x = loud_rows(T, H, dtype)
+    ref = oracle.compress(x, {"f16": oracle.F16, "bf16": oracle.BF16}[dtype], 8.0, (2, 3, 4, 6, 8), 0.1, 1, nthreads=8)
+    plan = tsq.Plan(T, H, dtype, 8.0, (2, 3, 4, 6, 8), 0.1, pipeline="fused", max_outliers=ref.nnz)
+    xd = torch.from_numpy(x.view(np.int16)).cuda()
+    blob, blob_intact = guarded(int(plan.layout.blob_bytes))
+    ws, ws_intact = guarded(int(plan.layout.workspace_bytes))
+    before = xd.clone()
+    for i in range(5):
+        tsq.tsq_workspace_reset(plan.handle, ws.data_ptr(), plan._stream())
+        tsq.tsq_plan_limit_waits(plan.handle, 1)
+        torch.cuda.synchronize()
+        print("call %d with waits of one look" % i, flush=True)
+        plan.compress(xd, blob, ws)
+        torch.cuda.synchronize()
+        assert blob_intact() and ws_intact() and torch.equal(xd, before)
+        assert int(ws.view(torch.int32)[CTL_ERROR]) != 0, "no wait expired"
+    tsq.tsq_plan_limit_waits(plan.handle, 1 << 20)
+    tsq.tsq_workspace_reset(plan.handle, ws.data_ptr(), plan._stream())
+    plan.compress(xd, blob, ws)
+    assert plan.info(blob).status == 0
+    sec = plan.sections(blob)
+    for k in SECTIONS:
+        assert np.array_equal(sec[k], getattr(ref, k)), k
+    assert blob_intact() and ws_intact()
+
+
 def test_a_damaged_eblob_is_decoded_to_the_end_and_touches_only_the_payload(tsq, oracle):
     """Tables, stream bytes and stream offsets of a valid eblob overwritten with noise: the decoder
     checks every offset against the stream capacity, reads past a stream's end as zeros and keeps
