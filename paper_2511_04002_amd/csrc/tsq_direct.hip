@@ -219,46 +219,46 @@ k_direct(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ 
             raise_error(error_flag);
             store_status(blob, kStatusInternal);
         }
-        return;
-    }
-    if (tid == 0) {
-        if (((t + 1u) & (kDirectBlock - 1u)) == 0) prefix_store(pre + t + 1u, prefix_word(tag, ew + words, ec + st.cnt));
-        reinterpret_cast<uint64_t *>(blob + p.off_pay_off)[t] = (uint64_t)ew << 2;
-        reinterpret_cast<uint64_t *>(blob + p.off_row_ptr)[t] = ec;
-    }
+    } else {
+        if (tid == 0) {
+            if (((t + 1u) & (kDirectBlock - 1u)) == 0) prefix_store(pre + t + 1u, prefix_word(tag, ew + words, ec + st.cnt));
+            reinterpret_cast<uint64_t *>(blob + p.off_pay_off)[t] = (uint64_t)ew << 2;
+            reinterpret_cast<uint64_t *>(blob + p.off_row_ptr)[t] = ec;
+        }
 
-    // ---- T_above of the lane's run, in column order
-    if (nl && (uint64_t)ec + st.cnt <= (uint64_t)outlier_capacity) {
-        uint32_t pos = ec + st.cnt_before + upto - nl;
-        uint16_t *col = reinterpret_cast<uint16_t *>(blob + p.off_out_col), *val = reinterpret_cast<uint16_t *>(blob + p.off_out_val);
-        for (uint32_t rest = omask; rest; rest &= rest - 1u) {
-            const uint32_t j = (uint32_t)__builtin_ctz(rest);
-            col[pos] = (uint16_t)(tid * kRun + j);
-            val[pos] = raw_element_sw(lrow, tid, j);
-            ++pos;
+        // ---- T_above of the lane's run, in column order
+        if (nl && (uint64_t)ec + st.cnt <= (uint64_t)outlier_capacity) {
+            uint32_t pos = ec + st.cnt_before + upto - nl;
+            uint16_t *col = reinterpret_cast<uint16_t *>(blob + p.off_out_col), *val = reinterpret_cast<uint16_t *>(blob + p.off_out_val);
+            for (uint32_t rest = omask; rest; rest &= rest - 1u) {
+                const uint32_t j = (uint32_t)__builtin_ctz(rest);
+                col[pos] = (uint16_t)(tid * kRun + j);
+                val[pos] = raw_element_sw(lrow, tid, j);
+                ++pos;
+            }
         }
-    }
-    // ---- the codes to their place in the blob, 16 bytes per lane and step
-    {
-        const uint32_t first = 64u * wv * c.width;                    // the wave's first word of the row
-        const uint32_t n = words > first ? (words - first < 64u * c.width ? words - first : 64u * c.width) : 0u;
-        const uint32_t *img = image + wv * (64u * 8u);
-        uint8_t *dst = blob + p.off_payload + 4ull * (ew + first);
-        const uint32_t quads = n >> 2, rest = n & 3u;
-        const __amdgpu_buffer_rsrc_t window = raw_window(dst, n << 2);
+        // ---- the codes to their place in the blob, 16 bytes per lane and step
+        {
+            const uint32_t first = 64u * wv * c.width;                    // the wave's first word of the row
+            const uint32_t n = words > first ? (words - first < 64u * c.width ? words - first : 64u * c.width) : 0u;
+            const uint32_t *img = image + wv * (64u * 8u);
+            uint8_t *dst = blob + p.off_payload + 4ull * (ew + first);
+            const uint32_t quads = n >> 2, rest = n & 3u;
+            const __amdgpu_buffer_rsrc_t window = raw_window(dst, n << 2);
 #pragma unroll
-        for (uint32_t k = 0; k < 2; ++k) {
-            const uint32_t i = lane + 64u * k;
-            if (i < quads) store_quad_through(window, 16u * i, *reinterpret_cast<const u32x4 *>(img + 4u * i));
+            for (uint32_t k = 0; k < 2; ++k) {
+                const uint32_t i = lane + 64u * k;
+                if (i < quads) store_quad_through(window, 16u * i, *reinterpret_cast<const u32x4 *>(img + 4u * i));
+            }
+            if (lane < rest) *reinterpret_cast<uint32_t *>(dst + 4u * (4u * quads + lane)) = img[4u * quads + lane];
         }
-        if (lane < rest) *reinterpret_cast<uint32_t *>(dst + 4u * (4u * quads + lane)) = img[4u * quads + lane];
     }
     if (!last || wv != 0) return;
 
-    // ---- the last token's first wave closes the blob
-    const uint32_t all_words = ew + words;
-    const uint64_t all_outliers = (uint64_t)ec + st.cnt;
-    word_store(tickets + lane * kTicketStride + kCntTickets, ((epoch + 1u) % 3u) << kTicketBits);   // everybody has this call's
+    // ---- the last token's first wave closes the blob, also if its own wait has expired (nobody else writes a header)
+    const uint32_t all_words = bad ? 0u : ew + words;
+    const uint64_t all_outliers = bad ? 0u : (uint64_t)ec + st.cnt;
+    if (!bad) word_store(tickets + lane * kTicketStride + kCntTickets, ((epoch + 1u) % 3u) << kTicketBits);   // everybody has this call's
     if (lane == 0) {
         const bool full = all_outliers > p.outlier_capacity;
         if (full) {

@@ -200,6 +200,38 @@ def test_a_call_whose_waits_expire_writes_nothing_outside_its_sections(tsq, orac
     assert blob_intact() and ws_intact()
 
 
+@pytest.mark.parametrize("T,H,dtype", EXPIRING + [(5000, 4096, "f16"), (2200, 8192, "bf16")])
+def test_a_call_whose_waits_expire_says_so_on_a_fresh_blob(tsq, oracle, T, H, dtype):
+    """Waits bounded to a single look, a blob that nobody has written to: the header is the plan's and says
+    TSQ_ERR_INTERNAL, restore refuses the blob, and the blocking call of a TSQ_PIPE_AUTO plan, whose own single pass
+    fails the same way, ends with the staged kernels' blob."""
+    import torch
+    x = loud_rows(T, H, dtype)
+    ref = oracle.compress(x, {"f16": oracle.F16, "bf16": oracle.BF16}[dtype], 8.0, (2, 3, 4, 6, 8), 0.1, 1, nthreads=8)
+    xd = torch.from_numpy(x.view(np.int16)).cuda()
+    fused, auto = (tsq.Plan(T, H, dtype, 8.0, (2, 3, 4, 6, 8), 0.1, pipeline=p, max_outliers=ref.nnz) for p in ("fused", "auto"))
+    blob, ws = fused.new_blob(), fused.new_workspace()
+    out = torch.full((T, H), 0x1234, dtype=torch.int16, device="cuda")
+    for plan in (fused, auto):
+        tsq.tsq_plan_limit_waits(plan.handle, 1)
+    blob.fill_(0xFF)
+    print("a call with waits of one look", flush=True)
+    fused.compress(xd, blob, ws)
+    info = fused.info(blob, check=False)
+    assert info.return_status == tsq.TSQ_ERR_INTERNAL and info.status == tsq.TSQ_ERR_INTERNAL
+    fused.decompress(blob, out)
+    torch.cuda.synchronize()
+    assert bool((out == 0x1234).all())
+    blob.fill_(0xFF)
+    tsq.tsq_workspace_reset(auto.handle, ws.data_ptr(), auto._stream())
+    print("the blocking call", flush=True)
+    info = tsq.tsq_compress_blocking(auto.handle, xd.data_ptr(), blob.data_ptr(), ws.data_ptr(), auto._stream(), check=False)
+    assert info.return_status == tsq.TSQ_OK and info.status == 0 and info.nnz == ref.nnz
+    sec = auto.sections(blob)
+    for k in SECTIONS:
+        assert np.array_equal(sec[k], getattr(ref, k)), k
+
+
 def test_a_damaged_eblob_is_decoded_to_the_end_and_touches_only_the_payload(tsq, oracle):
     """Tables, stream bytes and stream offsets of a valid eblob overwritten with noise: the decoder
     checks every offset against the stream capacity, reads past a stream's end as zeros and keeps
