@@ -261,14 +261,15 @@ k_direct(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ 
     if (!bad) word_store(tickets + lane * kTicketStride + kCntTickets, ((epoch + 1u) % 3u) << kTicketBits);   // everybody has this call's
     if (lane == 0) {
         const bool full = all_outliers > p.outlier_capacity;
-        if (full) {
+        if (full) {                            // (as the zero at the start: in its place before the error word is read again)
+            store_status(blob, kStatusCapacity);
             memory_operations_performed();
-            raised = word_load(error_flag + opaque_zero());
+            raised |= word_load(error_flag + opaque_zero());
         }
         reinterpret_cast<uint64_t *>(blob + p.off_row_ptr)[p.tokens] = all_outliers;
         reinterpret_cast<uint64_t *>(blob + p.off_pay_off)[p.tokens] = (uint64_t)all_words << 2;
         write_header_but_status(p, blob, all_outliers, (uint64_t)all_words << 2);
-        if (raised || full) store_status(blob, raised ? kStatusInternal : kStatusCapacity);
+        if (raised) store_status(blob, kStatusInternal);
     }
 }
 

@@ -232,6 +232,27 @@ def test_a_call_whose_waits_expire_says_so_on_a_fresh_blob(tsq, oracle, T, H, dt
         assert np.array_equal(sec[k], getattr(ref, k)), k
 
 
+@pytest.mark.parametrize("T,H,dtype", [(9000, 768, "f16"), (1500, 2048, "bf16"), (4096, 4096, "f16"), (5000, 4096, "f16")])
+def test_an_expired_wait_comes_before_a_side_stream_that_is_full(tsq, T, H, dtype):
+    """Waits of one look and a side stream that is too small, many calls: whenever the workspace's error word has
+    been raised the blob says TSQ_ERR_INTERNAL, whichever of the two the kernel came upon first; otherwise it says
+    TSQ_ERR_CAPACITY."""
+    import torch
+    x = loud_rows(T, H, dtype)
+    plan = tsq.Plan(T, H, dtype, 8.0, (2, 4, 8), 0.1, pipeline="fused", max_outliers=H)
+    xd = torch.from_numpy(x.view(np.int16)).cuda()
+    blob, ws = plan.new_blob(), plan.new_workspace()
+    print("a call with ordinary waits", flush=True)
+    plan.compress(xd, blob, ws)
+    assert plan.info(blob, check=False).return_status == tsq.TSQ_ERR_CAPACITY
+    tsq.tsq_plan_limit_waits(plan.handle, 1)
+    for i in range(50):
+        tsq.tsq_workspace_reset(plan.handle, ws.data_ptr(), plan._stream())
+        plan.compress(xd, blob, ws)
+        want = tsq.TSQ_ERR_INTERNAL if int(ws.view(torch.int32)[CTL_ERROR]) else tsq.TSQ_ERR_CAPACITY
+        assert plan.info(blob, check=False).return_status == want, i
+
+
 def test_a_damaged_eblob_is_decoded_to_the_end_and_touches_only_the_payload(tsq, oracle):
     """Tables, stream bytes and stream offsets of a valid eblob overwritten with noise: the decoder
     checks every offset against the stream capacity, reads past a stream's end as zeros and keeps
