@@ -465,6 +465,15 @@ def _find_current_stream():
     return lambda: raw(device())
 
 
+def _forget_current_stream():
+    # a forked child asks torch again, which refuses to use the device there
+    global _current_stream
+    _current_stream = None
+
+
+os.register_at_fork(after_in_child=_forget_current_stream)
+
+
 class Plan:
     """Owns one tsq_plan plus helpers that allocate torch buffers and pass their pointers."""
 
