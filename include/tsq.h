@@ -65,17 +65,26 @@ typedef enum {
 } tsq_return_rule;
 
 typedef enum {
-    TSQ_PIPE_AUTO   = 0,      /* the library picks: TSQ_PIPE_FUSED wherever the device can hold
-                                 two workgroups of its kernel at once, else TSQ_PIPE_STAGED     */
+    TSQ_PIPE_AUTO   = 0,      /* the library picks: TSQ_PIPE_FUSED, or TSQ_PIPE_STAGED where the
+                                 kernel for large calls (below) would be used and the device
+                                 cannot hold two of its workgroups at once                      */
     TSQ_PIPE_STAGED = 1,      /* row statistics -> device-wide scan -> pack: three launches,
                                  the input is read twice                                        */
-    TSQ_PIPE_FUSED  = 2       /* one launch, the input is read once.  Every token is handed out
-                                 by ticket counters in the workspace, so whichever workgroups
-                                 are running finish the call (none waits for one that has not
-                                 started); one workgroup scans the published sizes into the
-                                 tokens' places.  Every device-side wait is bounded: if the
-                                 workgroup that scans is kept from running for about a second,
-                                 the call ends with TSQ_ERR_INTERNAL in the blob's status      */
+    TSQ_PIPE_FUSED  = 2       /* one launch, the input is read once.  The shape alone says which of
+                                 two kernels runs.  With w = the waves that hold a row
+                                 (ceil(hidden / 2048), up to the next of 1, 2, 3, 4, 8, 16), calls
+                                 of tokens * w <= 8192, and of w = 1 and fewer than 2^26 tokens:
+                                 a workgroup per token, which waits for the sizes of the tokens
+                                 before it; it relies on every die of the device starting its
+                                 workgroups in the order of their index.  Larger calls: as many
+                                 workgroups as the device holds draw tokens from ticket counters
+                                 in the workspace (none waits for a token that no running
+                                 workgroup has); one more turns the published sizes into the
+                                 tokens' places and closes the blob when all have reported.
+                                 In both every workgroup of the launch has to get its turn, and
+                                 every device-side wait is bounded: if other work keeps some of
+                                 them from running (by holding a whole die, say) for about a
+                                 second, the call ends with TSQ_ERR_INTERNAL in the blob's status */
 } tsq_pipeline;
 
 /* Problem statement (Algorithm 1 "Require": T, Q-bar, Delta; Eq. (ts): tau). */

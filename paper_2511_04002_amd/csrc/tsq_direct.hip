@@ -9,10 +9,14 @@
 //
 // Placement: the tokens are cut into blocks of kDirectBlock.  A workgroup adds up, for itself, the published
 // words of the tokens before it in its block (one or a few words per thread) and the prefix word of the
-// block's first token, which the last token of the block before has published.  Whoever waits, waits for
-// tokens of lower index only, and workgroups start in index order (on each die, in the order of those it
-// gets): the lowest unfinished token never waits for one that has not started, so every call ends,
-// whatever the number of workgroups that fit the device.  Every wait is bounded by p.spin_limit all the same.
+// block's first token, which the last token of the block before has published.
+//
+// Progress: whoever waits, waits for tokens of lower index only, and every die starts the workgroups it gets in the
+// order of their index.  So when all tokens before one are finished, that one has started or is the next of its die to
+// start, and the call ends whatever the number of workgroups that fit the device.  This rests on that order, and on
+// other work leaving every die some room: a die that something else fills keeps its tokens from starting, and
+// those on the other dies wait for them (the persistent kernel hands such tokens to workgroups that run, but its
+// scanner waits for every workgroup in the end).  Every wait is bounded by p.spin_limit, about a second.
 //
 // The last token's workgroup closes the blob: by the time it has its prefix every token is published, so
 // everybody has read the call's epoch and it can be moved on.  The header's status word is stored (device
