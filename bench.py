@@ -309,7 +309,7 @@ def main():
     # as a run of back-to-back launches over the rotating buffers between two events (an event pair around every
     # single launch reads 2-4 us more than the kernel lasts).  Staged pipeline: HIP events around every launch
     # inside the library (tsq_compress_timed).
-    names = ["k_fused"] if pipe == "fused" else ["k_row_stats", "k_scan", "k_pack"]
+    names = [tsq.tsq_plan_kernel(plan.handle)] if pipe == "fused" else ["k_row_stats", "k_scan", "k_pack"]
     acc = [0.0] * len(names)
 
     def run_of(call):
@@ -341,7 +341,7 @@ def main():
                 acc[j] += ms[j]
         torch.cuda.synchronize()
     # algorithmic bytes of each kernel: what it must read and write once
-    kalg = {"k_fused": alg_c, "k_row_stats": 2 * n + 9 * T, "k_scan": 29 * T, "k_pack": alg_c,
+    kalg = {"k_fused": alg_c, "k_direct": alg_c, "k_row_stats": 2 * n + 9 * T, "k_scan": 29 * T, "k_pack": alg_c,
             "k_unpack": alg_d}
     kern = {nm: {"ms": acc[j] / n_split, "alg_bytes": kalg[nm]} for j, nm in enumerate(names)}
     # decompress in its place behind compress (it then finds most of the blob in the memory-side cache; a run of

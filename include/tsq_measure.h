@@ -38,6 +38,12 @@ tsq_status tsq_measure_copy(void *d_dst, const void *d_src, size_t bytes, void *
 tsq_status tsq_measure_read(const void *d_src, size_t bytes, void *d_sink, void *stream);
 
 /*
+ * Which kernel a plan's compress calls run: "k_direct" (a workgroup per token), "k_fused" (as many workgroups as
+ * the device holds; see TSQ_PIPE_AUTO in tsq.h for devices that hold too few), or "staged".  NULL for a NULL plan.
+ */
+const char *tsq_plan_kernel(const tsq_plan *plan);
+
+/*
  * Bounds every device-side wait of the plan's later single-pass calls to `rounds` looks (>= 1; a new
  * plan has 2^20, about a second), so that a test can see what a call does whose waits expire.  Host
  * only.  The one call that writes to a plan: not while another thread uses it.

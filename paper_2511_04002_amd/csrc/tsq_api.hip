@@ -646,6 +646,10 @@ int tsq_check_workspace_shape(uint32_t ws_tokens, uint32_t ws_hidden, uint32_t t
 }
 
 // ---- include/tsq_measure.h
+const char *tsq_plan_kernel(const tsq_plan *plan) {
+    if (!plan) return nullptr;
+    return plan->pipeline != TSQ_PIPE_FUSED ? "staged" : use_direct(plan) ? "k_direct" : "k_fused";
+}
 tsq_status tsq_plan_limit_waits(tsq_plan *plan, uint32_t rounds) {
     if (!plan || rounds == 0) return TSQ_ERR_INVALID_ARG;
     plan->p.spin_limit = rounds;

@@ -180,6 +180,22 @@ def test_entropy_sizes(L, T, H):
     assert tsq.tsq_entropy_blob_bytes(0) == 0 and tsq.tsq_entropy_workspace_bytes(0) == 0
 
 
+@pytest.mark.parametrize("T,H,kernel", [
+    (1, 8, "k_direct"), (1 << 20, 2048, "k_direct"), ((1 << 26) - 1, 8, "k_direct"), (1 << 26, 8, "k_fused"),
+    (4096, 4096, "k_direct"), (4097, 2056, "k_fused"), (2730, 6144, "k_direct"), (2731, 4104, "k_fused"),
+    (2048, 8192, "k_direct"), (2049, 6152, "k_fused"), (1024, 8200, "k_direct"), (1025, 16384, "k_fused"),
+    (512, 16392, "k_direct"), (513, 32768, "k_fused"), (131072, 8192, "k_fused")])
+def test_the_shape_says_which_kernel_compresses(L, T, H, kernel):
+    """The rule that tsq.h states under TSQ_PIPE_FUSED, on both sides of its lines."""
+    for pipeline, want in ((tsq.TSQ_PIPE_AUTO, kernel), (tsq.TSQ_PIPE_FUSED, kernel), (tsq.TSQ_PIPE_STAGED, "staged")):
+        plan = tsq.tsq_plan_create(cfg(tokens=T, hidden=H, pipeline=pipeline))
+        try:
+            assert tsq.tsq_plan_kernel(plan) == want
+        finally:
+            tsq.tsq_plan_destroy(plan)
+    assert L.tsq_plan_kernel(None) is None
+
+
 def test_status_strings(L):
     seen = {tsq.tsq_status_string(s) for s in range(7)}
     assert len(seen) == 7 and "ok" in seen

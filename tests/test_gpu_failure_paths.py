@@ -24,15 +24,17 @@ def tsq():
 CTL_ERROR, CTL_TOKENS, CTL_HIDDEN = 1, 2, 3       # 32-bit words at the start of a workspace
 
 
-@pytest.mark.parametrize("pipeline", ["fused", "staged"])
-def test_a_workspace_of_another_shape_is_left_alone_and_reported(tsq, oracle, pipeline):
+@pytest.mark.parametrize("pipeline,tokens,fewer,kernel", [("fused", 600, 200, "k_direct"), ("fused", 5000, 4400, "k_fused"),
+                                                           ("staged", 600, 200, "staged")])
+def test_a_workspace_of_another_shape_is_left_alone_and_reported(tsq, oracle, pipeline, tokens, fewer, kernel):
     """A workspace that was never reset (all-ones bytes here), and one reset for a plan of another shape:
     the call stores a header with TSQ_ERR_FORMAT and nothing else, the workspace keeps every byte, and the
     plan it was reset for still gets the oracle's blob from it."""
     import torch
-    x = synth.make_c2(tokens=600)
+    x = synth.make_c2(tokens=tokens)
     T, H = x.shape
     plan = tsq.Plan(T, H, "f16", 8.0, (2, 3, 4, 6, 8), 0.05, pipeline=pipeline)
+    assert tsq.tsq_plan_kernel(plan.handle) == kernel
     xd = torch.from_numpy(x.view(np.int16)).cuda()
     blob = plan.new_blob()
     ws = torch.empty(int(plan.layout.workspace_bytes), dtype=torch.uint8, device="cuda")
@@ -43,11 +45,12 @@ def test_a_workspace_of_another_shape_is_left_alone_and_reported(tsq, oracle, pi
     assert info.return_status == tsq.TSQ_ERR_FORMAT and info.status == tsq.TSQ_ERR_FORMAT
     assert bool((ws == 0xFF).all())
     # a smaller plan's workspace
-    small = tsq.Plan(200, H, "f16", 8.0, (2, 3, 4, 6, 8), 0.05, pipeline=pipeline)
+    small = tsq.Plan(fewer, H, "f16", 8.0, (2, 3, 4, 6, 8), 0.05, pipeline=pipeline)
     ws2 = small.new_workspace()
     torch.cuda.synchronize()
     before = ws2.clone()
-    print("compress on the workspace of a 200-token plan", flush=True)
+    assert tsq.tsq_plan_kernel(small.handle) == kernel
+    print("compress on the workspace of a %d-token plan" % fewer, flush=True)
     plan.compress(xd, blob, ws2)
     assert plan.info(blob, check=False).return_status == tsq.TSQ_ERR_FORMAT
     assert torch.equal(ws2, before)
@@ -55,23 +58,25 @@ def test_a_workspace_of_another_shape_is_left_alone_and_reported(tsq, oracle, pi
     plan.decompress(blob, out)                              # refused: the output stays as it was
     torch.cuda.synchronize()
     assert bool((out == 0x1234).all())
-    ref = oracle.compress(x[:200], oracle.F16, 8.0, (2, 3, 4, 6, 8), 0.05, 1)
-    b2 = small.compress(xd[:200].contiguous(), None, ws2)
+    ref = oracle.compress(x[:fewer], oracle.F16, 8.0, (2, 3, 4, 6, 8), 0.05, 1, nthreads=8)
+    b2 = small.compress(xd[:fewer].contiguous(), None, ws2)
     assert small.info(b2).status == 0
     sec = small.sections(b2)
     for k in SECTIONS:
         assert np.array_equal(sec[k], getattr(ref, k)), k
 
 
-def test_a_failed_workspace_stays_failed_until_it_is_reset(tsq, oracle):
+@pytest.mark.parametrize("tokens,kernel", [(900, "k_direct"), (4400, "k_fused")])
+def test_a_failed_workspace_stays_failed_until_it_is_reset(tsq, oracle, tokens, kernel):
     """The error word of a workspace set by hand (as a call whose wait expired leaves it): every call on it,
     also on a blob that still holds a good header from before, ends with TSQ_ERR_INTERNAL; the blocking call
     with TSQ_PIPE_AUTO resets the workspace and compresses again with the staged kernels."""
     import torch
-    x = synth.make_c2(tokens=900)
+    x = synth.make_c2(tokens=tokens)
     T, H = x.shape
     ref = oracle.compress(x, oracle.F16, 8.0, (2, 3, 4, 6, 8), 0.05, 1, nthreads=8)
     plan = tsq.Plan(T, H, "f16", 8.0, (2, 3, 4, 6, 8), 0.05, pipeline="auto")
+    assert tsq.tsq_plan_kernel(plan.handle) == kernel
     xd = torch.from_numpy(x.view(np.int16)).cuda()
     ws = plan.new_workspace()
     blob = plan.compress(xd, None, ws)
@@ -104,16 +109,19 @@ def test_a_failed_workspace_stays_failed_until_it_is_reset(tsq, oracle):
     assert info.return_status == tsq.TSQ_ERR_INTERNAL
 
 
-def test_a_workspace_in_an_arbitrary_state_is_reported_and_recovers(tsq, oracle):
+@pytest.mark.parametrize("tokens,kernel", [(3000, "k_direct"), (5000, "k_fused")])
+def test_a_workspace_in_an_arbitrary_state_is_reported_and_recovers(tsq, oracle, tokens, kernel):
     """A workspace of all-ones bytes behind a control block that carries the right shape: the error word is
-    set, the table words carry no valid tag and the ticket counters wrap around.  Every token index the kernel
-    forms from them is still checked against the token count, and every store against its section, so the
-    call runs to its end and says TSQ_ERR_INTERNAL; after a reset the same buffers give the oracle's blob."""
+    set, the table words carry no valid tag and the ticket counters wrap around.  Every token index the persistent
+    kernel (more tokens than workgroups: tickets are drawn) forms from them is still checked against the token count,
+    and every store against its section; a workgroup per token looks at the error word first.  The call runs to its
+    end and says TSQ_ERR_INTERNAL; after a reset the same buffers give the oracle's blob."""
     import torch
-    x = synth.make_c2(tokens=3000)                         # more tokens than workgroups: tickets are drawn
+    x = synth.make_c2(tokens=tokens)
     T, H = x.shape
     ref = oracle.compress(x, oracle.F16, 8.0, (2, 3, 4, 6, 8), 0.05, 1, nthreads=8)
     plan = tsq.Plan(T, H, "f16", 8.0, (2, 3, 4, 6, 8), 0.05, pipeline="fused", max_outliers=max(ref.nnz, 1))
+    assert tsq.tsq_plan_kernel(plan.handle) == kernel
     xd = torch.from_numpy(x.view(np.int16)).cuda()
     ws = torch.empty(int(plan.layout.workspace_bytes), dtype=torch.uint8, device="cuda")
     ws.fill_(0xFF)
@@ -255,7 +263,7 @@ def test_an_expired_wait_comes_before_a_side_stream_that_is_full(tsq, T, H, dtyp
 
 def test_a_damaged_eblob_is_decoded_to_the_end_and_touches_only_the_payload(tsq, oracle):
     """Tables, stream bytes and stream offsets of a valid eblob overwritten with noise: the decoder
-    checks every offset against the stream capacity, reads past a stream's end as zeros and keeps
+    checks every offset against the stream capacity, repeats a stream's last words past its end and keeps
     every table index inside its table, so it writes (wrong) codes into the payload section and
     nothing else.  What is compared is everything outside the payload section."""
     import torch
@@ -339,16 +347,18 @@ def test_a_damaged_blob_is_decompressed_without_leaving_its_sections(tsq, oracle
     run("columns (noise)", int(L.off_out_col), g.integers(0, 256, 2 * max(ref.nnz, 1), dtype=np.uint8), [])
 
 
-def test_calls_that_alternate_between_two_streams_do_not_stall_each_other(tsq, oracle):
+@pytest.mark.parametrize("tokens,kernel", [(2048, "k_direct"), (4400, "k_fused")])
+def test_calls_that_alternate_between_two_streams_do_not_stall_each_other(tsq, oracle, tokens, kernel):
     """Two single-pass kernels that shared the device could hold the compute units that the other one's
     workgroups still needed, until their bounded waits expired; the library therefore orders such calls.
     Many short calls, alternating between two streams with a workspace each: every blob complete and
     equal to the oracle's."""
     import torch
-    x = synth.make_c2(tokens=2048)
+    x = synth.make_c2(tokens=tokens)
     T, H = x.shape
     ref = oracle.compress(x, oracle.F16, 8.0, (2, 3, 4, 6, 8), 0.05, 1, nthreads=8)
     plan = tsq.Plan(T, H, "f16", 8.0, (2, 3, 4, 6, 8), 0.05, pipeline="fused", max_outliers=max(ref.nnz, 1))
+    assert tsq.tsq_plan_kernel(plan.handle) == kernel
     xd = torch.from_numpy(x.view(np.int16)).cuda()
     lanes = [(torch.cuda.Stream(), plan.new_workspace(), [plan.new_blob() for _ in range(2)], plan.new_output())
              for _ in range(2)]
@@ -368,22 +378,24 @@ def test_calls_that_alternate_between_two_streams_do_not_stall_each_other(tsq, o
         assert np.array_equal(out.cpu().numpy().view(np.uint16), oracle.decompress(ref, nthreads=8))
 
 
-@pytest.mark.parametrize("shape", ["C2", "C4 rows"])
-def test_a_decompress_stream_behind_a_compress_stream(tsq, oracle, shape):
+@pytest.mark.parametrize("shape,tokens,kernel", [("C2", 2048, "k_direct"), ("C2", 4400, "k_fused"),
+                                                 ("C4 rows", 1536, "k_direct"), ("C4 rows", 2300, "k_fused")])
+def test_a_decompress_stream_behind_a_compress_stream(tsq, oracle, shape, tokens, kernel):
     """The launch pattern that bench.py calls two streams: every compress call on one stream, every decompress
     call on a second one, behind its compress call by an event, a blob written again only after the call that
     read it.  A step's restore kernel then runs beside the next step's single-pass kernel, whose workgroups
     wait for one another; many steps, different inputs per buffer set, every output equal to the oracle's."""
     import torch
     if shape == "C2":
-        base, dtype, tau, bits, odt = synth.make_c2(tokens=2048), "f16", 8.0, (2, 3, 4, 6, 8), oracle.F16
+        base, dtype, tau, bits, odt = synth.make_c2(tokens=tokens), "f16", 8.0, (2, 3, 4, 6, 8), oracle.F16
     else:
-        base, dtype, tau, bits, odt = synth.make_c4(tokens=1536), "bf16", 10.0, (2, 3, 4, 5, 6, 8), oracle.BF16
+        base, dtype, tau, bits, odt = synth.make_c4(tokens=tokens), "bf16", 10.0, (2, 3, 4, 5, 6, 8), oracle.BF16
     T, H = base.shape
     nset = 3
     xs = [np.ascontiguousarray(np.roll(base, 7 * k, axis=0)) for k in range(nset)]     # a tensor of its own per set
     refs = [oracle.compress(x, odt, tau, bits, 0.05, 1, nthreads=8) for x in xs]
     plan = tsq.Plan(T, H, dtype, tau, bits, 0.05, pipeline="fused", max_outliers=max(max(r.nnz for r in refs), 1))
+    assert tsq.tsq_plan_kernel(plan.handle) == kernel
     xd = [torch.from_numpy(x.view(np.int16)).cuda() for x in xs]
     blobs, outs, ws = [plan.new_blob() for _ in range(nset)], [plan.new_output() for _ in range(nset)], plan.new_workspace()
     first, second = torch.cuda.Stream(), torch.cuda.Stream()

@@ -114,6 +114,17 @@ def test_more_tensors_than_the_grid_has_workgroups(tsq, oracle, pipeline):
     check_batch(tsq, oracle, parts, "f16", 6.0, (2, 3, 4, 8), 0.1, pipeline, "1500 tensors of 3 rows")
 
 
+@pytest.mark.parametrize("tensors,rows,H,dtype", [(50, 100, 4096, "f16"), (7, 700, 2120, "bf16"), (41, 71, 5000, "f16"),
+                                                  (2200, 1, 8192, "bf16"), (3, 400, 8200, "f16")])
+def test_batches_that_take_the_persistent_kernel(tsq, oracle, tensors, rows, H, dtype):
+    plan = tsq.Plan(tensors * rows, H, dtype, 6.0, (2, 3, 4, 8), 0.1, pipeline="fused")
+    assert tsq.tsq_plan_kernel(plan.handle) == "k_fused"
+    g = np.random.Generator(np.random.PCG64(tensors + H))
+    v = g.standard_normal((tensors, rows, H)) * g.lognormal(0.0, 0.8, (tensors, rows, 1))
+    parts = [synth.to_f16_bits(t) if dtype == "f16" else synth.to_bf16_bits(t) for t in v]
+    check_batch(tsq, oracle, parts, dtype, 6.0, (2, 3, 4, 8), 0.1, "fused", "%d tensors of %d rows" % (tensors, rows))
+
+
 def test_rows_per_tensor_must_divide_the_tokens(tsq):
     import torch
     plan = tsq.Plan(12, 64, "f16", 6.0, (4, 8), 0.05)

@@ -19,6 +19,15 @@ MODE = {"lsb": 0, "rel_rms": 1}
 PIPELINES = ["fused", "staged"]
 
 
+def BOTH_KERNELS(few, many):
+    """(pipeline, tokens): the single pass on either side of the line between its two kernels, and the staged pipeline."""
+    return [("fused", few), ("fused", many), ("staged", few)]
+
+
+def expected_kernel(pipeline, T, many):
+    return "staged" if pipeline == "staged" else "k_fused" if T == many else "k_direct"
+
+
 @pytest.fixture(scope="module")
 def tsq():
     import torch
@@ -217,13 +226,14 @@ def test_all_width_subsets_small(tsq, oracle, pipeline):
         check_parity(tsq, oracle, x, "f16", 4.0, bs, bud, mode, pipeline, label="subset %s" % (bs,))
 
 
-@pytest.mark.parametrize("pipeline", PIPELINES)
-def test_side_stream_overflow_is_reported_and_decompress_refuses(tsq, oracle, pipeline):
+@pytest.mark.parametrize("pipeline,T", BOTH_KERNELS(64, 4400))
+def test_side_stream_overflow_is_reported_and_decompress_refuses(tsq, oracle, pipeline, T):
     import torch
-    x = synth.make_c2(tokens=64)
+    x = synth.make_c2(tokens=T)
     ref = oracle.compress(x, F16, 8.0, (2, 4, 8), 0.05, 1, nthreads=4)
     assert ref.nnz > 40
-    plan = tsq.Plan(64, 4096, "f16", 8.0, (2, 4, 8), 0.05, pipeline=pipeline, max_outliers=ref.nnz - 1)
+    plan = tsq.Plan(T, 4096, "f16", 8.0, (2, 4, 8), 0.05, pipeline=pipeline, max_outliers=ref.nnz - 1)
+    assert tsq.tsq_plan_kernel(plan.handle) == expected_kernel(pipeline, T, 4400)
     xd = torch.from_numpy(x.view(np.int16)).cuda()
     blob = plan.compress(xd)
     info = plan.info(blob, check=False)
@@ -236,7 +246,7 @@ def test_side_stream_overflow_is_reported_and_decompress_refuses(tsq, oracle, pi
     plan.decompress(blob, out)
     assert bool((out == 0x1234).all())                          # nothing written
     # the exact capacity works
-    plan2 = tsq.Plan(64, 4096, "f16", 8.0, (2, 4, 8), 0.05, pipeline=pipeline, max_outliers=ref.nnz)
+    plan2 = tsq.Plan(T, 4096, "f16", 8.0, (2, 4, 8), 0.05, pipeline=pipeline, max_outliers=ref.nnz)
     blob2 = plan2.compress(xd)
     assert plan2.info(blob2).status == 0
     assert np.array_equal(plan2.decompress(blob2).cpu().numpy().view(np.uint16), oracle.decompress(ref))
@@ -255,12 +265,12 @@ def test_decompress_refuses_a_foreign_blob(tsq):
     assert info.return_status == tsq.TSQ_ERR_FORMAT
 
 
-@pytest.mark.parametrize("pipeline", PIPELINES)
-def test_workspace_and_plan_serve_many_calls(tsq, oracle, pipeline):
+@pytest.mark.parametrize("pipeline,T", BOTH_KERNELS(700, 4500))
+def test_workspace_and_plan_serve_many_calls(tsq, oracle, pipeline, T):
     # one plan, one workspace, eleven calls on changing inputs: whatever a call leaves in the
     # workspace (tags, ticket counters, epoch) must not leak into the next one
     import torch
-    T, H = 700, 2048
+    H = 2048 if T == 700 else 2104
     g = np.random.Generator(np.random.PCG64(11))
     xs = []
     for k in range(3):
@@ -269,6 +279,7 @@ def test_workspace_and_plan_serve_many_calls(tsq, oracle, pipeline):
         xs.append(synth.to_bf16_bits(v))
     refs = [oracle.compress(x, BF16, 8.0, (2, 4, 5, 8), 0.1, 1, nthreads=8) for x in xs]
     plan = tsq.Plan(T, H, "bf16", 8.0, (2, 4, 5, 8), 0.1, pipeline=pipeline)
+    assert tsq.tsq_plan_kernel(plan.handle) == expected_kernel(pipeline, T, 4500)
     ws = plan.new_workspace()
     blob = plan.new_blob()
     out = plan.new_output()
@@ -300,13 +311,15 @@ def test_token_counts_around_the_grid_size(tsq, oracle, pipeline, T, H):
     check_parity(tsq, oracle, x, "f16", 6.0, (2, 3, 4, 6, 8), 0.15, "rel_rms", pipeline, label="T=%d H=%d" % (T, H))
 
 
-@pytest.mark.parametrize("pipeline", PIPELINES)
-def test_tokens_with_more_outliers_than_the_stash_holds(tsq, oracle, pipeline):
-    # rows with more outliers per wave than the single-pass kernel keeps in LDS (232 per wave of 2048 elements
-    # for this row length) take its re-read path; counts on both sides of that limit, mixed with ordinary
+@pytest.mark.parametrize("pipeline,T", BOTH_KERNELS(300, 4300))
+def test_tokens_with_more_outliers_than_the_stash_holds(tsq, oracle, pipeline, T):
+    # rows with more outliers per wave than the persistent kernel keeps in LDS (232 per wave of 2048 elements
+    # for this row length) take its re-read path (the kernel of short calls keeps none); counts on both sides of that limit, mixed with ordinary
     # rows and with rows that are all outliers
     g = np.random.Generator(np.random.PCG64(5))
-    T, H = 300, 4096
+    H = 4096
+    plan = tsq.Plan(T, H, "bf16", 6.0, (2, 4, 8), 0.05, pipeline=pipeline)
+    assert tsq.tsq_plan_kernel(plan.handle) == expected_kernel(pipeline, T, 4300)
     v = g.standard_normal((T, H))
     heavy = g.choice(T, 40, replace=False)
     for i, t in enumerate(heavy):
@@ -318,14 +331,15 @@ def test_tokens_with_more_outliers_than_the_stash_holds(tsq, oracle, pipeline):
     assert (cnt > 512).sum() >= 20 and (cnt > 410).sum() >= 40 and cnt.max() == H
 
 
-@pytest.mark.parametrize("pipeline", PIPELINES)
-def test_calls_captured_in_a_hip_graph_replay_correctly(tsq, oracle, pipeline):
+@pytest.mark.parametrize("pipeline,T", BOTH_KERNELS(700, 4400))
+def test_calls_captured_in_a_hip_graph_replay_correctly(tsq, oracle, pipeline, T):
     # compress + decompress captured once, replayed on changing input with eager work and synchronisation in
     # between; every replay must give what the eager calls give (the workspace state moves on from call to call)
     import torch
-    T, H = 700, 4096
+    H = 4096
     g = np.random.Generator(np.random.PCG64(21))
     plan = tsq.Plan(T, H, "f16", 6.0, (2, 3, 4, 6, 8), 0.1, pipeline=pipeline)
+    assert tsq.tsq_plan_kernel(plan.handle) == expected_kernel(pipeline, T, 4400)
     x_static = torch.zeros((T, H), dtype=torch.int16, device="cuda")
     blob, out, ws = plan.new_blob(), plan.new_output(), plan.new_workspace()
     plan.compress(x_static, blob, ws)                         # warm-up outside the capture (first-call set-up)

@@ -31,11 +31,36 @@ def test_both_sides_of_the_line_and_block_edges(tsq, oracle, T, H, dtype):
     check_parity(tsq, oracle, rows(T, H, dtype), dtype, 6.0, (2, 3, 4, 6, 8), 0.1, "rel_rms", "fused", label="T=%d H=%d" % (T, H))
 
 
-@pytest.mark.parametrize("T,H,dtype", [(40, 4096, "f16"), (40, 1032, "bf16"), (3200, 4096, "f16"), (1600, 8192, "bf16")])
-def test_tokens_full_of_outliers(tsq, oracle, T, H, dtype):
+def kernel_of(tsq, T, H, dtype):
+    return tsq.tsq_plan_kernel(tsq.Plan(T, H, dtype, 6.0, (2, 4, 8), 0.05, pipeline="fused").handle)
+
+
+# rows that fill their waves and rows that do not, per kernel; only the persistent one keeps outliers in LDS
+@pytest.mark.parametrize("T,H,dtype,kernel", [(40, 4096, "f16", "k_direct"), (40, 1032, "bf16", "k_direct"),
+                                              (3200, 4096, "f16", "k_direct"), (1600, 8192, "bf16", "k_direct"),
+                                              (5000, 4096, "f16", "k_fused"), (4300, 4088, "bf16", "k_fused"),
+                                              (2800, 6000, "f16", "k_fused"), (2200, 8192, "bf16", "k_fused"),
+                                              (1200, 8200, "f16", "k_fused"), (600, 32768, "bf16", "k_fused")])
+def test_tokens_full_of_outliers(tsq, oracle, T, H, dtype, kernel):
+    assert kernel_of(tsq, T, H, dtype) == kernel
     ref, _ = check_parity(tsq, oracle, rows(T, H, dtype, heavy=30), dtype, 6.0, (2, 4, 8), 0.05, "rel_rms", "fused",
                           label="heavy rows T=%d H=%d" % (T, H))
     assert np.diff(ref.row_ptr.astype(np.int64)).max() == H
+
+
+# more tokens than the device holds workgroups for, so that tickets are drawn: every number of waves, both types,
+# whole and ragged rows, both return rules, both modes
+@pytest.mark.parametrize("T,H,dtype,mode,rule", [
+    (4400, 4096, "bf16", "rel_rms", "as_printed"), (9001, 4088, "f16", "lsb", "last_passing"),
+    (5600, 6144, "f16", "rel_rms", "as_printed"), (3001, 5000, "bf16", "lsb", "as_printed"),
+    (2300, 8192, "f16", "rel_rms", "last_passing"), (4001, 6152, "bf16", "rel_rms", "as_printed"),
+    (1100, 16384, "f16", "rel_rms", "last_passing"), (1501, 8200, "bf16", "lsb", "as_printed"),
+    (700, 32768, "f16", "rel_rms", "as_printed"), (601, 16392, "bf16", "lsb", "last_passing")])
+def test_the_persistent_form_at_every_number_of_waves(tsq, oracle, T, H, dtype, mode, rule):
+    assert kernel_of(tsq, T, H, dtype) == "k_fused"
+    ref, _ = check_parity(tsq, oracle, rows(T, H, dtype), dtype, 6.0, (2, 3, 4, 5, 6, 8), 0.2, mode, "fused",
+                          label="T=%d H=%d" % (T, H), rule=rule)
+    assert len(set(ref.bits.tolist())) > 1
 
 
 @pytest.mark.parametrize("T", [2 ** 26 - 4096, 2 ** 26])

@@ -46,10 +46,14 @@ def both_ways(tsq, x, dtype, bit_set, budget, pipeline):
 
 @pytest.mark.parametrize("pipeline", ["fused", "staged"])
 def test_static_workspace_calls_in_a_row(tsq, pipeline):
-    # large, then smaller (fewer and shorter rows), then another shape, then the first again: every call
-    # finds what the one before left in the array
+    # large, then smaller (fewer and shorter rows), then another shape, then the first again, calls of either
+    # single-pass kernel among them: every call finds what the one before left in the array
     cases = [(1500, 4096, "f16", (2, 3, 4, 6, 8), 0.1, 11), (200, 1024, "bf16", (2, 4, 8), 0.2, 12),
-             (37, 8192, "bf16", (2, 3, 4, 5, 6, 8), 0.05, 13), (1500, 4096, "f16", (2, 3, 4, 6, 8), 0.1, 11)]
+             (37, 8192, "bf16", (2, 3, 4, 5, 6, 8), 0.05, 13), (1500, 4096, "f16", (2, 3, 4, 6, 8), 0.1, 11),
+             (5000, 4096, "f16", (2, 3, 4, 6, 8), 0.1, 14), (300, 4096, "f16", (2, 3, 4, 6, 8), 0.1, 15),
+             (2300, 8000, "bf16", (2, 3, 4, 6, 8), 0.1, 16), (5000, 4096, "f16", (2, 3, 4, 6, 8), 0.1, 14)]
+    kernels = {tsq.tsq_plan_kernel(tsq.Plan(T, H, dtype, 8.0, b, e, pipeline="fused").handle) for T, H, dtype, b, e, _ in cases}
+    assert kernels == {"k_direct", "k_fused"}
     for T, H, dtype, bit_set, budget, seed in cases:
         print("case", T, H, dtype, bit_set, budget, pipeline, flush=True)
         ref, got, out, ref_out = both_ways(tsq, rows(seed, T, H, dtype), dtype, bit_set, budget, pipeline)
