@@ -59,9 +59,9 @@ constexpr uint32_t kNoToken = 0xFFFFFFFFu;
 
 constexpr uint32_t kScanWavesMax = 4;   // waves of workgroup 0 that scan
 // Groups of 64 table words per round.  A round takes about 1.8 us, so the window caps the tokens per second:
-// 1024 tokens for the scanners of one to three waves (short rows, up to 300 tokens per us), 512 for four waves
-// (rows of 8192 elements and more: at most 160 tokens per us; the smaller window polls fewer lines that the
-// computing workgroups are writing to, which they notice)
+// 1024 tokens for the scanners of one to three waves (rows of up to 6144 elements: 65536 x 4096 in 196 us are 335
+// tokens per us), 512 for four waves (longer rows: at most 175 tokens per us; the smaller window polls fewer lines that
+// the computing workgroups are writing to, which they notice)
 constexpr int scan_groups(int waves) { return waves >= 4 ? 8 : 16; }
 
 // Who writes the blob's pay_off and row_ptr entries of a token.  A round of the scanner ends when its stores have been
@@ -646,7 +646,7 @@ typedef void (*FusedKernel)(const Params, const uint16_t *, uint8_t *, uint8_t *
 template <int DT, bool FULL, bool BATCH>
 static FusedKernel fused_kernel_for(uint32_t nw) {
     switch (nw) {
-        case 1: return k_fused<DT, 1, FULL, BATCH>;
+        case 1: return k_fused<DT, 1, FULL, BATCH>;            // (only for more tokens than one launch can have workgroups for)
         case 2: return k_fused<DT, 2, FULL, BATCH>;
         case 3: return k_fused<DT, 3, FULL, BATCH>;
         case 4: return k_fused<DT, 4, FULL, BATCH>;

@@ -367,10 +367,10 @@ k_rans_gather(const Params p, const EntropyLayout e, const uint8_t *__restrict__
 // classes 57 us, this form 42, a token per workgroup 45.)
 //
 // What bounds it is instruction issue (and, at few tokens, the chain of a step: table, product, comparison, place, word).
-// A token per workgroup of one wave, with tables of its own in two steps (slot -> code -> f, cum) and the words of the
-// stream fetched out of other lanes' registers, took 25 vector and 3 LDS instructions per step and 600 per token
-// for the tables; this form 14 and 2 per step (21 with tables and ring).  8192 x 8192 bf16 48 -> 39 us, 32768 x 4096 f16
-// 116 -> 81, 131072 x 768 235 -> 163, 2000 x 16384 59 -> 45, 300 x 5120 21 -> 19.
+// Counted on 8192 x 8192, per step and wave, tables, ring and start included: 25.1 vector and 3.2 LDS instructions for a
+// token per workgroup of one wave, with tables of its own in two steps (slot -> code -> f, cum) and the words of the
+// stream fetched out of other lanes' registers; 18.6 and 2.6 for this form.  8192 x 8192 bf16 48 -> 39 us, 32768 x 4096
+// f16 116 -> 73, 131072 x 768 234 -> 141, 2000 x 16384 59 -> 46, 300 x 5120 21 -> 18.
 constexpr uint32_t kDecWaves = 16, kDecThreads = 64u * kDecWaves, kDecTables = 3, kDecTableWords = kProbScale;
 constexpr uint32_t kDecLists = 4, kDecListBytes = kProbScale + 256u * 4u;     // ranks, then the list
 // A wave's words of the stream: a ring of two halves of 128 words, and the first 64 of them once more behind it, so
