@@ -59,9 +59,6 @@ uint32_t threshold_pattern(float tau, int dtype) {
 
 uint32_t row_bytes_host(uint32_t H, uint32_t b) { return 4u * ((H * b + 31u) / 32u); }
 
-std::once_flag g_prepare_once;
-int g_prepare_rc = 0;
-
 tsq_status hip_rc(int e) { return e == 0 ? TSQ_OK : TSQ_ERR_HIP; }
 
 }  // namespace
@@ -205,14 +202,23 @@ tsq_status tsq_plan_layout(const tsq_plan *plan, tsq_layout *out) {
 size_t tsq_plan_blob_bytes(const tsq_plan *plan) { return plan ? (size_t)plan->layout.blob_bytes : 0; }
 size_t tsq_plan_workspace_bytes(const tsq_plan *plan) { return plan ? (size_t)plan->layout.workspace_bytes : 0; }
 
+// Raises the kernels' dynamic-LDS limits, once per device that calls are made on: the limit belongs to the current
+// device's copy of a kernel.
 static tsq_status ensure_prepared() {
-    std::call_once(g_prepare_once, [] {
-        g_prepare_rc = prepare_kernels();
-        if (g_prepare_rc == 0) g_prepare_rc = prepare_fused_kernels();
-        if (g_prepare_rc == 0) g_prepare_rc = prepare_direct_kernels();
-        if (g_prepare_rc == 0) g_prepare_rc = prepare_rans_kernels();
-    });
-    return hip_rc(g_prepare_rc);
+    struct Prepared { std::once_flag once; int rc = 0; };
+    static Prepared prepared[kStaticMaxDevicesForOrder];
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess) return TSQ_ERR_HIP;
+    const auto prepare = [] {
+        int rc = prepare_kernels();
+        if (rc == 0) rc = prepare_fused_kernels();
+        if (rc == 0) rc = prepare_direct_kernels();
+        if (rc == 0) rc = prepare_rans_kernels();
+        return rc;
+    };
+    if (dev < 0 || dev >= kStaticMaxDevicesForOrder) return hip_rc(prepare());
+    std::call_once(prepared[dev].once, [&] { prepared[dev].rc = prepare(); });
+    return hip_rc(prepared[dev].rc);
 }
 
 // Computing workgroups of the fused kernel: as many as the device holds at once next to the scanner

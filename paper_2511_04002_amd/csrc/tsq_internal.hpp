@@ -150,6 +150,6 @@ int launch_rans_encode(const Params &p, const Geometry &g, const EntropyLayout &
 int launch_rans_decode(const Params &p, const EntropyLayout &e, const void *d_eblob, void *d_blob, void *stream);
 int launch_plain_copy(void *d_dst, const void *d_src, size_t bytes, void *stream);     // measurement aids
 int launch_plain_read(const void *d_src, size_t bytes, void *d_sink, void *stream);
-int prepare_kernels();  // raises the dynamic-LDS limit of the row kernels once per process
+int prepare_kernels();  // raises the dynamic-LDS limit of the row kernels (on the current device)
 
 }  // namespace tsq
