@@ -31,9 +31,11 @@ int tsq_check_stream_span(uint64_t begin, uint64_t end, uint64_t capacity, uint3
 int tsq_check_stream_move(uint32_t bytes, uint32_t coders, uint32_t slot_bytes, uint64_t at, uint64_t capacity);
 /* Index into the 4096-entry frequency table from a coder state (always below 4096). */
 uint32_t tsq_check_frequency_slot(uint32_t state);
-/* The entropy encoder's division step, for n pairs (HOST arrays): q[i] = the encoder's first estimate of
- * floor(x[i] / f[i]), which is that quotient or one less whenever 1 <= f[i] <= 4096 and x[i] < f[i] << 20
- * (the encoder then corrects it by the size of the remainder). */
+/* The entropy encoder's division, for n pairs (HOST arrays): q[i] = floor(x[i] / f[i]) whenever 1 <= f[i] <= 4096 and
+ * x[i] >= f[i], whatever low[i] < 65536 stands in the lowest bits of the reciprocal (the encoder keeps a sum there). */
+void tsq_check_divisions(const uint32_t *x, const uint32_t *f, const uint32_t *low, uint32_t *q, uint64_t n);
+/* The same by a binary32 reciprocal (not the encoder's any more): q[i] = an estimate of floor(x[i] / f[i]), which is that
+ * quotient or one less whenever 1 <= f[i] <= 4096 and x[i] < f[i] << 20 (the size of the remainder tells). */
 void tsq_check_quotients(const uint32_t *x, const uint32_t *f, uint32_t *q, uint64_t n);
 /* The shape recorded in a workspace against the plan's. */
 int tsq_check_workspace_shape(uint32_t ws_tokens, uint32_t ws_hidden, uint32_t tokens, uint32_t hidden);

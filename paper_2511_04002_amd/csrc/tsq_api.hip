@@ -640,6 +640,9 @@ int tsq_check_column(uint32_t column, uint32_t hidden) { return column_ok(column
 int tsq_check_stream_span(uint64_t begin, uint64_t end, uint64_t capacity, uint32_t coders, uint32_t slot_bytes) {
     return stream_span_ok(begin, end, capacity, coders, slot_bytes) ? 1 : 0;
 }
+void tsq_check_divisions(const uint32_t *x, const uint32_t *f, const uint32_t *low, uint32_t *q, uint64_t n) {
+    for (uint64_t i = 0; i < n; ++i) q[i] = quotient(x[i], reciprocal_just_above(f[i], low[i]));
+}
 void tsq_check_quotients(const uint32_t *x, const uint32_t *f, uint32_t *q, uint64_t n) {
     for (uint64_t i = 0; i < n; ++i) q[i] = quotient_or_one_less(x[i], reciprocal_just_below(f[i]));
 }

@@ -54,7 +54,22 @@ TSQ_HD bool stream_move_ok(uint32_t bytes, uint32_t coders, uint32_t slot_bytes,
 // Index into the 4096-entry cumulative-frequency table from a coder state.
 TSQ_HD uint32_t frequency_slot(uint32_t state) { return state & 4095u; }
 
-// The entropy coder's division.  floor(x / f) or one less, for x < f << 20 (so the quotient is below 2^20)
+// The entropy coder's division: floor(x / f) for f <= x < 2^32 and 1 <= f <= 4096, from a binary64 number `above` in
+// (1 / f, (1 + d) / f] with d <= 2^-34.  The exact product v = x * above is then more than x / f and at most
+// x / f + 1 / (4 f), so it has the integer part of x / f and stays at least 3 / (4 f) below the next integer.  The one
+// rounding of v + (2^52 - 1/2), to a multiple of 1 since the sum is 2^52 or more (v > 1), is to the nearest: v - 1/2 lies
+// strictly between floor(v) - 1/2 and floor(v) + 1/2, so the result is 2^52 + floor(v), whose lower word is the quotient.
+// The lowest 16 bits of `above` are free: it is the rounded 1 / f with those bits cut off, plus 2^16 units of its last
+// place, plus any `low` < 2^16 units (at most 2^17 of them beyond 1 / f: d <= 2^-35).
+TSQ_HD double reciprocal_just_above(uint32_t f, uint32_t low) {
+    const uint64_t r = __builtin_bit_cast(uint64_t, 1.0 / (double)f);
+    return __builtin_bit_cast(double, (r & ~0xFFFFull) + 0x10000ull + low);
+}
+TSQ_HD uint32_t quotient(uint32_t x, double above) {
+    return (uint32_t)__builtin_bit_cast(uint64_t, __builtin_fma((double)x, above, 4503599627370495.5));
+}
+
+// The same in binary32, for callers that correct it: floor(x / f) or one less, for x < f << 20 (so the quotient is below 2^20)
 // and 1 <= f <= 4096, from `below` = the binary32 quotient 1 / f times (1 - 2^-21), rounded.  With e = 2^-24
 // the unit roundoff: below lies in [(1 - 2^-21)(1 - e)^2 / f, (1 - 2^-21)(1 + e)^2 / f], and the product of
 // (float)x and below carries two more roundings, so it lies in [x/f * (1 - 2^-21)(1 - e)^4,

@@ -130,13 +130,18 @@ k_rans_tables(const Params p, const EntropyLayout e, const uint8_t *__restrict__
     table[c] = (uint16_t)fc;
 }
 
-// The table of a token's class into LDS, by one wave (lane l owns the codes 4l .. 4l+3): per code
-// x = f | cum << 16 (cum = exclusive running sum, < 4096) and y = the binary32 pattern of a value a
-// little below 1 / f (see quotient_or_one_less).  Eight bytes per code: wider entries cost more LDS
-// time than the instructions they save.
+// What a step of the encoder needs of a code with frequency f, in LDS: a binary64 reciprocal of f (see quotient()) whose
+// lowest 16 bits are cum (the exclusive running sum, < 4096), and 4096 - f.  Two arrays of eight-byte places, read at one
+// offset by an instruction each: what is read sixteen bytes at a time (one entry, or two places by one instruction) meets
+// in the banks of LDS far more often (26 cycles a step against 11, counted on 8192 x 8192; 103 us a call against 80).
+struct EncodeTable {
+    double above[256];
+    uint2 step[256];           // .x: 4096 - f
+};
+// The table of a token's class, by one wave (lane l owns the codes 4l .. 4l+3).
 // A code the table does not know (f = 0; cannot happen for a table built from the blob that is
 // coded) is entered with f = 1, which keeps the division defined.
-__device__ __forceinline__ void load_table(const uint16_t *table, uint2 *ftab) {
+__device__ __forceinline__ void load_table(const uint16_t *table, EncodeTable &ftab) {
     const uint32_t lane = threadIdx.x & 63u;
     uint32_t f[4], s = 0;
 #pragma unroll
@@ -145,7 +150,8 @@ __device__ __forceinline__ void load_table(const uint16_t *table, uint2 *ftab) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const uint32_t fi = f[i] ? f[i] : 1u;
-        ftab[4u * lane + i] = make_uint2(fi | (cum << 16), __float_as_uint(reciprocal_just_below(fi)));
+        ftab.above[4u * lane + i] = reciprocal_just_above(fi, cum & (kProbScale - 1u));
+        ftab.step[4u * lane + i].x = kProbScale - fi;
         cum += f[i];
     }
 }
@@ -157,12 +163,45 @@ __device__ __forceinline__ uint32_t rank_in(uint64_t who) {
 
 // ---------------------------------------------------------------- encode
 
+// A SIMD holds the waves of eight tokens, each a chain of dependent steps, and its arbiter prefers the oldest
+// wave: left alone, the waves finish one after the other and the last ones run with the SIMD half idle.  A wave
+// therefore lowers its issue priority as it gets ahead (by quarters of its rounds), which keeps the eight in step.
+// `done` of `total` rounds are behind the wave (uniform).
+__device__ __forceinline__ void priority_by_progress(uint32_t done, uint32_t total) {
+    if (4u * done < total) __builtin_amdgcn_s_setprio(3);
+    else if (2u * done < total) __builtin_amdgcn_s_setprio(2);
+    else if (4u * done < 3u * total) __builtin_amdgcn_s_setprio(1);
+    else __builtin_amdgcn_s_setprio(0);
+}
+
+// a * b + c of 24-bit factors in one instruction (left to itself the compiler adds c and what it is the sum of to the
+// product, one instruction more and all of them behind the product)
+__device__ __forceinline__ uint32_t mad_u24(uint32_t a, uint32_t b, uint32_t c) {
+    uint32_t d;
+    asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    return d;
+}
+// 8 times byte k of w in one instruction
+__device__ __forceinline__ uint32_t eight_times_byte(uint32_t w, int k) {
+    uint32_t d;
+    const uint32_t three = 3;
+    if (k == 0) asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_0" : "=v"(d) : "v"(three), "v"(w));
+    else if (k == 1) asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_1" : "=v"(d) : "v"(three), "v"(w));
+    else if (k == 2) asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_2" : "=v"(d) : "v"(three), "v"(w));
+    else asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_3" : "=v"(d) : "v"(three), "v"(w));
+    return d;
+}
+
 // The steps of one round (run number `round` of every lane), last element first.  The words go
 // straight to the token's slot in the workspace, which fills from its end downwards.
-// WHOLE: every lane's run of this round lies inside the row (valid >= 32 everywhere), so no step
-// needs a range check.
+// Bound by the issue of vector instructions: 11 to 13 a step (19 with a binary32 estimate of the quotient, its
+// correction and a limit of its own per code), four cycles each, beside 11 cycles of LDS a step and compute unit.  The call on
+// 8192 x 8192 bf16 87 -> 76 us, 32768 x 4096 f16 169 -> 157, 131072 x 768 f16 344 -> 304, 16384 x 8192 151 -> 139,
+// 2048 x 4096 34 -> 33.  (Entries of four bytes a table, two addresses: 81, 158, 308.  The limit of a code looked up, too,
+// in sixteen bytes at once: 90, 177, 312.)
+// WHOLE: the run of every lane that takes part lies inside the row (valid >= 32), so no step needs a range check.
 template <int B, bool WHOLE>
-__device__ __forceinline__ void encode_round(const uint32_t *src_row, uint32_t run, int valid, const uint2 *ftab,
+__device__ __forceinline__ void encode_round(const uint32_t *src_row, uint32_t run, int valid, const EncodeTable &ftab,
                                              uint16_t *out, uint32_t &ptr, uint32_t &x) {
     uint32_t d[B];
     const uint32_t nd = (WHOLE || valid >= 32) ? (uint32_t)B : (valid > 0 ? ((uint32_t)valid * B + 31u) >> 5 : 0u);
@@ -172,31 +211,46 @@ __device__ __forceinline__ void encode_round(const uint32_t *src_row, uint32_t r
 #pragma unroll
         for (int k = 0; k < B; ++k) d[k] = (uint32_t)k < nd ? src_row[run * B + k] : 0u;
     }
+    // what the next step needs is looked up a step ahead
+    auto look_up = [&](int j, double &above, uint32_t &step) {
+        uint32_t at;                                               // 8 * code
+        if constexpr (B == 8) {
+            at = eight_times_byte(d[j >> 2], j & 3);
+        } else {
+            const int off = j * B, k = off >> 5, sh = off & 31;
+            uint32_t code = d[k] >> sh;
+            if (sh + B > 32) code |= d[k + 1 < B ? k + 1 : k] << (32 - sh);
+            at = (code & ((1u << B) - 1u)) << 3;
+        }
+        above = *reinterpret_cast<const double *>(reinterpret_cast<const uint8_t *>(ftab.above) + at);
+        step = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const uint8_t *>(ftab.step) + at);
+    };
+    double above, next_above;
+    uint32_t step, next_step;
+    look_up(31, next_above, next_step);
 #pragma unroll
     for (int j = 31; j >= 0; --j) {
-        const int off = j * B, k = off >> 5, sh = off & 31;
-        uint32_t code = d[k] >> sh;
-        if (sh + B > 32) code |= d[k + 1 < B ? k + 1 : k] << (32 - sh);
-        code &= (1u << B) - 1u;
         const bool active = WHOLE || j < valid;
-        const uint2 entry = ftab[code];
-        const uint32_t f = entry.x & 0xFFFFu;
-        const bool shed = active && (x >> 20) >= f;            // x >= f << 20, without overflow for f = 4096
-        const uint64_t who = __builtin_amdgcn_ballot_w64(shed);
+        above = next_above;
+        step = next_step;
+        if (j > 0) look_up(j - 1, next_above, next_step);
+        // q = floor(x / f); the state sheds a word if x >= f << 20, that is q >= 2^20, and the quotient of what is left
+        // is then q >> 16
+        uint32_t q = quotient(x, above);
+        const bool over = q >= (1u << 20), shed = active && over;
+        const uint64_t who = WHOLE ? __builtin_amdgcn_ballot_w64(over) : __builtin_amdgcn_ballot_w64(active) & __builtin_amdgcn_ballot_w64(over);
         ptr -= (uint32_t)__builtin_popcountll(who);
         if (shed) {
             // (a 32-bit byte offset from a uniform base: one instruction for the address)
             const uint32_t at = (ptr + rank_in(who)) << 1;
             *reinterpret_cast<uint16_t *>(reinterpret_cast<uint8_t *>(out) + at) = (uint16_t)x;
             x >>= 16;
+            q >>= 16;
         }
-        if (active) {
-            // x -> (q << 12) + (x - q f) + cum with q = floor(x / f) = q1 or q1 + 1
-            const uint32_t q1 = quotient_or_one_less(x, __uint_as_float(entry.y));
-            const uint32_t r1 = x - __umul24(q1, f);           // x - q1 f: the remainder, or f more
-            const uint32_t more = r1 >= f ? kProbScale - f : 0u;
-            x = (q1 << kProbBits) + r1 + (entry.x >> 16) + more;
-        }
+        // x -> (q << 12) + (x - q f) + cum = q (4096 - f) + (x + cum)
+        const uint32_t cum = (uint32_t)__builtin_bit_cast(uint64_t, above) & 0xFFFFu;
+        const uint32_t y = mad_u24(q, step, x + cum);
+        if (active) x = y;
     }
 }
 
@@ -205,7 +259,7 @@ __device__ __forceinline__ void encode_round(const uint32_t *src_row, uint32_t r
 __global__ void __launch_bounds__(64)
 k_rans_encode(const Params p, const EntropyLayout e, const uint8_t *__restrict__ blob, const uint8_t *__restrict__ eblob,
               uint8_t *__restrict__ ews) {
-    __shared__ uint2 ftab[256];
+    __shared__ EncodeTable ftab;
     const uint32_t t = blockIdx.x, lane = threadIdx.x;
     uint32_t *len = reinterpret_cast<uint32_t *>(ews + e.ws_len);
     if (!blob_is_valid(p, blob)) return;
@@ -223,29 +277,29 @@ k_rans_encode(const Params p, const EntropyLayout e, const uint8_t *__restrict__
     const uint32_t rounds = (p.runs + 63u) / 64u, cap = (e.slot_bytes - 256u) >> 1;   // one word per element at most
     uint32_t x = kRansLow, ptr = cap;
     for (uint32_t r = rounds; r-- > 0;) {
+        priority_by_progress(rounds - 1u - r, rounds);
         const uint32_t run = lane + 64u * r;
         const int valid = (int)p.hidden - (int)(run * kRun);          // may be <= 0: nothing of this run exists
-        if (__builtin_amdgcn_ballot_w64(valid < 32) == 0) {
-            switch (width) {
-                case 2: encode_round<2, true>(src_row, run, valid, ftab, out, ptr, x); break;
-                case 3: encode_round<3, true>(src_row, run, valid, ftab, out, ptr, x); break;
-                case 4: encode_round<4, true>(src_row, run, valid, ftab, out, ptr, x); break;
-                case 5: encode_round<5, true>(src_row, run, valid, ftab, out, ptr, x); break;
-                case 6: encode_round<6, true>(src_row, run, valid, ftab, out, ptr, x); break;
-                case 7: encode_round<7, true>(src_row, run, valid, ftab, out, ptr, x); break;
-                default: encode_round<8, true>(src_row, run, valid, ftab, out, ptr, x); break;
+#define TSQ_ENCODE_ROUND(WHOLE)    \
+    switch (width) {               \
+        case 2: encode_round<2, WHOLE>(src_row, run, valid, ftab, out, ptr, x); break;  \
+        case 3: encode_round<3, WHOLE>(src_row, run, valid, ftab, out, ptr, x); break;  \
+        case 4: encode_round<4, WHOLE>(src_row, run, valid, ftab, out, ptr, x); break;  \
+        case 5: encode_round<5, WHOLE>(src_row, run, valid, ftab, out, ptr, x); break;  \
+        case 6: encode_round<6, WHOLE>(src_row, run, valid, ftab, out, ptr, x); break;  \
+        case 7: encode_round<7, WHOLE>(src_row, run, valid, ftab, out, ptr, x); break;  \
+        default: encode_round<8, WHOLE>(src_row, run, valid, ftab, out, ptr, x); break; \
+    }
+        if (__builtin_amdgcn_ballot_w64(valid > 0 && valid < 32) == 0) {
+            // no run is cut: the lanes whose run lies beyond the row (the last ones, if any) sit the round out
+            if (valid > 0) {
+                TSQ_ENCODE_ROUND(true)
             }
+            ptr = uniform(ptr);
         } else {
-            switch (width) {
-                case 2: encode_round<2, false>(src_row, run, valid, ftab, out, ptr, x); break;
-                case 3: encode_round<3, false>(src_row, run, valid, ftab, out, ptr, x); break;
-                case 4: encode_round<4, false>(src_row, run, valid, ftab, out, ptr, x); break;
-                case 5: encode_round<5, false>(src_row, run, valid, ftab, out, ptr, x); break;
-                case 6: encode_round<6, false>(src_row, run, valid, ftab, out, ptr, x); break;
-                case 7: encode_round<7, false>(src_row, run, valid, ftab, out, ptr, x); break;
-                default: encode_round<8, false>(src_row, run, valid, ftab, out, ptr, x); break;
-            }
+            TSQ_ENCODE_ROUND(false)
         }
+#undef TSQ_ENCODE_ROUND
     }
     const uint32_t coders = p.runs < 64u ? p.runs : 64u;  // coders that own a run; the others still hold 2^16
     if (lane < coders) reinterpret_cast<uint32_t *>(slot)[lane] = x;
@@ -482,20 +536,6 @@ __device__ __forceinline__ void words_advance(Words &q, uint32_t n) {
         if (q.end == q.ring + 4u * kHalfWords) { q.at -= 4u * kHalfWords; q.end -= 4u * kHalfWords; }
         q.end += 2u * kHalfWords;
         q.ahead = pair_at(q, q.portion);
-    }
-}
-
-// A SIMD holds the waves of eight tokens, each a chain of dependent steps, and its arbiter prefers the oldest
-// wave: left alone, the waves finish one after the other and the last ones run with the SIMD half idle.  A wave
-// therefore lowers its issue priority as it gets ahead (by quarters of its rounds), which keeps the eight in
-// step.  (The encoder, whose steps wait less, gains nothing from it.)
-// `done` of `total` rounds are behind the wave (uniform).
-__device__ __forceinline__ void priority_by_progress(uint32_t done, uint32_t total) {
-    switch ((4u * done) / total) {
-        case 0: __builtin_amdgcn_s_setprio(3); break;
-        case 1: __builtin_amdgcn_s_setprio(2); break;
-        case 2: __builtin_amdgcn_s_setprio(1); break;
-        default: __builtin_amdgcn_s_setprio(0); break;
     }
 }
 

@@ -1,0 +1,29 @@
+"""The division of the entropy encoder (a binary64 product with a reciprocal just above 1 / f, rounded once), run on the
+host by the very routine that the kernel compiles: exact for every frequency, at and around multiples of it, at the
+ends of the range of states, and whatever stands in the lowest 16 bits of the reciprocal."""
+import numpy as np
+import pytest
+
+from paper_2511_04002_amd import build as tsq_build
+from paper_2511_04002_amd import tsq
+
+
+@pytest.mark.parametrize("low", [0, 1, 4095, 65535])
+def test_division_is_exact(low):
+    tsq_build.build()
+    g = np.random.Generator(np.random.PCG64(11 + low))
+    f = np.repeat(np.arange(1, 4097, dtype=np.int64), 160)
+    top = (1 << 32) - 1
+    q = g.integers(1, top // f + 1)
+    near = np.array([-1, 0, 1, 2])[g.integers(0, 4, f.size)]
+    x = np.where(g.random(f.size) < 0.7, q * f + near, g.integers(1 << 16, 1 << 32, f.size))
+    # the ends: the smallest state, the largest one that sheds nothing, the first that sheds, the largest word
+    edge = np.stack([f, (f << 20) - 1, f << 20, np.full_like(f, top), np.full_like(f, 1 << 16), top // f * f, top // f * f - 1])
+    pick = g.integers(0, 7, f.size)
+    x = np.where(g.random(f.size) < 0.1, edge[pick, np.arange(f.size)], x)
+    x = np.clip(x, f, top)
+    x32, f32 = x.astype(np.uint32), f.astype(np.uint32)
+    lows, out = np.full(f.size, low, np.uint32), np.zeros(f.size, np.uint32)
+    tsq.lib().tsq_check_divisions(x32.ctypes.data, f32.ctypes.data, lows.ctypes.data, out.ctypes.data, f.size)
+    wrong = np.nonzero(out.astype(np.int64) != x // f)[0]
+    assert wrong.size == 0, (x[wrong[:3]], f[wrong[:3]], out[wrong[:3]])
