@@ -15,10 +15,8 @@
 // workgroup which tag the tables of this call use.
 //
 // Per token a workgroup publishes one 32-bit word (tag, payload words, outliers) in a table.
-// The scanner reads the table in order, 512 or 1024 words per round, and for the leading run of
-// published tokens writes (tag, words before, outliers before) into a second table, and (except for
-// rows of two waves) the blob's pay_off / row_ptr entries on the way.  Nobody else adds anything up.  (One wave alone
-// does not keep up with 200 tokens per microsecond: its rounds are chains of dependent steps.)
+// The scanner reads the table in order, 1024 words per round, and for the leading run of
+// published tokens writes (tag, words before, outliers before) into a second table.  Nobody else adds anything up.
 //
 // A token is stored two iterations after it was computed: iteration i computes token i,
 // publishes it, stores token i-2 and then packs token i's codes into the payload image in LDS
@@ -58,35 +56,44 @@ constexpr uint32_t kNoToken = 0xFFFFFFFFu;
 // ---------------------------------------------------------------- the scanner (workgroup 0, one wave)
 
 constexpr uint32_t kScanWavesMax = 4;   // waves of workgroup 0 that scan
-// Groups of 64 table words per round.  A round takes about 1.8 us, so the window caps the tokens per second:
-// 1024 tokens for the scanners of one to three waves (rows of up to 6144 elements: 65536 x 4096 in 196 us are 335
-// tokens per us), 512 for four waves (longer rows: at most 175 tokens per us; the smaller window polls fewer lines that
-// the computing workgroups are writing to, which they notice)
-constexpr int scan_groups(int waves) { return waves >= 4 ? 8 : 16; }
+// A round looks at four groups of 256 table words, four consecutive words per lane.
+constexpr int kScanGroups = 4;
+constexpr uint32_t kScanGroupTokens = 256;
 
-// Who writes the blob's pay_off and row_ptr entries of a token.  A round of the scanner ends when its stores have been
-// acknowledged (loads and stores share one counter on this chip, so the next round's loads are waited for together with
-// them), and a scanner of two waves, 512 tokens each, is what bounds rows of up to 4096 elements: with the two entries
-// left to the workgroup that stores the token, 65536 x 4096 f16 goes from 237 to 196 us (187 without any wait for a prefix),
-// 16384 x 4096 bf16 from 68 to 62.  Three waves: 80 x 1024 x 5120 f16 314 us with the scanner's contiguous stores, 329
-// without; four: 131072 x 8192 748 against 760.
-template <int R> constexpr bool kComputeWritesOffsets = R == 2;
+// The blob's pay_off and row_ptr entries of a token are left to the workgroup that stores it: a round of the scanner ends
+// when its stores have been acknowledged (loads and stores share one counter on this chip, so the next round's loads are
+// waited for together with them).  With those stores in the scanner: 65536 x 8192 bf16 337 us against 323 (one width
+// only: 369 / 340), 65536 x 6144 f16 251 / 216, 131072 x 8192 708 / 702.
 
-// The scanner: R waves of workgroup 0 (this one has index wv) work in rounds.  A round looks at
-// the next 64 * scan_groups(R) tokens from the frontier on, cut into groups of 64 that are dealt out to
-// the waves in turn (group k to wave k % R).  Every wave sums up its groups' leading runs of
-// published tokens (lane l of a group is its l-th token: loads and stores are contiguous over
-// the wave) and leaves their lengths and totals in LDS; after a barrier every wave knows, from
-// those, which groups are usable (all before the first incomplete one, and that one up to its
-// first gap) and what lies before each of its own, stores the prefixes of its groups, and moves
-// the frontier, which all waves keep in step without exchanging it.
-// lds: 8 + 2 * 3 * 16 dwords of LDS (workgroup 0 uses none otherwise).  waves_total: computing
+// Payload words of a token from its table word.
+__device__ __forceinline__ uint32_t words_of(const Params &p, uint32_t word) {
+    return (__umul24(p.hidden, (word >> 26) & 15u) + 31u) >> 5;
+}
+// 16 bytes of a window that other dies write to (cache policy sc1, as an agent-scope load; volatile: never merged with
+// the same load of another round).
+__device__ __forceinline__ u32x4 load_quad_coherent(__amdgpu_buffer_rsrc_t window, uint32_t offset) {
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(window, (int)offset, 0, (int)(16u | (1u << 31))));
+}
+
+// The scanner: R waves of workgroup 0 (this one has index wv) work in rounds.  A round looks at the next 1024 tokens from
+// the frontier on, a multiple of four, cut into groups of 256 that are dealt out to the waves in turn (group k to wave
+// k % R).  A lane takes four consecutive words of a group in one load and counts if all four are published.  Every wave
+// sums up its groups' leading runs of such lanes and leaves their lengths and totals in LDS; after a barrier every wave
+// knows, from those, which groups are usable (all before the first incomplete one, and that one up to its
+// first gap) and what lies before each of its own, stores the prefixes of its groups (those of a gap's own published words,
+// too, though the frontier stops before them: nobody waits for a token after the one he waits for), and moves
+// the frontier, which all waves keep in step without exchanging it.  The prefixes go through LDS, so that a store
+// instruction writes consecutive bytes over the wave.
+// What bounds it is the latency of a round (two memory round trips), which every prefix waits for.  One word per lane and
+// 64 tokens a group, a scan each, made a round of two waves 3 us, and a prefix was written 6.7 us after the last size
+// before it: 65536 x 4096 f16 196 us, now 173; 16384 x 4096 bf16 62 / 54.
+// lds: kScanLds + R * 512 dwords of LDS (workgroup 0 uses none otherwise).  waves_total: computing
 // waves of the grid, each of which reports once when it is done.
+constexpr uint32_t kScanLds = 112;
 template <int R>
 __device__ void scan_tokens(const Params &p, uint8_t *blob, uint8_t *ws, uint32_t waves_total, uint32_t *lds,
                             uint32_t wv) {
-    constexpr int kScanPerWave = scan_groups(R) / R;
-    constexpr int kGroups = kScanPerWave * R;
+    constexpr int kScanPerWave = (kScanGroups + R - 1) / R;
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t T = p.tokens, C = p.fused_classes;
     uint32_t *ctrl = reinterpret_cast<uint32_t *>(ws + p.ws_ctrl);
@@ -107,81 +114,90 @@ __device__ void scan_tokens(const Params &p, uint8_t *blob, uint8_t *ws, uint32_
     const uint32_t epoch = (uniform(word_load(tickets + opaque_zero())) >> kTicketBits) % 3u;
     const uint32_t tag = epoch + 1u, tag3 = tag << 30;
 
-    // Rows of a multiple of 32 elements (the common case) take H/32 payload words per bit of width, so
-    // that one running sum serves both outputs: count + (width << 22) summed over 64 tokens carries
-    // neither into the other (counts <= 2^15 each, widths <= 8).  Other rows get two sums.
-    const bool packed = (p.hidden & 31u) == 0;
-    const uint32_t words_per_bit = p.hidden >> 5;
+    // pos: the frontier; bw, bc: payload words and outliers before it
     uint32_t pos = 0, bw = 0, bc = 0, idle = 0, round = 0;
+    uint32_t *turned = lds + kScanLds + wv * 512u;     // the wave's prefixes on their way through LDS
     // wave 0 decides when to give up (its verdict travels with the round's data): a workspace that an
     // earlier call left in its failed state (or that was never reset) stays failed
     bool bad = wv == 0 && uniform(word_load(error_flag + opaque_zero())) != 0;
     while (pos < T) {
         uint32_t *lead_at = lds + 8 + (round & 1u) * 48u, *sum_at = lead_at + 16, *sum2_at = lead_at + 32;
-        uint32_t w[kScanPerWave];
+        u32x4 w[kScanPerWave];
 #pragma unroll
         for (int i = 0; i < kScanPerWave; ++i) {
-            const uint32_t j = pos + 64u * (wv + (uint32_t)(R * i)) + lane;
-            w[i] = 0;                                   // past the end: not published
-            if (j < T) w[i] = word_load(sizes + j);
+            const uint32_t k = wv + (uint32_t)(R * i), start = pos + kScanGroupTokens * k;
+            const uint32_t left = k < (uint32_t)kScanGroups && start < T ? T - start : 0u;   // tokens from the group on
+            // (what lies past the end comes back as 0)
+            w[i] = load_quad_coherent(raw_window(sizes + start, left < kScanGroupTokens ? 4u * left : 4u * kScanGroupTokens), 16u * lane);
+            // past the end: published, and of no size
+#pragma unroll
+            for (uint32_t m = 0; m < 4; ++m)
+                if (4u * lane + m >= left) w[i][m] = tag3;
         }
         uint32_t before[kScanPerWave], before2[kScanPerWave], lead[kScanPerWave];
 #pragma unroll
         for (int i = 0; i < kScanPerWave; ++i) {
-            const uint64_t missing = __builtin_amdgcn_ballot_w64((w[i] & 0xC0000000u) != tag3);
-            lead[i] = missing ? (uint32_t)__builtin_ctzll(missing) : 64u;     // published tokens in front of the group
-            const bool mine = lane < lead[i];
-            const uint32_t width = (w[i] >> 26) & 15u, cnt = w[i] & 0xFFFFu;
-            uint32_t total, total2 = 0;
-            if (packed) {
-                const uint32_t v = mine ? cnt | (width << 22) : 0u;
-                const uint32_t upto = wave_incl_scan_u32(v);
-                before[i] = upto - v;
-                before2[i] = 0;
-                total = lane_value(upto, 63);
-            } else {
-                const uint32_t cw = mine ? row_bytes(p.hidden, width) >> 2 : 0u, cc = mine ? cnt : 0u;
-                const uint32_t iw = wave_incl_scan_u32(cw), ic = wave_incl_scan_u32(cc);
-                before[i] = ic - cc;
-                before2[i] = iw - cw;
-                total = lane_value(ic, 63);
-                total2 = lane_value(iw, 63);
+            const uint32_t unlike = (w[i][0] ^ tag3) | (w[i][1] ^ tag3) | (w[i][2] ^ tag3) | (w[i][3] ^ tag3);
+            const uint64_t missing = __builtin_amdgcn_ballot_w64((unlike & 0xC0000000u) != 0);
+            lead[i] = missing ? (uint32_t)__builtin_ctzll(missing) : 64u;     // whole lanes in front of the group
+            uint32_t cc = 0, cw = 0;
+#pragma unroll
+            for (uint32_t m = 0; m < 4; ++m) {
+                cc += w[i][m] & 0xFFFFu;
+                cw += words_of(p, w[i][m]);
             }
-            if (lane == 0) {
-                const uint32_t k = wv + (uint32_t)(R * i);
+            if (lane >= lead[i]) { cc = 0; cw = 0; }
+            const uint32_t ic = wave_incl_scan_u32(cc), iw = wave_incl_scan_u32(cw);
+            before[i] = ic - cc;
+            before2[i] = iw - cw;
+            if (lane == 63u) {
+                const uint32_t k = wv + (uint32_t)(R * i);      // (a group that is not there: written beyond the ones that count)
                 lead_at[k] = lead[i];
-                sum_at[k] = total;
-                sum2_at[k] = total2;
+                sum_at[k] = ic;
+                sum2_at[k] = iw;
             }
         }
         if (wv == 0 && lane == 0) lds[0] = bad ? 1u : 0u;
         lds_barrier();
         if (uniform(lds[0])) { bad = true; break; }
         // ---- which groups count, and what lies before each: lane k looks at group k
-        const uint32_t gl = lane < (uint32_t)kGroups ? lead_at[lane] : 64u;
+        const uint32_t gl = lane < (uint32_t)kScanGroups ? lead_at[lane] : 64u;
         const uint64_t gaps = __builtin_amdgcn_ballot_w64(gl != 64u);
-        const uint32_t first_gap = gaps ? (uint32_t)__builtin_ctzll(gaps) : (uint32_t)kGroups;   // groups before it are complete
-        const bool counts = lane <= first_gap && lane < (uint32_t)kGroups;
-        // (a packed group total is taken apart here: the widths of several groups would overflow their field)
-        const uint32_t raw = counts ? sum_at[lane] : 0u;
-        const uint32_t gs = packed ? raw & 0x3FFFFFu : raw;                                 // outliers of group `lane`
-        const uint32_t gs2 = packed ? (raw >> 22) * words_per_bit : (counts ? sum2_at[lane] : 0u);   // its payload words
+        const uint32_t first_gap = gaps ? (uint32_t)__builtin_ctzll(gaps) : (uint32_t)kScanGroups;   // groups before it are complete
+        const bool counts = lane <= first_gap && lane < (uint32_t)kScanGroups;
+        const uint32_t gs = counts ? sum_at[lane] : 0u;          // outliers of group `lane`
+        const uint32_t gs2 = counts ? sum2_at[lane] : 0u;        // its payload words
         const uint32_t upto = wave_incl_scan_u32(gs), upto2 = wave_incl_scan_u32(gs2);
-        const uint32_t gone = wave_sum_u32(counts ? gl : 0u);                 // tokens the frontier moves by
+        const uint32_t gone = 4u * wave_sum_u32(counts ? gl : 0u);            // tokens the frontier moves by
 #pragma unroll
         for (int i = 0; i < kScanPerWave; ++i) {
-            const uint32_t k = wv + (uint32_t)(R * i);
-            if (k <= first_gap && lane < lead[i]) {
-                const uint32_t gb = lane_value(upto - gs, (int)k), gb2 = lane_value(upto2 - gs2, (int)k);
-                // payload words / outliers before the lane's token
-                const uint32_t ew = bw + gb2 + (packed ? (before[i] >> 22) * words_per_bit : before2[i]);
-                const uint32_t ec = bc + gb + (packed ? before[i] & 0x3FFFFFu : before[i]);
-                const uint32_t j = pos + 64u * k + lane;
-                prefix_store(pre + j, prefix_word(tag, ew, ec));
-                if (!kComputeWritesOffsets<R>) {
-                    pay_off[j] = (uint64_t)ew << 2;
-                    row_ptr[j] = ec;
-                }
+            const uint32_t k = wv + (uint32_t)(R * i), start = pos + kScanGroupTokens * k;
+            if (k >= (uint32_t)kScanGroups || k > first_gap || start >= T) continue;
+            // payload words / outliers before the lane's first token (of the lane at the gap as well)
+            uint32_t ew = bw + lane_value(upto2 - gs2, (int)k) + before2[i];
+            uint32_t ec = bc + lane_value(upto - gs, (int)k) + before[i];
+            uint32_t known = 0;                                   // the lane's leading published words
+            uint32_t words[8];
+#pragma unroll
+            for (uint32_t m = 0; m < 4; ++m) {
+                const bool there = known == m && (w[i][m] >> 30) == tag;
+                known += there ? 1u : 0u;
+                const uint64_t v = prefix_word(tag, ew, ec);
+                words[2 * m] = there ? (uint32_t)v : 0u;          // (a word without the call's tag: nobody takes it)
+                words[2 * m + 1] = there ? (uint32_t)(v >> 32) : 0u;
+                ew += words_of(p, w[i][m]);
+                ec += w[i][m] & 0xFFFFu;
+            }
+            // tokens of the group whose prefix is known
+            uint32_t n = 4u * lead[i] + (lead[i] < 64u ? lane_value(known, (int)(lead[i] & 63u)) : 0u);
+            if (n > T - start) n = T - start;
+            *reinterpret_cast<uint4 *>(turned + 8u * lane) = make_uint4(words[0], words[1], words[2], words[3]);
+            *reinterpret_cast<uint4 *>(turned + 8u * lane + 4u) = make_uint4(words[4], words[5], words[6], words[7]);
+            const __amdgpu_buffer_rsrc_t window = raw_window(pre + start, 8u * ((n + 1u) & ~1u));   // (the table has T + 1 words)
+#pragma unroll
+            for (uint32_t h = 0; h < 2; ++h) {
+                const u32x4 v = *reinterpret_cast<const u32x4 *>(turned + 256u * h + 4u * lane);
+                if (2u * lane + 128u * h < n) store_quad_through(window, 16u * lane + 1024u * h, v);
             }
         }
         bw += lane_value(upto2, 63);
@@ -390,10 +406,9 @@ __device__ __forceinline__ bool store_wave_part(const StoreTargets &o, const Pen
     return true;
 }
 
-// The blob's offsets of a token whose prefix is known, where the workgroup that stores the token writes them.
-template <int NW>
+// The blob's offsets of a token whose prefix is known.
 __device__ __forceinline__ void write_offsets(uint64_t *pay_off, uint64_t *row_ptr, uint32_t token, const Prefix &x) {
-    if (!kComputeWritesOffsets<NW> || threadIdx.x != 0 || x.bad) return;
+    if (threadIdx.x != 0 || x.bad) return;
     pay_off[token] = (uint64_t)x.ew << 2;
     row_ptr[token] = x.ec;
 }
@@ -572,7 +587,7 @@ k_fused(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ b
 
         // ---- store this wave's part of the token of two iterations ago: its image and stash are needed now
         if (have_old) {
-            write_offsets<NW>(pay_off, row_ptr, old.token, xo);
+            write_offsets(pay_off, row_ptr, old.token, xo);
             if (xo.bad || !store_wave_part<DT, NW>(out, old, xo)) failed = 1;
             have_old = false;
         }
@@ -621,13 +636,13 @@ k_fused(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ b
     if (old_reread) reread_run(out, old.token, again);
     if (have_old) {
         const Prefix x = prefix_finish(p, pre, tag, old.token, last_old, error_flag);
-        write_offsets<NW>(pay_off, row_ptr, old.token, x);
+        write_offsets(pay_off, row_ptr, old.token, x);
         if (x.bad || !store_wave_part<DT, NW>(out, old, x, nullptr, old_reread ? &again : nullptr)) failed = 1;
     }
     if (have_young) {
         // the row of the workgroup's last token was not overwritten by a next one
         const Prefix x = prefix_finish(p, pre, tag, young.token, last_young, error_flag);
-        write_offsets<NW>(pay_off, row_ptr, young.token, x);
+        write_offsets(pay_off, row_ptr, young.token, x);
         if (x.bad || !store_wave_part<DT, NW>(out, young, x, lrow)) failed = 1;
     }
     // ---- this wave is done
