@@ -396,12 +396,25 @@ __device__ __forceinline__ uint32_t sum_squares_run(const uint32_t (&m)[8]) {
     return s;
 }
 
-// sum over the run of | (m0 >> sh) - mi |, bytewise
+// sum over the run of | (m0 >> sh) - mi |, bytewise, as kSadNone minus it.
+// The two differ by one at most, so the sum counts the bytes whose lowest bits differ.  With u = a / amax in [0, 1],
+// Q0 = 2^sh Qi + 2^sh - 1 and every rounding of the products below 2^-12 in all: m0 lies within 1/2 + 2^-12 of u Q0, so
+// (m0 >> sh) lies in (v - 1 - 2^-(sh+1) - 2^-12, v + 2^-(sh+1) + 2^-12] with v = u Q0 / 2^sh = u Qi + u (1 - 2^-sh); mi lies
+// within 1/2 + 2^-12 of u Qi; the difference is less than 2 and more than -2 for sh >= 1, and an integer.
+// Two words at a time: one 64-bit shift (what crosses into a byte from above stays clear of its lowest bit: sh < 8), the
+// differing lowest bits p of the first word and 255 - q of the second's, and one sum of absolute differences
+// |p - (255 - q)| = 255 - p - q: 16 instructions instead of 24.
+constexpr uint32_t kSadNone = 4u * 4u * 255u;
+constexpr int kXorAnd = (0xF0 ^ 0xCC) & 0xAA;           // (a ^ b) & c
 __device__ __forceinline__ uint32_t sad_run(const uint32_t (&m0)[8], const uint32_t (&mi)[8], uint32_t sh) {
-    const uint32_t keep = (0xFFu >> sh) * 0x01010101u;
     uint32_t s = 0;
 #pragma unroll
-    for (int g = 0; g < 8; ++g) s = __builtin_amdgcn_sad_u8((m0[g] >> sh) & keep, mi[g], s);
+    for (int g = 0; g < 8; g += 2) {
+        const uint64_t both = ((uint64_t)m0[g + 1] << 32 | m0[g]) >> sh;
+        const uint32_t p = bitop3<kXorAnd>((uint32_t)both, mi[g], 0x01010101u);
+        const uint32_t q = bitop3<(~kXorAnd & 0xFF)>((uint32_t)(both >> 32), mi[g + 1], 0x01010101u);
+        s = __builtin_amdgcn_sad_u8(p, q, s);
+    }
     return s;
 }
 
@@ -410,12 +423,13 @@ __device__ __forceinline__ uint32_t sad_run(const uint32_t (&m0)[8], const uint3
 //   REL_RMS:  L = (double)Q0 * (double)sad; L *= L; R = (double)budget * (double)Qi; R *= R; R *= (double)H;
 //             R *= (double)ss0; L > R
 // rhs is the part of the right-hand side that the host computed in that sequence (Params::test_rhs): all of it
-// (LSB), or R before its last factor (REL_RMS).
-__device__ __forceinline__ bool violates(int mode, double rhs, uint32_t Q0, uint32_t sad, uint32_t ss0) {
+// (LSB), or R before its last factor (REL_RMS).  Q0 * sad stays below 2^22 (Q0 <= 127, sad <= H <= 2^15), so that the
+// integer product is the fp64 one.
+__device__ __forceinline__ bool violates(int mode, double rhs, uint32_t Q0, uint32_t sad, double ss0) {
     if (mode == kModeLsb) return (double)sad > rhs;
-    double L = (double)Q0 * (double)sad;
+    double L = (double)(Q0 * sad);
     L *= L;
-    const double R = rhs * (double)ss0;
+    const double R = rhs * ss0;
     return L > R;
 }
 
@@ -543,100 +557,132 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 // ---- block collectives for NW waves (known at compile time) ----
-// A reduce area is 2*kMaxWaves dwords; slot w = wave w's first value, kMaxWaves + w its second.
-// The caller rotates over four areas, so a wave that is one barrier ahead never overwrites
-// values another wave still has to read.
+// Four DPP steps leave the result of each row of 16 lanes in its lanes; one lane of each row adds it, by an atomic of
+// LDS, to what the workgroup's waves share, and behind the barrier every wave reads one word per result: 4 DPP steps, a
+// read and a move to a scalar register per value.  (A wave's own sums through scalar registers and all waves' sums added up
+// by every wave were 15 vector instructions more per value in a workgroup of four waves, and their issue is what bounds the
+// compress kernels.)
+// A reduce area is 2*kMaxWaves dwords: words 0 and 1 are what the atomics add to and are zero before; words kMaxWaves + w
+// are wave w's own.  Four areas are used in rotation, one per reduction (`turn` counts them): behind the barrier of
+// turn k the area of turn k + 2 is cleared, which was read before the barrier of turn k - 1 and is added to behind that of
+// turn k + 1.
+__device__ __forceinline__ uint32_t *reduce_area(uint32_t *ring, uint32_t turn) { return ring + (turn & 3u) * 2u * kMaxWaves; }
+// Once per kernel, before the first reduction and with a barrier between.
+__device__ __forceinline__ void clear_areas(uint32_t *ring) {
+    if (threadIdx.x < 8u) ring[(threadIdx.x >> 1) * 2u * kMaxWaves + (threadIdx.x & 1u)] = 0;
+}
+__device__ __forceinline__ void clear_area_after_next(uint32_t *ring, uint32_t turn) {
+    if (threadIdx.x == 0) *reinterpret_cast<uint64_t *>(reduce_area(ring, turn + 2u)) = 0;
+}
+__device__ __forceinline__ bool first_of_row() { return (threadIdx.x & 15u) == 0; }
+__device__ __forceinline__ uint32_t row_max_u32(uint32_t v) {
+    uint32_t n;
+    n = dpp<kDppQuadXor1>(v);   v = n > v ? n : v;
+    n = dpp<kDppQuadXor2>(v);   v = n > v ? n : v;
+    n = dpp<kDppHalfMirror>(v); v = n > v ? n : v;
+    n = dpp<kDppRowMirror>(v);  v = n > v ? n : v;
+    return v;
+}
+__device__ __forceinline__ uint32_t row_sum_u32(uint32_t v) {
+    v += dpp<kDppQuadXor1>(v);
+    v += dpp<kDppQuadXor2>(v);
+    v += dpp<kDppHalfMirror>(v);
+    v += dpp<kDppRowMirror>(v);
+    return v;
+}
+// A zero in a vector register that the compiler knows nothing about: an atomic at a provably uniform address would be
+// turned into a reduction over the wave first.
+__device__ __forceinline__ uint32_t some_zero() {
+    uint32_t zero = 0;
+    asm("" : "+v"(zero));
+    return zero;
+}
 
-// max of mx, sum of sm over the block; pre = sum of sm over the waves before this one, own = over this wave
+// the sums of x and y over the block
 template <int NW>
-__device__ __forceinline__ void block_max_sum_prefix(uint32_t &mx, uint32_t &sm, uint32_t &pre, uint32_t &own,
-                                                     uint32_t *red) {
-    mx = wave_max_u32(mx);
-    sm = wave_sum_u32(sm);
-    own = sm;
-    pre = 0;
-    if (NW == 1) return;
-    const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (lane == 0) { red[wv] = mx; red[kMaxWaves + wv] = sm; }
-    lds_barrier();
-    uint32_t M = 0, S = 0, P = 0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        const uint32_t a = red[w], b = red[kMaxWaves + w];
-        M = a > M ? a : M;
-        S += b;
-        P += (uint32_t)w < wv ? b : 0u;
+__device__ __forceinline__ void block_sum2_nw(uint32_t &x, uint32_t &y, uint32_t *ring, uint32_t &turn) {
+    if (NW == 1) {
+        x = wave_sum_u32(x);
+        y = wave_sum_u32(y);
+        return;
     }
-    mx = uniform(M); sm = uniform(S); pre = uniform(P);
+    uint32_t *red = reduce_area(ring, turn);
+    x = row_sum_u32(x);
+    y = row_sum_u32(y);
+    // (neither sum reaches 2^32)
+    if (first_of_row())
+        __hip_atomic_fetch_add(reinterpret_cast<uint64_t *>(red) + some_zero(), (uint64_t)y << 32 | x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    lds_barrier();
+    const uint2 v = *reinterpret_cast<const uint2 *>(red);
+    clear_area_after_next(ring, turn);
+    ++turn;
+    x = uniform(v.x); y = uniform(v.y);
 }
 template <int NW>
-__device__ __forceinline__ void block_sum2_nw(uint32_t &x, uint32_t &y, uint32_t *red) {
-    x = wave_sum_u32(x);
-    y = wave_sum_u32(y);
-    if (NW == 1) return;
-    const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (lane == 0) { red[wv] = x; red[kMaxWaves + wv] = y; }
+__device__ __forceinline__ void block_sum1_nw(uint32_t &x, uint32_t *ring, uint32_t &turn) {
+    if (NW == 1) {
+        x = wave_sum_u32(x);
+        return;
+    }
+    uint32_t *red = reduce_area(ring, turn);
+    x = row_sum_u32(x);
+    if (first_of_row()) __hip_atomic_fetch_add(red + some_zero(), x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     lds_barrier();
-    uint32_t X = 0, Y = 0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) { X += red[w]; Y += red[kMaxWaves + w]; }
-    x = uniform(X); y = uniform(Y);
-}
-template <int NW>
-__device__ __forceinline__ void block_sum1_nw(uint32_t &x, uint32_t *red) {
-    x = wave_sum_u32(x);
-    if (NW == 1) return;
-    const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (lane == 0) red[wv] = x;
-    lds_barrier();
-    uint32_t X = 0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) X += red[w];
-    x = uniform(X);
+    const uint32_t v = *red;
+    clear_area_after_next(ring, turn);
+    ++turn;
+    x = uniform(v);
 }
 
-// Inlier absmax and outlier count of the token of this block (one barrier).  ring: four reduce
-// areas; turn: running count of reductions; lanes that own no run pass omask = 0, amax_bits = 0.
-template <int NW>
-__device__ __forceinline__ RowStats reduce_row_stats(uint32_t omask, uint32_t amax_bits, uint32_t *ring,
-                                                     uint32_t &turn) {
-    uint32_t mx = amax_bits;              // non-negative binary32 patterns order like unsigned integers
-    uint32_t cnt = (uint32_t)__builtin_popcount(omask);
-    RowStats st;
-    block_max_sum_prefix<NW>(mx, cnt, st.cnt_before, st.cnt_wave, ring + (turn++ & 3u) * 2 * kMaxWaves);
-    st.amax = __uint_as_float(mx);
-    st.cnt = cnt;
-    return st;
-}
-
-// The same with the wave's outlier count already summed by the caller.
+// Inlier absmax and outlier counts of the token of this block (one barrier).  cnt_wave: the wave's outliers; lanes that
+// own no run pass amax_bits = 0.
 template <int NW>
 __device__ __forceinline__ RowStats reduce_row_stats_counted(uint32_t amax_bits, uint32_t cnt_wave, uint32_t *ring,
                                                              uint32_t &turn) {
     RowStats st;
-    uint32_t mx = wave_max_u32(amax_bits), cnt = cnt_wave, before = 0;
-    if (NW > 1) {
-        uint32_t *red = ring + (turn++ & 3u) * 2 * kMaxWaves;
-        const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-        if (lane == 0) { red[wv] = mx; red[kMaxWaves + wv] = cnt_wave; }
-        lds_barrier();
-        uint32_t M = 0, S = 0, P = 0;
+    st.cnt_wave = cnt_wave;
+    if (NW == 1) {
+        st.amax = __uint_as_float(wave_max_u32(amax_bits));
+        st.cnt = cnt_wave;
+        st.cnt_before = 0;
+        return st;
+    }
+    uint32_t *red = reduce_area(ring, turn);
+    const uint32_t wv = uniform(threadIdx.x >> 6);
+    const uint32_t mx = row_max_u32(amax_bits);      // non-negative binary32 patterns order like unsigned integers
+    if (first_of_row()) __hip_atomic_fetch_max(red + some_zero(), mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if ((threadIdx.x & 63u) == 0) red[kMaxWaves + wv] = cnt_wave;
+    lds_barrier();
+    const uint32_t most = *red;
+    uint32_t all = 0, before = 0;
+    if constexpr (NW <= 4) {
+        uint32_t c[NW];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) c[w] = red[kMaxWaves + w];
+        // (moved to scalar registers first: the sums are scalar instructions)
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
-            const uint32_t a = red[w], b = red[kMaxWaves + w];
-            M = a > M ? a : M;
-            S += b;
-            P += (uint32_t)w < wv ? b : 0u;
+            const uint32_t n = uniform(c[w]);
+            all += n;
+            before += (uint32_t)w < wv ? n : 0u;
         }
-        mx = uniform(M); cnt = uniform(S); before = uniform(P);
     } else {
-        ++turn;
+        const uint32_t w = threadIdx.x & 15u;
+        const uint32_t n = w < (uint32_t)NW ? red[kMaxWaves + w] : 0u;
+        all = uniform(row_sum_u32(n));
+        before = uniform(row_sum_u32(w < wv ? n : 0u));
     }
-    st.amax = __uint_as_float(mx);
-    st.cnt = cnt;
+    clear_area_after_next(ring, turn);
+    ++turn;
+    st.amax = __uint_as_float(uniform(most));
+    st.cnt = all;
     st.cnt_before = before;
-    st.cnt_wave = cnt_wave;
     return st;
+}
+// The same from the lanes' outlier flags (omask = 0 for lanes that own no run).
+template <int NW>
+__device__ __forceinline__ RowStats reduce_row_stats(uint32_t omask, uint32_t amax_bits, uint32_t *ring, uint32_t &turn) {
+    return reduce_row_stats_counted<NW>(amax_bits, wave_sum_u32((uint32_t)__builtin_popcount(omask)), ring, turn);
 }
 
 // Algorithm 1 for the token of this block, given its inlier absmax.  live: false for lanes that
@@ -651,7 +697,8 @@ __device__ __forceinline__ Choice search_width(const Params &p, const Mags<DT> &
     float quot = 0.0f;
     if ((lane & 7u) < p.n_widths && lane < 16u && amax >= kAmaxFloor) {
         const float q = level_count(width_at(p, lane & 7u));
-        quot = lane < 8u ? q / amax : amax / q;
+        const bool scale = lane >= 8u;
+        quot = (scale ? amax : q) / (scale ? q : amax);      // (one division: a branch each would issue two)
     }
     const uint32_t quot_bits = __float_as_uint(quot);
 
@@ -664,16 +711,22 @@ __device__ __forceinline__ Choice search_width(const Params &p, const Mags<DT> &
 #pragma unroll
         for (int g = 0; g < 8; ++g) m0[g] = m[g];
         uint32_t ss0 = live ? sum_squares_run(m0) : 0u;
+        double ss0d = 0.0;
         for (uint32_t i = 1; i < p.n_widths; ++i) {
             const uint32_t bi = width_at(p, i);
             uint32_t mi[8];
             quantize_run<DT>(af, __uint_as_float(__builtin_amdgcn_readlane(quot_bits, (int)i)), mi);
-            uint32_t sad = live ? sad_run(m0, mi, b0 - bi) : 0u;
-            uint32_t *red = ring + (turn++ & 3u) * 2 * kMaxWaves;
-            if (i == 1) block_sum2_nw<NW>(sad, ss0, red); else block_sum1_nw<NW>(sad, red);
+            uint32_t sad = live ? sad_run(m0, mi, b0 - bi) : kSadNone;
+            if (i == 1) {
+                block_sum2_nw<NW>(sad, ss0, ring, turn);
+                ss0d = (double)ss0;
+            } else {
+                block_sum1_nw<NW>(sad, ring, turn);
+            }
+            sad = 64u * NW * kSadNone - sad;
             // (Algorithm 1 as printed returns the quantization that failed the test; the default keeps
             // the last one that passed)
-            const bool failed = violates(p.mode, p.test_rhs[i], Q0, sad, ss0);
+            const bool failed = violates(p.mode, p.test_rhs[i], Q0, sad, ss0d);
             if (failed && !p.return_failing) break;
             sel = bi;
             sel_i = i;

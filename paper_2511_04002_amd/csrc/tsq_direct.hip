@@ -78,6 +78,10 @@ k_direct(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ 
     uint32_t *error_flag = ctrl + kCtlError;
     const uint32_t *mine = lane == 0 ? error_flag : lane == 1 ? ctrl + kCtlTokens : lane == 2 ? ctrl + kCtlHidden : tickets + kCntTickets;
     const uint32_t state = __hip_atomic_load(mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (NW > 1) {
+        clear_areas(ring);
+        lds_barrier();
+    }
 
     write_row_part_sw<FULL>(lrow, runs, part);
     Mags<DT> mg;
@@ -203,16 +207,16 @@ k_direct(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ 
         }
     }
     if (NW > 1) {
-        // (a reduce area holds two values per wave; the third travels in the next one)
-        uint32_t *also = ring + ((turn + 1u) & 3u) * 2 * kMaxWaves;
+        // (the third value travels in the waves' own words of the area)
+        uint32_t *also = reduce_area(ring, turn) + kMaxWaves;
         if (lane == 0) also[wv] = bad;
-        block_sum2_nw<NW>(ew, ec, ring + (turn & 3u) * 2 * kMaxWaves);
+        block_sum2_nw<NW>(ew, ec, ring, turn);
         bad = 0;
 #pragma unroll
         for (int k = 0; k < NW; ++k) bad |= also[k];
         bad = uniform(bad);
     } else {
-        block_sum2_nw<NW>(ew, ec, ring);
+        block_sum2_nw<NW>(ew, ec, ring, turn);
     }
 
     const uint32_t words = token_words(p, c.width);

@@ -467,6 +467,7 @@ k_fused(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ b
     uint16_t *out_val = reinterpret_cast<uint16_t *>(blob + p.off_out_val);
     const uint32_t hidden = FULL ? 2048u * NW : p.hidden;
 
+    clear_areas(ring);
     // ---- the first ticket: this workgroup's first token
     if (tid == 0) {
         // (the counters lie at the same place in every workspace; the ticket is drawn while the shape is

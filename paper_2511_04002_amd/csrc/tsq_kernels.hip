@@ -83,6 +83,8 @@ k_row_stats(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict
 
     RowPart pre;
     fetch_row_part(reinterpret_cast<const uint4 *>(row_address(p, in, t, p.hidden)), p.pieces, pre);
+    clear_areas(ring);
+    lds_barrier();
     write_row_part(lrow, p.runs, pre);
 
     Mags<DT> mg;

@@ -1,6 +1,5 @@
 """The persistent compress kernel's placement at the token counts where its scanner can go wrong (a lane takes four tokens,
 a group 256, a round 1024).  Whole blobs against the oracle."""
-import numpy as np
 import pytest
 
 from test_gpu_parity import check_parity, tsq  # noqa: F401
