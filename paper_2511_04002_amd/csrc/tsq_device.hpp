@@ -196,8 +196,8 @@ __device__ __forceinline__ void write_row_part(uint32_t *lrow, uint32_t runs, co
 //   bf16: 32 binary32 values;
 //   fp16: 16 dwords of packed half-precision values (the multiply reads them directly
 //         through v_fma_mix_f32).
-// The values keep their sign (the multiply takes the magnitude through its source modifier, the
-// packing takes the sign bit from here), outlier slots hold +0 in both forms.
+// The values keep their sign (the multiply takes the magnitude through its source modifier), outlier
+// slots hold +0 in both forms.
 template <int DT> struct Mags;
 template <> struct Mags<kBF16> { float v[32]; };
 template <> struct Mags<kF16> { uint32_t v[16]; };
@@ -228,7 +228,6 @@ __device__ __forceinline__ uint32_t bitop3(uint32_t a, uint32_t b, uint32_t c) {
 }
 constexpr int kAndOr = (0xF0 & 0xCC) | 0xAA;            // (a & b) | c
 constexpr int kSelect = (0xF0 & 0xCC) | (~0xF0 & 0xAA & 0xFF);   // a ? b : c, bit by bit
-constexpr int kOrAnd = (0xF0 | 0xCC) & 0xAA;            // (a | b) & c
 constexpr int kAnd3 = 0xF0 & 0xCC & 0xAA;               // a & b & c
 
 // bits `sel` of keep into old
@@ -439,25 +438,10 @@ __device__ __forceinline__ float level_count(uint32_t width) { return (float)((1
 
 // ---------------------------------------------------------------- bit packing of one run
 
-// The sign bits of elements 4g .. 4g+3 in bit 7 of bytes 0 .. 3 (the other bits are whatever the
-// top bytes of the values hold), and-ed with `keep`.
-template <int DT>
-__device__ __forceinline__ uint32_t sign_bytes_and(const Mags<DT> &mg, int g, uint32_t keep) {
-    if constexpr (DT == kBF16) {
-        // the top byte of two binary32 values per v_perm_b32: bytes 0, 1 from the first pair, 2, 3 from the second
-        const uint32_t p01 = __builtin_amdgcn_perm(__float_as_uint(mg.v[4 * g + 1]), __float_as_uint(mg.v[4 * g]), 0x0c0c0703u);
-        const uint32_t p23 = __builtin_amdgcn_perm(__float_as_uint(mg.v[4 * g + 3]), __float_as_uint(mg.v[4 * g + 2]), 0x07030c0cu);
-        return bitop3<kOrAnd>(p01, p23, keep);
-    } else {
-        // byte k <- high byte of element 4g+k
-        return __builtin_amdgcn_perm(mg.v[2 * g + 1], mg.v[2 * g], 0x07050301u) & keep;
-    }
-}
-
-// out[0..B) = the run's 32 codes, LSB first.  m: magnitude bytes; mg: the run's T_below (sign
-// bits).  The sign is dropped where the magnitude is 0.
-template <int B, int DT>
-__device__ __forceinline__ void pack_regs(const uint32_t (&m)[8], const Mags<DT> &mg, uint32_t (&out)[B]) {
+// out[0..B) = the run's 32 codes, LSB first.  m: magnitude bytes; w: the run's 16-bit values two by two, for their sign bits
+// (T_above may be among them, or zeros in its place: the sign is dropped where the magnitude is 0).
+template <int B>
+__device__ __forceinline__ void pack_regs(const uint32_t (&m)[8], const uint32_t (&w)[16], uint32_t (&out)[B]) {
     constexpr uint32_t K = (1u << (B - 1)) - 1u;
     uint64_t acc = 0;
     int filled = 0, od = 0;
@@ -465,17 +449,13 @@ __device__ __forceinline__ void pack_regs(const uint32_t (&m)[8], const Mags<DT>
     for (int g = 0; g < 8; ++g) {
         const uint32_t mb = m[g];
         const uint32_t nzb = mb + K * 0x01010101u;                       // bit B-1 of each byte: m > 0
-        uint32_t code;
-        if (B == 8) {
-            code = bitop3<kAndOr>(sign_bytes_and<DT>(mg, g, nzb), 0x80808080u, mb);
-        } else {
-            const uint32_t sg = sign_bytes_and<DT>(mg, g, 0x80808080u) >> (8 - B);   // sign now at bit B-1 of each byte
-            code = bitop3<kAndOr>(sg, nzb, mb);
-        }
+        // byte k <- high byte of element 4g+k: its sign in bit 7
+        const uint32_t sb = __builtin_amdgcn_perm(w[2 * g + 1], w[2 * g], 0x07050301u);
         uint32_t chunk;
         if (B == 8) {
-            chunk = code;
+            chunk = bitop3<kAnd3>(sb, nzb, 0x80808080u) | mb;
         } else {
+            const uint32_t code = bitop3<kAndOr>((sb & 0x80808080u) >> (8 - B), nzb, mb);
             // two codes per 16-bit half side by side, then the two halves side by side: right shifts and
             // three-input bit operations only (left shifts and the fused shift-or forms issue at half rate)
             constexpr uint32_t F = (1u << B) - 1u, M = (1u << (2 * B)) - 1u;

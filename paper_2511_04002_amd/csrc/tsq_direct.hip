@@ -48,10 +48,10 @@ __device__ __forceinline__ void memory_operations_performed() { asm volatile("s_
 // Payload words of a token of width b (0 for the width 0 of a word that counts nothing).
 __device__ __forceinline__ uint32_t token_words(const Params &p, uint32_t b) { return (p.hidden * b + 31u) >> 5; }
 
-template <int B, int DT>
-__device__ __forceinline__ void pack_codes(const uint32_t (&m)[8], const Mags<DT> &mg, uint32_t (&o)[8]) {
+template <int B>
+__device__ __forceinline__ void pack_codes(const uint32_t (&m)[8], const uint32_t (&w)[16], uint32_t (&o)[8]) {
     uint32_t t[B];
-    pack_regs<B, DT>(m, mg, t);
+    pack_regs<B>(m, w, t);
 #pragma unroll
     for (int k = 0; k < 8; ++k) o[k] = k < B ? t[k] : 0u;
 }
@@ -127,15 +127,16 @@ k_direct(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ 
     }
 
     // ---- codes of the lane's run at the chosen width
-    uint32_t codes[8];
+    uint32_t codes[8], values[16];
+    signed_values<DT>(mg, lrow, owns ? tid : 0u, values);
     switch (c.width) {
-        case 2: pack_codes<2, DT>(m, mg, codes); break;
-        case 3: pack_codes<3, DT>(m, mg, codes); break;
-        case 4: pack_codes<4, DT>(m, mg, codes); break;
-        case 5: pack_codes<5, DT>(m, mg, codes); break;
-        case 6: pack_codes<6, DT>(m, mg, codes); break;
-        case 7: pack_codes<7, DT>(m, mg, codes); break;
-        default: pack_codes<8, DT>(m, mg, codes); break;
+        case 2: pack_codes<2>(m, values, codes); break;
+        case 3: pack_codes<3>(m, values, codes); break;
+        case 4: pack_codes<4>(m, values, codes); break;
+        case 5: pack_codes<5>(m, values, codes); break;
+        case 6: pack_codes<6>(m, values, codes); break;
+        case 7: pack_codes<7>(m, values, codes); break;
+        default: pack_codes<8>(m, values, codes); break;
     }
     // ---- ... into the wave's part of their place in LDS.  Before anybody looks for the tokens before: a look that comes
     //      too early costs a memory round trip (codes put there behind the wait, over the row: 512 x 5120 step 14.5 us

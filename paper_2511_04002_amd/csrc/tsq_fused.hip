@@ -599,14 +599,16 @@ k_fused(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ b
         if (owns) {
             uint32_t *dst = images + (it & 1u) * runs * 8u + wv * (64u * 8u) + (run & 63u) * c.width;
             const uint32_t nd = (FULL || left >= 4) ? c.width : ((left * c.width + 3u) >> 2);
+            uint32_t w[16];
+            signed_values<DT>(mg, lrow, run, w);
             switch (c.width) {
-                case 2: pack_to_image<2, DT, FULL>(m, mg, dst, nd); break;
-                case 3: pack_to_image<3, DT, FULL>(m, mg, dst, nd); break;
-                case 4: pack_to_image<4, DT, FULL>(m, mg, dst, nd); break;
-                case 5: pack_to_image<5, DT, FULL>(m, mg, dst, nd); break;
-                case 6: pack_to_image<6, DT, FULL>(m, mg, dst, nd); break;
-                case 7: pack_to_image<7, DT, FULL>(m, mg, dst, nd); break;
-                default: pack_to_image<8, DT, FULL>(m, mg, dst, nd); break;
+                case 2: pack_to_image<2, FULL>(m, w, dst, nd); break;
+                case 3: pack_to_image<3, FULL>(m, w, dst, nd); break;
+                case 4: pack_to_image<4, FULL>(m, w, dst, nd); break;
+                case 5: pack_to_image<5, FULL>(m, w, dst, nd); break;
+                case 6: pack_to_image<6, FULL>(m, w, dst, nd); break;
+                case 7: pack_to_image<7, FULL>(m, w, dst, nd); break;
+                default: pack_to_image<8, FULL>(m, w, dst, nd); break;
             }
         }
         // ---- T_above of token t, this wave's part: into the wave's stash of this parity (free since the

@@ -16,11 +16,11 @@ namespace tsq {
 
 // ---------------------------------------------------------------- payload + CSR output of one token
 
-template <int B, int DT>
-__device__ __forceinline__ void store_codes(const uint32_t (&m)[8], const Mags<DT> &mg, uint32_t *dst_row,
+template <int B>
+__device__ __forceinline__ void store_codes(const uint32_t (&m)[8], const uint32_t (&w)[16], uint32_t *dst_row,
                                             uint32_t run, uint32_t valid_pieces) {
     uint32_t out[B];
-    pack_regs<B, DT>(m, mg, out);
+    pack_regs<B>(m, w, out);
     uint32_t *dst = dst_row + run * B;
     if (valid_pieces >= 4) {
         store_run_words<B>(dst, out);
@@ -32,17 +32,16 @@ __device__ __forceinline__ void store_codes(const uint32_t (&m)[8], const Mags<D
     }
 }
 
-template <int DT>
-__device__ __forceinline__ void store_codes_any(uint32_t width, const uint32_t (&m)[8], const Mags<DT> &mg,
+__device__ __forceinline__ void store_codes_any(uint32_t width, const uint32_t (&m)[8], const uint32_t (&w)[16],
                                                 uint32_t *dst_row, uint32_t run, uint32_t valid_pieces) {
     switch (width) {
-        case 2: store_codes<2, DT>(m, mg, dst_row, run, valid_pieces); break;
-        case 3: store_codes<3, DT>(m, mg, dst_row, run, valid_pieces); break;
-        case 4: store_codes<4, DT>(m, mg, dst_row, run, valid_pieces); break;
-        case 5: store_codes<5, DT>(m, mg, dst_row, run, valid_pieces); break;
-        case 6: store_codes<6, DT>(m, mg, dst_row, run, valid_pieces); break;
-        case 7: store_codes<7, DT>(m, mg, dst_row, run, valid_pieces); break;
-        default: store_codes<8, DT>(m, mg, dst_row, run, valid_pieces); break;
+        case 2: store_codes<2>(m, w, dst_row, run, valid_pieces); break;
+        case 3: store_codes<3>(m, w, dst_row, run, valid_pieces); break;
+        case 4: store_codes<4>(m, w, dst_row, run, valid_pieces); break;
+        case 5: store_codes<5>(m, w, dst_row, run, valid_pieces); break;
+        case 6: store_codes<6>(m, w, dst_row, run, valid_pieces); break;
+        case 7: store_codes<7>(m, w, dst_row, run, valid_pieces); break;
+        default: store_codes<8>(m, w, dst_row, run, valid_pieces); break;
     }
 }
 
@@ -195,7 +194,9 @@ k_pack(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ bl
             uint32_t m[8];
             quantize_run<DT>(mg, r, m);
             const uint32_t left = p.pieces - 4 * run;
-            store_codes_any<DT>(width, m, mg, reinterpret_cast<uint32_t *>(blob + p.off_payload + po), run,
+            uint32_t w[16];
+            load_run_padded(lrow + run * kRunLdsDw, w);
+            store_codes_any(width, m, w, reinterpret_cast<uint32_t *>(blob + p.off_payload + po), run,
                                 left < 4 ? left : 4);
         }
     }
