@@ -168,10 +168,12 @@ __device__ __forceinline__ uint32_t rank_in(uint64_t who) {
 // therefore lowers its issue priority as it gets ahead (by quarters of its rounds), which keeps the eight in step.
 // `done` of `total` rounds are behind the wave (uniform).
 __device__ __forceinline__ void priority_by_progress(uint32_t done, uint32_t total) {
-    if (4u * done < total) __builtin_amdgcn_s_setprio(3);
-    else if (2u * done < total) __builtin_amdgcn_s_setprio(2);
-    else if (4u * done < 3u * total) __builtin_amdgcn_s_setprio(1);
-    else __builtin_amdgcn_s_setprio(0);
+    switch ((4u * done) / total) {
+        case 0: __builtin_amdgcn_s_setprio(3); break;
+        case 1: __builtin_amdgcn_s_setprio(2); break;
+        case 2: __builtin_amdgcn_s_setprio(1); break;
+        default: __builtin_amdgcn_s_setprio(0); break;
+    }
 }
 
 // a * b + c of 24-bit factors in one instruction (left to itself the compiler adds c and what it is the sum of to the
@@ -277,7 +279,7 @@ k_rans_encode(const Params p, const EntropyLayout e, const uint8_t *__restrict__
     const uint32_t rounds = (p.runs + 63u) / 64u, cap = (e.slot_bytes - 256u) >> 1;   // one word per element at most
     uint32_t x = kRansLow, ptr = cap;
     for (uint32_t r = rounds; r-- > 0;) {
-        priority_by_progress(rounds - 1u - r, rounds);
+        if (rounds > 1u) priority_by_progress(rounds - 1u - r, rounds);
         const uint32_t run = lane + 64u * r;
         const int valid = (int)p.hidden - (int)(run * kRun);          // may be <= 0: nothing of this run exists
 #define TSQ_ENCODE_ROUND(WHOLE)    \
