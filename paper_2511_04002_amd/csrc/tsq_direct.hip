@@ -1,5 +1,5 @@
-// Single-pass compress for calls of few tokens (gfx950): one workgroup per token, dispatched in token order,
-// nothing handed out and nobody in between.
+// Single-pass compress for calls of few tokens and for rows of one wave (gfx950): one workgroup per token, or per eight
+// tokens of one wave, dispatched in token order, nothing handed out and nobody in between.
 //
 // With as many workgroups as tokens a call is one chain of latencies: row from HBM, threshold split, width
 // search, publication of the token's size, sizes of the tokens before it, stores.  The persistent kernel
@@ -54,6 +54,28 @@ __device__ __forceinline__ void pack_codes(const uint32_t (&m)[8], const uint32_
     pack_regs<B>(m, w, t);
 #pragma unroll
     for (int k = 0; k < 8; ++k) o[k] = k < B ? t[k] : 0u;
+}
+
+// The last workgroup's first wave closes the blob, also if its own wait has expired (nobody else writes a header).
+// raised: the error word as it was before that workgroup published its size.
+__device__ __forceinline__ void close_blob(const Params &p, uint8_t *blob, uint32_t *tickets, uint32_t *error_flag, uint32_t epoch,
+                                           uint32_t bad, uint32_t words_in_all, uint64_t outliers_in_all, uint32_t raised) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t all_words = bad ? 0u : words_in_all;
+    const uint64_t all_outliers = bad ? 0u : outliers_in_all;
+    if (!bad) word_store(tickets + lane * kTicketStride + kCntTickets, ((epoch + 1u) % 3u) << kTicketBits);   // everybody has this call's
+    if (lane == 0) {
+        const bool full = all_outliers > p.outlier_capacity;
+        if (full) {                            // (as the zero at the start: in its place before the error word is read again)
+            store_status(blob, kStatusCapacity);
+            memory_operations_performed();
+            raised |= word_load(error_flag + opaque_zero());
+        }
+        reinterpret_cast<uint64_t *>(blob + p.off_row_ptr)[p.tokens] = all_outliers;
+        reinterpret_cast<uint64_t *>(blob + p.off_pay_off)[p.tokens] = (uint64_t)all_words << 2;
+        write_header_but_status(p, blob, all_outliers, (uint64_t)all_words << 2);
+        if (raised) store_status(blob, kStatusInternal);
+    }
 }
 
 // LDS map (dynamic): row: runs*16 dwords | codes: runs*8 | ring (rows of more than one wave): four reduce areas
@@ -262,24 +284,196 @@ k_direct(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ 
             if (lane < rest) *reinterpret_cast<uint32_t *>(dst + 4u * (4u * quads + lane)) = img[4u * quads + lane];
         }
     }
-    if (!last || wv != 0) return;
+    if (last && wv == 0) close_blob(p, blob, tickets, error_flag, epoch, bad, ew + words, (uint64_t)ec + st.cnt, raised);
+}
 
-    // ---- the last token's first wave closes the blob, also if its own wait has expired (nobody else writes a header)
-    const uint32_t all_words = bad ? 0u : ew + words;
-    const uint64_t all_outliers = bad ? 0u : (uint64_t)ec + st.cnt;
-    if (!bad) word_store(tickets + lane * kTicketStride + kCntTickets, ((epoch + 1u) % 3u) << kTicketBits);   // everybody has this call's
-    if (lane == 0) {
-        const bool full = all_outliers > p.outlier_capacity;
-        if (full) {                            // (as the zero at the start: in its place before the error word is read again)
-            store_status(blob, kStatusCapacity);
-            memory_operations_performed();
-            raised |= word_load(error_flag + opaque_zero());
-        }
-        reinterpret_cast<uint64_t *>(blob + p.off_row_ptr)[p.tokens] = all_outliers;
-        reinterpret_cast<uint64_t *>(blob + p.off_pay_off)[p.tokens] = (uint64_t)all_words << 2;
-        write_header_but_status(p, blob, all_outliers, (uint64_t)all_words << 2);
-        if (raised) store_status(blob, kStatusInternal);
+// ---------------------------------------------------------------- eight short rows a workgroup
+
+// Rows of one wave, calls of many tokens: a workgroup of eight waves takes eight consecutive tokens, one a wave, and places
+// them together: one word per eight tokens is published (tag | payload words << 16 | outliers), looked for and added
+// up, by all of the workgroup's waves, and the waves' own sums go through LDS.  With a workgroup per token thousands of waves
+// at a time look for every word there is, and those looks hold up the stores that they wait for: 360 tokens per us, whatever
+// the length of the rows.  131072 x 768 f16 352 us, now 156; 131072 x 2048 bf16 430 / 226; 65536 x 1024 f16 193 / 89;
+// 10^6 x 8 f16 2823 / 1415; 4000 x 768 f16 15.0 / 9.9.  What bounds it now is the workgroup's life, from the row's arrival to
+// the last store, and how many of them fit the device (24 to 32 waves a compute unit, none of which fetches ahead).
+constexpr uint32_t kGroupTokens = 8;
+constexpr uint32_t kGroupWordsMax = kGroupTokens * (2048u * 8u / 32u), kGroupOutliersMax = kGroupTokens * 2048u;
+static_assert(kGroupWordsMax < (1u << 14) && kGroupOutliersMax < (1u << 16), "fields of a group's word");
+constexpr uint32_t kGroupExchange = 6u * kGroupTokens;      // dwords: three values per wave, twice
+
+// LDS map (dynamic): per wave: row: runs*16 dwords, codes: runs*8 | exchange
+template <int DT, bool FULL>
+__global__ void __launch_bounds__(64 * kGroupTokens, DT == kF16 ? 8 : 6)
+k_direct_group(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ blob, uint8_t *__restrict__ ws) {
+    extern __shared__ __align__(16) uint32_t lds[];
+    const uint32_t u = blockIdx.x, tid = threadIdx.x, lane = tid & 63u, wv = uniform(tid >> 6);
+    const uint32_t t = u * kGroupTokens + wv;
+    const bool have = t < p.tokens, last = u == gridDim.x - 1u;
+    const uint32_t runs = FULL ? 64u : p.runs, pieces = FULL ? 256u : p.pieces;
+    const bool owns = FULL || lane < runs;
+    const uint32_t left = FULL ? 4u : (owns ? pieces - 4u * lane : 0u);    // 16-byte pieces of the lane's run inside the row
+    uint32_t *lrow = lds + wv * runs * 24u, *image = lrow + runs * 16u, *exchange = lds + kGroupTokens * runs * 24u;
+
+    u32x4 part[4] = {};
+    if (have) {
+        const GlobalBytes src = (GlobalBytes)row_address(p, in, t, FULL ? 2048u : p.hidden);
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k)
+            if (FULL || lane + 64u * k < pieces)
+                part[k] = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4 *)(src + 16u * lane + 1024u * k));
     }
+    // error word, shape and epoch of the workspace, one per lane of one load
+    uint32_t *ctrl = reinterpret_cast<uint32_t *>(ws + p.ws_ctrl);
+    uint32_t *tickets = reinterpret_cast<uint32_t *>(ws + p.ws_tickets);
+    uint32_t *error_flag = ctrl + kCtlError;
+    const uint32_t *mine = lane == 0 ? error_flag : lane == 1 ? ctrl + kCtlTokens : lane == 2 ? ctrl + kCtlHidden : tickets + kCntTickets;
+    const uint32_t state = __hip_atomic_load(mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+        const uint32_t q = lane + 64u * k, r = q >> 2, c = (q & 3u) ^ ((r >> 1) & 3u);
+        if (FULL || r < runs) *reinterpret_cast<u32x4 *>(lrow + r * 16u + c * 4u) = part[k];
+    }
+    Mags<DT> mg;
+    uint32_t omask = 0, amax_bits = 0, turn = 0;
+    {
+        uint32_t w[16];
+        load_run_sw(lrow, owns ? lane : 0u, w);
+        split_regs<DT, true>(w, p.thr_pk, mg, omask, amax_bits);
+    }
+    if (!owns || !have) { omask = 0; amax_bits = 0; }
+
+    // (a workspace that must not be used: the waves decide together, as in k_direct)
+    const bool shape_ok = workspace_shape_ok(lane_value(state, 1), lane_value(state, 2), p.tokens, p.hidden);
+    const uint32_t refused = (lane_value(state, 0) ? kSawError : 0u) + (shape_ok ? 0u : kSawShape);
+    const uint32_t epoch = (lane_value(state, 3) >> kTicketBits) % 3u, tag = epoch + 1u;
+    if (last && tid == 0) store_status(blob, 0u);
+
+    const uint32_t nl = (uint32_t)__builtin_popcount(omask);
+    const uint32_t upto = wave_incl_scan_u32(nl);                 // outliers of the token's lanes up to this one
+    const uint32_t cnt = lane_value(upto, 63);
+    const RowStats st = reduce_row_stats_counted<1>(amax_bits, cnt, nullptr, turn);
+    uint32_t m[8];
+    const Choice c = search_width<DT, 1>(p, mg, st.amax, owns, nullptr, turn, m);
+    const uint32_t words = have ? token_words(p, c.width) : 0u;
+
+    uint32_t *sizes = reinterpret_cast<uint32_t *>(ws + p.ws_sizes);
+    uint64_t *pre = reinterpret_cast<uint64_t *>(ws + p.ws_prefix);
+    // (the last workgroup looks for failures now, with the status word's zero in place: see k_direct)
+    uint32_t raised = 0;
+    if (last && wv == 0) {
+        memory_operations_performed();
+        raised = word_load(error_flag + opaque_zero());
+    }
+    if (lane == 0) { exchange[wv] = words; exchange[kGroupTokens + wv] = cnt; exchange[2u * kGroupTokens + wv] = refused; }
+    lds_barrier();
+    // lane w has what wave w left; its own wave's share, and that of the workgroup
+    const uint32_t gw = lane < kGroupTokens ? exchange[lane] : 0u, gc = lane < kGroupTokens ? exchange[kGroupTokens + lane] : 0u;
+    const uint32_t gr = lane < kGroupTokens ? exchange[2u * kGroupTokens + lane] : 0u;
+    if (__builtin_amdgcn_ballot_w64(gr != 0) != 0) {
+        if (last && tid == 0) write_header(p, blob, 0, 0, __builtin_amdgcn_ballot_w64(gr >= kSawShape) != 0 ? kStatusFormat : kStatusInternal);
+        return;
+    }
+    const uint32_t upto_w = wave_incl_scan_u32(gw), upto_c = wave_incl_scan_u32(gc);
+    const uint32_t group_words = lane_value(upto_w, 63), group_outliers = lane_value(upto_c, 63);
+    const uint32_t words_before = lane_value(upto_w - gw, (int)wv), outliers_before = lane_value(upto_c - gc, (int)wv);
+    if (tid == 0) word_store(sizes + u, (tag << 30) | (group_words << 16) | group_outliers);
+    if (lane == 0 && have) {
+        blob[p.off_bits + t] = (uint8_t)c.width;
+        reinterpret_cast<float *>(blob + p.off_scale)[t] = c.scale;
+    }
+
+    // ---- codes of the lane's run at the chosen width, into their place in LDS
+    if (owns && have) {
+        uint32_t values[16];
+        signed_values<DT>(mg, lrow, lane, values);
+        uint32_t *dst = image + lane * c.width;
+        const uint32_t nd = (FULL || left >= 4) ? c.width : ((left * c.width + 3u) >> 2);
+        switch (c.width) {
+            case 2: pack_to_image<2, FULL>(m, values, dst, nd); break;
+            case 3: pack_to_image<3, FULL>(m, values, dst, nd); break;
+            case 4: pack_to_image<4, FULL>(m, values, dst, nd); break;
+            case 5: pack_to_image<5, FULL>(m, values, dst, nd); break;
+            case 6: pack_to_image<6, FULL>(m, values, dst, nd); break;
+            case 7: pack_to_image<7, FULL>(m, values, dst, nd); break;
+            default: pack_to_image<8, FULL>(m, values, dst, nd); break;
+        }
+    }
+
+    // ---- what lies before the group, a word per thread at a time, the lowest first
+    uint32_t ew = 0, ec = 0, bad = 0, spins = 0;
+    const uint32_t u0 = u & ~(kDirectBlock - 1u), none = tag << 30;
+    uint64_t base = (uint64_t)none << 32;
+    if (u0 && wv == 0) base = prefix_load(pre + u0 + opaque_zero());
+    for (uint32_t j0 = u0; j0 < u && !bad; j0 += 64u * kGroupTokens) {
+        const uint32_t j = j0 + tid;
+        uint32_t w = j < u ? word_load(sizes + j) : none;
+        while (__builtin_amdgcn_ballot_w64((w >> 30) != tag) != 0) {
+            if (!keep_waiting(spins, p.spin_limit, error_flag)) { bad = 1; break; }
+            if ((w >> 30) != tag) w = word_load(sizes + j);
+        }
+        ew += (w >> 16) & 0x3FFFu;
+        ec += w & 0xFFFFu;
+    }
+    if (wv == 0) {
+        while ((uint32_t)(base >> 62) != tag && !bad) {
+            if (!keep_waiting(spins, p.spin_limit, error_flag)) bad = 1;
+            else base = prefix_load(pre + u0 + opaque_zero());
+        }
+        if (lane == 0) {
+            ew += (uint32_t)(base >> 32) & 0x3FFFFFFFu;
+            ec += (uint32_t)base;
+        }
+    }
+    ew = wave_sum_u32(ew);
+    ec = wave_sum_u32(ec);
+    uint32_t *sums = exchange + 3u * kGroupTokens;
+    if (lane == 0) { sums[wv] = ew; sums[kGroupTokens + wv] = ec; sums[2u * kGroupTokens + wv] = bad; }
+    lds_barrier();
+    ew = wave_sum_u32(lane < kGroupTokens ? sums[lane] : 0u);
+    ec = wave_sum_u32(lane < kGroupTokens ? sums[kGroupTokens + lane] : 0u);
+    bad = __builtin_amdgcn_ballot_w64(lane < kGroupTokens && sums[2u * kGroupTokens + lane] != 0) != 0 ? 1u : 0u;
+
+    const uint32_t payload_words = (uint32_t)(p.payload_capacity >> 2), outlier_capacity = (uint32_t)p.outlier_capacity;
+    if ((uint64_t)ew + group_words > (uint64_t)payload_words) bad = 1;     // never leaves the section, whatever the tables said
+    if (bad) {
+        if (lane == 0) {
+            raise_error(error_flag);
+            store_status(blob, kStatusInternal);
+        }
+    } else {
+        if (tid == 0 && ((u + 1u) & (kDirectBlock - 1u)) == 0)
+            prefix_store(pre + u + 1u, prefix_word(tag, ew + group_words, ec + group_outliers));
+        const uint32_t my_word = ew + words_before, my_outlier = ec + outliers_before;
+        if (have && lane == 0) {
+            reinterpret_cast<uint64_t *>(blob + p.off_pay_off)[t] = (uint64_t)my_word << 2;
+            reinterpret_cast<uint64_t *>(blob + p.off_row_ptr)[t] = my_outlier;
+        }
+        // ---- T_above of the lane's run, in column order
+        if (nl && (uint64_t)my_outlier + cnt <= (uint64_t)outlier_capacity) {
+            uint32_t pos = my_outlier + upto - nl;
+            uint16_t *col = reinterpret_cast<uint16_t *>(blob + p.off_out_col), *val = reinterpret_cast<uint16_t *>(blob + p.off_out_val);
+            for (uint32_t rest = omask; rest; rest &= rest - 1u) {
+                const uint32_t j = (uint32_t)__builtin_ctz(rest);
+                col[pos] = (uint16_t)(lane * kRun + j);
+                val[pos] = raw_element_sw(lrow, lane, j);
+                ++pos;
+            }
+        }
+        // ---- the codes to their place in the blob, 16 bytes per lane and step
+        {
+            uint8_t *dst = blob + p.off_payload + 4ull * my_word;
+            const uint32_t quads = words >> 2, rest = words & 3u;
+            const __amdgpu_buffer_rsrc_t window = raw_window(dst, words << 2);
+#pragma unroll
+            for (uint32_t k = 0; k < 2; ++k) {
+                const uint32_t i = lane + 64u * k;
+                if (i < quads) store_quad_through(window, 16u * i, *reinterpret_cast<const u32x4 *>(image + 4u * i));
+            }
+            if (lane < rest) *reinterpret_cast<uint32_t *>(dst + 4u * (4u * quads + lane)) = image[4u * quads + lane];
+        }
+    }
+    if (last && wv == 0) close_blob(p, blob, tickets, error_flag, epoch, bad, ew + group_words, (uint64_t)ec + group_outliers, raised);
 }
 
 // ---------------------------------------------------------------- launcher
@@ -317,10 +511,22 @@ int prepare_direct_kernels() {
     return 0;
 }
 
+// Rows of one wave: eight tokens a workgroup from this number of tokens on.  Fewer do not fill the device with workgroups of
+// eight: 500 x 768 f16 6.0 us with a token per workgroup against 6.5, 1000 x 2048 bf16 7.9 / 7.7, 2000 x 768 9.3 / 6.8.
+constexpr uint32_t kGroupFrom = 1024;
 int launch_direct(const Params &p, const Geometry &g, const void *d_in, void *d_blob, void *d_ws, void *stream) {
-    hipLaunchKernelGGL(direct_kernel(p.dtype, g.waves, p.hidden == 2048u * g.waves), dim3(p.tokens), dim3(64u * g.waves),
-                       direct_lds_bytes(p.runs), reinterpret_cast<hipStream_t>(stream), p, static_cast<const uint16_t *>(d_in),
-                       static_cast<uint8_t *>(d_blob), static_cast<uint8_t *>(d_ws));
+    const bool full = p.hidden == 2048u * g.waves;
+    DirectKernel kernel = direct_kernel(p.dtype, g.waves, full);
+    uint32_t grid = p.tokens, threads = 64u * g.waves, lds = direct_lds_bytes(p.runs);
+    if (g.waves == 1 && p.tokens >= kGroupFrom) {
+        if (p.dtype == (uint32_t)kF16) kernel = full ? k_direct_group<kF16, true> : k_direct_group<kF16, false>;
+        else kernel = full ? k_direct_group<kBF16, true> : k_direct_group<kBF16, false>;
+        grid = (p.tokens + kGroupTokens - 1u) / kGroupTokens;
+        threads = 64u * kGroupTokens;
+        lds = (kGroupTokens * p.runs * 24u + kGroupExchange) * 4u;
+    }
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), lds, reinterpret_cast<hipStream_t>(stream), p,
+                       static_cast<const uint16_t *>(d_in), static_cast<uint8_t *>(d_blob), static_cast<uint8_t *>(d_ws));
     return (int)hipGetLastError();
 }
 

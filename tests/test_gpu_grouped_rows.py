@@ -1,0 +1,41 @@
+"""Short rows, eight tokens a workgroup: token counts around the first that takes that form, around whole groups and around a
+block of 2048 groups; rows that fill their wave, that end inside a run, and of a single piece; tokens full of outliers;
+a table of tensors.  Whole blobs against the oracle."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import check_parity, tsq  # noqa: F401
+from test_gpu_single_pass_forms import kernel_of, rows
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,H,dtype", [(1023, 2048, "f16"), (1024, 2048, "bf16"), (1025, 2048, "f16"), (1031, 2040, "bf16"),
+                                       (1032, 1032, "f16"), (2049, 768, "bf16"), (4095, 520, "f16"), (16383, 264, "bf16"),
+                                       (16384, 256, "f16"), (16385, 256, "bf16"), (16393, 40, "f16"), (32771, 8, "bf16")])
+def test_token_counts_around_groups_and_blocks(tsq, oracle, T, H, dtype):
+    assert kernel_of(tsq, T, H, dtype) == "k_direct"
+    check_parity(tsq, oracle, rows(T, H, dtype), dtype, 6.0, (2, 3, 4, 6, 8), 0.1, "rel_rms", "fused", label="T=%d H=%d" % (T, H))
+
+
+@pytest.mark.parametrize("T,H,dtype,mode,rule", [(1500, 2048, "f16", "lsb", "as_printed"), (2001, 1000, "bf16", "rel_rms", "as_printed"),
+                                                 (1999, 776, "f16", "rel_rms", "last_passing"), (3003, 2048, "bf16", "lsb", "last_passing")])
+def test_groups_with_tokens_full_of_outliers(tsq, oracle, T, H, dtype, mode, rule):
+    ref, _ = check_parity(tsq, oracle, rows(T, H, dtype, heavy=40), dtype, 6.0, (2, 3, 4, 5, 6, 8), 0.2, mode, "fused",
+                          label="heavy T=%d H=%d" % (T, H), rule=rule)
+    assert np.diff(ref.row_ptr.astype(np.int64)).max() == H
+
+
+def test_groups_over_a_table_of_tensors(tsq, oracle):
+    import torch
+    T, H, n = 1365, 1024, 13                                  # tensors end inside groups
+    x = rows(T, H, "f16")
+    ref = oracle.compress(x, oracle.F16, 6.0, (2, 4, 8), 0.1, 1, nthreads=8)
+    plan = tsq.Plan(T, H, "f16", 6.0, (2, 4, 8), 0.1, max_outliers=ref.nnz)
+    parts = [torch.from_numpy(x[i * (T // n):(i + 1) * (T // n)].view(np.int16).copy()).cuda() for i in range(n)]
+    blob, ws = plan.new_blob(), plan.new_workspace()
+    plan.compress_batch(parts, blob, ws)
+    assert plan.info(blob).status == 0
+    sec = plan.sections(blob)
+    for k in ("bits", "pay_off", "row_ptr", "payload", "out_col", "out_val"):
+        assert np.array_equal(sec[k], getattr(ref, k)), k
