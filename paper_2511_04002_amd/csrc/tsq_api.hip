@@ -279,6 +279,12 @@ static bool use_direct(const tsq_plan *plan) {
     return plan->g.waves == 1 ? 64u * waves < (1ull << 32) : waves <= 8192u;
 }
 
+// How many consecutive tokens a workgroup of the plan's compress calls takes (its logarithm), which is how restore deals
+// them out to the dies.
+static uint32_t group_log2(const tsq_plan *plan) {
+    return plan->pipeline == TSQ_PIPE_FUSED && use_direct(plan) ? direct_group_log2(plan->p, plan->g) : 0u;
+}
+
 static int launch_ordered(const Params &p, const Geometry &g, uint32_t grid, const void *d_in, void *d_blob,
                                 void *d_ws, void *stream) {
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
@@ -431,7 +437,7 @@ tsq_status tsq_decompress(const tsq_plan *plan, const void *d_blob, void *d_out,
     if (((uintptr_t)d_out & 15u) || ((uintptr_t)d_blob & 255u)) return TSQ_ERR_INVALID_ARG;
     tsq_status st = ensure_prepared();
     if (st != TSQ_OK) return st;
-    return hip_rc(launch_unpack(plan->p, plan->g, d_blob, d_out, stream));
+    return hip_rc(launch_unpack(plan->p, plan->g, group_log2(plan), d_blob, d_out, stream));
 }
 
 tsq_status tsq_decompress_batch(const tsq_plan *plan, const void *d_blob, void *const *d_out_ptrs,
@@ -443,7 +449,7 @@ tsq_status tsq_decompress_batch(const tsq_plan *plan, const void *d_blob, void *
     if (st != TSQ_OK) return st;
     Params p = plan->p;
     p.rows_per_tensor = rows_per_tensor;
-    return hip_rc(launch_unpack(p, plan->g, d_blob, const_cast<void **>(d_out_ptrs), stream));
+    return hip_rc(launch_unpack(p, plan->g, group_log2(plan), d_blob, const_cast<void **>(d_out_ptrs), stream));
 }
 
 tsq_status tsq_code_histogram(const tsq_plan *plan, const void *d_blob, void *d_hist, void *stream) {

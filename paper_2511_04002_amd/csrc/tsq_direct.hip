@@ -514,11 +514,12 @@ int prepare_direct_kernels() {
 // Rows of one wave: eight tokens a workgroup from this number of tokens on.  Fewer do not fill the device with workgroups of
 // eight: 500 x 768 f16 6.0 us with a token per workgroup against 6.5, 1000 x 2048 bf16 7.9 / 7.7, 2000 x 768 9.3 / 6.8.
 constexpr uint32_t kGroupFrom = 1024;
+uint32_t direct_group_log2(const Params &p, const Geometry &g) { return g.waves == 1 && p.tokens >= kGroupFrom ? 3u : 0u; }
 int launch_direct(const Params &p, const Geometry &g, const void *d_in, void *d_blob, void *d_ws, void *stream) {
     const bool full = p.hidden == 2048u * g.waves;
     DirectKernel kernel = direct_kernel(p.dtype, g.waves, full);
     uint32_t grid = p.tokens, threads = 64u * g.waves, lds = direct_lds_bytes(p.runs);
-    if (g.waves == 1 && p.tokens >= kGroupFrom) {
+    if (direct_group_log2(p, g)) {
         if (p.dtype == (uint32_t)kF16) kernel = full ? k_direct_group<kF16, true> : k_direct_group<kF16, false>;
         else kernel = full ? k_direct_group<kBF16, true> : k_direct_group<kBF16, false>;
         grid = (p.tokens + kGroupTokens - 1u) / kGroupTokens;

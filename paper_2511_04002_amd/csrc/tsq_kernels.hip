@@ -228,12 +228,24 @@ __device__ __forceinline__ void load_and_unpack(const uint32_t *src_row, uint32_
         *reinterpret_cast<uint4 *>(lrun + 4 * k) = make_uint4(o[4 * k], o[4 * k + 1], o[4 * k + 2], o[4 * k + 3]);
 }
 
+// The token of a workgroup of k_unpack.  Workgroups go to the chip's eight dies in turn, in compress as here, and what a die
+// wrote is in its L2: where compress takes 2^group_log2 consecutive tokens a workgroup, the tokens are dealt out to the dies in
+// the same way (what does not fill all eight dies keeps its order).  Without that, restore behind compress took 12.7 us instead
+// of 7.3 on 2000 x 2048 bf16.
+constexpr uint32_t kDies = 8;
+__device__ __forceinline__ uint32_t token_of_workgroup(uint32_t b, uint32_t tokens, uint32_t group_log2) {
+    const uint32_t group = 1u << group_log2;
+    if (group_log2 == 0 || b >= (tokens & ~(kDies * group - 1u))) return b;
+    const uint32_t die = b % kDies, i = b / kDies;
+    return ((((i >> group_log2) * kDies) + die) << group_log2) + (i & (group - 1u));
+}
+
 template <int DT>
 __global__ void __launch_bounds__(1024)
-k_unpack(const Params p, const uint8_t *__restrict__ blob, uint16_t *__restrict__ out) {
+k_unpack(const Params p, const uint8_t *__restrict__ blob, uint16_t *__restrict__ out, uint32_t group_log2) {
     extern __shared__ __align__(16) uint32_t lds[];
     uint32_t *lrow = lds;
-    const uint32_t t = blockIdx.x;
+    const uint32_t t = token_of_workgroup(blockIdx.x, p.tokens, group_log2);
     const uint32_t run = threadIdx.x;
 
     // the blob must be this plan's and must have been completed without error
@@ -429,14 +441,14 @@ int launch_pack(const Params &p, const Geometry &g, const void *d_in, void *d_bl
     return (int)hipGetLastError();
 }
 
-int launch_unpack(const Params &p, const Geometry &g, const void *d_blob, void *d_out, void *stream) {
+int launch_unpack(const Params &p, const Geometry &g, uint32_t group_log2, const void *d_blob, void *d_out, void *stream) {
     const dim3 grid(p.tokens), block(g.block);
     if (p.dtype == kF16)
         hipLaunchKernelGGL(k_unpack<kF16>, grid, block, g.lds_bytes, as_stream(stream), p,
-                           static_cast<const uint8_t *>(d_blob), static_cast<uint16_t *>(d_out));
+                           static_cast<const uint8_t *>(d_blob), static_cast<uint16_t *>(d_out), group_log2);
     else
         hipLaunchKernelGGL(k_unpack<kBF16>, grid, block, g.lds_bytes, as_stream(stream), p,
-                           static_cast<const uint8_t *>(d_blob), static_cast<uint16_t *>(d_out));
+                           static_cast<const uint8_t *>(d_blob), static_cast<uint16_t *>(d_out), group_log2);
     return (int)hipGetLastError();
 }
 

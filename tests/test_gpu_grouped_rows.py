@@ -39,3 +39,20 @@ def test_groups_over_a_table_of_tensors(tsq, oracle):
     sec = plan.sections(blob)
     for k in ("bits", "pay_off", "row_ptr", "payload", "out_col", "out_val"):
         assert np.array_equal(sec[k], getattr(ref, k)), k
+
+
+@pytest.mark.parametrize("T,H", [(1087, 264), (1088, 264), (1089, 264), (1151, 2048), (1024, 8)])
+def test_restore_writes_every_row_of_such_a_call_once(tsq, oracle, T, H):
+    # the order in which restore takes the tokens follows the groups: counts around the multiples of 64 where it changes
+    import torch
+    x = rows(T, H, "bf16")
+    ref = oracle.compress(x, oracle.BF16, 6.0, (2, 4, 8), 0.1, 1, nthreads=8)
+    plan = tsq.Plan(T, H, "bf16", 6.0, (2, 4, 8), 0.1, max_outliers=ref.nnz)
+    blob, ws = plan.new_blob(), plan.new_workspace()
+    plan.compress(torch.from_numpy(x.view(np.int16).copy()).cuda(), blob, ws)
+    want = oracle.decompress(ref, nthreads=8)
+    assert np.array_equal(plan.decompress(blob).cpu().numpy().view(np.uint16), want)
+    if T % 17 == 0:
+        outs = [torch.zeros((T // 17, H), dtype=torch.int16, device="cuda") for _ in range(17)]
+        plan.decompress_batch(blob, outs)
+        assert np.array_equal(torch.cat(outs).cpu().numpy().view(np.uint16), want)
