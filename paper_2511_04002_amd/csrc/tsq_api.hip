@@ -272,6 +272,8 @@ static int launch_single_pass(const Params &p, const Geometry &g, uint32_t grid,
 // compute units): 2048 x 4096 f16 12.6 us against 17.4, 4096 x 4096 21.8 / 22.8, 2048 x 8192 bf16 17.9 / 20.6, 700 x 12000
 // 14.3 / 19.8, but 2200 x 8192 f16 19.7 / 19.1 and 5000 x 4096 f16 26.0 / 25.2.  Rows of one wave gain at any number of
 // tokens, eight of them a workgroup (k_direct_group): 131072 x 768 f16 156 us against 357, 131072 x 2048 bf16 226 / 389.
+// Rows of two waves, two of them a workgroup, would gain a little beyond the line and then lose: 5000 x 4096 f16 20.3 against
+// 22.1, 8192 x 4096 32.1 / 30.4, 131072 x 4096 475 / 337; they keep the line of the others.
 // Up to 2^26 - 1 tokens, that is: a launch counts its threads in 32 bits, and the persistent
 // kernel's grid does not grow with the tokens.
 static bool use_direct(const tsq_plan *plan) {

@@ -665,14 +665,9 @@ __device__ __forceinline__ RowStats reduce_row_stats(uint32_t omask, uint32_t am
     return reduce_row_stats_counted<NW>(amax_bits, wave_sum_u32((uint32_t)__builtin_popcount(omask)), ring, turn);
 }
 
-// Algorithm 1 for the token of this block, given its inlier absmax.  live: false for lanes that
-// own no run (they compute on a copy of run 0 and are left out of every sum).  On return m holds
-// the magnitude bytes of the run at the chosen width.
 // The divisions of Eq. (Proposed) for all allowed widths are one division per wave: lane k < 8
 // computes Q_k / amax, lane 8 + k computes amax / Q_k (the scale, should width k be chosen).
-template <int DT, int NW>
-__device__ __forceinline__ Choice search_width(const Params &p, const Mags<DT> &af, float amax, bool live,
-                                               uint32_t *ring, uint32_t &turn, uint32_t (&m)[8]) {
+__device__ __forceinline__ float quotients_of(const Params &p, float amax) {
     const uint32_t lane = threadIdx.x & 63;
     float quot = 0.0f;
     if ((lane & 7u) < p.n_widths && lane < 16u && amax >= kAmaxFloor) {
@@ -680,7 +675,16 @@ __device__ __forceinline__ Choice search_width(const Params &p, const Mags<DT> &
         const bool scale = lane >= 8u;
         quot = (scale ? amax : q) / (scale ? q : amax);      // (one division: a branch each would issue two)
     }
-    const uint32_t quot_bits = __float_as_uint(quot);
+    return quot;
+}
+
+// Algorithm 1 for the token of this block, given its inlier absmax.  live: false for lanes that
+// own no run (they compute on a copy of run 0 and are left out of every sum).  On return m holds
+// the magnitude bytes of the run at the chosen width.
+template <int DT, int NW>
+__device__ __forceinline__ Choice search_width(const Params &p, const Mags<DT> &af, float amax, bool live,
+                                               uint32_t *ring, uint32_t &turn, uint32_t (&m)[8]) {
+    const uint32_t quot_bits = __float_as_uint(quotients_of(p, amax));
 
     const uint32_t b0 = width_at(p, 0);
     const uint32_t Q0 = (1u << (b0 - 1)) - 1u;

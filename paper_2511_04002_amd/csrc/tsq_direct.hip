@@ -1,5 +1,5 @@
 // Single-pass compress for calls of few tokens and for rows of one wave (gfx950): one workgroup per token, or per eight
-// tokens of one wave, dispatched in token order, nothing handed out and nobody in between.
+// tokens of one wave, or per two of two waves, dispatched in token order, nothing handed out and nobody in between.
 //
 // With as many workgroups as tokens a call is one chain of latencies: row from HBM, threshold split, width
 // search, publication of the token's size, sizes of the tokens before it, stores.  The persistent kernel
@@ -296,49 +296,124 @@ k_direct(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ 
 // the length of the rows.  131072 x 768 f16 352 us, now 156; 131072 x 2048 bf16 430 / 226; 65536 x 1024 f16 193 / 89;
 // 10^6 x 8 f16 2823 / 1415; 4000 x 768 f16 15.0 / 9.9.  What bounds it now is the workgroup's life, from the row's arrival to
 // the last store, and how many of them fit the device (24 to 32 waves a compute unit, none of which fetches ahead).
-constexpr uint32_t kGroupTokens = 8;
-constexpr uint32_t kGroupWordsMax = kGroupTokens * (2048u * 8u / 32u), kGroupOutliersMax = kGroupTokens * 2048u;
-static_assert(kGroupWordsMax < (1u << 14) && kGroupOutliersMax < (1u << 16), "fields of a group's word");
-constexpr uint32_t kGroupExchange = 6u * kGroupTokens;      // dwords: three values per wave, twice
+// Rows of two waves: two tokens a workgroup, which halves the polling and, more, the number of workgroups that live at once:
+// 2000 x 4096 f16 12.0 us with a token per workgroup against 10.5; 3000 x 4096 15.6 / 12.8; 4000 x 4096 21.5 / 16.8; 3000 x
+// 2304 bf16 16.0 / 13.4.  Four tokens a workgroup were slower than two, and rows of three and four waves gained nothing.
+constexpr uint32_t group_tokens(uint32_t nw) { return nw == 1u ? 8u : 2u; }
+constexpr uint32_t kGroupWaves = 8;                         // at most
+static_assert(kGroupWaves * 512u < (1u << 14) && kGroupWaves * 2048u < (1u << 16), "fields of a group's word");
+constexpr uint32_t kGroupExchange = 6u * kGroupWaves;       // dwords: three values per wave, twice
+constexpr uint32_t kGroupRing = 4u * 2u * kMaxWaves;        // four reduce areas: two words per token; one word per wave
 
-// LDS map (dynamic): per wave: row: runs*16 dwords, codes: runs*8 | exchange
-template <int DT, bool FULL>
-__global__ void __launch_bounds__(64 * kGroupTokens, DT == kF16 ? 8 : 6)
+__device__ __forceinline__ void clear_group_area(uint32_t *ring, uint32_t turn) {
+    if (threadIdx.x < 8u) reduce_area(ring, turn)[threadIdx.x] = 0;
+}
+
+// Algorithm 1 for the tokens of a workgroup, NW waves each (this wave's is number g of G), as search_width does it for one.
+// The tokens go through the candidates together, since a barrier is the whole workgroup's: whoever is done waits there for
+// the others; lane k of every wave makes the test of token k, so that all waves know who goes on.  present: bit k: there is
+// a token k.
+template <int DT, int NW, int G>
+__device__ __forceinline__ Choice search_widths(const Params &p, const Mags<DT> &af, float amax, bool live, uint32_t g,
+                                                uint32_t present, uint32_t *ring, uint32_t &turn, uint32_t (&m)[8]) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t quot_bits = __float_as_uint(quotients_of(p, amax));
+    const uint32_t b0 = width_at(p, 0);
+    const uint32_t Q0 = (1u << (b0 - 1)) - 1u;
+    quantize_run<DT>(af, __uint_as_float(lane_value(quot_bits, 0)), m);
+    uint32_t sel = b0, sel_i = 0;
+    if (p.n_widths > 1) {
+        uint32_t m0[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) m0[k] = m[k];
+        double ss0d = 0.0;                                   // lane k: token k's
+        uint32_t active = present;
+        for (uint32_t i = 1; i < p.n_widths && active; ++i) {
+            const uint32_t bi = width_at(p, i);
+            const bool mine = (active >> g) & 1u;
+            uint32_t *red = reduce_area(ring, turn);
+            uint32_t mi[8];
+            if (mine) {
+                quantize_run<DT>(af, __uint_as_float(lane_value(quot_bits, (int)i)), mi);
+                const uint32_t sad = row_sum_u32(live ? sad_run(m0, mi, b0 - bi) : kSadNone);
+                if (i == 1) {
+                    const uint32_t ss0 = row_sum_u32(live ? sum_squares_run(m0) : 0u);
+                    if (first_of_row())
+                        __hip_atomic_fetch_add(reinterpret_cast<uint64_t *>(red) + g + some_zero(), (uint64_t)ss0 << 32 | sad,
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                } else if (first_of_row()) {
+                    __hip_atomic_fetch_add(red + 2u * g + some_zero(), sad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+            }
+            lds_barrier();
+            const uint2 v = *reinterpret_cast<const uint2 *>(red + 2u * (lane & (G - 1)));
+            clear_group_area(ring, turn + 2u);
+            ++turn;
+            if (i == 1) ss0d = (double)v.y;
+            const bool over = violates(p.mode, p.test_rhs[i], Q0, 64u * NW * kSadNone - v.x, ss0d);
+            const uint32_t fails = (uint32_t)__builtin_amdgcn_ballot_w64(over) & active;
+            if (mine && (!((fails >> g) & 1u) || p.return_failing)) {
+                sel = bi;
+                sel_i = i;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) m[k] = mi[k];
+            }
+            active &= ~fails;
+        }
+    }
+    Choice c;
+    c.width = sel;
+    c.scale = __uint_as_float(lane_value(quot_bits, (int)(8u + sel_i)));
+    return c;
+}
+
+// LDS map (dynamic): per token: row: runs*16 dwords, codes: runs*8 | exchange | ring (rows of more than one wave)
+template <int DT, int NW, bool FULL>
+__global__ void __launch_bounds__(64 * NW * group_tokens(NW), DT == kF16 ? 8 : 6)
 k_direct_group(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ blob, uint8_t *__restrict__ ws) {
     extern __shared__ __align__(16) uint32_t lds[];
+    constexpr uint32_t G = group_tokens(NW), W = NW * G;     // tokens and waves of the workgroup
     const uint32_t u = blockIdx.x, tid = threadIdx.x, lane = tid & 63u, wv = uniform(tid >> 6);
-    const uint32_t t = u * kGroupTokens + wv;
+    const uint32_t g = wv / NW, part = wv % NW;              // the wave's token in the group, and its part of it
+    const uint32_t t = u * G + g;
     const bool have = t < p.tokens, last = u == gridDim.x - 1u;
-    const uint32_t runs = FULL ? 64u : p.runs, pieces = FULL ? 256u : p.pieces;
-    const bool owns = FULL || lane < runs;
-    const uint32_t left = FULL ? 4u : (owns ? pieces - 4u * lane : 0u);    // 16-byte pieces of the lane's run inside the row
-    uint32_t *lrow = lds + wv * runs * 24u, *image = lrow + runs * 16u, *exchange = lds + kGroupTokens * runs * 24u;
+    const uint32_t runs = FULL ? 64u * NW : p.runs, pieces = FULL ? 256u * NW : p.pieces;
+    const uint32_t run = 64u * part + lane;
+    const bool owns = FULL || run < runs;
+    const uint32_t left = FULL ? 4u : (owns ? pieces - 4u * run : 0u);    // 16-byte pieces of the lane's run inside the row
+    uint32_t *lrow = lds + g * runs * 24u, *image = lrow + runs * 16u, *exchange = lds + G * runs * 24u, *ring = exchange + kGroupExchange;
 
-    u32x4 part[4] = {};
+    u32x4 piece[4] = {};
+    const uint32_t q0 = 256u * part + lane;
     if (have) {
-        const GlobalBytes src = (GlobalBytes)row_address(p, in, t, FULL ? 2048u : p.hidden);
+        const GlobalBytes src = (GlobalBytes)row_address(p, in, t, FULL ? 2048u * NW : p.hidden);
 #pragma unroll
         for (uint32_t k = 0; k < 4; ++k)
-            if (FULL || lane + 64u * k < pieces)
-                part[k] = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4 *)(src + 16u * lane + 1024u * k));
+            if (FULL || q0 + 64u * k < pieces)
+                piece[k] = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4 *)(src + 16u * q0 + 1024u * k));
     }
     // error word, shape and epoch of the workspace, one per lane of one load
     uint32_t *ctrl = reinterpret_cast<uint32_t *>(ws + p.ws_ctrl);
     uint32_t *tickets = reinterpret_cast<uint32_t *>(ws + p.ws_tickets);
     uint32_t *error_flag = ctrl + kCtlError;
-    const uint32_t *mine = lane == 0 ? error_flag : lane == 1 ? ctrl + kCtlTokens : lane == 2 ? ctrl + kCtlHidden : tickets + kCntTickets;
-    const uint32_t state = __hip_atomic_load(mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    const uint32_t *looked = lane == 0 ? error_flag : lane == 1 ? ctrl + kCtlTokens : lane == 2 ? ctrl + kCtlHidden : tickets + kCntTickets;
+    const uint32_t state = __hip_atomic_load(looked, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (NW > 1) {
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) clear_group_area(ring, k);
+        lds_barrier();
+    }
 
 #pragma unroll
     for (uint32_t k = 0; k < 4; ++k) {
-        const uint32_t q = lane + 64u * k, r = q >> 2, c = (q & 3u) ^ ((r >> 1) & 3u);
-        if (FULL || r < runs) *reinterpret_cast<u32x4 *>(lrow + r * 16u + c * 4u) = part[k];
+        const uint32_t q = q0 + 64u * k, r = q >> 2, c = (q & 3u) ^ ((r >> 1) & 3u);
+        if (FULL || r < runs) *reinterpret_cast<u32x4 *>(lrow + r * 16u + c * 4u) = piece[k];
     }
     Mags<DT> mg;
     uint32_t omask = 0, amax_bits = 0, turn = 0;
     {
         uint32_t w[16];
-        load_run_sw(lrow, owns ? lane : 0u, w);
+        load_run_sw(lrow, owns ? run : 64u * part, w);
         split_regs<DT, true>(w, p.thr_pk, mg, omask, amax_bits);
     }
     if (!owns || !have) { omask = 0; amax_bits = 0; }
@@ -350,12 +425,25 @@ k_direct_group(const Params p, const uint16_t *__restrict__ in, uint8_t *__restr
     if (last && tid == 0) store_status(blob, 0u);
 
     const uint32_t nl = (uint32_t)__builtin_popcount(omask);
-    const uint32_t upto = wave_incl_scan_u32(nl);                 // outliers of the token's lanes up to this one
-    const uint32_t cnt = lane_value(upto, 63);
-    const RowStats st = reduce_row_stats_counted<1>(amax_bits, cnt, nullptr, turn);
+    const uint32_t upto = wave_incl_scan_u32(nl);                 // outliers of the wave's lanes up to this one
+    const uint32_t cnt = lane_value(upto, 63);                    // ... of the wave
     uint32_t m[8];
-    const Choice c = search_width<DT, 1>(p, mg, st.amax, owns, nullptr, turn, m);
-    const uint32_t words = have ? token_words(p, c.width) : 0u;
+    Choice c;
+    if constexpr (NW == 1) {
+        const RowStats st = reduce_row_stats_counted<1>(amax_bits, cnt, nullptr, turn);
+        c = search_width<DT, 1>(p, mg, st.amax, owns, nullptr, turn, m);
+    } else {
+        uint32_t *red = reduce_area(ring, turn);
+        const uint32_t mx = row_max_u32(amax_bits);
+        if (first_of_row()) __hip_atomic_fetch_max(red + 2u * g + some_zero(), mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        lds_barrier();
+        const float amax = __uint_as_float(uniform(red[2u * g]));
+        clear_group_area(ring, turn + 2u);
+        ++turn;
+        const uint32_t there = p.tokens - u * G < G ? (1u << (p.tokens - u * G)) - 1u : (1u << G) - 1u;
+        c = search_widths<DT, NW, G>(p, mg, amax, owns, g, there, ring, turn, m);
+    }
+    const uint32_t words = have ? token_words(p, c.width) : 0u;   // of the token
 
     uint32_t *sizes = reinterpret_cast<uint32_t *>(ws + p.ws_sizes);
     uint64_t *pre = reinterpret_cast<uint64_t *>(ws + p.ws_prefix);
@@ -365,20 +453,23 @@ k_direct_group(const Params p, const uint16_t *__restrict__ in, uint8_t *__restr
         memory_operations_performed();
         raised = word_load(error_flag + opaque_zero());
     }
-    if (lane == 0) { exchange[wv] = words; exchange[kGroupTokens + wv] = cnt; exchange[2u * kGroupTokens + wv] = refused; }
+    if (lane == 0) { exchange[wv] = part == 0 ? words : 0u; exchange[W + wv] = cnt; exchange[2u * W + wv] = refused; }
     lds_barrier();
     // lane w has what wave w left; its own wave's share, and that of the workgroup
-    const uint32_t gw = lane < kGroupTokens ? exchange[lane] : 0u, gc = lane < kGroupTokens ? exchange[kGroupTokens + lane] : 0u;
-    const uint32_t gr = lane < kGroupTokens ? exchange[2u * kGroupTokens + lane] : 0u;
+    const uint32_t gw = lane < W ? exchange[lane] : 0u, gc = lane < W ? exchange[W + lane] : 0u;
+    const uint32_t gr = lane < W ? exchange[2u * W + lane] : 0u;
     if (__builtin_amdgcn_ballot_w64(gr != 0) != 0) {
         if (last && tid == 0) write_header(p, blob, 0, 0, __builtin_amdgcn_ballot_w64(gr >= kSawShape) != 0 ? kStatusFormat : kStatusInternal);
         return;
     }
     const uint32_t upto_w = wave_incl_scan_u32(gw), upto_c = wave_incl_scan_u32(gc);
     const uint32_t group_words = lane_value(upto_w, 63), group_outliers = lane_value(upto_c, 63);
-    const uint32_t words_before = lane_value(upto_w - gw, (int)wv), outliers_before = lane_value(upto_c - gc, (int)wv);
+    const uint32_t words_before = lane_value(upto_w - gw, (int)(wv - part));                // before the token
+    const uint32_t token_first = lane_value(upto_c - gc, (int)(wv - part));                 // outliers before the token
+    const uint32_t token_outliers = lane_value(upto_c, (int)(wv - part + NW - 1u)) - token_first;
+    const uint32_t outliers_before = lane_value(upto_c - gc, (int)wv);                      // before the wave's part
     if (tid == 0) word_store(sizes + u, (tag << 30) | (group_words << 16) | group_outliers);
-    if (lane == 0 && have) {
+    if (lane == 0 && part == 0 && have) {
         blob[p.off_bits + t] = (uint8_t)c.width;
         reinterpret_cast<float *>(blob + p.off_scale)[t] = c.scale;
     }
@@ -386,8 +477,8 @@ k_direct_group(const Params p, const uint16_t *__restrict__ in, uint8_t *__restr
     // ---- codes of the lane's run at the chosen width, into their place in LDS
     if (owns && have) {
         uint32_t values[16];
-        signed_values<DT>(mg, lrow, lane, values);
-        uint32_t *dst = image + lane * c.width;
+        signed_values<DT>(mg, lrow, run, values);
+        uint32_t *dst = image + part * (64u * 8u) + lane * c.width;
         const uint32_t nd = (FULL || left >= 4) ? c.width : ((left * c.width + 3u) >> 2);
         switch (c.width) {
             case 2: pack_to_image<2, FULL>(m, values, dst, nd); break;
@@ -405,7 +496,7 @@ k_direct_group(const Params p, const uint16_t *__restrict__ in, uint8_t *__restr
     const uint32_t u0 = u & ~(kDirectBlock - 1u), none = tag << 30;
     uint64_t base = (uint64_t)none << 32;
     if (u0 && wv == 0) base = prefix_load(pre + u0 + opaque_zero());
-    for (uint32_t j0 = u0; j0 < u && !bad; j0 += 64u * kGroupTokens) {
+    for (uint32_t j0 = u0; j0 < u && !bad; j0 += 64u * W) {
         const uint32_t j = j0 + tid;
         uint32_t w = j < u ? word_load(sizes + j) : none;
         while (__builtin_amdgcn_ballot_w64((w >> 30) != tag) != 0) {
@@ -427,12 +518,12 @@ k_direct_group(const Params p, const uint16_t *__restrict__ in, uint8_t *__restr
     }
     ew = wave_sum_u32(ew);
     ec = wave_sum_u32(ec);
-    uint32_t *sums = exchange + 3u * kGroupTokens;
-    if (lane == 0) { sums[wv] = ew; sums[kGroupTokens + wv] = ec; sums[2u * kGroupTokens + wv] = bad; }
+    uint32_t *sums = exchange + 3u * W;
+    if (lane == 0) { sums[wv] = ew; sums[W + wv] = ec; sums[2u * W + wv] = bad; }
     lds_barrier();
-    ew = wave_sum_u32(lane < kGroupTokens ? sums[lane] : 0u);
-    ec = wave_sum_u32(lane < kGroupTokens ? sums[kGroupTokens + lane] : 0u);
-    bad = __builtin_amdgcn_ballot_w64(lane < kGroupTokens && sums[2u * kGroupTokens + lane] != 0) != 0 ? 1u : 0u;
+    ew = wave_sum_u32(lane < W ? sums[lane] : 0u);
+    ec = wave_sum_u32(lane < W ? sums[W + lane] : 0u);
+    bad = __builtin_amdgcn_ballot_w64(lane < W && sums[2u * W + lane] != 0) != 0 ? 1u : 0u;
 
     const uint32_t payload_words = (uint32_t)(p.payload_capacity >> 2), outlier_capacity = (uint32_t)p.outlier_capacity;
     if ((uint64_t)ew + group_words > (uint64_t)payload_words) bad = 1;     // never leaves the section, whatever the tables said
@@ -444,33 +535,36 @@ k_direct_group(const Params p, const uint16_t *__restrict__ in, uint8_t *__restr
     } else {
         if (tid == 0 && ((u + 1u) & (kDirectBlock - 1u)) == 0)
             prefix_store(pre + u + 1u, prefix_word(tag, ew + group_words, ec + group_outliers));
-        const uint32_t my_word = ew + words_before, my_outlier = ec + outliers_before;
-        if (have && lane == 0) {
+        const uint32_t my_word = ew + words_before;
+        if (have && lane == 0 && part == 0) {
             reinterpret_cast<uint64_t *>(blob + p.off_pay_off)[t] = (uint64_t)my_word << 2;
-            reinterpret_cast<uint64_t *>(blob + p.off_row_ptr)[t] = my_outlier;
+            reinterpret_cast<uint64_t *>(blob + p.off_row_ptr)[t] = ec + token_first;
         }
         // ---- T_above of the lane's run, in column order
-        if (nl && (uint64_t)my_outlier + cnt <= (uint64_t)outlier_capacity) {
-            uint32_t pos = my_outlier + upto - nl;
+        if (nl && (uint64_t)(ec + token_first) + token_outliers <= (uint64_t)outlier_capacity) {
+            uint32_t pos = ec + outliers_before + upto - nl;
             uint16_t *col = reinterpret_cast<uint16_t *>(blob + p.off_out_col), *val = reinterpret_cast<uint16_t *>(blob + p.off_out_val);
             for (uint32_t rest = omask; rest; rest &= rest - 1u) {
                 const uint32_t j = (uint32_t)__builtin_ctz(rest);
-                col[pos] = (uint16_t)(lane * kRun + j);
-                val[pos] = raw_element_sw(lrow, lane, j);
+                col[pos] = (uint16_t)(run * kRun + j);
+                val[pos] = raw_element_sw(lrow, run, j);
                 ++pos;
             }
         }
         // ---- the codes to their place in the blob, 16 bytes per lane and step
         {
-            uint8_t *dst = blob + p.off_payload + 4ull * my_word;
-            const uint32_t quads = words >> 2, rest = words & 3u;
-            const __amdgpu_buffer_rsrc_t window = raw_window(dst, words << 2);
+            const uint32_t first = 64u * part * c.width;                  // the wave's first word of the row
+            const uint32_t n = words > first ? (words - first < 64u * c.width ? words - first : 64u * c.width) : 0u;
+            const uint32_t *img = image + part * (64u * 8u);
+            uint8_t *dst = blob + p.off_payload + 4ull * (my_word + first);
+            const uint32_t quads = n >> 2, rest = n & 3u;
+            const __amdgpu_buffer_rsrc_t window = raw_window(dst, n << 2);
 #pragma unroll
             for (uint32_t k = 0; k < 2; ++k) {
                 const uint32_t i = lane + 64u * k;
-                if (i < quads) store_quad_through(window, 16u * i, *reinterpret_cast<const u32x4 *>(image + 4u * i));
+                if (i < quads) store_quad_through(window, 16u * i, *reinterpret_cast<const u32x4 *>(img + 4u * i));
             }
-            if (lane < rest) *reinterpret_cast<uint32_t *>(dst + 4u * (4u * quads + lane)) = image[4u * quads + lane];
+            if (lane < rest) *reinterpret_cast<uint32_t *>(dst + 4u * (4u * quads + lane)) = img[4u * quads + lane];
         }
     }
     if (last && wv == 0) close_blob(p, blob, tickets, error_flag, epoch, bad, ew + group_words, (uint64_t)ec + group_outliers, raised);
@@ -496,6 +590,18 @@ static DirectKernel direct_kernel(uint32_t dtype, uint32_t nw, bool full) {
     return full ? direct_kernel_for<kBF16, true>(nw) : direct_kernel_for<kBF16, false>(nw);
 }
 
+template <int DT, bool FULL>
+static DirectKernel group_kernel_for(uint32_t nw) {
+    switch (nw) {
+        case 1: return k_direct_group<DT, 1, FULL>;
+        default: return k_direct_group<DT, 2, FULL>;
+    }
+}
+static DirectKernel group_kernel(uint32_t dtype, uint32_t nw, bool full) {
+    if (dtype == (uint32_t)kF16) return full ? group_kernel_for<kF16, true>(nw) : group_kernel_for<kF16, false>(nw);
+    return full ? group_kernel_for<kBF16, true>(nw) : group_kernel_for<kBF16, false>(nw);
+}
+
 static uint32_t direct_lds_bytes(uint32_t runs) { return (runs * 24u + (runs > 64u ? kDirectRing : 0u)) * 4u; }
 
 int prepare_direct_kernels() {
@@ -513,18 +619,21 @@ int prepare_direct_kernels() {
 
 // Rows of one wave: eight tokens a workgroup from this number of tokens on.  Fewer do not fill the device with workgroups of
 // eight: 500 x 768 f16 6.0 us with a token per workgroup against 6.5, 1000 x 2048 bf16 7.9 / 7.7, 2000 x 768 9.3 / 6.8.
+// Rows of two waves, two tokens: 700 x 4096 f16 8.7 / 8.6, 1024 x 4096 8.5 / 8.0, 1100 x 4096 bf16 9.8 / 8.9.
 constexpr uint32_t kGroupFrom = 1024;
-uint32_t direct_group_log2(const Params &p, const Geometry &g) { return g.waves == 1 && p.tokens >= kGroupFrom ? 3u : 0u; }
+uint32_t direct_group_log2(const Params &p, const Geometry &g) {
+    return g.waves > 2 || p.tokens < kGroupFrom ? 0u : g.waves == 1 ? 3u : 1u;
+}
 int launch_direct(const Params &p, const Geometry &g, const void *d_in, void *d_blob, void *d_ws, void *stream) {
     const bool full = p.hidden == 2048u * g.waves;
     DirectKernel kernel = direct_kernel(p.dtype, g.waves, full);
     uint32_t grid = p.tokens, threads = 64u * g.waves, lds = direct_lds_bytes(p.runs);
-    if (direct_group_log2(p, g)) {
-        if (p.dtype == (uint32_t)kF16) kernel = full ? k_direct_group<kF16, true> : k_direct_group<kF16, false>;
-        else kernel = full ? k_direct_group<kBF16, true> : k_direct_group<kBF16, false>;
-        grid = (p.tokens + kGroupTokens - 1u) / kGroupTokens;
-        threads = 64u * kGroupTokens;
-        lds = (kGroupTokens * p.runs * 24u + kGroupExchange) * 4u;
+    const uint32_t G = 1u << direct_group_log2(p, g);
+    if (G > 1) {
+        kernel = group_kernel(p.dtype, g.waves, full);
+        grid = (p.tokens + G - 1u) / G;
+        threads = 64u * g.waves * G;
+        lds = (G * p.runs * 24u + kGroupExchange + (g.waves > 1 ? kGroupRing : 0u)) * 4u;
     }
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), lds, reinterpret_cast<hipStream_t>(stream), p,
                        static_cast<const uint16_t *>(d_in), static_cast<uint8_t *>(d_blob), static_cast<uint8_t *>(d_ws));

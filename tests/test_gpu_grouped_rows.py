@@ -1,4 +1,4 @@
-"""Short rows, eight tokens a workgroup: token counts around the first that takes that form, around whole groups and around a
+"""Short rows, eight tokens a workgroup (rows of two waves: two): token counts around the first that takes that form, around whole groups and around a
 block of 2048 groups; rows that fill their wave, that end inside a run, and of a single piece; tokens full of outliers;
 a table of tensors.  Whole blobs against the oracle."""
 import numpy as np
@@ -56,3 +56,16 @@ def test_restore_writes_every_row_of_such_a_call_once(tsq, oracle, T, H):
         outs = [torch.zeros((T // 17, H), dtype=torch.int16, device="cuda") for _ in range(17)]
         plan.decompress_batch(blob, outs)
         assert np.array_equal(torch.cat(outs).cpu().numpy().view(np.uint16), want)
+
+
+@pytest.mark.parametrize("T,H,dtype,mode,rule,heavy", [
+    (1023, 4096, "f16", "rel_rms", "last_passing", 0), (1024, 4096, "bf16", "rel_rms", "as_printed", 0),
+    (1025, 2056, "f16", "lsb", "as_printed", 0), (1535, 2856, "bf16", "lsb", "last_passing", 40),
+    (2049, 4088, "f16", "rel_rms", "as_printed", 40), (4095, 2080, "bf16", "rel_rms", "last_passing", 0),
+    (4096, 4096, "f16", "lsb", "as_printed", 0)])
+def test_rows_of_two_waves_two_tokens_a_workgroup(tsq, oracle, T, H, dtype, mode, rule, heavy):
+    # both tokens of a workgroup go through the widths together: many widths, tokens that leave at different ones; whole
+    # blocks of 2048 groups; a last group of one token
+    assert kernel_of(tsq, T, H, dtype) == "k_direct"
+    x = rows(T, H, dtype, heavy=heavy) if heavy else rows(T, H, dtype)
+    check_parity(tsq, oracle, x, dtype, 6.0, (2, 3, 4, 5, 6, 8), 0.2, mode, "fused", label="T=%d H=%d" % (T, H), rule=rule)
