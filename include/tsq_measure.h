@@ -38,8 +38,8 @@ tsq_status tsq_measure_copy(void *d_dst, const void *d_src, size_t bytes, void *
 tsq_status tsq_measure_read(const void *d_src, size_t bytes, void *d_sink, void *stream);
 
 /*
- * Which kernel a plan's compress calls run: "k_direct" (a workgroup per token, or per eight
- * tokens of up to 2048 elements), "k_fused" (as many workgroups as
+ * Which kernel a plan's compress calls run: "k_direct" (a workgroup per token, or per group of eight or two
+ * tokens of up to 2048 or 4096 elements), "k_fused" (as many workgroups as
  * the device holds; see TSQ_PIPE_AUTO in tsq.h for devices that hold too few), or "staged".  NULL for a NULL plan.
  */
 const char *tsq_plan_kernel(const tsq_plan *plan);
