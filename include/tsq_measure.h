@@ -45,6 +45,13 @@ tsq_status tsq_measure_read(const void *d_src, size_t bytes, void *d_sink, void 
 const char *tsq_plan_kernel(const tsq_plan *plan);
 
 /*
+ * How the compress calls of a plan that run "k_direct" are launched: out[0] = tokens per workgroup (1, or 8 or 2: the
+ * kernel of groups), out[1] = workgroups, out[2] = threads per workgroup, out[3] = bytes of LDS per workgroup.
+ * TSQ_ERR_UNSUPPORTED for a plan that runs another kernel.  Host only.
+ */
+tsq_status tsq_plan_direct_launch(const tsq_plan *plan, uint32_t *out);
+
+/*
  * Bounds every device-side wait of the plan's later single-pass calls to `rounds` looks (>= 1; a new
  * plan has 2^20, about a second), so that a test can see what a call does whose waits expire.  Host
  * only.  The one call that writes to a plan: not while another thread uses it.

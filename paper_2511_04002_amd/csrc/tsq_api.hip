@@ -274,8 +274,8 @@ static int launch_single_pass(const Params &p, const Geometry &g, uint32_t grid,
 // tokens, eight of them a workgroup (k_direct_group): 131072 x 768 f16 156 us against 357, 131072 x 2048 bf16 226 / 389.
 // Rows of two waves, two of them a workgroup, would gain a little beyond the line and then lose: 5000 x 4096 f16 20.3 against
 // 22.1, 8192 x 4096 32.1 / 30.4, 131072 x 4096 475 / 337; they keep the line of the others.
-// Up to 2^26 - 1 tokens, that is: a launch counts its threads in 32 bits, and the persistent
-// kernel's grid does not grow with the tokens.
+// Up to 2^26 - 1 tokens, that is (64 threads a token; eight a workgroup up to 2^26 - 8): a launch counts its threads in
+// 32 bits, and the persistent kernel's grid does not grow with the tokens.
 static bool use_direct(const tsq_plan *plan) {
     const uint64_t waves = (uint64_t)plan->p.tokens * plan->g.waves;
     return plan->g.waves == 1 ? 64u * waves < (1ull << 32) : waves <= 8192u;
@@ -666,6 +666,16 @@ int tsq_check_workspace_shape(uint32_t ws_tokens, uint32_t ws_hidden, uint32_t t
 const char *tsq_plan_kernel(const tsq_plan *plan) {
     if (!plan) return nullptr;
     return plan->pipeline != TSQ_PIPE_FUSED ? "staged" : use_direct(plan) ? "k_direct" : "k_fused";
+}
+tsq_status tsq_plan_direct_launch(const tsq_plan *plan, uint32_t *out) {
+    if (!plan || !out) return TSQ_ERR_INVALID_ARG;
+    if (plan->pipeline != TSQ_PIPE_FUSED || !use_direct(plan)) return TSQ_ERR_UNSUPPORTED;
+    const DirectLaunch l = direct_launch(plan->p, plan->g);
+    out[0] = l.tokens;
+    out[1] = l.workgroups;
+    out[2] = l.threads;
+    out[3] = l.lds_bytes;
+    return TSQ_OK;
 }
 tsq_status tsq_plan_limit_waits(tsq_plan *plan, uint32_t rounds) {
     if (!plan || rounds == 0) return TSQ_ERR_INVALID_ARG;

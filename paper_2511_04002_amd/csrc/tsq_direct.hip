@@ -620,22 +620,26 @@ int prepare_direct_kernels() {
 // Rows of one wave: eight tokens a workgroup from this number of tokens on.  Fewer do not fill the device with workgroups of
 // eight: 500 x 768 f16 6.0 us with a token per workgroup against 6.5, 1000 x 2048 bf16 7.9 / 7.7, 2000 x 768 9.3 / 6.8.
 // Rows of two waves, two tokens: 700 x 4096 f16 8.7 / 8.6, 1024 x 4096 8.5 / 8.0, 1100 x 4096 bf16 9.8 / 8.9.
+// A launch counts its threads in 32 bits, those of a last group's missing tokens included: the seven token counts of rows of
+// one wave (2^26 - 7 .. 2^26 - 1) whose groups would be 2^32 threads take a workgroup per token, which is 64 a token.
 constexpr uint32_t kGroupFrom = 1024;
 uint32_t direct_group_log2(const Params &p, const Geometry &g) {
-    return g.waves > 2 || p.tokens < kGroupFrom ? 0u : g.waves == 1 ? 3u : 1u;
+    if (g.waves > 2 || p.tokens < kGroupFrom) return 0u;
+    const uint32_t log2 = g.waves == 1 ? 3u : 1u;
+    const uint64_t groups = ((uint64_t)p.tokens + (1u << log2) - 1u) >> log2;
+    return (groups * 64u * g.waves) << log2 < (1ull << 32) ? log2 : 0u;
+}
+DirectLaunch direct_launch(const Params &p, const Geometry &g) {
+    const uint32_t log2 = direct_group_log2(p, g), G = 1u << log2;
+    if (log2 == 0) return {1u, p.tokens, 64u * g.waves, direct_lds_bytes(p.runs)};
+    return {G, (p.tokens + G - 1u) >> log2, 64u * g.waves * G,
+            (G * p.runs * 24u + kGroupExchange + (g.waves > 1 ? kGroupRing : 0u)) * 4u};
 }
 int launch_direct(const Params &p, const Geometry &g, const void *d_in, void *d_blob, void *d_ws, void *stream) {
     const bool full = p.hidden == 2048u * g.waves;
-    DirectKernel kernel = direct_kernel(p.dtype, g.waves, full);
-    uint32_t grid = p.tokens, threads = 64u * g.waves, lds = direct_lds_bytes(p.runs);
-    const uint32_t G = 1u << direct_group_log2(p, g);
-    if (G > 1) {
-        kernel = group_kernel(p.dtype, g.waves, full);
-        grid = (p.tokens + G - 1u) / G;
-        threads = 64u * g.waves * G;
-        lds = (G * p.runs * 24u + kGroupExchange + (g.waves > 1 ? kGroupRing : 0u)) * 4u;
-    }
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), lds, reinterpret_cast<hipStream_t>(stream), p,
+    const DirectLaunch l = direct_launch(p, g);
+    const DirectKernel kernel = l.tokens > 1 ? group_kernel(p.dtype, g.waves, full) : direct_kernel(p.dtype, g.waves, full);
+    hipLaunchKernelGGL(kernel, dim3(l.workgroups), dim3(l.threads), l.lds_bytes, reinterpret_cast<hipStream_t>(stream), p,
                        static_cast<const uint16_t *>(d_in), static_cast<uint8_t *>(d_blob), static_cast<uint8_t *>(d_ws));
     return (int)hipGetLastError();
 }

@@ -142,7 +142,10 @@ int prepare_direct_kernels();
 int prepare_rans_kernels();
 int launch_ws_reset(const Params &p, void *d_ws, void *stream);
 int launch_unpack(const Params &p, const Geometry &g, uint32_t group_log2, const void *d_blob, void *d_out, void *stream);
-uint32_t direct_group_log2(const Params &p, const Geometry &g);    // of the tokens per workgroup, where launch_direct is taken
+// How launch_direct launches a plan's calls, where it is taken: tokens per workgroup (and their logarithm), workgroups, ...
+struct DirectLaunch { uint32_t tokens, workgroups, threads, lds_bytes; };
+DirectLaunch direct_launch(const Params &p, const Geometry &g);
+uint32_t direct_group_log2(const Params &p, const Geometry &g);
 int launch_code_hist(const Params &p, const Geometry &g, const void *d_blob, void *d_hist, void *stream);
 int launch_code_pool(const Params &p, const Geometry &g, const EntropyLayout &e, const void *d_blob, void *d_counts,
                      void *stream);

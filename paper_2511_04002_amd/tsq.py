@@ -28,6 +28,7 @@ EXPORTS = ("tsq_plan_create", "tsq_plan_destroy", "tsq_plan_layout", "tsq_plan_b
            "tsq_code_histogram", "tsq_blob_info", "tsq_prefix_bytes", "tsq_status_string",
            # tsq_measure.h
            "tsq_compress_timed", "tsq_measure_copy", "tsq_measure_read", "tsq_plan_kernel", "tsq_plan_limit_waits",
+           "tsq_plan_direct_launch",
            # tsq_ranges.h
            "tsq_check_payload_span", "tsq_check_csr_slice", "tsq_check_csr_slice_holds", "tsq_check_column",
            "tsq_check_stream_span", "tsq_check_stream_move", "tsq_check_frequency_slot", "tsq_check_workspace_shape",
@@ -143,6 +144,8 @@ def lib():
         L.tsq_measure_read.argtypes = [vp, C.c_size_t, vp, vp]
         L.tsq_plan_kernel.restype = C.c_char_p
         L.tsq_plan_kernel.argtypes = [vp]
+        L.tsq_plan_direct_launch.restype = u
+        L.tsq_plan_direct_launch.argtypes = [vp, C.POINTER(C.c_uint32)]
         L.tsq_plan_limit_waits.restype = u
         L.tsq_plan_limit_waits.argtypes = [vp, C.c_uint32]
         u32, u64 = C.c_uint32, C.c_uint64
@@ -275,6 +278,15 @@ def tsq_measure_read(d_src: int, nbytes: int, d_sink: int, stream: int = 0) -> N
 
 def tsq_plan_kernel(plan: int) -> str:
     return lib().tsq_plan_kernel(plan).decode()
+
+
+def tsq_plan_direct_launch(plan: int):
+    """-> (tokens per workgroup, workgroups, threads per workgroup, bytes of LDS) of a plan that runs k_direct."""
+    out = (C.c_uint32 * 4)()
+    st = lib().tsq_plan_direct_launch(plan, out)
+    if st != TSQ_OK:
+        raise TsqError(st, "tsq_plan_direct_launch")
+    return tuple(out)
 
 
 def tsq_plan_limit_waits(plan: int, rounds: int) -> None:

@@ -196,6 +196,40 @@ def test_the_shape_says_which_kernel_compresses(L, T, H, kernel):
     assert L.tsq_plan_kernel(None) is None
 
 
+M26 = 1 << 26
+
+
+# one token a workgroup below 1024 tokens and for rows of more than two waves, else eight (rows of one wave) or two; where
+# the groups' threads would be 2^32 (a last group counts as a whole one): a token a workgroup again
+@pytest.mark.parametrize("T,H,tokens,workgroups", [
+    (1, 8, 1, 1), (1023, 2048, 1, 1023), (1024, 2048, 8, 128), (1025, 8, 8, 129), (1 << 20, 2048, 8, 1 << 17),
+    (1023, 4096, 1, 1023), (1024, 2056, 2, 512), (4095, 4096, 2, 2048), (1024, 4104, 1, 1024), (512, 32768, 1, 512),
+    (M26 - 9, 8, 8, M26 // 8 - 1), (M26 - 8, 56, 8, M26 // 8 - 1), (M26 - 7, 8, 1, M26 - 7), (M26 - 1, 56, 1, M26 - 1)])
+def test_a_launch_holds_every_token_and_counts_its_threads_in_32_bits(L, T, H, tokens, workgroups):
+    plan = tsq.tsq_plan_create(cfg(tokens=T, hidden=H))
+    try:
+        assert tsq.tsq_plan_kernel(plan) == "k_direct"
+        per, n, threads, lds = tsq.tsq_plan_direct_launch(plan)
+        assert (per, n) == (tokens, workgroups)
+        assert (n - 1) * per < T <= n * per
+        assert threads <= 1024 and threads % 64 == 0 and n * threads < 1 << 32
+        assert lds >= per * 3 * H
+    finally:
+        tsq.tsq_plan_destroy(plan)
+
+
+def test_other_plans_have_no_such_launch(L):
+    for kw in (dict(tokens=M26, hidden=8), dict(pipeline=tsq.TSQ_PIPE_STAGED)):
+        plan = tsq.tsq_plan_create(cfg(**kw))
+        try:
+            with pytest.raises(tsq.TsqError) as e:
+                tsq.tsq_plan_direct_launch(plan)
+            assert e.value.status == tsq.TSQ_ERR_UNSUPPORTED
+            assert L.tsq_plan_direct_launch(plan, None) == tsq.TSQ_ERR_INVALID_ARG
+        finally:
+            tsq.tsq_plan_destroy(plan)
+
+
 def test_status_strings(L):
     seen = {tsq.tsq_status_string(s) for s in range(7)}
     assert len(seen) == 7 and "ok" in seen

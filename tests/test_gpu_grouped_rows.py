@@ -69,3 +69,39 @@ def test_rows_of_two_waves_two_tokens_a_workgroup(tsq, oracle, T, H, dtype, mode
     assert kernel_of(tsq, T, H, dtype) == "k_direct"
     x = rows(T, H, dtype, heavy=heavy) if heavy else rows(T, H, dtype)
     check_parity(tsq, oracle, x, dtype, 6.0, (2, 3, 4, 5, 6, 8), 0.2, mode, "fused", label="T=%d H=%d" % (T, H), rule=rule)
+
+
+@pytest.mark.parametrize("T,per_workgroup", [(2 ** 26 - 8, 8), (2 ** 26 - 1, 1)])
+def test_the_most_tokens_that_groups_and_single_tokens_take(tsq, oracle, T, per_workgroup):
+    """A launch's threads are counted in 32 bits: the last token count whose groups fit that, and the last that a workgroup
+    per token does.  The tokens are copies of a block of 4096 and the front of one; compared on the card."""
+    import torch
+    H, B = 8, 4096
+    x = rows(B, H, "f16")
+    copies, rest = divmod(T, B)
+    ref = oracle.compress(x, oracle.F16, 6.0, (2, 4, 8), 0.05, 1, nthreads=8)
+    end = oracle.compress(x[:rest], oracle.F16, 6.0, (2, 4, 8), 0.05, 1, nthreads=8)
+    assert end.nnz > 0 and len(set(end.bits.tolist())) > 1
+    nnz = copies * ref.nnz + end.nnz
+    plan = tsq.Plan(T, H, "f16", 6.0, (2, 4, 8), 0.05, pipeline="fused", max_outliers=nnz)
+    assert tsq.tsq_plan_direct_launch(plan.handle)[0] == per_workgroup
+    xd = torch.from_numpy(x.view(np.int16)).cuda().repeat(copies + 1, 1)[:T]
+    blob, ws = plan.new_blob(), plan.new_workspace()
+    torch.cuda.synchronize()
+    print("compress", T, "tokens", flush=True)
+    plan.compress(xd, blob, ws)
+    info = plan.info(blob)
+    assert info.status == 0 and info.nnz == nnz and info.payload_bytes == copies * ref.payload_bytes + end.payload_bytes
+    L = plan.layout
+
+    for at, name in ((L.off_bits, "bits"), (L.off_scale, "scale"), (L.off_payload, "payload"), (L.off_out_col, "out_col"),
+                     (L.off_out_val, "out_val")):
+        w, e = (torch.from_numpy(getattr(r, name).view(np.uint8).copy()).cuda() for r in (ref, end))
+        at, n = int(at), w.numel()
+        assert bool((blob[at:at + copies * n].view(copies, n) == w).all()), name
+        assert torch.equal(blob[at + copies * n:at + copies * n + e.numel()], e), name
+    for at, name, total in ((L.off_pay_off, "pay_off", ref.payload_bytes), (L.off_row_ptr, "row_ptr", ref.nnz)):
+        got = blob[int(at):int(at) + 8 * (T + 1)].view(torch.int64)
+        w, e = (torch.from_numpy(getattr(r, name).astype(np.int64)).cuda() for r in (ref, end))
+        assert bool((got[:copies * B].view(copies, B) == w[:B] + total * torch.arange(copies, device="cuda").view(-1, 1)).all()), name
+        assert torch.equal(got[copies * B:], e + copies * total), name
