@@ -619,12 +619,19 @@ int prepare_direct_kernels() {
 
 // Rows of one wave: eight tokens a workgroup from this number of tokens on.  Fewer do not fill the device with workgroups of
 // eight: 500 x 768 f16 6.0 us with a token per workgroup against 6.5, 1000 x 2048 bf16 7.9 / 7.7, 2000 x 768 9.3 / 6.8.
-// Rows of two waves, two tokens: 700 x 4096 f16 8.7 / 8.6, 1024 x 4096 8.5 / 8.0, 1100 x 4096 bf16 9.8 / 8.9.
+// Rows of two waves, two tokens: 700 x 4096 f16 8.7 / 8.6, 1024 x 4096 8.5 / 8.0, 1100 x 4096 bf16 9.8 / 8.9, and with six
+// widths and the LSB criterion 1237 x 4096 bf16 10.2 / 10.0, 3000 x 4096 14.8 / 14.3.
+// Rows that do not fill their two waves gain nothing while pairs give a compute unit more tokens than it had (256 compute
+// units: 6 against 5 up to 1280 tokens): 1024 x 2304 bf16, LSB, six widths 9.1 / 9.7, 1237 x 2856 10.3 / 10.6; a fifth of the
+// elements outliers 1280 x 2856 f16 11.2 / 12.1.  Beyond: 1350 x 2856 bf16, LSB 10.2 / 9.4, 1500 x 3400 f16 10.4 / 9.6,
+// 3000 x 2856 15.2 / 13.7; slower only now and then: bf16, LSB, six widths 3000 x 3400 14.7 / 15.4 (2000 x 3400 12.9 / 12.8),
+// and a fifth of the elements outliers 2000 x 2856 f16 14.0 / 15.1 (3000 x 2856 20.9 / 19.0).
 // A launch counts its threads in 32 bits, those of a last group's missing tokens included: the seven token counts of rows of
 // one wave (2^26 - 7 .. 2^26 - 1) whose groups would be 2^32 threads take a workgroup per token, which is 64 a token.
-constexpr uint32_t kGroupFrom = 1024;
+constexpr uint32_t kGroupFrom = 1024, kRaggedPairsFrom = 5u * 256u + 1u;
 uint32_t direct_group_log2(const Params &p, const Geometry &g) {
-    if (g.waves > 2 || p.tokens < kGroupFrom) return 0u;
+    const bool ragged_pairs = g.waves == 2 && p.hidden != 4096u;
+    if (g.waves > 2 || p.tokens < (ragged_pairs ? kRaggedPairsFrom : kGroupFrom)) return 0u;
     const uint32_t log2 = g.waves == 1 ? 3u : 1u;
     const uint64_t groups = ((uint64_t)p.tokens + (1u << log2) - 1u) >> log2;
     return (groups * 64u * g.waves) << log2 < (1ull << 32) ? log2 : 0u;

@@ -199,11 +199,12 @@ def test_the_shape_says_which_kernel_compresses(L, T, H, kernel):
 M26 = 1 << 26
 
 
-# one token a workgroup below 1024 tokens and for rows of more than two waves, else eight (rows of one wave) or two; where
-# the groups' threads would be 2^32 (a last group counts as a whole one): a token a workgroup again
+# one token a workgroup below 1024 tokens (1281 where rows do not fill their two waves) and for rows of more than two waves,
+# else eight (rows of one wave) or two; where the groups' threads would be 2^32 (a last group counts as a whole one): a token a workgroup again
 @pytest.mark.parametrize("T,H,tokens,workgroups", [
     (1, 8, 1, 1), (1023, 2048, 1, 1023), (1024, 2048, 8, 128), (1025, 8, 8, 129), (1 << 20, 2048, 8, 1 << 17),
-    (1023, 4096, 1, 1023), (1024, 2056, 2, 512), (4095, 4096, 2, 2048), (1024, 4104, 1, 1024), (512, 32768, 1, 512),
+    (1023, 4096, 1, 1023), (1024, 4096, 2, 512), (1280, 2056, 1, 1280),
+    (1281, 4088, 2, 641), (4095, 4096, 2, 2048), (1024, 4104, 1, 1024), (512, 32768, 1, 512),
     (M26 - 9, 8, 8, M26 // 8 - 1), (M26 - 8, 56, 8, M26 // 8 - 1), (M26 - 7, 8, 1, M26 - 7), (M26 - 1, 56, 1, M26 - 1)])
 def test_a_launch_holds_every_token_and_counts_its_threads_in_32_bits(L, T, H, tokens, workgroups):
     plan = tsq.tsq_plan_create(cfg(tokens=T, hidden=H))
