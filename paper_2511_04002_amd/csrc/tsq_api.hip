@@ -185,7 +185,7 @@ tsq_status tsq_plan_create(const tsq_config *cfg, tsq_plan **out) {
     pl->g.lds_bytes = (p.runs * kRunLdsDw + kScratchDw) * 4u;
     pl->g.waves = compress_waves(p.runs);
     // row 16 + two images 8 dwords per run, reduce areas and ticket slots, two stashes per wave
-    pl->g.lds_fused_bytes = (p.runs * 32u + kFusedScratchDw + 2u * pl->g.waves * kStashWave) * 4u;
+    pl->g.lds_fused_bytes = fused_lds_dwords(p.runs, pl->g.waves) * 4u;
     pl->pipeline = cfg->pipeline == TSQ_PIPE_STAGED ? TSQ_PIPE_STAGED : TSQ_PIPE_FUSED;
     *out = pl;
     return TSQ_OK;

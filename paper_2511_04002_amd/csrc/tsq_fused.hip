@@ -87,9 +87,10 @@ __device__ __forceinline__ u32x4 load_quad_coherent(__amdgpu_buffer_rsrc_t windo
 // What bounds it is the latency of a round (two memory round trips), which every prefix waits for.  One word per lane and
 // 64 tokens a group, a scan each, made a round of two waves 3 us, and a prefix was written 6.7 us after the last size
 // before it: 65536 x 4096 f16 196 us, now 173; 16384 x 4096 bf16 62 / 54.
-// lds: kScanLds + R * 512 dwords of LDS (workgroup 0 uses none otherwise).  waves_total: computing
+// lds: scan_lds_dwords(R) of LDS (workgroup 0 uses none otherwise).  waves_total: computing
 // waves of the grid, each of which reports once when it is done.
 constexpr uint32_t kScanLds = 112;
+constexpr uint32_t scan_lds_dwords(uint32_t scan_waves) { return kScanLds + scan_waves * 512u; }
 template <int R>
 __device__ void scan_tokens(const Params &p, uint8_t *blob, uint8_t *ws, uint32_t waves_total, uint32_t *lds,
                             uint32_t wv) {
@@ -242,6 +243,9 @@ __device__ void scan_tokens(const Params &p, uint8_t *blob, uint8_t *ws, uint32_
         write_header(p, blob, bc, (uint64_t)bw << 2, (uint64_t)bc > p.outlier_capacity ? 3u : 0u);
     }
 }
+
+// Runs of the shortest row that takes workgroups of nw waves (see compress_waves).
+constexpr uint32_t fewest_runs(uint32_t nw) { return 64u * (nw <= 4u ? nw - 1u : nw / 2u) + 1u; }
 
 // ---------------------------------------------------------------- computing workgroups
 
@@ -433,6 +437,9 @@ k_fused(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ b
     extern __shared__ __align__(16) uint32_t lds[];
     if (blockIdx.x == 0) {
         constexpr int kScanWaves = NW < (int)kScanWavesMax ? NW : (int)kScanWavesMax;
+        // (the launch's LDS is that of the computing workgroups, least for the shortest row of this many waves; rows of one
+        // run leave eight dwords)
+        static_assert(scan_lds_dwords(kScanWaves) <= fused_lds_dwords(fewest_runs(NW), NW), "the scanner's LDS");
         if (threadIdx.x < 64u * kScanWaves)
             scan_tokens<kScanWaves>(p, blob, ws, (gridDim.x - 1u) * NW, lds, threadIdx.x >> 6);
         return;
@@ -690,7 +697,7 @@ uint32_t compress_waves(uint32_t runs) {
 }
 
 int prepare_fused_kernels() {
-    const int big = (int)(((kMaxHidden / kRun) * 32u + kFusedScratchDw + 2u * kMaxWaves * kStashWave) * 4);
+    const int big = (int)(fused_lds_dwords(kMaxHidden / kRun, kMaxWaves) * 4u);
     static const uint32_t sizes[] = {1, 2, 3, 4, 8, 16};
     for (uint32_t dt = 0; dt < 2; ++dt)
         for (uint32_t nw : sizes)
