@@ -3,7 +3,7 @@
  * read from a blob, an entropy-coded blob or a workspace before using them as addresses, evaluated
  * on the HOST.  Each call runs the very predicate the kernels compile (one source, built for both
  * sides), so that a test without a GPU can drive it with wrapping offsets and noise.  Plain values
- * in, 1 (admissible) or 0 out; no device, no errors.  tsq_check_quotients does the same for the one step of
+ * in, 1 (admissible) or 0 out; no device, no errors.  tsq_check_divisions does the same for the one step of
  * the entropy coder's arithmetic that rests on a rounding argument.
  */
 #ifndef TSQ_RANGES_H
@@ -34,9 +34,6 @@ uint32_t tsq_check_frequency_slot(uint32_t state);
 /* The entropy encoder's division, for n pairs (HOST arrays): q[i] = floor(x[i] / f[i]) whenever 1 <= f[i] <= 4096 and
  * x[i] >= f[i], whatever low[i] < 65536 stands in the lowest bits of the reciprocal (the encoder keeps a sum there). */
 void tsq_check_divisions(const uint32_t *x, const uint32_t *f, const uint32_t *low, uint32_t *q, uint64_t n);
-/* The same by a binary32 reciprocal (not the encoder's any more): q[i] = an estimate of floor(x[i] / f[i]), which is that
- * quotient or one less whenever 1 <= f[i] <= 4096 and x[i] < f[i] << 20 (the size of the remainder tells). */
-void tsq_check_quotients(const uint32_t *x, const uint32_t *f, uint32_t *q, uint64_t n);
 /* The shape recorded in a workspace against the plan's. */
 int tsq_check_workspace_shape(uint32_t ws_tokens, uint32_t ws_hidden, uint32_t tokens, uint32_t hidden);
 

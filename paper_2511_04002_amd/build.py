@@ -13,7 +13,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtsq.so")
 SOURCES = ["tsq_api.hip", "tsq_kernels.hip", "tsq_fused.hip", "tsq_direct.hip", "tsq_entropy.hip", "tsq_rans.hip", "tsq_link.cpp"]
-HEADERS = ["tsq_internal.hpp", "tsq_device.hpp", "tsq_pass.hpp", os.path.join(ROOT, "include", "tsq.h")]
+HEADERS = ["tsq_internal.hpp", "tsq_device.hpp", "tsq_pass.hpp", "tsq_ranges.hpp"] + \
+    [os.path.join(ROOT, "include", h) for h in ("tsq.h", "tsq_measure.h", "tsq_ranges.h")]
 
 # -ffp-contract=off: the quantizer's multiply and every fp64 product of the budget test must
 #   stay single IEEE operations; -packed-fp32-ops off: scalar fp32 code is not merged into

@@ -69,15 +69,6 @@ TSQ_HD uint32_t quotient(uint32_t x, double above) {
     return (uint32_t)__builtin_bit_cast(uint64_t, __builtin_fma((double)x, above, 4503599627370495.5));
 }
 
-// The same in binary32, for callers that correct it: floor(x / f) or one less, for x < f << 20 (so the quotient is below 2^20)
-// and 1 <= f <= 4096, from `below` = the binary32 quotient 1 / f times (1 - 2^-21), rounded.  With e = 2^-24
-// the unit roundoff: below lies in [(1 - 2^-21)(1 - e)^2 / f, (1 - 2^-21)(1 + e)^2 / f], and the product of
-// (float)x and below carries two more roundings, so it lies in [x/f * (1 - 2^-21)(1 - e)^4,
-// x/f * (1 - 2^-21)(1 + e)^4]: never above x/f (4e < 2^-21), and less than x/f * 12e < 0.75 below it.  Its
-// integer part is therefore floor(x/f) or floor(x/f) - 1, which the size of the remainder tells.
-TSQ_HD float reciprocal_just_below(uint32_t f) { return (1.0f / (float)f) * 0.999999523162841796875f; }   // 1 - 2^-21
-TSQ_HD uint32_t quotient_or_one_less(uint32_t x, float below) { return (uint32_t)((float)x * below); }
-
 // A workspace's recorded shape against the plan's.
 TSQ_HD bool workspace_shape_ok(uint32_t ws_tokens, uint32_t ws_hidden, uint32_t tokens, uint32_t hidden) {
     return ws_tokens == tokens && ws_hidden == hidden;
