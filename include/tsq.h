@@ -74,9 +74,12 @@ typedef enum {
                                  two kernels runs.  With w = the waves that hold a row
                                  (ceil(hidden / 2048), up to the next of 1, 2, 3, 4, 8, 16), calls
                                  of tokens * w <= 8192, and of w = 1 and fewer than 2^26 tokens:
-                                 a workgroup per token, which waits for the sizes of the tokens
-                                 before it; it relies on every die of the device starting its
-                                 workgroups in the order of their index.  Larger calls: as many
+                                 a workgroup per token, or from 1024 tokens on (1281 if w = 2 and
+                                 hidden < 4096) per eight tokens (w = 1) or two (w = 2), which
+                                 waits for the sizes of the tokens before its own; it relies on
+                                 every die of the device starting its workgroups in the order of
+                                 their index, and having room for one (up to 1024 lanes and
+                                 97 KB of LDS; 512 and 49 KB for eight tokens).  Larger calls: as many
                                  workgroups as the device holds draw tokens from ticket counters
                                  in the workspace (none waits for a token that no running
                                  workgroup has); one more turns the published sizes into the

@@ -261,19 +261,19 @@ static bool is_capturing(hipStream_t s) {
     return st != hipStreamCaptureStatusNone;
 }
 
-// grid: computing workgroups of the persistent kernel; 0: one workgroup per token
+// grid: computing workgroups of the persistent kernel; 0: a workgroup per token or per few tokens (tsq_direct.hip)
 static int launch_single_pass(const Params &p, const Geometry &g, uint32_t grid, const void *d_in, void *d_blob, void *d_ws,
                               void *stream) {
     return grid ? launch_fused(p, g, grid, d_in, d_blob, d_ws, stream) : launch_direct(p, g, d_in, d_blob, d_ws, stream);
 }
 // Which of the two a plan's calls take.  A function of the shape alone: a workspace serves every plan of its shape,
 // and the persistent kernel must find no prefix words in it that another call left out.
-// One workgroup per token is the faster form while the call fits the device about once (32 waves on each of 256
-// compute units): 2048 x 4096 f16 12.6 us against 17.4, 4096 x 4096 21.8 / 22.8, 2048 x 8192 bf16 17.9 / 20.6, 700 x 12000
-// 14.3 / 19.8, but 2200 x 8192 f16 19.7 / 19.1 and 5000 x 4096 f16 26.0 / 25.2.  Rows of one wave gain at any number of
-// tokens, eight of them a workgroup (k_direct_group): 131072 x 768 f16 156 us against 357, 131072 x 2048 bf16 226 / 389.
+// A workgroup per token, or per few tokens (k_direct_group), is the faster form while the call fits the device about once (32
+// waves on each of 256 compute units): 2048 x 4096 f16 10.8 us against 15.2, 4096 x 4096 17.0 / 19.9, 2048 x 8192 bf16 17.4 /
+// 19.1, 700 x 12000 12.7 / 18.3, but 2200 x 8192 f16 19.2 / 18.5.  Rows of one wave gain at any number of tokens, eight of
+// them a workgroup: 131072 x 768 f16 168 us against 355, 131072 x 2048 bf16 225 / 389.
 // Rows of two waves, two of them a workgroup, would gain a little beyond the line and then lose: 5000 x 4096 f16 20.3 against
-// 22.1, 8192 x 4096 32.1 / 30.4, 131072 x 4096 475 / 337; they keep the line of the others.
+// 22.1, 8192 x 4096 32.3 / 30.3, 131072 x 4096 476 / 337; they keep the line of the others.
 // Up to 2^26 - 1 tokens, that is (64 threads a token; eight a workgroup up to 2^26 - 8): a launch counts its threads in
 // 32 bits, and the persistent kernel's grid does not grow with the tokens.
 static bool use_direct(const tsq_plan *plan) {

@@ -14,7 +14,8 @@
 // Progress: whoever waits, waits for tokens of lower index only, and every die starts the workgroups it gets in the
 // order of their index.  So when all tokens before one are finished, that one has started or is the next of its die to
 // start, and the call ends whatever the number of workgroups that fit the device.  This rests on that order, and on
-// other work leaving every die some room: a die that something else fills keeps its tokens from starting, and
+// other work leaving every die room for a workgroup (up to 16 waves and 97 KB of LDS with a token each; groups of eight
+// short rows take 8 waves and up to 49 KB, where one of them by itself takes 1 and 6): a die that something else fills keeps its tokens from starting, and
 // those on the other dies wait for them (the persistent kernel hands such tokens to workgroups that run, but its
 // scanner waits for every workgroup in the end).  Every wait is bounded by p.spin_limit, about a second.
 //
@@ -162,7 +163,7 @@ k_direct(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ 
     }
     // ---- ... into the wave's part of their place in LDS.  Before anybody looks for the tokens before: a look that comes
     //      too early costs a memory round trip (codes put there behind the wait, over the row: 512 x 5120 step 14.5 us
-    //      against 12.6, 128 x 768 f16 6.7 / 5.9, 65536 x 768 201 / 189)
+    //      against 12.6, 128 x 768 f16 6.7 / 5.9)
     if (owns) {
         uint32_t *dst = image + wv * (64u * 8u) + lane * c.width;
         const uint32_t nd = (FULL || left >= 4) ? c.width : ((left * c.width + 3u) >> 2);
@@ -179,8 +180,8 @@ k_direct(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ 
     uint32_t ew = 0, ec = 0, bad = 0, spins = 0;
 
     // ---- what lies before the token, 256 words at a time, the lowest first: by the time the next ones are asked for
-    //      they have been published, too.  (512 words at a time: 2048 x 4096 f16 13.3 us against 12.1, 700 x 8192 11.3 / 9.7;
-    //      128: 14.6 / 12.1; all 2048 at once 18.7)
+    //      they have been published, too.  (512 words at a time: 700 x 8192 11.3 us against 9.7;
+    //      2048 x 4096 f16, as it was with a token per workgroup, 13.3 / 12.1; 128: 14.6 / 12.1; all 2048 at once 18.7)
     constexpr uint32_t kReaders = NW < 4 ? NW : 4, kAhead = 4 / kReaders;
     const uint32_t t0 = t & ~(kDirectBlock - 1u);
     const uint32_t none = tag << 30;                              // a word that counts nothing

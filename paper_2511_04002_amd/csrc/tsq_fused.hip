@@ -14,7 +14,7 @@
 // counter's top byte carries the call's epoch (mod 3), so the first ticket also tells the
 // workgroup which tag the tables of this call use.
 //
-// Per token a workgroup publishes one 32-bit word (tag, payload words, outliers) in a table.
+// Per token a workgroup publishes one 32-bit word (tag, width, outliers) in a table.
 // The scanner reads the table in order, 1024 words per round, and for the leading run of
 // published tokens writes (tag, words before, outliers before) into a second table.  Nobody else adds anything up.
 //
@@ -53,7 +53,7 @@ namespace tsq {
 
 constexpr uint32_t kNoToken = 0xFFFFFFFFu;
 
-// ---------------------------------------------------------------- the scanner (workgroup 0, one wave)
+// ---------------------------------------------------------------- the scanner (workgroup 0, up to four waves)
 
 constexpr uint32_t kScanWavesMax = 4;   // waves of workgroup 0 that scan
 // A round looks at four groups of 256 table words, four consecutive words per lane.

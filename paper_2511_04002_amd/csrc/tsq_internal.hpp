@@ -27,7 +27,7 @@ constexpr uint32_t kFusedGridCap = 4096;
 constexpr uint32_t kTicketClasses = 64, kTicketStride = 64;
 constexpr uint32_t kFusedScratchDw = 4 * 2 * kMaxWaves + 8;
 constexpr uint32_t fused_lds_dwords(uint32_t runs, uint32_t waves) { return runs * 32u + kFusedScratchDw + 2u * waves * kStashWave; }
-// one workgroup per token (tsq_direct.hip): tokens per block of the placement
+// tsq_direct.hip: tokens, or groups of tokens, per block of the placement
 constexpr uint32_t kDirectBlock = 2048;
 // words of a workspace's control block
 constexpr uint32_t kCtlError = 1, kCtlTokens = 2, kCtlHidden = 3;
