@@ -65,12 +65,6 @@ __device__ __forceinline__ void count_token_any(const Params &p, uint32_t b, con
     }
 }
 
-__device__ __forceinline__ bool blob_is_this_plans(const Params &p, const uint8_t *blob) {
-    const BlobHeader *h = reinterpret_cast<const BlobHeader *>(blob);
-    return h->magic == kMagic && h->version == kVersion && h->status == 0 && h->tokens == p.tokens &&
-           h->hidden == p.hidden && h->dtype == p.dtype && h->off_payload == p.off_payload;
-}
-
 // Per token: hist[t][c] = how often code c occurs in token t.  One workgroup per token, one lane per run of
 // 32 codes, as in k_unpack; kCopies copies of the 256 bins, 257 words apart (equal codes of different
 // copies fall into different banks), added up at the end, one bin per thread.  (A wave per token with
@@ -122,10 +116,7 @@ k_code_hist(const Params p, const uint8_t *__restrict__ blob, uint32_t *__restri
     const uint32_t t = blockIdx.x, run = threadIdx.x;
 
     // the blob must be this plan's and must have been completed without error
-    const BlobHeader *h = reinterpret_cast<const BlobHeader *>(blob);
-    if (h->magic != kMagic || h->version != kVersion || h->status != 0 || h->tokens != p.tokens ||
-        h->hidden != p.hidden || h->dtype != p.dtype || h->off_payload != p.off_payload)
-        return;
+    if (!blob_is_plans<false>(p, blob)) return;
     const uint32_t width = blob[p.off_bits + t];
     const uint64_t po = reinterpret_cast<const uint64_t *>(blob + p.off_pay_off)[t];
     // a damaged token is skipped rather than read out of bounds
@@ -163,7 +154,7 @@ constexpr uint32_t kPoolThreads = 1024, kPoolWaves = kPoolThreads / 64;
 __global__ void __launch_bounds__(kPoolThreads, 8)     // 8 waves per SIMD (two workgroups per compute unit): at most 64 vector registers
 k_code_pool(const Params p, const uint8_t *__restrict__ blob, uint32_t *__restrict__ counts, uint32_t per) {
     __shared__ uint32_t bins[kPoolWords];
-    if (!blob_is_this_plans(p, blob)) return;
+    if (!blob_is_plans<false>(p, blob)) return;
     const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6;
     const uint32_t t0 = blockIdx.x * per, t1 = t0 + per < p.tokens ? t0 + per : p.tokens;
     const uint32_t rounds = (p.runs + 63u) / 64u;

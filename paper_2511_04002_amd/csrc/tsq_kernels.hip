@@ -249,11 +249,7 @@ k_unpack(const Params p, const uint8_t *__restrict__ blob, uint16_t *__restrict_
     const uint32_t run = threadIdx.x;
 
     // the blob must be this plan's and must have been completed without error
-    const BlobHeader *h = reinterpret_cast<const BlobHeader *>(blob);
-    if (h->magic != kMagic || h->version != kVersion || h->status != 0 || h->tokens != p.tokens ||
-        h->hidden != p.hidden || h->dtype != p.dtype || h->off_payload != p.off_payload ||
-        h->off_out_col != p.off_out_col || h->off_out_val != p.off_out_val)
-        return;
+    if (!blob_is_plans<true>(p, blob)) return;
 
     const uint32_t width = blob[p.off_bits + t];
     const float s = reinterpret_cast<const float *>(blob + p.off_scale)[t];

@@ -29,15 +29,12 @@ namespace tsq {
 constexpr uint32_t kProbBits = 12, kProbScale = 1u << kProbBits, kRansLow = 1u << 16;
 static_assert(kProbScale == 4096, "frequency_slot() masks 12 bits");
 
-__device__ __forceinline__ bool blob_is_valid(const Params &p, const uint8_t *blob) {
-    const BlobHeader *h = reinterpret_cast<const BlobHeader *>(blob);
-    return h->magic == kMagic && h->version == kVersion && h->status == 0 && h->tokens == p.tokens &&
-           h->hidden == p.hidden && h->dtype == p.dtype && h->off_payload == p.off_payload;
-}
 __device__ __forceinline__ bool eblob_is_valid(const Params &p, const EntropyLayout &e, const uint8_t *eblob) {
+    // (as blob_is_plans: one wait)
     const EntropyHeader *h = reinterpret_cast<const EntropyHeader *>(eblob);
-    return h->magic == kEntropyMagic && h->version == kVersion && h->tokens == p.tokens && h->hidden == p.hidden &&
-           h->off_streams == e.off_streams && h->stream_bytes <= e.stream_capacity;
+    const uint64_t off = h->off_streams ^ e.off_streams;
+    const uint32_t unlike = (h->magic ^ kEntropyMagic) | (h->version ^ kVersion) | (h->tokens ^ p.tokens) | (h->hidden ^ p.hidden);
+    return ((unlike | (uint32_t)off | (uint32_t)(off >> 32)) == 0) & (h->stream_bytes <= e.stream_capacity);
 }
 
 // ---------------------------------------------------------------- pooled counts and tables
@@ -66,7 +63,7 @@ __global__ void __launch_bounds__(256)
 k_rans_tables(const Params p, const EntropyLayout e, const uint8_t *__restrict__ blob, uint8_t *__restrict__ eblob,
               const uint8_t *__restrict__ ews) {
     __shared__ uint32_t part[3][4];
-    if (!blob_is_valid(p, blob)) return;
+    if (!blob_is_plans<false>(p, blob)) return;
     const uint32_t k = blockIdx.x, c = threadIdx.x;
     // this class's counts: the sets that the counting workgroups added to, added up
     const uint32_t *counts = reinterpret_cast<const uint32_t *>(ews + e.ws_pooled) + k * 256u;
@@ -264,7 +261,7 @@ k_rans_encode(const Params p, const EntropyLayout e, const uint8_t *__restrict__
     __shared__ EncodeTable ftab;
     const uint32_t t = blockIdx.x, lane = threadIdx.x;
     uint32_t *len = reinterpret_cast<uint32_t *>(ews + e.ws_len);
-    if (!blob_is_valid(p, blob)) return;
+    if (!blob_is_plans<false>(p, blob)) return;
     const uint32_t width = blob[p.off_bits + t];
     const uint64_t po = reinterpret_cast<const uint64_t *>(blob + p.off_pay_off)[t];
     if (!token_in_range(p, width, po)) {
@@ -353,7 +350,7 @@ __global__ void __launch_bounds__(64)
 k_rans_gather(const Params p, const EntropyLayout e, const uint8_t *__restrict__ blob, uint8_t *__restrict__ eblob,
               const uint8_t *__restrict__ ews) {
     static_assert(kLenBlock == 256, "four lengths per lane inside a block");
-    if (!blob_is_valid(p, blob)) return;
+    if (!blob_is_plans<false>(p, blob)) return;
     const uint32_t t = blockIdx.x, lane = threadIdx.x;
     const uint32_t *len = reinterpret_cast<const uint32_t *>(ews + e.ws_len);
     const uint32_t *block = reinterpret_cast<const uint32_t *>(ews + e.ws_block);
@@ -620,7 +617,8 @@ k_rans_decode(const Params p, const EntropyLayout e, const uint8_t *__restrict__
     const uint32_t t0 = blockIdx.x * per, t1 = p.tokens - t0 < per ? p.tokens : t0 + per;
     const uint32_t coders = p.runs < 64u ? p.runs : 64u;  // states in the stream; the other coders start (and stay) at 2^16
     const uint32_t rounds = (p.runs + 63u) / 64u;
-    if (!blob_is_valid(p, blob) || !eblob_is_valid(p, e, eblob)) return;
+    const bool blob_ours = blob_is_plans<false>(p, blob), eblob_ours = eblob_is_valid(p, e, eblob);     // (both in one wait)
+    if (!blob_ours || !eblob_ours) return;
     uint32_t t = t0 + wv;
     CodedToken next = {};
     if (t < t1) ask_for_token(p, e, blob, eblob, t, next);
