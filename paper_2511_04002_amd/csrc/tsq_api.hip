@@ -175,7 +175,9 @@ tsq_status tsq_plan_create(const tsq_config *cfg, tsq_plan **out) {
     E.pool_tokens = (T + kMaxPoolGroups - 1u) / kMaxPoolGroups;
     if (E.pool_tokens < 16u) E.pool_tokens = 16u;    // a token per wave of a counting workgroup
     E.pool_groups = (T + E.pool_tokens - 1u) / E.pool_tokens;
-    E.ws_pooled = ew;  ew = align_up(ew + (uint64_t)kPoolCopies * 7ull * 256 * 4, 256);
+    E.ws_pooled = ew;  ew = align_up(ew + (uint64_t)E.pool_groups * kPoolSetWords * 4, 256);
+    E.ws_parts = ew;   ew = align_up(ew + (uint64_t)kMaxTableSlices * 7ull * 256 * 4, 256);
+    E.ws_arrived = ew; ew = align_up(ew + 7ull * kBlockStride * 4, 256);
     E.ws_block = ew;   ew = align_up(ew + 4ull * kBlockStride * ((T + kLenBlock - 1u) / kLenBlock), 256);
     E.ws_len = ew;     ew = align_up(ew + 4ull * T, 256);
     E.ws_slots = ew;   ew = align_up(ew + (uint64_t)T * E.slot_bytes, 256);
@@ -468,7 +470,7 @@ tsq_status tsq_entropy_encode(const tsq_plan *plan, const void *d_blob, void *d_
     if (((uintptr_t)d_blob & 255u) || ((uintptr_t)d_eblob & 255u) || ((uintptr_t)d_ews & 255u)) return TSQ_ERR_INVALID_ARG;
     tsq_status st = ensure_prepared();
     if (st != TSQ_OK) return st;
-    return hip_rc(launch_rans_encode(plan->p, plan->g, plan->e, d_blob, d_eblob, d_ews, stream));
+    return hip_rc(launch_rans_encode(plan->p, plan->e, d_blob, d_eblob, d_ews, stream));
 }
 
 tsq_status tsq_entropy_decode(const tsq_plan *plan, const void *d_eblob, void *d_blob, void *stream) {

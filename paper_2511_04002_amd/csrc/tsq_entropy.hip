@@ -145,16 +145,25 @@ k_code_hist(const Params p, const uint8_t *__restrict__ blob, uint32_t *__restri
 // from).  A workgroup of sixteen waves counts `per` consecutive tokens into bins that stay in LDS until
 // all its tokens are counted: one bin per (width, code) pair and lane % 16, word
 // (2^b - 4 + code) * 16 + lane % 16; that is 508 pairs.  At the end thread k adds up the 16 words of
-// pair k and adds the sum to one of kPoolCopies sets counts[set][7][256] (row b - 2: width b; zeroed
-// by the caller), which k_rans_tables adds up: atomic adds on one address from all over the chip
-// take about 30 ns each, one after the other, so both the number of counting workgroups and the
-// number of them that share a set are kept small.
+// pair k and stores the sum into the workgroup's own set, which k_rans_tables adds up (with sets that workgroups shared
+// and added to by atomics, a kernel of its own had to zero them first: 4.8 us a call).
+// The first kernel of an encode call: it also puts into their initial state what the kernels behind it add to (the slices
+// that have arrived, the stream bytes per block of tokens) and the coded blob's header, which becomes valid when the last
+// kernel of the call has run.
 constexpr uint32_t kPoolPairs = 508, kPoolLanes = 16, kPoolWords = kPoolPairs * kPoolLanes;
 constexpr uint32_t kPoolThreads = 1024, kPoolWaves = kPoolThreads / 64;
 __global__ void __launch_bounds__(kPoolThreads, 8)     // 8 waves per SIMD (two workgroups per compute unit): at most 64 vector registers
-k_code_pool(const Params p, const uint8_t *__restrict__ blob, uint32_t *__restrict__ counts, uint32_t per) {
+k_code_pool(const Params p, const EntropyLayout e, const uint8_t *__restrict__ blob, uint8_t *__restrict__ eblob,
+            uint8_t *__restrict__ ews) {
     __shared__ uint32_t bins[kPoolWords];
+    const uint32_t n_blocks = (p.tokens + kLenBlock - 1u) / kLenBlock;
+    for (uint32_t i = blockIdx.x * kPoolThreads + threadIdx.x; i < n_blocks + 7u; i += gridDim.x * kPoolThreads) {
+        if (i < n_blocks) reinterpret_cast<uint32_t *>(ews + e.ws_block)[(size_t)i * kBlockStride] = 0;
+        else reinterpret_cast<uint32_t *>(ews + e.ws_arrived)[(i - n_blocks) * kBlockStride] = 0;
+    }
+    if (blockIdx.x == 0 && threadIdx.x < sizeof(EntropyHeader) / 4) reinterpret_cast<uint32_t *>(eblob)[threadIdx.x] = 0;
     if (!blob_is_plans<false>(p, blob)) return;
+    const uint32_t per = e.pool_tokens;
     const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6;
     const uint32_t t0 = blockIdx.x * per, t1 = t0 + per < p.tokens ? t0 + per : p.tokens;
     const uint32_t rounds = (p.runs + 63u) / 64u;
@@ -184,9 +193,7 @@ k_code_pool(const Params p, const uint8_t *__restrict__ blob, uint32_t *__restri
         uint32_t n = 0;
 #pragma unroll
         for (uint32_t k = 0; k < kPoolLanes; ++k) n += bins[pair * kPoolLanes + ((k + pair) & (kPoolLanes - 1u))];
-        // pair = 2^b - 4 + code
-        const uint32_t bw = 31u - (uint32_t)__builtin_clz(pair + 4u), code = pair + 4u - (1u << bw);
-        if (n) atomicAdd(counts + (blockIdx.x % kPoolCopies) * 7u * 256u + (bw - 2u) * 256u + code, n);
+        reinterpret_cast<uint32_t *>(ews + e.ws_pooled)[(size_t)blockIdx.x * kPoolSetWords + pair] = n;
     }
 }
 
@@ -196,10 +203,9 @@ int launch_code_hist(const Params &p, const Geometry &g, const void *d_blob, voi
     return (int)hipGetLastError();
 }
 
-int launch_code_pool(const Params &p, const Geometry &g, const EntropyLayout &e, const void *d_blob, void *d_counts,
-                     void *stream) {
-    hipLaunchKernelGGL(k_code_pool, dim3(e.pool_groups), dim3(kPoolThreads), 0, reinterpret_cast<hipStream_t>(stream), p,
-                       static_cast<const uint8_t *>(d_blob), static_cast<uint32_t *>(d_counts), e.pool_tokens);
+int launch_code_pool(const Params &p, const EntropyLayout &e, const void *d_blob, void *d_eblob, void *d_ews, void *stream) {
+    hipLaunchKernelGGL(k_code_pool, dim3(e.pool_groups), dim3(kPoolThreads), 0, reinterpret_cast<hipStream_t>(stream), p, e,
+                       static_cast<const uint8_t *>(d_blob), static_cast<uint8_t *>(d_eblob), static_cast<uint8_t *>(d_ews));
     return (int)hipGetLastError();
 }
 

@@ -54,7 +54,9 @@ static_assert(sizeof(EntropyHeader) == 256, "entropy header must be 256 bytes");
 // Sections of the eblob and of the encoder's workspace (bytes), fixed by the plan.
 struct EntropyLayout {
     uint64_t off_tables, off_stream_off, off_streams, stream_capacity, eblob_bytes;
-    uint64_t ws_pooled;     // u32[kPoolCopies][7][256] code counts per width class (a counting workgroup adds to set id % kPoolCopies)
+    uint64_t ws_pooled;     // u32[pool_groups][kPoolSetWords] code counts per width class, a set per counting workgroup
+    uint64_t ws_parts;      // u32[kMaxTableSlices][7][256] the sets' sums by slices of kTableSlice sets (more than one slice)
+    uint64_t ws_arrived;    // u32[7][kBlockStride], word 0 of each: slices of the class that are summed up
     uint64_t ws_block;      // u32[ceil(T / kLenBlock)][kBlockStride], word 0 of each: padded stream bytes of the block of kLenBlock tokens
     uint64_t ws_len;        // u32[T] stream bytes per token
     uint64_t ws_slots;      // T slots of slot_bytes: the streams before they are moved together
@@ -69,7 +71,9 @@ constexpr uint32_t kBlockStride = 64;   // 32-bit words from one partial sum to 
                                         // adds to one 128-byte line from all over the chip hold up the stores queued behind them
 constexpr uint32_t kMaxPoolGroups = 512;    // counting workgroups of 1024 threads: two fit a compute unit, 256 compute units: one round
 constexpr uint32_t kMaxDecodeGroups = 512;  // decoding workgroups of 1024 threads: the same
-constexpr uint32_t kPoolCopies = 16;    // sets of pooled counts: 16 times fewer atomic adds per address
+constexpr uint32_t kPoolSetWords = 512; // words of a counting workgroup's set: 508 (width, code) pairs
+constexpr uint32_t kTableSlice = 64;    // sets that a workgroup of k_rans_tables adds up
+constexpr uint32_t kMaxTableSlices = kMaxPoolGroups / kTableSlice;
 
 // Kernel argument block (passed by value).
 struct Params {
@@ -148,10 +152,8 @@ struct DirectLaunch { uint32_t tokens, workgroups, threads, lds_bytes; };
 DirectLaunch direct_launch(const Params &p, const Geometry &g);
 uint32_t direct_group_log2(const Params &p, const Geometry &g);
 int launch_code_hist(const Params &p, const Geometry &g, const void *d_blob, void *d_hist, void *stream);
-int launch_code_pool(const Params &p, const Geometry &g, const EntropyLayout &e, const void *d_blob, void *d_counts,
-                     void *stream);
-int launch_rans_encode(const Params &p, const Geometry &g, const EntropyLayout &e, const void *d_blob, void *d_eblob,
-                       void *d_ews, void *stream);
+int launch_code_pool(const Params &p, const EntropyLayout &e, const void *d_blob, void *d_eblob, void *d_ews, void *stream);
+int launch_rans_encode(const Params &p, const EntropyLayout &e, const void *d_blob, void *d_eblob, void *d_ews, void *stream);
 int launch_rans_decode(const Params &p, const EntropyLayout &e, const void *d_eblob, void *d_blob, void *stream);
 int launch_plain_copy(void *d_dst, const void *d_src, size_t bytes, void *stream);     // measurement aids
 int launch_plain_read(const void *d_src, size_t bytes, void *d_sink, void *stream);

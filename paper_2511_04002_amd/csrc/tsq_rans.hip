@@ -12,7 +12,7 @@
 // is the final states of the coders that own a run (min(64, runs) of them) followed by the words
 // in the order the decoder reads them, padded to 4 bytes.
 //
-// Encode: code counts per width, added to one of 16 sets (k_code_pool) -> sets added up,
+// Encode: code counts per width, a set per counting workgroup (k_code_pool) -> sets added up,
 // tables (k_rans_tables) -> one wave per token codes its stream into a slot of the workspace
 // (k_rans_encode) and adds its length to the stream bytes of its block of 256 tokens -> every token
 // finds its offset from the block sums before it and the lengths before it inside its block, and its
@@ -39,92 +39,122 @@ __device__ __forceinline__ bool eblob_is_valid(const Params &p, const EntropyLay
 
 // ---------------------------------------------------------------- pooled counts and tables
 
-// What the kernels of a call add to starts at zero: the pooled code counts and the stream bytes per block of
-// tokens (one thread per word).
-constexpr uint32_t kBeginThreads = 1024;
-__global__ void __launch_bounds__(kBeginThreads)
-k_rans_begin(const Params p, const EntropyLayout e, uint8_t *__restrict__ eblob, uint8_t *__restrict__ ews) {
-    const uint32_t i = blockIdx.x * kBeginThreads + threadIdx.x, n_counts = kPoolCopies * 7u * 256u;
-    const uint32_t n_blocks = (p.tokens + kLenBlock - 1u) / kLenBlock;
-    if (i < n_counts) reinterpret_cast<uint32_t *>(ews + e.ws_pooled)[i] = 0;
-    else if (i - n_counts < n_blocks) reinterpret_cast<uint32_t *>(ews + e.ws_block)[(i - n_counts) * kBlockStride] = 0;
-    // the header becomes valid only when the last kernel of the call has run
-    if (blockIdx.x == 0 && threadIdx.x < sizeof(EntropyHeader) / 4) reinterpret_cast<uint32_t *>(eblob)[threadIdx.x] = 0;
-}
-
-// One workgroup per width class: counts -> 12-bit frequencies.  f_c = max(1, floor(n_c * 4096 / N))
+// Counts -> 12-bit frequencies, per width class.  f_c = max(1, floor(n_c * 4096 / N))
 // for n_c > 0; while the sum exceeds 4096, one is taken from the largest f (lowest code on ties);
 // a remaining deficit goes to the code with the largest count (lowest code on ties).
 // Taking E times one from the current largest entry is a cut at a level: with
 // g(v) = sum_c max(f_c - v, 0), the level is the v with g(v + 1) < E <= g(v); every entry above
 // v + 1 comes down to v + 1, and the first E - g(v + 1) entries (in code order) that then stand at
-// v + 1 go down to v.  The level is found by bisection, each probe a workgroup-wide sum.
-__global__ void __launch_bounds__(256)
-k_rans_tables(const Params p, const EntropyLayout e, const uint8_t *__restrict__ blob, uint8_t *__restrict__ eblob,
-              const uint8_t *__restrict__ ews) {
-    __shared__ uint32_t part[3][4];
-    if (!blob_is_plans<false>(p, blob)) return;
-    const uint32_t k = blockIdx.x, c = threadIdx.x;
-    // this class's counts: the sets that the counting workgroups added to, added up
-    const uint32_t *counts = reinterpret_cast<const uint32_t *>(ews + e.ws_pooled) + k * 256u;
-    uint16_t *table = reinterpret_cast<uint16_t *>(eblob + e.off_tables) + k * 256u;
-    // workgroup-wide sum of one value per thread: wave sums, exchanged through one of three areas in
-    // rotation (an area is written again two barriers after it was read), one barrier per sum
-    uint32_t turn = 0;
-    auto block_sum = [&](uint32_t v) {
-        uint32_t *area = part[turn % 3u];
-        ++turn;
-        const uint32_t w = wave_sum_u32(v);
-        if ((c & 63u) == 0) area[c >> 6] = w;
-        __syncthreads();
-        return area[0] + area[1] + area[2] + area[3];
-    };
-    auto block_max = [&](uint32_t v) {
-        uint32_t *area = part[turn % 3u];
-        ++turn;
-        const uint32_t w = wave_max_u32(v);
-        if ((c & 63u) == 0) area[c >> 6] = w;
-        __syncthreads();
-        const uint32_t a = area[0] > area[1] ? area[0] : area[1], b = area[2] > area[3] ? area[2] : area[3];
-        return a > b ? a : b;
-    };
-    uint32_t nc = 0;
+// v + 1 go down to v.  The level is found by bisection, each probe a sum over the wave.
+// By one wave, lane l the codes 4l .. 4l + 3 with counts nc.
+__device__ __forceinline__ void build_table(const uint32_t (&nc)[4], uint16_t *table) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t N = wave_sum_u32(nc[0] + nc[1] + nc[2] + nc[3]);
+    uint32_t f[4], s = 0;
 #pragma unroll
-    for (uint32_t g = 0; g < kPoolCopies; ++g) nc += counts[g * 7u * 256u + c];
-    const uint32_t N = block_sum(nc);
-    uint32_t fc = 0;
-    if (N && nc) {
-        fc = (uint32_t)(((uint64_t)nc << kProbBits) / N);
-        if (fc == 0) fc = 1;
+    for (int i = 0; i < 4; ++i) {
+        // (4096 n_c and N are exact in binary64; a quotient below an integer is so by 2^-32 at least, more than its rounding)
+        f[i] = nc[i] ? (uint32_t)((double)((uint64_t)nc[i] << kProbBits) / (double)N) : 0u;
+        if (nc[i] && f[i] == 0) f[i] = 1;
+        s += f[i];
     }
-    const uint32_t S = block_sum(fc);
+    const uint32_t S = wave_sum_u32(s);
+    auto above_level = [&](uint32_t v) {
+        uint32_t g = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) g += f[i] > v ? f[i] - v : 0u;
+        return wave_sum_u32(g);
+    };
     if (S > kProbScale) {
         const uint32_t E = S - kProbScale;
-        uint32_t lo = 0, hi = kProbScale;        // g(lo) >= E always (g(0) = S > E); g(hi) = 0 < E
+        // g(lo) >= E always (g(0) = S > E, and the largest entry alone gives g(most - E) >= E); g(hi) = 0 < E
+        const uint32_t a = f[0] > f[1] ? f[0] : f[1], b = f[2] > f[3] ? f[2] : f[3], most = wave_max_u32(a > b ? a : b);
+        uint32_t lo = most > E ? most - E : 0u, hi = most;
         while (hi - lo > 1u) {                   // invariant: g(lo) >= E > g(hi)
             const uint32_t mid = (lo + hi) >> 1;
-            const uint32_t g = block_sum(fc > mid ? fc - mid : 0u);
-            if (g >= E) lo = mid; else hi = mid;
+            if (above_level(mid) >= E) lo = mid; else hi = mid;
         }
         // level lo: g(lo + 1) < E <= g(lo)
-        const uint32_t above = block_sum(fc > lo + 1u ? fc - (lo + 1u) : 0u);
-        const uint32_t rest = E - above;         // entries at lo + 1 (after the cut) that go one further down
-        // rank of this code among those above the level, in code order: lanes below in the wave, waves before
-        const uint64_t mine = __builtin_amdgcn_ballot_w64(fc > lo);
-        uint32_t *area = part[turn % 3u];
-        ++turn;
-        if ((c & 63u) == 0) area[c >> 6] = (uint32_t)__builtin_popcountll(mine);
-        __syncthreads();
-        uint32_t rank = (uint32_t)__builtin_popcountll(mine & ((1ull << (c & 63u)) - 1ull));
-        for (uint32_t w = 0; w < (c >> 6); ++w) rank += area[w];
-        if (fc > lo) fc = rank < rest ? lo : lo + 1u;
+        const uint32_t rest = E - above_level(lo + 1u);     // entries at lo + 1 (after the cut) that go one further down
+        uint32_t n = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) n += f[i] > lo ? 1u : 0u;
+        uint32_t rank = wave_incl_scan_u32(n) - n;          // of the lane's first code among those above the level
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (f[i] > lo) {
+                f[i] = rank < rest ? lo : lo + 1u;
+                ++rank;
+            }
     } else if (N && S < kProbScale) {
         // the lowest code among those with the largest count: the largest of 256 - c over them
-        const uint32_t most = block_max(nc);
-        const uint32_t pick = block_max(nc == most ? 256u - c : 0u);
-        if (256u - c == pick) fc += kProbScale - S;
+        const uint32_t a = nc[0] > nc[1] ? nc[0] : nc[1], b = nc[2] > nc[3] ? nc[2] : nc[3];
+        const uint32_t most = wave_max_u32(a > b ? a : b);
+        uint32_t mine = 0;
+#pragma unroll
+        for (int i = 3; i >= 0; --i)
+            if (nc[i] == most) mine = 256u - (4u * lane + i);
+        const uint32_t pick = wave_max_u32(mine);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (256u - (4u * lane + i) == pick) f[i] += kProbScale - S;
     }
-    table[c] = (uint16_t)fc;
+    *reinterpret_cast<uint2 *>(table + 4u * lane) = make_uint2(f[0] | (f[1] << 16), f[2] | (f[3] << 16));
+}
+
+// Workgroup (s, k): the sets 64 s .. 64 s + 63 of the counting workgroups are added up for width class k.  With more than one
+// slice the sums travel through the workspace (agent scope), and whoever arrives last adds those up and builds the
+// class's table; nobody waits for anybody.
+// A set per counting workgroup, up to 512 of them, is 1 MB to add up: by one workgroup per class it took longer than the
+// kernel that zeroed sixteen shared sets (8192 x 8192 90 us a call against 87).
+constexpr uint32_t kTableThreads = 1024;
+__global__ void __launch_bounds__(kTableThreads)
+k_rans_tables(const Params p, const EntropyLayout e, const uint8_t *__restrict__ blob, uint8_t *__restrict__ eblob,
+              uint8_t *__restrict__ ews) {
+    __shared__ uint32_t sums[4][256];
+    __shared__ uint32_t last;
+    const uint32_t slice = blockIdx.x, slices = gridDim.x, k = blockIdx.y, c = threadIdx.x & 255u, q = threadIdx.x >> 8;
+    const uint32_t codes = 4u << k, *sets = reinterpret_cast<const uint32_t *>(ews + e.ws_pooled) + codes - 4u + (c & (codes - 1u));
+    const uint32_t g0 = slice * kTableSlice, left = e.pool_groups - g0;
+    // (all loads at once: what is beyond the class's codes or the last set is read within them and dropped)
+    uint32_t v[kTableSlice / 4u], n = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < kTableSlice / 4u; ++i) {
+        const uint32_t g = 4u * i + q;
+        v[i] = sets[(size_t)(g0 + (g < left ? g : 0u)) * kPoolSetWords];
+    }
+    if (!blob_is_plans<false>(p, blob)) return;
+#pragma unroll
+    for (uint32_t i = 0; i < kTableSlice / 4u; ++i) n += 4u * i + q < left ? v[i] : 0u;
+    sums[q][c] = c < codes ? n : 0u;
+    __syncthreads();
+    uint32_t *parts = reinterpret_cast<uint32_t *>(ews + e.ws_parts) + k * 256u;
+    if (slices > 1u) {
+        if (q == 0) {
+            n = sums[0][c] + sums[1][c] + sums[2][c] + sums[3][c];
+            __hip_atomic_store(parts + slice * 7u * 256u + c, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // (performed before the arrival is counted)
+        }
+        __syncthreads();
+        if (threadIdx.x == 0)
+            last = __hip_atomic_fetch_add(reinterpret_cast<uint32_t *>(ews + e.ws_arrived) + k * kBlockStride, 1u,
+                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == slices - 1u;
+        __syncthreads();
+        if (!last) return;
+        const uint32_t a = __hip_atomic_load(parts + (q < slices ? q : 0u) * 7u * 256u + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t b = __hip_atomic_load(parts + (q + 4u < slices ? q + 4u : 0u) * 7u * 256u + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        sums[q][c] = (q < slices ? a : 0u) + (q + 4u < slices ? b : 0u);
+        __syncthreads();
+    }
+    if (threadIdx.x >= 64u) return;
+    uint32_t nc[4];
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i) {
+        const uint32_t at = 4u * threadIdx.x + i;
+        nc[i] = sums[0][at] + sums[1][at] + sums[2][at] + sums[3][at];
+    }
+    static_assert(kMaxTableSlices == 8, "two parts per thread");
+    build_table(nc, reinterpret_cast<uint16_t *>(eblob + e.off_tables) + k * 256u);
 }
 
 // What a step of the encoder needs of a code with frequency f, in LDS: a binary64 reciprocal of f (see quotient()) whose
@@ -319,29 +349,10 @@ k_rans_encode(const Params p, const EntropyLayout e, const uint8_t *__restrict__
 // of the last token also writes the end offset and the header.
 //
 // The words stand at the end of the slot's room, which holds an even number of them: they start at an
-// odd word exactly when their number is odd.  They move eight at a time (16 bytes; the last ones two at a
-// time); in the odd case a pair is the high half of one 32-bit word of the room and the low half of the
-// next, and the pair after the last word of the room is the padding to 4 bytes.
-struct StreamSource {
-    const uint32_t *src;      // the 32-bit word of the room that holds the first word of the stream
-    uint32_t left;            // 32-bit words from there to the end of the room
-    uint32_t odd;             // the stream starts in the high half of *src
-};
-__device__ __forceinline__ uint32_t stream_pair(const StreamSource &q, uint32_t i) {
-    uint32_t v = q.src[i];
-    if (q.odd) v = (v >> 16) | ((i + 1u < q.left ? q.src[i + 1u] : 0u) << 16);
-    return v;
-}
-// pairs 4c .. 4c+3 (all of them exist)
-__device__ __forceinline__ Words4 stream_pairs4(const StreamSource &q, uint32_t c) {
-    const Words4 a = *reinterpret_cast<const Words4 *>(q.src + 4u * c);
-    if (!q.odd) return a;
-    const uint32_t next = 4u * c + 4u < q.left ? q.src[4u * c + 4u] : 0u;
-    Words4 v;
-    v.x = (a.x >> 16) | (a.y << 16); v.y = (a.y >> 16) | (a.z << 16);
-    v.z = (a.z >> 16) | (a.w << 16); v.w = (a.w >> 16) | (next << 16);
-    return v;
-}
+// odd word exactly when their number is odd.  They move eight at a time by 16-byte loads that need no more than the two
+// bytes' alignment of a word (put together from 4-byte aligned words, the loads of an odd stream waited for one another:
+// 8192 x 8192 16.9 us); the last ones, fewer than eight, move two at a time, with the padding to 4 bytes behind an odd one.
+typedef uint32_t Words4_a2 __attribute__((ext_vector_type(4), aligned(2)));
 
 // 16-byte pieces per lane that are loaded before the offset is known: 6 KB, a whole stream of up to about 8192 elements (2 KB:
 // 8192 x 8192 76.5 us a call against 75.2, 32768 x 4096 157.8 / 154.7, 16384 x 8192 135.0 / 132.6; 8 KB as 6)
@@ -363,26 +374,32 @@ k_rans_gather(const Params p, const EntropyLayout e, const uint8_t *__restrict__
     // (a length that k_rans_encode wrote passes; anything else moves nothing)
     const bool sane = bytes >= 4u * coders && bytes <= e.slot_bytes && ((bytes - 4u * coders) >> 1) <= room;
     const uint32_t nwords = sane ? (bytes - 4u * coders) >> 1 : 0u;
-    const uint32_t first = room - nwords, pairs = (nwords + 1u) >> 1, pieces = pairs >> 2;
-    StreamSource q;
-    q.src = reinterpret_cast<const uint32_t *>(slot + 256) + (first >> 1);
-    q.left = (room >> 1) - (first >> 1);
-    q.odd = first & 1u;
+    const uint32_t pieces = nwords >> 3;
+    const uint32_t at_words = 256u + 2u * (room - nwords);  // of the stream's words in the slot
     Words4 early[kGatherEarly];
 #pragma unroll
     for (uint32_t k = 0; k < kGatherEarly; ++k) {
         const uint32_t c = lane + 64u * k;
-        early[k] = c < pieces ? stream_pairs4(q, c) : Words4{0u, 0u, 0u, 0u};
+        // (on every path, or the loads would wait for one another: a piece that is not there is the slot's first 16 bytes)
+        early[k] = *reinterpret_cast<const Words4_a2 *>(slot + (c < pieces ? at_words + 16u * c : 0u));
     }
-    const uint32_t state = lane < coders && sane ? reinterpret_cast<const uint32_t *>(slot)[lane] : 0u;
+    // the last words, fewer than eight, two per lane (a word that is not there: the slot's first)
+    const uint32_t i = 8u * pieces + 2u * lane;
+    const uint32_t lo = *reinterpret_cast<const uint16_t *>(slot + (i < nwords ? at_words + 2u * i : 0u));
+    const uint32_t hi = *reinterpret_cast<const uint16_t *>(slot + (i + 1u < nwords ? at_words + 2u * i + 2u : 0u));
+    const uint32_t pair = i + 1u < nwords ? lo | (hi << 16) : lo;
+    const uint32_t state = reinterpret_cast<const uint32_t *>(slot)[lane];     // (the room for 64 states is always there)
 
-    uint64_t s = 0;
-    for (uint32_t b = lane; b < blk; b += 64u) s += block[b * kBlockStride];
+    uint32_t before[kLenBlock / 64u];
 #pragma unroll
     for (uint32_t k = 0; k < kLenBlock / 64u; ++k) {
         const uint32_t u = blk * kLenBlock + lane + 64u * k;
-        if (u < t) s += (len[u] + 3u) & ~3u;
+        before[k] = len[u < t ? u : t];
     }
+    uint64_t s = 0;
+    for (uint32_t b = lane; b < blk; b += 64u) s += block[b * kBlockStride];
+#pragma unroll
+    for (uint32_t k = 0; k < kLenBlock / 64u; ++k) s += blk * kLenBlock + lane + 64u * k < t ? (before[k] + 3u) & ~3u : 0u;
     const uint64_t at = (uint64_t)wave_sum_u32((uint32_t)s & 0xFFFFFFu) + ((uint64_t)wave_sum_u32((uint32_t)(s >> 24)) << 24);
 
     uint64_t *off = reinterpret_cast<uint64_t *>(eblob + e.off_stream_off);
@@ -407,9 +424,9 @@ k_rans_gather(const Params p, const EntropyLayout e, const uint8_t *__restrict__
         const uint32_t c = lane + 64u * k;
         if (c < pieces) *reinterpret_cast<Words4 *>(out + 4u * c) = early[k];
     }
-    for (uint32_t c = lane + 64u * kGatherEarly; c < pieces; c += 64u) *reinterpret_cast<Words4 *>(out + 4u * c) = stream_pairs4(q, c);
-    const uint32_t i = 4u * pieces + lane;                  // the last pairs, fewer than four
-    if (i < pairs) out[i] = stream_pair(q, i);
+    for (uint32_t c = lane + 64u * kGatherEarly; c < pieces; c += 64u)
+        *reinterpret_cast<Words4 *>(out + 4u * c) = *reinterpret_cast<const Words4_a2 *>(slot + at_words + 16u * c);
+    if (i < nwords) out[i >> 1] = pair;
 }
 
 // ---------------------------------------------------------------- decode
@@ -712,16 +729,15 @@ k_rans_decode(const Params p, const EntropyLayout e, const uint8_t *__restrict__
 
 static hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s); }
 
-int launch_rans_encode(const Params &p, const Geometry &g, const EntropyLayout &e, const void *d_blob, void *d_eblob,
+int launch_rans_encode(const Params &p, const EntropyLayout &e, const void *d_blob, void *d_eblob,
                        void *d_ews, void *stream) {
     const uint8_t *blob = static_cast<const uint8_t *>(d_blob);
     uint8_t *eblob = static_cast<uint8_t *>(d_eblob), *ews = static_cast<uint8_t *>(d_ews);
     hipStream_t s = as_stream(stream);
-    const uint32_t to_zero = kPoolCopies * 7u * 256u + (p.tokens + kLenBlock - 1u) / kLenBlock;
-    hipLaunchKernelGGL(k_rans_begin, dim3((to_zero + kBeginThreads - 1u) / kBeginThreads), dim3(kBeginThreads), 0, s, p, e, eblob, ews);
-    int rc = launch_code_pool(p, g, e, d_blob, ews + e.ws_pooled, stream);
+    int rc = launch_code_pool(p, e, d_blob, d_eblob, d_ews, stream);
     if (rc != 0) return rc;
-    hipLaunchKernelGGL(k_rans_tables, dim3(7), dim3(256), 0, s, p, e, blob, eblob, ews);
+    hipLaunchKernelGGL(k_rans_tables, dim3((e.pool_groups + kTableSlice - 1u) / kTableSlice, 7), dim3(kTableThreads), 0, s, p, e, blob,
+                       eblob, ews);
     hipLaunchKernelGGL(k_rans_encode, dim3(p.tokens), dim3(64), 0, s, p, e, blob, eblob, ews);
     hipLaunchKernelGGL(k_rans_gather, dim3(p.tokens), dim3(64), 0, s, p, e, blob, eblob, ews);
     return (int)hipGetLastError();
