@@ -65,8 +65,9 @@ TSQ_HD double reciprocal_just_above(uint32_t f, uint32_t low) {
     const uint64_t r = __builtin_bit_cast(uint64_t, 1.0 / (double)f);
     return __builtin_bit_cast(double, (r & ~0xFFFFull) + 0x10000ull + low);
 }
+constexpr double kQuotientAddend = 4503599627370495.5;      // 2^52 - 1/2
 TSQ_HD uint32_t quotient(uint32_t x, double above) {
-    return (uint32_t)__builtin_bit_cast(uint64_t, __builtin_fma((double)x, above, 4503599627370495.5));
+    return (uint32_t)__builtin_bit_cast(uint64_t, __builtin_fma((double)x, above, kQuotientAddend));
 }
 
 // A workspace's recorded shape against the plan's.

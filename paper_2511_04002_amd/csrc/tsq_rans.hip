@@ -26,6 +26,7 @@
 
 namespace tsq {
 
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 constexpr uint32_t kProbBits = 12, kProbScale = 1u << kProbBits, kRansLow = 1u << 16;
 static_assert(kProbScale == 4096, "frequency_slot() masks 12 bits");
 
@@ -210,6 +211,15 @@ __device__ __forceinline__ uint32_t mad_u24(uint32_t a, uint32_t b, uint32_t c) 
     asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
     return d;
 }
+// quotient(x, above), with its addend in registers for the whole kernel and named as such: left to itself the compiler copies
+// it for half of the steps, to accumulate into the copy
+__device__ __forceinline__ uint32_t quotient_with(uint32_t x, double above, double addend) {
+    double d;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"((double)x), "v"(above), "v"(addend));
+    return (uint32_t)__builtin_bit_cast(uint64_t, d);
+}
+// x >> 16, in x's own register
+__device__ __forceinline__ void drop_word(uint32_t &x) { asm volatile("v_lshrrev_b32 %0, 16, %0" : "+v"(x)); }
 // 8 times byte k of w in one instruction
 __device__ __forceinline__ uint32_t eight_times_byte(uint32_t w, int k) {
     uint32_t d;
@@ -221,17 +231,25 @@ __device__ __forceinline__ uint32_t eight_times_byte(uint32_t w, int k) {
     return d;
 }
 
+// A 16-bit store to byte `offset` (uniform) + 2 * `index` of a buffer of 2-byte elements.
+__device__ void store_short(short v, i32x4 window, int index, int zero, int offset, int policy) __asm("llvm.amdgcn.struct.buffer.store.i16");
+__device__ __forceinline__ i32x4 words_window(const void *base, uint32_t words) {
+    const uint64_t a = (uint64_t)base;
+    return i32x4{(int)(uint32_t)a, (int)((uint32_t)(a >> 32) & 0xFFFFu) | (2 << 16), (int)words, 0x00027000};
+}
+
 // The steps of one round (run number `round` of every lane), last element first.  The words go
 // straight to the token's slot in the workspace, which fills from its end downwards.
-// Bound by the issue of vector instructions: 11 to 13 a step (19 with a binary32 estimate of the quotient, its
-// correction and a limit of its own per code), four cycles each, beside 11 cycles of LDS a step and compute unit.  The call on
-// 8192 x 8192 bf16 87 -> 76 us, 32768 x 4096 f16 169 -> 157, 131072 x 768 f16 344 -> 304, 16384 x 8192 151 -> 139,
-// 2048 x 4096 34 -> 33.  (Entries of four bytes a table, two addresses: 81, 158, 308.  The limit of a code looked up, too,
-// in sixteen bytes at once: 90, 177, 312.)
+// Bound by the issue of vector instructions, 10 to 12 a step and about four cycles each, six scalar ones (4.15 cycles each on
+// the unit that four SIMDs share), and 11 cycles of LDS a step and compute unit: a step takes a SIMD 74 cycles; without the
+// look-ups it would take 61, without the stores 72.  Two instructions less (the place of a shed word by the memory pipeline, no
+// copies of the quotient's addend): 8192 x 8192 bf16 72.4 us a call -> 71.3, 32768 x 4096 f16 147.8 -> 146.6.
+// (Before that, the quotient from binary64 instead of a binary32 estimate with its correction: 87 -> 76, 169 -> 157.  Entries of
+// four bytes a table, two addresses, were slower; so was a code's limit looked up, too, in sixteen bytes at once.)
 // WHOLE: the run of every lane that takes part lies inside the row (valid >= 32), so no step needs a range check.
 template <int B, bool WHOLE>
 __device__ __forceinline__ void encode_round(const uint32_t *src_row, uint32_t run, int valid, const EncodeTable &ftab,
-                                             uint16_t *out, uint32_t &ptr, uint32_t &x) {
+                                             i32x4 out, uint32_t &ptr, uint32_t &x) {
     uint32_t d[B];
     const uint32_t nd = (WHOLE || valid >= 32) ? (uint32_t)B : (valid > 0 ? ((uint32_t)valid * B + 31u) >> 5 : 0u);
     if (WHOLE) {
@@ -254,7 +272,8 @@ __device__ __forceinline__ void encode_round(const uint32_t *src_row, uint32_t r
         above = *reinterpret_cast<const double *>(reinterpret_cast<const uint8_t *>(ftab.above) + at);
         step = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const uint8_t *>(ftab.step) + at);
     };
-    double above, next_above;
+    double above, next_above, addend = kQuotientAddend;
+    asm("" : "+v"(addend));
     uint32_t step, next_step;
     look_up(31, next_above, next_step);
 #pragma unroll
@@ -265,16 +284,15 @@ __device__ __forceinline__ void encode_round(const uint32_t *src_row, uint32_t r
         if (j > 0) look_up(j - 1, next_above, next_step);
         // q = floor(x / f); the state sheds a word if x >= f << 20, that is q >= 2^20, and the quotient of what is left
         // is then q >> 16
-        uint32_t q = quotient(x, above);
+        uint32_t q = quotient_with(x, above, addend);
         const bool over = q >= (1u << 20), shed = active && over;
         const uint64_t who = WHOLE ? __builtin_amdgcn_ballot_w64(over) : __builtin_amdgcn_ballot_w64(active) & __builtin_amdgcn_ballot_w64(over);
-        ptr -= (uint32_t)__builtin_popcountll(who);
+        ptr -= 2u * (uint32_t)__builtin_popcountll(who);
         if (shed) {
-            // (a 32-bit byte offset from a uniform base: one instruction for the address)
-            const uint32_t at = (ptr + rank_in(who)) << 1;
-            *reinterpret_cast<uint16_t *>(reinterpret_cast<uint8_t *>(out) + at) = (uint16_t)x;
-            x >>= 16;
-            q >>= 16;
+            // (the memory pipeline doubles the rank: no instruction for the address)
+            store_short((short)x, out, (int)rank_in(who), 0, (int)ptr, 0);
+            drop_word(x);
+            drop_word(q);
         }
         // x -> (q << 12) + (x - q f) + cum = q (4096 - f) + (x + cum)
         const uint32_t cum = (uint32_t)__builtin_bit_cast(uint64_t, above) & 0xFFFFu;
@@ -302,9 +320,9 @@ k_rans_encode(const Params p, const EntropyLayout e, const uint8_t *__restrict__
     __syncthreads();
     const uint32_t *src_row = reinterpret_cast<const uint32_t *>(blob + p.off_payload + po);
     uint8_t *slot = ews + e.ws_slots + (size_t)t * e.slot_bytes;
-    uint16_t *out = reinterpret_cast<uint16_t *>(slot + 256);
-    const uint32_t rounds = (p.runs + 63u) / 64u, cap = (e.slot_bytes - 256u) >> 1;   // one word per element at most
-    uint32_t x = kRansLow, ptr = cap;
+    const uint32_t rounds = (p.runs + 63u) / 64u, cap = e.slot_bytes - 256u;   // one word per element at most
+    const i32x4 out = words_window(slot + 256, cap >> 1);
+    uint32_t x = kRansLow, ptr = cap;                             // ptr: the place of the last word that was shed, in bytes
     for (uint32_t r = rounds; r-- > 0;) {
         if (rounds > 1u) priority_by_progress(rounds - 1u - r, rounds);
         const uint32_t run = lane + 64u * r;
@@ -333,7 +351,7 @@ k_rans_encode(const Params p, const EntropyLayout e, const uint8_t *__restrict__
     const uint32_t coders = p.runs < 64u ? p.runs : 64u;  // coders that own a run; the others still hold 2^16
     if (lane < coders) reinterpret_cast<uint32_t *>(slot)[lane] = x;
     if (lane == 0) {
-        const uint32_t bytes = 4u * coders + 2u * (cap - ptr);
+        const uint32_t bytes = 4u * coders + (cap - ptr);
         len[t] = bytes;                                     // unpadded; the stream is padded to 4 bytes when it is placed
         // padded stream bytes of the token's block of kLenBlock tokens (kLenBlock slots of at most 64 KiB + 256
         // bytes: the sum fits 32 bits)
