@@ -449,78 +449,90 @@ k_rans_gather(const Params p, const EntropyLayout e, const uint8_t *__restrict__
 
 // ---------------------------------------------------------------- decode
 
-// What a slot decodes to, in one word: (f - 1) << 20 | (slot - cum) << 8 | code, so that a step of the decoder is one
-// look-up and x -> f (x >> 12) + slot - cum.  A class's 4096 words take 16 KB; two workgroups' worth of LDS holds three
-// such tables each, for the classes that most of the workgroup's tokens have.  The other classes (four at most) get
-// 5 KB: the rank of a slot's code among the codes that occur, a byte per slot, and a list of those codes with cum in the
-// place of slot - cum.  (Four tables, and a second turn for the tokens of further classes: 8192 x 8192 bf16 with five
+// What a slot decodes to, in one word: f << 20 | c << 8 | code with c = (slot - cum) - floor(f slot / 4096), which lies
+// between -1024 and 1024 (as f + cum <= 4096), so that a step of the decoder is one look-up and
+// x -> f (x >> 12) + slot - cum = floor((f << 20) x / 2^32) + c: the product's upper half, with no shift of x or f before it.
+// (f = 4096, the only code of its class, is entered as 0: see decode_round.)  A class's 4096 words take 16 KB; two workgroups'
+// worth of LDS holds three such tables each, for the classes that most of the workgroup's tokens have.  The other classes (four at most) get
+// 5 KB: the rank of a slot's code among the codes that occur, a byte per slot, and a list of those codes, (f - 1) << 20 |
+// cum << 8 | code.  (Four tables, and a second turn for the tokens of further classes: 8192 x 8192 bf16 with five
 // classes 57 us, this form 42, a token per workgroup 45.)
 //
-// What bounds it is instruction issue (and, at few tokens, the chain of a step: table, product, comparison, place, word).
-// Counted on 8192 x 8192, per step and wave, tables, ring and start included: 25.1 vector and 3.2 LDS instructions for a
-// token per workgroup of one wave, with tables of its own in two steps (slot -> code -> f, cum) and the words of the
-// stream fetched out of other lanes' registers; 18.6 and 2.6 for this form.  8192 x 8192 bf16 48 -> 39 us, 32768 x 4096
-// f16 116 -> 73, 131072 x 768 234 -> 141, 2000 x 16384 59 -> 46, 300 x 5120 21 -> 18.
+// What bounds it is instruction issue, vector and scalar (and, at few tokens, the chain of a step: table, product, comparison, place, word).
+// 8192 x 8192 bf16: 13 vector instructions a step (49 cycles of a SIMD's issue; a word of f - 1, slot - cum and code had one
+// more) and four scalar ones, and a third of what changes with a portion of the stream, which was 16 scalar and five vector
+// instructions and is seven and one: 39.2 us a call -> 35.2; 32768 x 4096 f16 72.3 / 68.9, 20000 x 768 bf16 30.4 / 27.7, 2048 x
+// 4096 f16 16.8 / 16.1.  (With a token per workgroup of one wave, and tables of its own in two steps, 48.)
 constexpr uint32_t kDecWaves = 16, kDecThreads = 64u * kDecWaves, kDecTables = 3, kDecTableWords = kProbScale;
 constexpr uint32_t kDecLists = 4, kDecListBytes = kProbScale + 256u * 4u;     // ranks, then the list
-// A wave's words of the stream: a ring of two halves of 128 words, and the first 64 of them once more behind it, so
+// A wave's words of the stream: a ring of two halves of 128 words, and the first half once more behind it, so
 // that the up to 64 words of a step always stand in a row.
-constexpr uint32_t kHalfWords = 128, kRingWords = 2 * kHalfWords + 64;
+constexpr uint32_t kHalfWords = 128, kRingWords = 3 * kHalfWords;
 constexpr uint32_t kDecLdsLists = kDecTables * kDecTableWords * 4u, kDecLdsRings = kDecLdsLists + kDecLists * kDecListBytes;
 constexpr uint32_t kDecLdsBytes = kDecLdsRings + kDecWaves * kRingWords * 2u;
 // While tables are laid out the rings' place holds, per class, one bit per slot where a code's range starts (128
-// words), and behind those the lists of the classes with a table (256 words each).
+// words) and the number of those bits before each of these words, and behind them the lists of the classes with a table
+// (256 words each).
 constexpr uint32_t kMarkWords = 128, kDecClasses = kDecTables + kDecLists;
-static_assert((kDecClasses * kMarkWords + kDecTables * 256u) * 4u <= kDecWaves * kRingWords * 2u, "scratch of the table builders");
+static_assert((kDecClasses * 2u * kMarkWords + kDecTables * 256u) * 4u <= kDecWaves * kRingWords * 2u, "scratch of the table builders");
 static_assert(kDecClasses == 7, "a place for every width");
 static_assert(2u * kDecLdsBytes <= 160u * 1024u, "two workgroups per compute unit");
 
-// Step 1, by one wave per table: lane l takes the codes 4l .. 4l+3.  The codes that occur are listed in the form
-// of a table word with cum in the place of slot - cum, and the slots where their ranges start are marked.
-__device__ __forceinline__ void list_codes(const uint16_t *freq, uint32_t *list, uint32_t *starts) {
+// Step 1, by one wave per table: lane l takes the codes 4l .. 4l+3.  The codes that occur are listed in the form of a
+// list (RANKS), or with f in the place of f - 1; the slots where their ranges start are marked, and the marks counted.
+__device__ __forceinline__ void list_codes(const uint16_t *freq, uint32_t *list, uint32_t *starts, bool ranks) {
     const uint32_t lane = threadIdx.x & 63u;
     uint32_t f[4], s = 0, n = 0;
+    const uint2 four = *reinterpret_cast<const uint2 *>(freq + 4u * lane);
+    f[0] = four.x & 0xFFFFu; f[1] = four.x >> 16; f[2] = four.y & 0xFFFFu; f[3] = four.y >> 16;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        f[i] = freq[4u * lane + i];
         s += f[i];
         n += f[i] ? 1u : 0u;
     }
-    starts[lane] = 0;
-    starts[64u + lane] = 0;
+    *reinterpret_cast<uint2 *>(starts + 2u * lane) = make_uint2(0u, 0u);
     uint32_t cum = wave_incl_scan_u32(s) - s, rank = wave_incl_scan_u32(n) - n;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         if (f[i]) {
             const uint32_t at = frequency_slot(cum);              // masked: a damaged table stays inside the array
-            list[rank] = ((f[i] - 1u) << 20) | (at << 8) | (4u * lane + i);
+            list[rank] = ((ranks ? f[i] - 1u : f[i]) << 20) | (at << 8) | (4u * lane + i);
             atomicOr(starts + (at >> 5), 1u << (at & 31u));
             ++rank;
         }
         cum += f[i];
     }
+    const uint2 marks = *reinterpret_cast<const uint2 *>(starts + 2u * lane);
+    const uint32_t a = (uint32_t)__builtin_popcount(marks.x), b = (uint32_t)__builtin_popcount(marks.y);
+    const uint32_t before = wave_incl_scan_u32(a + b) - a - b;
+    *reinterpret_cast<uint2 *>(starts + kMarkWords + 2u * lane) = make_uint2(before, before + a);
 }
-// Step 2, by all waves (this one is number `part` of `parts`), 64 slots at a time: the rank of a slot's code is the
-// number of ranges that start up to it.  Fills the table, or (RANKS) the ranks.
+// Step 2, by all threads, four slots each: the rank of a slot's code is the number of ranges that start up to it.  Fills the
+// table, or (RANKS) the ranks.
 template <bool RANKS>
-__device__ __forceinline__ void fill_table(const uint32_t *list, const uint32_t *starts, uint32_t *table, uint32_t part,
-                                           uint32_t parts) {
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t lo = starts[2u * lane], hi = starts[2u * lane + 1u];       // the marks of slots 64 lane .. 64 lane + 63
-    const uint32_t n = (uint32_t)__builtin_popcount(lo) + (uint32_t)__builtin_popcount(hi);
-    const uint32_t before = wave_incl_scan_u32(n) - n;
-    for (uint32_t i = part; i < kProbScale / 64u; i += parts) {
-        const uint32_t mlo = lane_value(lo, (int)i), mhi = lane_value(hi, (int)i);
-        const uint64_t above = (((uint64_t)mhi << 32) | mlo) >> 1;            // a lane counts the marks up to its own
-        uint32_t rank = lane_value(before, (int)i) + (mlo & 1u) + rank_in(above);
-        rank = rank ? rank - 1u : 0u;                                         // (0: only in a damaged table)
-        const uint32_t slot = 64u * i + lane;
-        if (RANKS) {
-            reinterpret_cast<uint8_t *>(table)[slot] = (uint8_t)rank;
-        } else {
-            const uint32_t entry = list[rank & 255u];
-            table[slot] = (entry & 0xFFF000FFu) | (((slot - (entry >> 8)) & 0xFFFu) << 8);
+__device__ __forceinline__ void fill_table(const uint32_t *list, const uint32_t *starts, uint32_t *table) {
+    static_assert(kDecThreads * 4u == kProbScale, "four slots a thread");
+    const uint32_t word = threadIdx.x >> 3, shift = 4u * (threadIdx.x & 7u);
+    const uint32_t marks = starts[word];
+    uint32_t upto = starts[kMarkWords + word] + (uint32_t)__builtin_popcount(marks & ((1u << shift) - 1u)), out[4];
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+        upto += (marks >> (shift + k)) & 1u;
+        out[k] = upto ? upto - 1u : 0u;                           // (0: only in a damaged table)
+    }
+    if (RANKS) {
+        table[threadIdx.x] = (out[0] & 255u) | ((out[1] & 255u) << 8) | ((out[2] & 255u) << 16) | (out[3] << 24);
+    } else {
+        uint32_t entry[4];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) entry[k] = list[out[k] & 255u];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) {
+            const uint32_t slot = 4u * threadIdx.x + k, f = entry[k] >> 20, cum = (entry[k] >> 8) & 0xFFFu;
+            const uint32_t c = slot - cum - (__umul24(f, slot) >> kProbBits);
+            out[k] = bitop3<kSelect>(0xFFFu << 8, c << 8, entry[k]);
         }
+        *reinterpret_cast<uint4 *>(table + 4u * threadIdx.x) = make_uint4(out[0], out[1], out[2], out[3]);
     }
 }
 
@@ -532,34 +544,40 @@ template <typename T> __device__ __forceinline__ T lds_at(uint32_t address) {
 
 // The words of a token's stream on their way into the wave's ring, 128 (two per lane) at a time: two portions in
 // the ring, one in a register, which replaces the older of the two when that is used up, and the one behind it
-// is asked for.  Past the end of the stream a lane repeats the stream's last words: a stream that is not damaged is
-// never read there.
+// is asked for.  What lies past the end of the stream is read as zeros: a stream that is not damaged never gets there.
+// A portion lasts about three steps, so what changes with it counts, too: the memory pipeline checks the range, and every lane
+// writes the copy behind the ring.
 typedef uint32_t __attribute__((may_alias)) TwoWords;       // (written two words at a time, read one at a time)
+typedef __attribute__((address_space(3))) TwoWords *RingWords;
 struct Words {
-    const uint32_t *src;
-    uint32_t last;             // index of the last pair of words
-    uint32_t ahead, portion;   // the portion in the register and its number
-    uint32_t ring;             // LDS address of the wave's ring
+    __amdgpu_buffer_rsrc_t src;
+    uint32_t next, ahead;      // the lane's byte of the portion that is asked for next; the portion in the register
+    uint32_t put;              // LDS address of the lane's two words in the first half
+    uint32_t ring;             // ... of the wave's ring
     uint32_t at, end;          // ... of the next word, and of the end of the half it is in
 };
-__device__ __forceinline__ uint32_t pair_at(const Words &q, uint32_t portion) {
-    const uint32_t i = portion * (kHalfWords / 2u) + (threadIdx.x & 63u);
-    return q.src[i < q.last ? i : q.last];
+__device__ __forceinline__ uint32_t next_portion(Words &q) {
+    const uint32_t v = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(q.src, (int)q.next, 0, 0);
+    q.next += 2u * kHalfWords;
+    return v;
 }
-__device__ __forceinline__ void put_portion(const Words &q, uint32_t half, uint32_t v) {
-    const uint32_t lane = threadIdx.x & 63u;
-    __attribute__((address_space(3))) TwoWords *ring = reinterpret_cast<__attribute__((address_space(3))) TwoWords *>(q.ring);
-    ring[half * (kHalfWords / 2u) + lane] = v;
-    if (half == 0 && lane < 32u) ring[kHalfWords + lane] = v;
+__device__ __forceinline__ void put_first(const Words &q, uint32_t v) {
+    RingWords ring = reinterpret_cast<RingWords>(q.put);
+    ring[0] = v;
+    ring[kHalfWords] = v;                                     // (words are counted in pairs)
 }
-// count words at src; `fallback` is readable memory for the case of no words at all (both 4-byte aligned)
-__device__ __forceinline__ void words_open(Words &q, const uint32_t *src, uint32_t count, const uint32_t *fallback, uint32_t ring) {
-    q.src = count ? src : fallback; q.last = count ? (count - 1u) >> 1 : 0u; q.ring = ring;
-    const uint32_t a = pair_at(q, 0), b = pair_at(q, 1);
-    q.ahead = pair_at(q, 2);
-    q.portion = 2;
-    put_portion(q, 0, a);
-    put_portion(q, 1, b);
+__device__ __forceinline__ void put_second(const Words &q, uint32_t v) { reinterpret_cast<RingWords>(q.put)[kHalfWords / 2u] = v; }
+// `bytes` of words at src (uniform, 4-byte aligned)
+__device__ __forceinline__ void words_open(Words &q, const uint32_t *src, uint32_t bytes, uint32_t ring) {
+    const uint64_t a = (uint64_t)src;
+    q.src = raw_window(reinterpret_cast<void *>((uint64_t)uniform((uint32_t)(a >> 32)) << 32 | uniform((uint32_t)a)), uniform(bytes));
+    q.next = 4u * (threadIdx.x & 63u);
+    q.ring = ring;
+    q.put = ring + q.next;
+    const uint32_t first = next_portion(q), second = next_portion(q);
+    q.ahead = next_portion(q);
+    put_first(q, first);
+    put_second(q, second);
     q.at = ring;
     q.end = ring + 2u * kHalfWords;
 }
@@ -567,11 +585,15 @@ __device__ __forceinline__ void words_open(Words &q, const uint32_t *src, uint32
 __device__ __forceinline__ void words_advance(Words &q, uint32_t n) {
     q.at += 2u * n;
     if (q.at >= q.end) {                                      // (uniform)
-        put_portion(q, q.portion & 1u, q.ahead);
-        ++q.portion;
-        if (q.end == q.ring + 4u * kHalfWords) { q.at -= 4u * kHalfWords; q.end -= 4u * kHalfWords; }
-        q.end += 2u * kHalfWords;
-        q.ahead = pair_at(q, q.portion);
+        if (q.end == q.ring + 2u * kHalfWords) {
+            put_first(q, q.ahead);
+            q.end = q.ring + 4u * kHalfWords;
+        } else {
+            put_second(q, q.ahead);
+            q.at -= 4u * kHalfWords;
+            q.end = q.ring + 2u * kHalfWords;
+        }
+        q.ahead = next_portion(q);
     }
 }
 
@@ -585,28 +607,30 @@ __device__ __forceinline__ uint32_t append_code(uint32_t entry, uint32_t d, int 
 // keeps them from taking words.  table: LDS address of the class's table, a multiple of its size, or (RANKS) of its
 // ranks and list.
 // A step is bound by instruction issue, so what the compiler would make more of than there is to it is pinned down by
-// empty asm statements: the comparison with a register, the word read by every lane, x + off before the product.
+// empty asm statements: the comparison with a register, the word read by every lane.
+// takes: a state below it takes a word (kRansLow; 0 for a class whose only code has f = 4096: its states never change, and
+// what they are does not matter, since every slot holds that code).
 template <int B, bool WHOLE, bool RANKS>
-__device__ __forceinline__ void decode_round(uint32_t *dst_row, uint32_t run, int valid, uint32_t table, Words &q, uint32_t &x) {
+__device__ __forceinline__ void decode_round(uint32_t *dst_row, uint32_t run, int valid, uint32_t table, uint32_t takes, Words &q,
+                                             uint32_t &x) {
     uint32_t d[B];
 #pragma unroll
     for (int k = 0; k < B; ++k) d[k] = 0;
-    uint32_t limit = valid > 0 ? kRansLow : 0u, mask = 4u * (kDecTableWords - 1u), base = table;
+    uint32_t limit = valid > 0 ? takes : 0u, mask = 4u * (kDecTableWords - 1u), base = table;
     asm("" : "+v"(limit), "+v"(mask), "+v"(base));
 #pragma unroll
     for (int j = 0; j < 32; ++j) {
         uint32_t entry, y;
-        const uint32_t xh = x >> kProbBits;
         if (RANKS) {
-            const uint32_t slot = frequency_slot(x);
+            const uint32_t xh = x >> kProbBits, slot = frequency_slot(x);
             entry = lds_at<uint32_t>(table + kProbScale + 4u * lds_at<uint8_t>(table + slot));
             y = xh + slot - ((entry >> 8) & 0xFFFu);
+            asm("" : "+v"(y));
+            y = __umul24(entry >> 20, xh) + y;                             // f <= 2^12, x >> 12 < 2^20
         } else {
             entry = lds_at<uint32_t>(bitop3<kAndOr>(x << 2, mask, base));
-            y = xh + ((entry >> 8) & 0xFFFu);
+            y = __umulhi(entry & 0xFFF00000u, x) + (uint32_t)((int)(entry << 12) >> 20);
         }
-        asm("" : "+v"(y));
-        y = __umul24(entry >> 20, xh) + y;                                 // f <= 2^12, x >> 12 < 2^20
         const int off = j * B, k = off >> 5, room = 32 - (off & 31);
         d[k] = append_code(entry, d[k], room < B ? room : B);
         if (room < B) d[k + 1 < B ? k + 1 : k] = (entry >> room) << (32 - (B - room));
@@ -682,17 +706,18 @@ k_rans_decode(const Params p, const EntropyLayout e, const uint8_t *__restrict__
 
     // ---- the tables
     uint32_t *scratch = lds + kDecLdsRings / 4u;
-    auto marks_at = [&](uint32_t place) { return scratch + place * kMarkWords; };
+    auto marks_at = [&](uint32_t place) { return scratch + place * 2u * kMarkWords; };
     auto list_at = [&](uint32_t place) {
-        return place < kDecTables ? scratch + kDecClasses * kMarkWords + place * 256u
+        return place < kDecTables ? scratch + kDecClasses * 2u * kMarkWords + place * 256u
                                   : lds + (kDecLdsLists + (place - kDecTables) * kDecListBytes + kProbScale) / 4u;
     };
     if (wv < n)
-        list_codes(reinterpret_cast<const uint16_t *>(eblob + e.off_tables) + ((class_at >> (4u * wv)) & 15u) * 256u, list_at(wv), marks_at(wv));
+        list_codes(reinterpret_cast<const uint16_t *>(eblob + e.off_tables) + ((class_at >> (4u * wv)) & 15u) * 256u, list_at(wv), marks_at(wv),
+                   wv >= kDecTables);
     __syncthreads();
     for (uint32_t place = 0; place < n; ++place) {
-        if (place < kDecTables) fill_table<false>(list_at(place), marks_at(place), lds + place * kDecTableWords, wv, kDecWaves);
-        else fill_table<true>(nullptr, marks_at(place), list_at(place) - kProbScale / 4u, wv, kDecWaves);
+        if (place < kDecTables) fill_table<false>(list_at(place), marks_at(place), lds + place * kDecTableWords);
+        else fill_table<true>(nullptr, marks_at(place), list_at(place) - kProbScale / 4u);
     }
     __syncthreads();
 
@@ -711,7 +736,8 @@ k_rans_decode(const Params p, const EntropyLayout e, const uint8_t *__restrict__
         uint32_t x = kRansLow;
         if (lane < coders) x = stream[lane];
         Words q;
-        words_open(q, stream + coders, (uint32_t)(c.b - c.a - 4u * coders) >> 1, stream, ring);
+        words_open(q, stream + coders, (uint32_t)(c.b - c.a - 4u * coders), ring);
+        const uint32_t takes = ranks || lds_at<uint32_t>(table) >> 20 ? kRansLow : 0u;
         uint32_t *dst_row = reinterpret_cast<uint32_t *>(blob + p.off_payload + c.po);
         for (uint32_t r = 0; r < rounds; ++r) {
             priority_by_progress(r, rounds);
@@ -719,13 +745,13 @@ k_rans_decode(const Params p, const EntropyLayout e, const uint8_t *__restrict__
             const int valid = (int)p.hidden - (int)(run * kRun);
 #define TSQ_DECODE_ROUND(WHOLE, RANKS) \
     switch (width) {                   \
-        case 2: decode_round<2, WHOLE, RANKS>(dst_row, run, valid, table, q, x); break;  \
-        case 3: decode_round<3, WHOLE, RANKS>(dst_row, run, valid, table, q, x); break;  \
-        case 4: decode_round<4, WHOLE, RANKS>(dst_row, run, valid, table, q, x); break;  \
-        case 5: decode_round<5, WHOLE, RANKS>(dst_row, run, valid, table, q, x); break;  \
-        case 6: decode_round<6, WHOLE, RANKS>(dst_row, run, valid, table, q, x); break;  \
-        case 7: decode_round<7, WHOLE, RANKS>(dst_row, run, valid, table, q, x); break;  \
-        default: decode_round<8, WHOLE, RANKS>(dst_row, run, valid, table, q, x); break; \
+        case 2: decode_round<2, WHOLE, RANKS>(dst_row, run, valid, table, takes, q, x); break;  \
+        case 3: decode_round<3, WHOLE, RANKS>(dst_row, run, valid, table, takes, q, x); break;  \
+        case 4: decode_round<4, WHOLE, RANKS>(dst_row, run, valid, table, takes, q, x); break;  \
+        case 5: decode_round<5, WHOLE, RANKS>(dst_row, run, valid, table, takes, q, x); break;  \
+        case 6: decode_round<6, WHOLE, RANKS>(dst_row, run, valid, table, takes, q, x); break;  \
+        case 7: decode_round<7, WHOLE, RANKS>(dst_row, run, valid, table, takes, q, x); break;  \
+        default: decode_round<8, WHOLE, RANKS>(dst_row, run, valid, table, takes, q, x); break; \
     }
             if (__builtin_amdgcn_ballot_w64(valid > 0 && valid < 32) == 0) {
                 if (ranks) {
