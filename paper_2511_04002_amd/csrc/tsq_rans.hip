@@ -474,33 +474,41 @@ constexpr uint32_t kDecLdsBytes = kDecLdsRings + kDecWaves * kRingWords * 2u;
 // words) and the number of those bits before each of these words, and behind them the lists of the classes with a table
 // (256 words each).
 constexpr uint32_t kMarkWords = 128, kDecClasses = kDecTables + kDecLists;
-static_assert((kDecClasses * 2u * kMarkWords + kDecTables * 256u) * 4u <= kDecWaves * kRingWords * 2u, "scratch of the table builders");
+static_assert((kDecClasses * 2u * kMarkWords + kDecTables * 256u + 2u) * 4u <= kDecWaves * kRingWords * 2u, "scratch of the table builders");
 static_assert(kDecClasses == 7, "a place for every width");
 static_assert(2u * kDecLdsBytes <= 160u * 1024u, "two workgroups per compute unit");
 
-// Step 1, by one wave per table: lane l takes the codes 4l .. 4l+3.  The codes that occur are listed in the form of a
-// list (RANKS), or with f in the place of f - 1; the slots where their ranges start are marked, and the marks counted.
-__device__ __forceinline__ void list_codes(const uint16_t *freq, uint32_t *list, uint32_t *starts, bool ranks) {
-    const uint32_t lane = threadIdx.x & 63u;
-    uint32_t f[4], s = 0, n = 0;
-    const uint2 four = *reinterpret_cast<const uint2 *>(freq + 4u * lane);
-    f[0] = four.x & 0xFFFFu; f[1] = four.x >> 16; f[2] = four.y & 0xFFFFu; f[3] = four.y >> 16;
+// Step 1, by one wave per class: lane l takes the codes 4l .. 4l+3, whose frequencies are f, cum and rank what lies before
+// them.  The codes that occur are listed in the form of a list (RANKS), or with f in the place of f - 1; the slots where
+// their ranges start are marked, and the marks counted.
+struct Codes {
+    uint32_t f[4], cum, rank;
+};
+__device__ __forceinline__ Codes codes_of(uint2 four) {
+    Codes c;
+    c.f[0] = four.x & 0xFFFFu; c.f[1] = four.x >> 16; c.f[2] = four.y & 0xFFFFu; c.f[3] = four.y >> 16;
+    uint32_t s = 0, n = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        s += f[i];
-        n += f[i] ? 1u : 0u;
+        s += c.f[i];
+        n += c.f[i] ? 1u : 0u;
     }
+    c.cum = wave_incl_scan_u32(s) - s;
+    c.rank = wave_incl_scan_u32(n) - n;
+    return c;
+}
+__device__ __forceinline__ void list_codes(Codes c, uint32_t *list, uint32_t *starts, bool ranks) {
+    const uint32_t lane = threadIdx.x & 63u;
     *reinterpret_cast<uint2 *>(starts + 2u * lane) = make_uint2(0u, 0u);
-    uint32_t cum = wave_incl_scan_u32(s) - s, rank = wave_incl_scan_u32(n) - n;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        if (f[i]) {
-            const uint32_t at = frequency_slot(cum);              // masked: a damaged table stays inside the array
-            list[rank] = ((ranks ? f[i] - 1u : f[i]) << 20) | (at << 8) | (4u * lane + i);
+        if (c.f[i]) {
+            const uint32_t at = frequency_slot(c.cum);            // masked: a damaged table stays inside the array
+            list[c.rank] = ((ranks ? c.f[i] - 1u : c.f[i]) << 20) | (at << 8) | (4u * lane + i);
             atomicOr(starts + (at >> 5), 1u << (at & 31u));
-            ++rank;
+            ++c.rank;
         }
-        cum += f[i];
+        c.cum += c.f[i];
     }
     const uint2 marks = *reinterpret_cast<const uint2 *>(starts + 2u * lane);
     const uint32_t a = (uint32_t)__builtin_popcount(marks.x), b = (uint32_t)__builtin_popcount(marks.y);
@@ -556,8 +564,11 @@ struct Words {
     uint32_t ring;             // ... of the wave's ring
     uint32_t at, end;          // ... of the next word, and of the end of the half it is in
 };
+__device__ __forceinline__ uint32_t load_word(__amdgpu_buffer_rsrc_t src, uint32_t at) {
+    return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(src, (int)at, 0, 0);
+}
 __device__ __forceinline__ uint32_t next_portion(Words &q) {
-    const uint32_t v = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(q.src, (int)q.next, 0, 0);
+    const uint32_t v = load_word(q.src, q.next);
     q.next += 2u * kHalfWords;
     return v;
 }
@@ -567,17 +578,22 @@ __device__ __forceinline__ void put_first(const Words &q, uint32_t v) {
     ring[kHalfWords] = v;                                     // (words are counted in pairs)
 }
 __device__ __forceinline__ void put_second(const Words &q, uint32_t v) { reinterpret_cast<RingWords>(q.put)[kHalfWords / 2u] = v; }
-// `bytes` of words at src (uniform, 4-byte aligned)
-__device__ __forceinline__ void words_open(Words &q, const uint32_t *src, uint32_t bytes, uint32_t ring) {
-    const uint64_t a = (uint64_t)src;
-    q.src = raw_window(reinterpret_cast<void *>((uint64_t)uniform((uint32_t)(a >> 32)) << 32 | uniform((uint32_t)a)), uniform(bytes));
-    q.next = 4u * (threadIdx.x & 63u);
+// The words of the stream in window src, from byte `first` on, are asked for; when the ring is the wave's, they go there.
+struct FirstWords {
+    uint32_t first, second, ahead, next;
+};
+__device__ __forceinline__ FirstWords ask_for_words(__amdgpu_buffer_rsrc_t src, uint32_t first) {
+    const uint32_t at = first + 4u * (threadIdx.x & 63u);
+    return {load_word(src, at), load_word(src, at + 2u * kHalfWords), load_word(src, at + 4u * kHalfWords), at + 6u * kHalfWords};
+}
+__device__ __forceinline__ void words_open(Words &q, __amdgpu_buffer_rsrc_t src, const FirstWords &w, uint32_t ring) {
+    q.src = src;
+    q.next = w.next;
+    q.ahead = w.ahead;
     q.ring = ring;
-    q.put = ring + q.next;
-    const uint32_t first = next_portion(q), second = next_portion(q);
-    q.ahead = next_portion(q);
-    put_first(q, first);
-    put_second(q, second);
+    q.put = ring + 4u * (threadIdx.x & 63u);
+    put_first(q, w.first);
+    put_second(q, w.second);
     q.at = ring;
     q.end = ring + 2u * kHalfWords;
 }
@@ -667,8 +683,59 @@ __device__ __forceinline__ void ask_for_token(const Params &p, const EntropyLayo
     k.a = off[t];
     k.b = off[t + 1];
 }
+// ... and what it has asked for: states and first words.  A damaged token (ok = 0) is skipped rather than read or written out
+// of bounds: its stream has no bytes.
+struct OpenToken {
+    uint32_t ok, width;
+    uint64_t po;
+    __amdgpu_buffer_rsrc_t stream;
+    uint32_t state;
+    FirstWords words;
+};
+__device__ __forceinline__ OpenToken open_token(const Params &p, const EntropyLayout &e, const uint8_t *eblob, const CodedToken &c, uint32_t coders) {
+    OpenToken o;
+    o.width = uniform(c.width);
+    o.po = c.po;
+    o.ok = token_in_range(p, o.width, c.po) && stream_span_ok(c.a, c.b, e.stream_capacity, coders, e.slot_bytes) ? 1u : 0u;
+    const uint64_t at = (uint64_t)(eblob + e.off_streams) + (o.ok ? c.a : 0u);
+    o.stream = raw_window(reinterpret_cast<void *>((uint64_t)uniform((uint32_t)(at >> 32)) << 32 | uniform((uint32_t)at)),
+                          uniform(o.ok ? (uint32_t)(c.b - c.a) : 0u));
+    o.state = load_word(o.stream, 4u * (threadIdx.x & 63u));
+    o.words = ask_for_words(o.stream, 4u * coders);
+    return o;
+}
 
-// Workgroup g decodes the tokens per * g .. per * g + per - 1, a token per wave and turn.
+// How many of the tokens t0 .. t1 - 1 have which width, and the places of the classes that occur, the most frequent first:
+// places 0 .. kDecTables - 1 are tables.  Four bits per class: its place; and the number of classes.  By one
+// wave (every wave for itself, with scalar comparisons, took 1.9 us of 8192 x 8192's 35).
+struct Places {
+    uint32_t place_of, n;
+};
+__device__ __forceinline__ Places places_of(const uint8_t *bits, uint32_t t0, uint32_t t1) {
+    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t count[kDecClasses] = {};
+    for (uint32_t i = t0; i < t1; i += 64u) {
+        const uint32_t b = i + lane < t1 ? bits[i + lane] : 0u;
+#pragma unroll
+        for (uint32_t k = 0; k < kDecClasses; ++k) count[k] += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(b == k + 2u));
+    }
+    // lane k: class k's count, and before it the lower class's that has the same
+    uint32_t mine = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kDecClasses; ++k) mine = lane == k ? (count[k] << 3) + 7u - k : mine;
+    uint32_t place = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kDecClasses; ++k) place += lane_value(mine, (int)k) > mine ? 1u : 0u;
+    const bool is_class = lane < kDecClasses;
+    Places r;
+    r.place_of = wave_sum_u32(is_class ? place << (4u * lane) : 0u);
+    r.n = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(is_class && (mine >> 3)));
+    return r;
+}
+
+// Workgroup g decodes the tokens per * g .. per * g + per - 1, a token per wave and turn.  Before the first one can start, its
+// workgroup's tables have to be laid out; the wave's first words and what the tables are made of are asked for together, and
+// only then waited for.
 __global__ void __launch_bounds__(kDecThreads, 8)    // 8 waves per SIMD: two workgroups per compute unit
 k_rans_decode(const Params p, const EntropyLayout e, const uint8_t *__restrict__ eblob, uint8_t *__restrict__ blob, uint32_t per) {
     extern __shared__ __align__(4 * kDecTableWords) uint32_t lds[];     // (tables, each at a multiple of its size; then the rings)
@@ -679,41 +746,28 @@ k_rans_decode(const Params p, const EntropyLayout e, const uint8_t *__restrict__
     const bool blob_ours = blob_is_plans<false>(p, blob), eblob_ours = eblob_is_valid(p, e, eblob);     // (both in one wait)
     if (!blob_ours || !eblob_ours) return;
     uint32_t t = t0 + wv;
-    CodedToken next = {};
-    if (t < t1) ask_for_token(p, e, blob, eblob, t, next);
-    // how many of the workgroup's tokens have width k + 2
-    uint32_t count[kDecClasses] = {};
-    for (uint32_t i = t0; i < t1; i += 64u) {
-        const uint32_t b = i + lane < t1 ? blob[p.off_bits + i + lane] : 0u;
-#pragma unroll
-        for (uint32_t k = 0; k < kDecClasses; ++k) count[k] += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(b == k + 2u));
-    }
-    // the places of the classes that occur, the most frequent first: places 0 .. kDecTables - 1 are tables.  Four bits
-    // per class: its place (place_of), and the class at a place (class_at)
-    uint32_t place_of = 0, class_at = 0, n = 0;
-#pragma unroll
-    for (uint32_t k = 0; k < kDecClasses; ++k) {
-        uint32_t place = 0;
-#pragma unroll
-        for (uint32_t o = 0; o < kDecClasses; ++o) place += count[o] > count[k] || (count[o] == count[k] && o < k) ? 1u : 0u;
-        place_of |= place << (4u * k);
-        class_at |= k << (4u * place);
-        n += count[k] ? 1u : 0u;
-    }
-    place_of = uniform(place_of);
-    class_at = uniform(class_at);
-    n = uniform(n);
+    // (a wave without a token looks at the last one's and decodes none)
+    CodedToken next;
+    ask_for_token(p, e, blob, eblob, t < t1 ? t : t1 - 1u, next);
+    const uint2 four = reinterpret_cast<const uint2 *>(eblob + e.off_tables)[(wv < kDecClasses ? wv : 0u) * 64u + lane];
 
     // ---- the tables
-    uint32_t *scratch = lds + kDecLdsRings / 4u;
+    uint32_t *scratch = lds + kDecLdsRings / 4u, *told = scratch + kDecClasses * 2u * kMarkWords + kDecTables * 256u;
     auto marks_at = [&](uint32_t place) { return scratch + place * 2u * kMarkWords; };
     auto list_at = [&](uint32_t place) {
         return place < kDecTables ? scratch + kDecClasses * 2u * kMarkWords + place * 256u
                                   : lds + (kDecLdsLists + (place - kDecTables) * kDecListBytes + kProbScale) / 4u;
     };
-    if (wv < n)
-        list_codes(reinterpret_cast<const uint16_t *>(eblob + e.off_tables) + ((class_at >> (4u * wv)) & 15u) * 256u, list_at(wv), marks_at(wv),
-                   wv >= kDecTables);
+    if (wv == kDecWaves - 1u) {
+        const Places r = places_of(blob + p.off_bits, t0, t1);
+        if (lane == 0) { told[0] = r.place_of; told[1] = r.n; }
+    }
+    OpenToken o = open_token(p, e, eblob, next, coders);
+    const Codes codes = codes_of(four);
+    __syncthreads();
+    const uint32_t place_of = uniform(told[0]), n = uniform(told[1]);
+    const uint32_t own = (place_of >> (4u * (wv < kDecClasses ? wv : 0u))) & 15u;      // the place of the class that this wave lists
+    if (wv < kDecClasses && own < n) list_codes(codes, list_at(own), marks_at(own), own >= kDecTables);
     __syncthreads();
     for (uint32_t place = 0; place < n; ++place) {
         if (place < kDecTables) fill_table<false>(list_at(place), marks_at(place), lds + place * kDecTableWords);
@@ -723,26 +777,21 @@ k_rans_decode(const Params p, const EntropyLayout e, const uint8_t *__restrict__
 
     const uint32_t ring = lds_address(lds) + kDecLdsRings + wv * kRingWords * 2u;
     // ---- the tokens
-    for (; t < t1; t += kDecWaves) {
-        const CodedToken c = next;
-        if (t + kDecWaves < t1) ask_for_token(p, e, blob, eblob, t + kDecWaves, next);
-        const uint32_t width = uniform(c.width);
-        // a damaged token is skipped rather than read or written out of bounds
-        if (!token_in_range(p, width, c.po) || !stream_span_ok(c.a, c.b, e.stream_capacity, coders, e.slot_bytes)) continue;
-        const uint32_t place = (place_of >> (4u * (width - 2u))) & 15u;
-        const bool ranks = place >= kDecTables;
-        const uint32_t table = lds_address(lds) + (ranks ? kDecLdsLists + (place - kDecTables) * kDecListBytes : place * (4u * kDecTableWords));
-        const uint32_t *stream = reinterpret_cast<const uint32_t *>(eblob + e.off_streams + c.a);
-        uint32_t x = kRansLow;
-        if (lane < coders) x = stream[lane];
-        Words q;
-        words_open(q, stream + coders, (uint32_t)(c.b - c.a - 4u * coders), ring);
-        const uint32_t takes = ranks || lds_at<uint32_t>(table) >> 20 ? kRansLow : 0u;
-        uint32_t *dst_row = reinterpret_cast<uint32_t *>(blob + p.off_payload + c.po);
-        for (uint32_t r = 0; r < rounds; ++r) {
-            priority_by_progress(r, rounds);
-            const uint32_t run = lane + 64u * r;
-            const int valid = (int)p.hidden - (int)(run * kRun);
+    while (t < t1) {
+        const uint32_t width = o.width;
+        if (o.ok) {
+            const uint32_t place = (place_of >> (4u * (width - 2u))) & 15u;
+            const bool ranks = place >= kDecTables;
+            const uint32_t table = lds_address(lds) + (ranks ? kDecLdsLists + (place - kDecTables) * kDecListBytes : place * (4u * kDecTableWords));
+            uint32_t x = lane < coders ? o.state : kRansLow;
+            Words q;
+            words_open(q, o.stream, o.words, ring);
+            const uint32_t takes = ranks || lds_at<uint32_t>(table) >> 20 ? kRansLow : 0u;
+            uint32_t *dst_row = reinterpret_cast<uint32_t *>(blob + p.off_payload + o.po);
+            for (uint32_t r = 0; r < rounds; ++r) {
+                priority_by_progress(r, rounds);
+                const uint32_t run = lane + 64u * r;
+                const int valid = (int)p.hidden - (int)(run * kRun);
 #define TSQ_DECODE_ROUND(WHOLE, RANKS) \
     switch (width) {                   \
         case 2: decode_round<2, WHOLE, RANKS>(dst_row, run, valid, table, takes, q, x); break;  \
@@ -753,18 +802,24 @@ k_rans_decode(const Params p, const EntropyLayout e, const uint8_t *__restrict__
         case 7: decode_round<7, WHOLE, RANKS>(dst_row, run, valid, table, takes, q, x); break;  \
         default: decode_round<8, WHOLE, RANKS>(dst_row, run, valid, table, takes, q, x); break; \
     }
-            if (__builtin_amdgcn_ballot_w64(valid > 0 && valid < 32) == 0) {
-                if (ranks) {
-                    TSQ_DECODE_ROUND(true, true)
+                if (__builtin_amdgcn_ballot_w64(valid > 0 && valid < 32) == 0) {
+                    if (ranks) {
+                        TSQ_DECODE_ROUND(true, true)
+                    } else {
+                        TSQ_DECODE_ROUND(true, false)
+                    }
+                } else if (ranks) {
+                    TSQ_DECODE_ROUND(false, true)
                 } else {
-                    TSQ_DECODE_ROUND(true, false)
+                    TSQ_DECODE_ROUND(false, false)
                 }
-            } else if (ranks) {
-                TSQ_DECODE_ROUND(false, true)
-            } else {
-                TSQ_DECODE_ROUND(false, false)
-            }
 #undef TSQ_DECODE_ROUND
+            }
+        }
+        t += kDecWaves;
+        if (t < t1) {
+            ask_for_token(p, e, blob, eblob, t, next);
+            o = open_token(p, e, eblob, next, coders);
         }
     }
 }
