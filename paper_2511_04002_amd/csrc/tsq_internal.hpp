@@ -126,7 +126,7 @@ inline __host__ __device__ uint32_t width_at(const Params &p, uint32_t i) {
 // Launch geometry fixed by the plan.
 struct Geometry {
     uint32_t block;         // threads per workgroup of unpack = 64 * ceil(runs / 64)
-    uint32_t lds_bytes;     // dynamic LDS of the staged row kernels and of unpack
+    uint32_t lds_bytes;     // dynamic LDS of the staged row kernels
     uint32_t waves;         // waves per workgroup of the compress kernels (an instantiated size >= block / 64)
     uint32_t lds_fused_bytes;  // dynamic LDS of the fused kernel: row, scratch, outlier stash
 };

@@ -437,13 +437,26 @@ int launch_pack(const Params &p, const Geometry &g, const void *d_in, void *d_bl
     return (int)hipGetLastError();
 }
 
+// LDS of a workgroup of k_unpack: its row.  Long calls wait for memory with as many waves as there are, so nothing but the row: 65536 x
+// 4096 f16 in 64 tensors 129.0 us with 28 waves a compute unit, 121.1 with 32; 60000 x 8192 bf16 225 / 217.  While the restored tensor fits
+// the 256 MB memory-side cache, waves that restore and waves that still read get in each other's way: rows of two and three
+// waves run 24 a compute unit, of four waves 28, by taking that share of its 160 KB (allocated by 1280 bytes): 4000 x 4096 bf16 12.1
+// us with 32 waves, 11.2 with 24; 32768 x 4096 f16 56.8 / 56.6; 16384 x 6144 bf16 42.6 / 42.5; 2000 x 8192 bf16 14.1 / 13.8 (28).
+// Rows of one wave, and of eight and more, gain nothing by fewer: 60000 x 1024 bf16 27.9 us with 32 waves, 34.0 with 24.
+static uint32_t unpack_lds_bytes(const Params &p, const Geometry &g) {
+    const uint32_t row = p.runs * kRunLdsDw * 4u, waves = g.block / 64u;
+    if (waves < 2u || waves > 4u || (uint64_t)p.tokens * p.hidden * 2u > (256ull << 20)) return row;
+    const uint32_t workgroups = waves == 4u ? 7u : 24u / waves, share = 160u * 1024u / workgroups / 1280u * 1280u;
+    return row > share ? row : share;
+}
 int launch_unpack(const Params &p, const Geometry &g, uint32_t group_log2, const void *d_blob, void *d_out, void *stream) {
     const dim3 grid(p.tokens), block(g.block);
+    const uint32_t lds = unpack_lds_bytes(p, g);
     if (p.dtype == kF16)
-        hipLaunchKernelGGL(k_unpack<kF16>, grid, block, g.lds_bytes, as_stream(stream), p,
+        hipLaunchKernelGGL(k_unpack<kF16>, grid, block, lds, as_stream(stream), p,
                            static_cast<const uint8_t *>(d_blob), static_cast<uint16_t *>(d_out), group_log2);
     else
-        hipLaunchKernelGGL(k_unpack<kBF16>, grid, block, g.lds_bytes, as_stream(stream), p,
+        hipLaunchKernelGGL(k_unpack<kBF16>, grid, block, lds, as_stream(stream), p,
                            static_cast<const uint8_t *>(d_blob), static_cast<uint16_t *>(d_out), group_log2);
     return (int)hipGetLastError();
 }
