@@ -36,6 +36,13 @@ __device__ __forceinline__ uint32_t pk_ashr15_i16(uint32_t a) {
     return __builtin_bit_cast(uint32_t, (i16x2)(__builtin_bit_cast(i16x2, a) >> 15));
 }
 
+// A value that the compiler is to keep in a vector register: binary32 multiplies and the simplest integer instructions take
+// half the issue time with vector operands only (2.3 cycles against 4.2).
+template <typename T> __device__ __forceinline__ T in_vector(T v) {
+    asm("" : "+v"(v));
+    return v;
+}
+
 // ---------------------------------------------------------------- wave / block collectives
 
 // DPP controls (gfx9): quad_perm [1,0,3,2] and [2,3,0,1], mirror inside 8 lanes, mirror inside a
@@ -369,8 +376,11 @@ __device__ __forceinline__ float mul_f16_hi(uint32_t pk, float r) {
 // tie rows of the parity tests) and saturates at 255.  A clamp min(., Q) to the code range never
 // binds: a <= amax and r = fl(Q/amax) give a*r <= Q*(1+2^-24)^2 < Q + 1/2, so rint already
 // yields at most Q.
+// (r in a vector register: 131072 x 8192 bf16 685 us -> 675, 8192 x 8192 47.0 / 46.4, 60000 x 1024 82.1 / 80.4.  The same for the
+// constants of the split or of sad_run costs the long calls 2 to 5 %: the persistent kernel has no registers left for them.)
 template <int DT>
 __device__ __forceinline__ void quantize_run(const Mags<DT> &mg, float r, uint32_t (&m)[8]) {
+    r = in_vector(r);
 #pragma unroll
     for (int g = 0; g < 8; ++g) {
         uint32_t acc = 0;
@@ -470,13 +480,6 @@ __device__ __forceinline__ void pack_regs(const uint32_t (&m)[8], const uint32_t
             filled -= 32;
         }
     }
-}
-
-// A value that the compiler is to keep in a vector register: binary32 multiplies and the simplest integer instructions take
-// half the issue time with vector operands only (2.3 cycles against 4.2).
-template <typename T> __device__ __forceinline__ T in_vector(T v) {
-    asm("" : "+v"(v));
-    return v;
 }
 
 // The run's 32 codes a byte each, code 4g+k in byte k of c[g]; the bits above a code's B are anything.
