@@ -625,6 +625,23 @@ __device__ __forceinline__ uint32_t append_code(uint32_t entry, uint32_t d, int 
     return __builtin_amdgcn_alignbit(entry, d, bits);
 }
 
+// store_run_words with streaming stores: for codes that would not be in the caches any more when somebody reads them.
+template <int B>
+__device__ __forceinline__ void store_run_words_past_caches(uint32_t *dst, const uint32_t (&d)[B]) {
+    int k = 0;
+#pragma unroll
+    for (; k + 4 <= B; k += 4) {
+        Words4 v; v.x = d[k]; v.y = d[k + 1]; v.z = d[k + 2]; v.w = d[k + 3];
+        __builtin_nontemporal_store(v, reinterpret_cast<Words4 *>(dst + k));
+    }
+    if (k + 2 <= B) {
+        Words2 v; v.x = d[k]; v.y = d[k + 1];
+        __builtin_nontemporal_store(v, reinterpret_cast<Words2 *>(dst + k));
+        k += 2;
+    }
+    if (k < B) __builtin_nontemporal_store(d[k], dst + k);
+}
+
 // The 32 steps of one round (a lane's run number `run`).  WHOLE: every lane's run lies inside the row or wholly
 // beyond it (valid >= 32 or <= 0): no step needs a range check, the lanes beyond the row run idle with a limit that
 // keeps them from taking words.  table: LDS address of the class's table, a multiple of its size, or (RANKS) of its
@@ -633,7 +650,7 @@ __device__ __forceinline__ uint32_t append_code(uint32_t entry, uint32_t d, int 
 // empty asm statements: the comparison with a register, the word read by every lane.
 // takes: a state below it takes a word (kRansLow; 0 for a class whose only code has f = 4096: its states never change, and
 // what they are does not matter, since every slot holds that code).
-template <int B, bool WHOLE, bool RANKS>
+template <int B, bool WHOLE, bool RANKS, bool PAST_CACHES>
 __device__ __forceinline__ void decode_round(uint32_t *dst_row, uint32_t run, int valid, uint32_t table, uint32_t takes, Words &q,
                                              uint32_t &x) {
     uint32_t d[B];
@@ -667,7 +684,10 @@ __device__ __forceinline__ void decode_round(uint32_t *dst_row, uint32_t run, in
         words_advance(q, (uint32_t)__builtin_popcountll(who));
     }
     if (WHOLE) {
-        if (valid > 0) store_run_words<B>(dst_row + run * B, d);
+        if (valid > 0) {
+            if (PAST_CACHES) store_run_words_past_caches<B>(dst_row + run * B, d);
+            else store_run_words<B>(dst_row + run * B, d);
+        }
     } else {
         // what the steps beyond the end of the row left in the last word goes
         const int bits = (valid < 32 ? valid : 32) * B;
@@ -743,6 +763,7 @@ __device__ __forceinline__ Places places_of(const uint8_t *bits, uint32_t t0, ui
 // Workgroup g decodes the tokens per * g .. per * g + per - 1, a token per wave and turn.  Before the first one can start, its
 // workgroup's tables have to be laid out; the wave's first words and what the tables are made of are asked for together, and
 // only then waited for.
+template <bool PAST_CACHES>
 __global__ void __launch_bounds__(kDecThreads, 8)    // 8 waves per SIMD: two workgroups per compute unit
 k_rans_decode(const Params p, const EntropyLayout e, const uint8_t *__restrict__ eblob, uint8_t *__restrict__ blob, uint32_t per) {
     extern __shared__ __align__(4 * kDecTableWords) uint32_t lds[];     // (tables, each at a multiple of its size; then the rings)
@@ -801,13 +822,13 @@ k_rans_decode(const Params p, const EntropyLayout e, const uint8_t *__restrict__
                 const int valid = (int)p.hidden - (int)(run * kRun);
 #define TSQ_DECODE_ROUND(WHOLE, RANKS) \
     switch (width) {                   \
-        case 2: decode_round<2, WHOLE, RANKS>(dst_row, run, valid, table, takes, q, x); break;  \
-        case 3: decode_round<3, WHOLE, RANKS>(dst_row, run, valid, table, takes, q, x); break;  \
-        case 4: decode_round<4, WHOLE, RANKS>(dst_row, run, valid, table, takes, q, x); break;  \
-        case 5: decode_round<5, WHOLE, RANKS>(dst_row, run, valid, table, takes, q, x); break;  \
-        case 6: decode_round<6, WHOLE, RANKS>(dst_row, run, valid, table, takes, q, x); break;  \
-        case 7: decode_round<7, WHOLE, RANKS>(dst_row, run, valid, table, takes, q, x); break;  \
-        default: decode_round<8, WHOLE, RANKS>(dst_row, run, valid, table, takes, q, x); break; \
+        case 2: decode_round<2, WHOLE, RANKS, PAST_CACHES>(dst_row, run, valid, table, takes, q, x); break;  \
+        case 3: decode_round<3, WHOLE, RANKS, PAST_CACHES>(dst_row, run, valid, table, takes, q, x); break;  \
+        case 4: decode_round<4, WHOLE, RANKS, PAST_CACHES>(dst_row, run, valid, table, takes, q, x); break;  \
+        case 5: decode_round<5, WHOLE, RANKS, PAST_CACHES>(dst_row, run, valid, table, takes, q, x); break;  \
+        case 6: decode_round<6, WHOLE, RANKS, PAST_CACHES>(dst_row, run, valid, table, takes, q, x); break;  \
+        case 7: decode_round<7, WHOLE, RANKS, PAST_CACHES>(dst_row, run, valid, table, takes, q, x); break;  \
+        default: decode_round<8, WHOLE, RANKS, PAST_CACHES>(dst_row, run, valid, table, takes, q, x); break; \
     }
                 if (__builtin_amdgcn_ballot_w64(valid > 0 && valid < 32) == 0) {
                     if (ranks) {
@@ -850,15 +871,22 @@ int launch_rans_encode(const Params &p, const EntropyLayout &e, const void *d_bl
 }
 
 int prepare_rans_kernels() {
-    return (int)hipFuncSetAttribute(reinterpret_cast<const void *>(k_rans_decode), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)kDecLdsBytes);
+    for (const void *kernel : {reinterpret_cast<const void *>(k_rans_decode<false>), reinterpret_cast<const void *>(k_rans_decode<true>)}) {
+        const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDecLdsBytes);
+        if (e != hipSuccess) return (int)e;
+    }
+    return 0;
 }
 
 int launch_rans_decode(const Params &p, const EntropyLayout &e, const void *d_eblob, void *d_blob, void *stream) {
     // one round of workgroups (two on each of 256 compute units), a token per wave if there are enough of them;
     // fewer tokens are spread over as many workgroups as there are
     const uint32_t per = (p.tokens + kMaxDecodeGroups - 1u) / kMaxDecodeGroups;
-    hipLaunchKernelGGL(k_rans_decode, dim3((p.tokens + per - 1u) / per), dim3(kDecThreads), kDecLdsBytes, as_stream(stream), p, e,
+    // Codes of more than about 96 MB (at the largest width) are not in the memory-side cache any more when restore reads them, and
+    // on their way there they push out the streams: they bypass it.  32768 x 4096 f16 67.9 us -> 63.6, with restore behind it 144.5 /
+    // 135.0; 8192 x 8192 bf16 by itself 34.5 / 33.1, but with restore behind it 69.4 / 71.3.
+    const auto kernel = p.payload_capacity > (96ull << 20) ? k_rans_decode<true> : k_rans_decode<false>;
+    hipLaunchKernelGGL(kernel, dim3((p.tokens + per - 1u) / per), dim3(kDecThreads), kDecLdsBytes, as_stream(stream), p, e,
                        static_cast<const uint8_t *>(d_eblob), static_cast<uint8_t *>(d_blob), per);
     return (int)hipGetLastError();
 }
