@@ -384,14 +384,21 @@ k_direct_group(const Params p, const uint16_t *__restrict__ in, uint8_t *__restr
     const uint32_t left = FULL ? 4u : (owns ? pieces - 4u * run : 0u);    // 16-byte pieces of the lane's run inside the row
     uint32_t *lrow = lds + g * runs * 24u, *image = lrow + runs * 16u, *exchange = lds + G * runs * 24u, *ring = exchange + kGroupExchange;
 
-    u32x4 piece[4] = {};
+    // (a token that is not there: the last one's row, whose results are dropped; the pieces as scalars: as vectors the loads of
+    // rows that end inside a wave waited for one another)
+    RowPart piece;
     const uint32_t q0 = 256u * part + lane;
-    if (have) {
-        const GlobalBytes src = (GlobalBytes)row_address(p, in, t, FULL ? 2048u * NW : p.hidden);
+    {
+        const GlobalBytes src = (GlobalBytes)row_address(p, in, have ? t : p.tokens - 1u, FULL ? 2048u * NW : p.hidden);
 #pragma unroll
-        for (uint32_t k = 0; k < 4; ++k)
-            if (FULL || q0 + 64u * k < pieces)
-                piece[k] = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4 *)(src + 16u * q0 + 1024u * k));
+        for (uint32_t k = 0; k < 4; ++k) {
+            uint32_t x = 0, y = 0, z = 0, w = 0;
+            if (FULL || q0 + 64u * k < pieces) {
+                const u32x4 v = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4 *)(src + 16u * q0 + 1024u * k));
+                x = v.x; y = v.y; z = v.z; w = v.w;
+            }
+            piece.w[4 * k] = x; piece.w[4 * k + 1] = y; piece.w[4 * k + 2] = z; piece.w[4 * k + 3] = w;
+        }
     }
     // error word, shape and epoch of the workspace, one per lane of one load
     uint32_t *ctrl = reinterpret_cast<uint32_t *>(ws + p.ws_ctrl);
@@ -408,7 +415,9 @@ k_direct_group(const Params p, const uint16_t *__restrict__ in, uint8_t *__restr
 #pragma unroll
     for (uint32_t k = 0; k < 4; ++k) {
         const uint32_t q = q0 + 64u * k, r = q >> 2, c = (q & 3u) ^ ((r >> 1) & 3u);
-        if (FULL || r < runs) *reinterpret_cast<u32x4 *>(lrow + r * 16u + c * 4u) = piece[k];
+        if (FULL || r < runs)
+            *reinterpret_cast<uint4 *>(lrow + r * 16u + c * 4u) =
+                make_uint4(piece.w[4 * k], piece.w[4 * k + 1], piece.w[4 * k + 2], piece.w[4 * k + 3]);
     }
     Mags<DT> mg;
     uint32_t omask = 0, amax_bits = 0, turn = 0;
