@@ -57,6 +57,22 @@ __device__ __forceinline__ void pack_codes(const uint32_t (&m)[8], const uint32_
     for (int k = 0; k < 8; ++k) o[k] = k < B ? t[k] : 0u;
 }
 
+// The pieces q, q + 64, q + 128 and q + 192 (16 bytes each) of a row at a uniform address, zeros for those behind its end, which
+// the memory pipeline checks: a branch per piece made the loads of some rows wait for one another, and took its time where
+// nothing else is to do.  Streaming: the input is read once.
+template <bool FULL>
+__device__ __forceinline__ void fetch_row_once(const uint16_t *row, uint32_t pieces, uint32_t q, RowPart &part) {
+    const GlobalBytes src = (GlobalBytes)row;
+    const __amdgpu_buffer_rsrc_t window = raw_window(const_cast<uint16_t *>(row), 16u * pieces);
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+        u32x4 v;
+        if constexpr (FULL) v = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4 *)(src + 16u * q + 1024u * k));
+        else v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(window, (int)(16u * q + 1024u * k), 0, 2));
+        part.w[4 * k] = v.x; part.w[4 * k + 1] = v.y; part.w[4 * k + 2] = v.z; part.w[4 * k + 3] = v.w;
+    }
+}
+
 // The last workgroup's first wave closes the blob, also if its own wait has expired (nobody else writes a header).
 // raised: the error word as it was before that workgroup published its size.
 __device__ __forceinline__ void close_blob(const Params &p, uint8_t *blob, uint32_t *tickets, uint32_t *error_flag, uint32_t epoch,
@@ -93,7 +109,7 @@ k_direct(const Params p, const uint16_t *__restrict__ in, uint8_t *__restrict__ 
     const bool last = t == p.tokens - 1u;
 
     RowPart part;
-    fetch_row_part<FULL>(reinterpret_cast<const uint4 *>(row_address(p, in, t, FULL ? 2048u * NW : p.hidden)), pieces, part);
+    fetch_row_once<FULL>(row_address(p, in, t, FULL ? 2048u * NW : p.hidden), pieces, 256u * wv + lane, part);
 
     // error word, shape and epoch of the workspace, one per lane of one load
     uint32_t *ctrl = reinterpret_cast<uint32_t *>(ws + p.ws_ctrl);
@@ -384,22 +400,10 @@ k_direct_group(const Params p, const uint16_t *__restrict__ in, uint8_t *__restr
     const uint32_t left = FULL ? 4u : (owns ? pieces - 4u * run : 0u);    // 16-byte pieces of the lane's run inside the row
     uint32_t *lrow = lds + g * runs * 24u, *image = lrow + runs * 16u, *exchange = lds + G * runs * 24u, *ring = exchange + kGroupExchange;
 
-    // (a token that is not there: the last one's row, whose results are dropped; the pieces as scalars: as vectors the loads of
-    // rows that end inside a wave waited for one another)
+    // (a token that is not there: the last one's row, whose results are dropped)
     RowPart piece;
     const uint32_t q0 = 256u * part + lane;
-    {
-        const GlobalBytes src = (GlobalBytes)row_address(p, in, have ? t : p.tokens - 1u, FULL ? 2048u * NW : p.hidden);
-#pragma unroll
-        for (uint32_t k = 0; k < 4; ++k) {
-            uint32_t x = 0, y = 0, z = 0, w = 0;
-            if (FULL || q0 + 64u * k < pieces) {
-                const u32x4 v = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4 *)(src + 16u * q0 + 1024u * k));
-                x = v.x; y = v.y; z = v.z; w = v.w;
-            }
-            piece.w[4 * k] = x; piece.w[4 * k + 1] = y; piece.w[4 * k + 2] = z; piece.w[4 * k + 3] = w;
-        }
-    }
+    fetch_row_once<FULL>(row_address(p, in, have ? t : p.tokens - 1u, FULL ? 2048u * NW : p.hidden), pieces, q0, piece);
     // error word, shape and epoch of the workspace, one per lane of one load
     uint32_t *ctrl = reinterpret_cast<uint32_t *>(ws + p.ws_ctrl);
     uint32_t *tickets = reinterpret_cast<uint32_t *>(ws + p.ws_tickets);
