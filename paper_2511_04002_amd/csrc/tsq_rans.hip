@@ -625,7 +625,7 @@ __device__ __forceinline__ uint32_t append_code(uint32_t entry, uint32_t d, int 
     return __builtin_amdgcn_alignbit(entry, d, bits);
 }
 
-// store_run_words with streaming stores: for codes that would not be in the caches any more when somebody reads them.
+// store_run_words with streaming stores: see kCachedCodes.
 template <int B>
 __device__ __forceinline__ void store_run_words_past_caches(uint32_t *dst, const uint32_t (&d)[B]) {
     int k = 0;
@@ -650,9 +650,9 @@ __device__ __forceinline__ void store_run_words_past_caches(uint32_t *dst, const
 // empty asm statements: the comparison with a register, the word read by every lane.
 // takes: a state below it takes a word (kRansLow; 0 for a class whose only code has f = 4096: its states never change, and
 // what they are does not matter, since every slot holds that code).
-template <int B, bool WHOLE, bool RANKS, bool PAST_CACHES>
-__device__ __forceinline__ void decode_round(uint32_t *dst_row, uint32_t run, int valid, uint32_t table, uint32_t takes, Words &q,
-                                             uint32_t &x) {
+template <int B, bool WHOLE, bool RANKS>
+__device__ __forceinline__ void decode_round(uint32_t *dst_row, uint32_t run, int valid, uint32_t table, uint32_t takes, bool past_caches,
+                                             Words &q, uint32_t &x) {
     uint32_t d[B];
 #pragma unroll
     for (int k = 0; k < B; ++k) d[k] = 0;
@@ -685,8 +685,14 @@ __device__ __forceinline__ void decode_round(uint32_t *dst_row, uint32_t run, in
     }
     if (WHOLE) {
         if (valid > 0) {
-            if (PAST_CACHES) store_run_words_past_caches<B>(dst_row + run * B, d);
-            else store_run_words<B>(dst_row + run * B, d);
+            if (past_caches) {                                // (uniform)
+                // (the fences keep the two forms apart: the compiler makes one of them, an ordinary store, where it can)
+                asm volatile("" ::: "memory");
+                store_run_words_past_caches<B>(dst_row + run * B, d);
+                asm volatile("" ::: "memory");
+            } else {
+                store_run_words<B>(dst_row + run * B, d);
+            }
         }
     } else {
         // what the steps beyond the end of the row left in the last word goes
@@ -760,10 +766,20 @@ __device__ __forceinline__ Places places_of(const uint8_t *bits, uint32_t t0, ui
     return r;
 }
 
+// A call that writes more than kCachedCodes bytes of codes stores them past the caches: restore finds few of them there by the
+// time it reads them, and on their way they push out the streams.  Up to there restore reads them from the memory-side cache (256
+// MB), which is worth more to the two calls than what decode gains by itself.  Decode with restore behind it, stored past the
+// caches against not: 25 MB of codes (13000 x 8192 bf16 at two bits) 101.1 us / 88.7, 107 MB (16384 x 8192 f16) 123.1 / 117.7, 130 MB
+// (20000 x 8192 bf16) 154.5 / 145.6; 158 MB (40000 x 5120 f16) 207.9 / 217.1, 206 MB (65536 x 4096 f16) 252.8 / 264.1, 198 MB (50000 x
+// 5120) 252.8 / 269.6; rows of 8192 and more differ by 4 % either way from 150 to 250 MB.  Decode by itself: 13000 x 8192 48.5 /
+// 50.0, 16384 x 8192 57.6 / 60.2, 20000 x 8192 73.2 / 74.8, 65536 x 4096 125.1 / 129.4.
+// The bytes are those that the blob holds: what the plan has room for says little about them (a line at 96 MB of room for the largest
+// width sent the 25 MB of the first example past the caches).
+constexpr uint64_t kCachedCodes = 160ull << 20;
+
 // Workgroup g decodes the tokens per * g .. per * g + per - 1, a token per wave and turn.  Before the first one can start, its
 // workgroup's tables have to be laid out; the wave's first words and what the tables are made of are asked for together, and
 // only then waited for.
-template <bool PAST_CACHES>
 __global__ void __launch_bounds__(kDecThreads, 8)    // 8 waves per SIMD: two workgroups per compute unit
 k_rans_decode(const Params p, const EntropyLayout e, const uint8_t *__restrict__ eblob, uint8_t *__restrict__ blob, uint32_t per) {
     extern __shared__ __align__(4 * kDecTableWords) uint32_t lds[];     // (tables, each at a multiple of its size; then the rings)
@@ -773,6 +789,7 @@ k_rans_decode(const Params p, const EntropyLayout e, const uint8_t *__restrict__
     const uint32_t rounds = (p.runs + 63u) / 64u;
     const bool blob_ours = blob_is_plans<false>(p, blob), eblob_ours = eblob_is_valid(p, e, eblob);     // (both in one wait)
     if (!blob_ours || !eblob_ours) return;
+    const bool past_caches = reinterpret_cast<const BlobHeader *>(blob)->payload_bytes > kCachedCodes;
     uint32_t t = t0 + wv;
     // (a wave without a token looks at the last one's and decodes none)
     CodedToken next;
@@ -822,13 +839,13 @@ k_rans_decode(const Params p, const EntropyLayout e, const uint8_t *__restrict__
                 const int valid = (int)p.hidden - (int)(run * kRun);
 #define TSQ_DECODE_ROUND(WHOLE, RANKS) \
     switch (width) {                   \
-        case 2: decode_round<2, WHOLE, RANKS, PAST_CACHES>(dst_row, run, valid, table, takes, q, x); break;  \
-        case 3: decode_round<3, WHOLE, RANKS, PAST_CACHES>(dst_row, run, valid, table, takes, q, x); break;  \
-        case 4: decode_round<4, WHOLE, RANKS, PAST_CACHES>(dst_row, run, valid, table, takes, q, x); break;  \
-        case 5: decode_round<5, WHOLE, RANKS, PAST_CACHES>(dst_row, run, valid, table, takes, q, x); break;  \
-        case 6: decode_round<6, WHOLE, RANKS, PAST_CACHES>(dst_row, run, valid, table, takes, q, x); break;  \
-        case 7: decode_round<7, WHOLE, RANKS, PAST_CACHES>(dst_row, run, valid, table, takes, q, x); break;  \
-        default: decode_round<8, WHOLE, RANKS, PAST_CACHES>(dst_row, run, valid, table, takes, q, x); break; \
+        case 2: decode_round<2, WHOLE, RANKS>(dst_row, run, valid, table, takes, past_caches, q, x); break;  \
+        case 3: decode_round<3, WHOLE, RANKS>(dst_row, run, valid, table, takes, past_caches, q, x); break;  \
+        case 4: decode_round<4, WHOLE, RANKS>(dst_row, run, valid, table, takes, past_caches, q, x); break;  \
+        case 5: decode_round<5, WHOLE, RANKS>(dst_row, run, valid, table, takes, past_caches, q, x); break;  \
+        case 6: decode_round<6, WHOLE, RANKS>(dst_row, run, valid, table, takes, past_caches, q, x); break;  \
+        case 7: decode_round<7, WHOLE, RANKS>(dst_row, run, valid, table, takes, past_caches, q, x); break;  \
+        default: decode_round<8, WHOLE, RANKS>(dst_row, run, valid, table, takes, past_caches, q, x); break; \
     }
                 if (__builtin_amdgcn_ballot_w64(valid > 0 && valid < 32) == 0) {
                     if (ranks) {
@@ -871,22 +888,14 @@ int launch_rans_encode(const Params &p, const EntropyLayout &e, const void *d_bl
 }
 
 int prepare_rans_kernels() {
-    for (const void *kernel : {reinterpret_cast<const void *>(k_rans_decode<false>), reinterpret_cast<const void *>(k_rans_decode<true>)}) {
-        const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDecLdsBytes);
-        if (e != hipSuccess) return (int)e;
-    }
-    return 0;
+    return (int)hipFuncSetAttribute(reinterpret_cast<const void *>(k_rans_decode), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDecLdsBytes);
 }
 
 int launch_rans_decode(const Params &p, const EntropyLayout &e, const void *d_eblob, void *d_blob, void *stream) {
     // one round of workgroups (two on each of 256 compute units), a token per wave if there are enough of them;
     // fewer tokens are spread over as many workgroups as there are
     const uint32_t per = (p.tokens + kMaxDecodeGroups - 1u) / kMaxDecodeGroups;
-    // Codes of more than about 96 MB (at the largest width) are not in the memory-side cache any more when restore reads them, and
-    // on their way there they push out the streams: they bypass it.  32768 x 4096 f16 67.9 us -> 63.6, with restore behind it 144.5 /
-    // 135.0; 8192 x 8192 bf16 by itself 34.5 / 33.1, but with restore behind it 69.4 / 71.3.
-    const auto kernel = p.payload_capacity > (96ull << 20) ? k_rans_decode<true> : k_rans_decode<false>;
-    hipLaunchKernelGGL(kernel, dim3((p.tokens + per - 1u) / per), dim3(kDecThreads), kDecLdsBytes, as_stream(stream), p, e,
+    hipLaunchKernelGGL(k_rans_decode, dim3((p.tokens + per - 1u) / per), dim3(kDecThreads), kDecLdsBytes, as_stream(stream), p, e,
                        static_cast<const uint8_t *>(d_eblob), static_cast<uint8_t *>(d_blob), per);
     return (int)hipGetLastError();
 }
