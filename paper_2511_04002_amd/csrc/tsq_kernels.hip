@@ -437,17 +437,26 @@ int launch_pack(const Params &p, const Geometry &g, const void *d_in, void *d_bl
     return (int)hipGetLastError();
 }
 
-// LDS of a workgroup of k_unpack: its row.  Long calls wait for memory with as many waves as there are, so nothing but the row: 65536 x
-// 4096 f16 in 64 tensors 129.0 us with 28 waves a compute unit, 121.1 with 32; 60000 x 8192 bf16 225 / 217.  While the restored tensor fits
-// the 256 MB memory-side cache, waves that restore and waves that still read get in each other's way: rows of two and three
-// waves run 24 a compute unit, of four waves 28, by taking that share of its 160 KB (allocated by 1280 bytes): 4000 x 4096 bf16 12.1
-// us with 32 waves, 11.2 with 24; 32768 x 4096 f16 56.8 / 56.6; 16384 x 6144 bf16 42.6 / 42.5; 2000 x 8192 bf16 14.1 / 13.8 (28).
-// Rows of one wave, and of eight and more, gain nothing by fewer: 60000 x 1024 bf16 27.9 us with 32 waves, 34.0 with 24.
+// LDS of a workgroup of k_unpack: its row, or the share of a compute unit's 160 KB (allocated by 1280 bytes) that keeps the number
+// of workgroups there down.  With as many waves as fit, waves that restore and waves that still read get in each other's way where the codes come
+// from the caches; where they come from memory, every wave more helps.  Both sides of each line, a call repeated on its buffers ("again") and
+// calls that go round 1 GB of buffers, as a receiver's do whose blob has just arrived ("new"), bf16 at 0.05 (6 to 7 bits) unless 0.2 (4 to 5 bits) is said:
+//   restored tensor up to 256 MB, rows that fill two or three waves: 24 waves a compute unit against 32: 4096 columns, 250 MB, again 0.2 49.5
+//     us / 51.0, new 0.2 50.3 / 51.4, new 67.1 / 63.3; 6144, 250 MB, again 0.2 48.6 / 49.7, new 64.5 / 61.9; 128 MB again 0.2 26.1 / 26.5, new 34.2 / 32.9;
+//   rows that leave a third of two waves' lanes without a run: 32 (24 are too little in flight): 2304 columns, 160 MB, again 36.6 against 40.2 with
+//     24, new 49.0 / 53.2; 2688 47.2 / 51.4, 2504, 250 MB, new 73.2 / 82.6.  (28 for 3400 columns: 250 MB again 0.2 57.0 against 52.7 with 24, new 67.5 / 70.3.)
+//   rows that leave a sixth of three waves' lanes without one: as many lanes with a run as the full rows have, 27 or 30 waves: 5120 columns, 250 MB, new
+//     68.0 against 70.5 with 24, again 54.2 / 53.1, again 0.2 48.0 / 49.1; 4608 new 66.5 / 72.8; 4104 68.6 / 75.8.  (27 for 5400 columns: again 0.2 54.7 / 51.2.)
+//   rows of four waves: 28 against 32: 2048 x 8192 again 8.5 / 8.7, new 14.1 / 14.3; 250 MB, 0.5 (two bits) again 41.6 / 44.0; but 64 MB new 22.9 / 22.2;
+//   beyond 256 MB: all that fit.  4096 columns, 512 MB: again 110 against 109 with 24, 0.2 99.7 / 97.3, at two bits 91 / 79; but new 122 / 139, 0.2 118 / 132.
+// Rows of one wave gain nothing by fewer (60000 x 1024 27.9 us with 32, 34.0 with 24), nor do rows of eight and more where the blob is new: 16384
+// columns, 200 MB, new 49.6 against 52.1 with 24, again 43.7 / 43.4.
 static uint32_t unpack_lds_bytes(const Params &p, const Geometry &g) {
     const uint32_t row = p.runs * kRunLdsDw * 4u, waves = g.block / 64u;
-    if (waves < 2u || waves > 4u || (uint64_t)p.tokens * p.hidden * 2u > (256ull << 20)) return row;
-    const uint32_t workgroups = waves == 4u ? 7u : 24u / waves, share = 160u * 1024u / workgroups / 1280u * 1280u;
-    return row > share ? row : share;
+    if (waves < 2u || waves > 4u || (waves == 2u && 3u * p.runs <= 4u * 64u) || (uint64_t)p.tokens * p.hidden * 2u > (256ull << 20)) return row;
+    // (80 bytes of row a run; a share is 91 to 106 of them, less the granule: never below the row)
+    const uint32_t workgroups = waves == 4u ? 7u : waves == 3u && 6u * p.runs <= 5u * 64u * 3u ? 24u * 64u / p.runs : 24u / waves;
+    return 160u * 1024u / workgroups / 1280u * 1280u;
 }
 int launch_unpack(const Params &p, const Geometry &g, uint32_t group_log2, const void *d_blob, void *d_out, void *stream) {
     const dim3 grid(p.tokens), block(g.block);
