@@ -178,7 +178,8 @@ tsq_status tsq_plan_create(const tsq_config *cfg, tsq_plan **out) {
     // (never below sixteen sets of seven full tables: the least that the size has always held besides lengths and slots)
     const uint64_t sets = (uint64_t)E.pool_groups * kPoolSetWords, least = 16ull * 7 * 256;
     E.ws_pooled = ew;  ew = align_up(ew + (sets > least ? sets : least) * 4, 256);
-    E.ws_parts = ew;   ew = align_up(ew + (uint64_t)kMaxTableSlices * 7ull * 256 * 4, 256);
+    const uint64_t slices = (E.pool_groups + kTableSlice - 1u) / kTableSlice;
+    E.ws_parts = ew;   ew = align_up(ew + (slices > 1u ? slices * kPoolSetWords * 4ull : 0ull), 256);
     E.ws_arrived = ew; ew = align_up(ew + 7ull * kBlockStride * 4, 256);
     E.ws_block = ew;   ew = align_up(ew + 4ull * kBlockStride * ((T + kLenBlock - 1u) / kLenBlock), 256);
     E.ws_len = ew;     ew = align_up(ew + 4ull * T, 256);

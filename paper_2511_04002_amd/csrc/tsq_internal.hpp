@@ -55,7 +55,7 @@ static_assert(sizeof(EntropyHeader) == 256, "entropy header must be 256 bytes");
 struct EntropyLayout {
     uint64_t off_tables, off_stream_off, off_streams, stream_capacity, eblob_bytes;
     uint64_t ws_pooled;     // u32[pool_groups][kPoolSetWords] code counts per width class, a set per counting workgroup
-    uint64_t ws_parts;      // u32[kMaxTableSlices][7][256] the sets' sums by slices of kTableSlice sets (more than one slice)
+    uint64_t ws_parts;      // u32[slices][kPoolSetWords] the sets' sums by slices of kTableSlice sets (nothing for one slice)
     uint64_t ws_arrived;    // u32[7][kBlockStride], word 0 of each: slices of the class that are summed up
     uint64_t ws_block;      // u32[ceil(T / kLenBlock)][kBlockStride], word 0 of each: padded stream bytes of the block of kLenBlock tokens
     uint64_t ws_len;        // u32[T] stream bytes per token

@@ -115,7 +115,8 @@ k_rans_tables(const Params p, const EntropyLayout e, const uint8_t *__restrict__
     __shared__ uint32_t sums[4][256];
     __shared__ uint32_t last;
     const uint32_t slice = blockIdx.x, slices = gridDim.x, k = blockIdx.y, c = threadIdx.x & 255u, q = threadIdx.x >> 8;
-    const uint32_t codes = 4u << k, *sets = reinterpret_cast<const uint32_t *>(ews + e.ws_pooled) + codes - 4u + (c & (codes - 1u));
+    const uint32_t codes = 4u << k, at_set = codes - 4u + (c & (codes - 1u));   // the code's word of a set
+    const uint32_t *sets = reinterpret_cast<const uint32_t *>(ews + e.ws_pooled) + at_set;
     const uint32_t g0 = slice * kTableSlice, left = e.pool_groups - g0;
     // (all loads at once: what is beyond the class's codes or the last set is read within them and dropped)
     uint32_t v[kTableSlice / 4u], n = 0;
@@ -129,11 +130,11 @@ k_rans_tables(const Params p, const EntropyLayout e, const uint8_t *__restrict__
     for (uint32_t i = 0; i < kTableSlice / 4u; ++i) n += 4u * i + q < left ? v[i] : 0u;
     sums[q][c] = c < codes ? n : 0u;
     __syncthreads();
-    uint32_t *parts = reinterpret_cast<uint32_t *>(ews + e.ws_parts) + k * 256u;
+    uint32_t *parts = reinterpret_cast<uint32_t *>(ews + e.ws_parts) + at_set;
     if (slices > 1u) {
-        if (q == 0) {
+        if (q == 0 && c < codes) {
             n = sums[0][c] + sums[1][c] + sums[2][c] + sums[3][c];
-            __hip_atomic_store(parts + slice * 7u * 256u + c, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(parts + slice * kPoolSetWords, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // (performed before the arrival is counted)
         }
         __syncthreads();
@@ -142,9 +143,9 @@ k_rans_tables(const Params p, const EntropyLayout e, const uint8_t *__restrict__
                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == slices - 1u;
         __syncthreads();
         if (!last) return;
-        const uint32_t a = __hip_atomic_load(parts + (q < slices ? q : 0u) * 7u * 256u + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const uint32_t b = __hip_atomic_load(parts + (q + 4u < slices ? q + 4u : 0u) * 7u * 256u + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sums[q][c] = (q < slices ? a : 0u) + (q + 4u < slices ? b : 0u);
+        const uint32_t a = __hip_atomic_load(parts + (q < slices ? q : 0u) * kPoolSetWords, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t b = __hip_atomic_load(parts + (q + 4u < slices ? q + 4u : 0u) * kPoolSetWords, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        sums[q][c] = c < codes ? (q < slices ? a : 0u) + (q + 4u < slices ? b : 0u) : 0u;
         __syncthreads();
     }
     if (threadIdx.x >= 64u) return;

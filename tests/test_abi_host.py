@@ -180,6 +180,19 @@ def test_entropy_sizes(L, T, H):
     assert tsq.tsq_entropy_blob_bytes(0) == 0 and tsq.tsq_entropy_workspace_bytes(0) == 0
 
 
+# the most counting workgroups (512, a set of counts each) and numbers of them around a change in tokens per set or in slices of sets
+@pytest.mark.parametrize("T,H", [(8192, 8192), (8177, 8), (8176, 8), (8193, 64), (16384, 4096), (16353, 8), (1024, 40), (1025, 40),
+                                 (6000, 8), (7169, 8), (131072, 8192), (1 << 20, 8)])
+def test_entropy_workspace_keeps_its_bound(L, T, H):
+    """... at most 1 MiB and 8 bytes a token besides the slots, whatever the shape."""
+    plan = tsq.tsq_plan_create(cfg(tokens=T, hidden=H))
+    try:
+        slot = 256 + 2 * ((H + 1) // 2 * 2)
+        assert T * slot + 4 * T < tsq.tsq_entropy_workspace_bytes(plan) <= T * slot + 8 * T + (1 << 20)
+    finally:
+        tsq.tsq_plan_destroy(plan)
+
+
 @pytest.mark.parametrize("T,H,kernel", [
     (1, 8, "k_direct"), (1 << 20, 2048, "k_direct"), ((1 << 26) - 1, 8, "k_direct"), (1 << 26, 8, "k_fused"),
     (4096, 4096, "k_direct"), (4097, 2056, "k_fused"), (2730, 6144, "k_direct"), (2731, 4104, "k_fused"),
