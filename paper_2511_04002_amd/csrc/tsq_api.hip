@@ -654,7 +654,7 @@ int tsq_check_stream_span(uint64_t begin, uint64_t end, uint64_t capacity, uint3
     return stream_span_ok(begin, end, capacity, coders, slot_bytes) ? 1 : 0;
 }
 void tsq_check_divisions(const uint32_t *x, const uint32_t *f, const uint32_t *low, uint32_t *q, uint64_t n) {
-    for (uint64_t i = 0; i < n; ++i) q[i] = quotient(x[i], reciprocal_just_above(f[i], low[i]));
+    for (uint64_t i = 0; i < n; ++i) q[i] = quotient(x[i], reciprocal_just_above(f[i], low[i]), kQuotientAddend);
 }
 int tsq_check_stream_move(uint32_t bytes, uint32_t coders, uint32_t slot_bytes, uint64_t at, uint64_t capacity) {
     return stream_move_ok(bytes, coders, slot_bytes, at, capacity) ? 1 : 0;

@@ -66,8 +66,16 @@ TSQ_HD double reciprocal_just_above(uint32_t f, uint32_t low) {
     return __builtin_bit_cast(double, (r & ~0xFFFFull) + 0x10000ull + low);
 }
 constexpr double kQuotientAddend = 4503599627370495.5;      // 2^52 - 1/2
-TSQ_HD uint32_t quotient(uint32_t x, double above) {
-    return (uint32_t)__builtin_bit_cast(uint64_t, __builtin_fma((double)x, above, kQuotientAddend));
+// addend: kQuotientAddend, which a kernel keeps in registers for all its divisions.  There the product is named as the
+// instruction that it is: left to itself the compiler copies the addend for half of them, to accumulate into the copy.
+TSQ_HD uint32_t quotient(uint32_t x, double above, double addend) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    double v;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(v) : "v"((double)x), "v"(above), "v"(addend));
+#else
+    const double v = __builtin_fma((double)x, above, addend);
+#endif
+    return (uint32_t)__builtin_bit_cast(uint64_t, v);
 }
 
 // A workspace's recorded shape against the plan's.

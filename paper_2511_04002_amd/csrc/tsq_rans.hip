@@ -212,13 +212,6 @@ __device__ __forceinline__ uint32_t mad_u24(uint32_t a, uint32_t b, uint32_t c) 
     asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
     return d;
 }
-// quotient(x, above), with its addend in registers for the whole kernel and named as such: left to itself the compiler copies
-// it for half of the steps, to accumulate into the copy
-__device__ __forceinline__ uint32_t quotient_with(uint32_t x, double above, double addend) {
-    double d;
-    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"((double)x), "v"(above), "v"(addend));
-    return (uint32_t)__builtin_bit_cast(uint64_t, d);
-}
 // x >> 16, in x's own register
 __device__ __forceinline__ void drop_word(uint32_t &x) { asm volatile("v_lshrrev_b32 %0, 16, %0" : "+v"(x)); }
 // 8 times byte k of w in one instruction
@@ -285,7 +278,7 @@ __device__ __forceinline__ void encode_round(const uint32_t *src_row, uint32_t r
         if (j > 0) look_up(j - 1, next_above, next_step);
         // q = floor(x / f); the state sheds a word if x >= f << 20, that is q >= 2^20, and the quotient of what is left
         // is then q >> 16
-        uint32_t q = quotient_with(x, above, addend);
+        uint32_t q = quotient(x, above, addend);
         const bool over = q >= (1u << 20), shed = active && over;
         const uint64_t who = WHOLE ? __builtin_amdgcn_ballot_w64(over) : __builtin_amdgcn_ballot_w64(active) & __builtin_amdgcn_ballot_w64(over);
         ptr -= 2u * (uint32_t)__builtin_popcountll(who);

@@ -1,11 +1,20 @@
 """The division of the entropy encoder (a binary64 product with a reciprocal just above 1 / f, rounded once), run on the
 host by the very routine that the kernel compiles: exact for every frequency, at and around multiples of it, at the
 ends of the range of states, and whatever stands in the lowest 16 bits of the reciprocal."""
+import os
+
 import numpy as np
 import pytest
 
 from paper_2511_04002_amd import build as tsq_build
 from paper_2511_04002_amd import tsq
+
+
+def test_the_encoder_divides_by_the_routine_that_is_tested():
+    """tsq_check_divisions and the encoder call quotient() of tsq_ranges.hpp, and the encoder has no product of its own beside it."""
+    read = lambda name: open(os.path.join(tsq_build.CSRC, name)).read()
+    assert "quotient(" in read("tsq_rans.hip") and "fma_f64" not in read("tsq_rans.hip")
+    assert "quotient(x[i], reciprocal_just_above(" in read("tsq_api.hip")
 
 
 @pytest.mark.parametrize("low", [0, 1, 4095, 65535])
