@@ -762,9 +762,10 @@ __device__ __forceinline__ Choice search_width(const Params &p, const Mags<DT> &
     return c;
 }
 
-// The blob is this plan's and was completed without error.  One expression without short cuts: the header's words are asked
-// for together and waited for once.  Taken one after the other, each behind the last one's verdict, they were nine waits at the
-// head of a kernel: restore of 2048 x 4096 f16 6.4 us a call, now 6.1; 300 x 5120 bf16 5.6 / 5.3.
+// The blob is this plan's and was completed without error.  One expression without short cuts: no word of the header waits for
+// the verdict on another.  How many batches the words are fetched in is the compiler's choice: one in the encoder's kernels, two
+// with a wait between them in restore and the decoder (status and hidden follow).  Taken one after the other, each behind the last
+// one's verdict, they were nine waits at the head of a kernel: restore of 2048 x 4096 f16, repeated, 6.4 us a call / 6.1.
 // CSR: restore, which also takes the side stream's place from the plan.
 template <bool CSR>
 __device__ __forceinline__ bool blob_is_plans(const Params &p, const uint8_t *__restrict__ blob) {
